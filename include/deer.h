@@ -248,10 +248,10 @@ int deer_debug_stream_read(deer_ctx *c, const void *buf_dev, size_t bytes, int32
  * pass of `model`; launch < 0 switches recording off.  Waits for the stream. */
 int deer_debug_gemm_stamps(deer_ctx *c, int model, int launch, uint64_t *stamps_host, int32_t max_blocks, int32_t *blocks);
 
-/* GEMMs of passes with at least 256 rows run blocked for the matrix cores (256 x 256 tiles through LDS)
- * where a launch has at least `min_tiles` such tiles (default 128: enough to fill the chip), else as the
- * weight-streaming kernel.  0 switches the blocked kernel off; tests lower the threshold to cover it at
- * small sizes.  Results agree within rounding (different summation order over K). */
+/* GEMMs of passes of several row tiles run blocked (128 x 128 or 128 x 256 tiles through LDS) where that is estimated
+ * to be faster than the weight-streaming kernel (min_tiles = 128, the default; larger values: the same).  0 switches the
+ * blocked kernel off; 1 .. 127 make every GEMM of a pass with at least 256 rows take it (tests cover it at small sizes).
+ * Results agree within rounding (different summation order over K). */
 int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles);
 
 /* Current committed length j per sequence (host mirror). */

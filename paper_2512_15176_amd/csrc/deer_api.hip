@@ -1,7 +1,7 @@
 // Host side of libdeer: context, buffer carving, call-order state machine, kernel launches.
 // The C ABI is declared in include/deer.h.  Nothing here allocates device memory.
 #include "deer_kernels.hpp"
-#include "deer_tiled.hpp"
+#include "deer_block.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -35,7 +35,7 @@ thread_local std::string g_init_error;
 
 
 constexpr int STAMP_MAX_BLOCKS = 4096;   // workgroups whose stamps deer_debug_gemm_stamps can record (8 stamps each)
-// rows of a prefill chunk / 32: dense models take 4096 rows per pass through the LDS-tiled GEMM, mixtures 512
+// rows of a prefill chunk / 32: dense models take 4096 rows per pass through the blocked GEMM, mixtures 512
 // (their grouped expert buffers grow with the rows of a pass)
 constexpr int PREFILL_TILES_DENSE = 128, PREFILL_TILES_MOE = 16;
 int prefill_tiles(const deer_init_params &p) { return (p.target.n_experts || p.drafter.n_experts) ? PREFILL_TILES_MOE : PREFILL_TILES_DENSE; }
@@ -107,7 +107,7 @@ struct deer_ctx {
     int cur_k = 0;
     float cur_T = 0.f;
     int max_tiles = 0;
-    int tiled_min_tiles = 128;       // the LDS-tiled GEMM runs where a launch has at least this many 256 x 256 tiles; 0: never
+    int block_gemm = 128;            // deer_debug_gemm_tiled: 0 never blocked; 128 where it is estimated to be faster; less: from 8 row tiles on
     // deer_debug_gemm_stamps: which streaming-GEMM launch of which model's passes records its stamps
     int stamp_model = 0, stamp_launch = -1, stamp_blocks = 0, gemm_launch_idx = 0, cur_pass_model = 0;
     int route_spread = 0;            // deer_debug_route_spread: synthetic uniform routing for mixture models
@@ -342,6 +342,47 @@ unsigned long long *stamp_buffer(deer_ctx *c, size_t workgroups) {
     return c->wk.stamps + (size_t)stamp_rel * (STAMP_MAX_BLOCKS / 2) * 8;
 }
 
+// What a GEMM launch takes, in microseconds: rounds of workgroups on 256 compute units, a fixed part for the first loads
+// and the epilogue, a part per k-step of a workgroup, and what the shares of a split K cost.  The constants are fitted to
+// launches of the 4B, 8B and drafter matrices (K = 896 .. 12288, N = 896 .. 24576) over 2 .. 128 row tiles and are good to
+// about 15 %; the choice between kernels needs no more, since near a boundary both take the same time.
+// Streaming kernel with MT row tiles per workgroup (8B gate/up at 16 tiles: 6 rounds, 227 us; down: 1 round, 105 us):
+// (an odd number of many tiles leaves one per workgroup, whose weights come from L2 once per tile: 0.1 us per k-step)
+double stream_us(int N, int KS, int MT, int zg, int S) {
+    const double rounds = std::ceil((double)(N / CG) * S * zg / 256.0);
+    return 5.0 + rounds * (MT == 2 ? 5.0 + 0.125 * KS / S : 4.0 + (zg > 16 ? 0.1 : 0.07) * KS / S) + (S > 1 ? 6.0 : 0.0);
+}
+// narrow workgroups of a small model (drafter: O 6 us up to 8 tiles, 10.6 at 16, 64 at 105; QKV 8, 14 and 61)
+double narrow_us(int ntiles, bool qkv) {
+    return qkv ? 8.0 + 6.2 * std::max(0.0, ntiles * 24 / 256.0 - 1.0) : 6.0 + 9.0 * std::max(0.0, ntiles * 32 / 512.0 - 0.5);
+}
+// Blocked kernel: NB = 4 (128 x 256 per workgroup, two on a compute unit: 0.34 us per k-step each up to two of them, 0.40
+// when all are busy for long) or NB = 2 (128 x 128; 0.245 us alone on its compute unit, 0.225 otherwise).
+struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; };
+BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, size_t part_floats) {
+    BlockPlan best;
+    const int nrb = (ntiles + BK_RT - 1) / BK_RT;
+    // 128 columns per wave keep K in one chain of sums (see BK_FOLD): only where the error enters once and last (the LM head:
+    // no difference measured) or in large launches (1024 rows on, 128 blocks of 256 x 256), where no kernel here folds
+    const bool wide_ok = lm_head || (ntiles >= 32 && ((ntiles + 7) / 8) * ((N / CG + 1) / 2) >= 128);
+    for (int NB = wide_ok ? 4 : 2; NB >= 2; NB -= 2) {
+        const int ncb = (N + 64 * NB - 1) / (64 * NB);
+        for (int S = 1; S <= (lm_head ? 1 : 8); ++S) {
+            const int per = (KS + S - 1) / S;
+            if (S > 1 && (per < 16 || (S - 1) * per >= KS)) continue;                          // every share has k-steps
+            const double tile_bytes = 4.0 * S * nrb * ncb * 128 * 64 * NB;
+            if (S > 1 && tile_bytes > 4.0 * (double)part_floats) continue;
+            // rounds of workgroups: two share a compute unit and fill each other's gaps
+            const double q = (double)nrb * ncb * S / 256.0;
+            const double units = q <= 1.0 ? 1.0 : q > 2.0 ? 0.5 * (q + std::ceil(q)) : NB == 4 ? 2.0 : 1.45 + 0.5 * (q - 1.0);
+            const double step = NB == 4 ? (q <= 2.0 ? 0.34 : 0.40) : (q <= 1.0 ? 0.245 : 0.225);
+            const double us = 10.0 + units * per * step + (S > 1 ? 4.0 + 2.0 * tile_bytes / 4e6 : 0.0);
+            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0, us};
+        }
+    }
+    return best;
+}
+
 template <int EPI>
 int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     a.KS = K / 16;
@@ -359,24 +400,25 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     const int MT = pairs ? 2 : 1;
     const int zg = ntiles / MT;
     a.rows_total = ntiles * 32;
-    {   // many rows and enough 256 x 256 tiles to fill the chip: blocked for the matrix cores
-        const int ncg = a.N / CG;
-        const int tiles = ((ntiles + TG_RT - 1) / TG_RT) * ((ncg + 1) / 2);
-        // measured: at 512 and 1024 rows (two and four row blocks) the streaming kernel with shared L2 lines is still
-        // ahead (config-5 verify 41.9 against 47.7 ms); from 1024 rows on the blocked kernel wins where it has 128 tiles
-        // (prefill 133 against 167 ms; two 512-token sequences recomputed per iteration 44.3 against 46.8 ms)
-        constexpr int rows_tiles = 32;
-        const int min_rows_tiles = c->tiled_min_tiles >= 128 ? rows_tiles : TG_RT;   // tests lower both thresholds
-        if (c->tiled_min_tiles > 0 && EPI != EPI_ROUTER && ntiles >= min_rows_tiles && a.KS % TG_KST == 0 && tiles >= c->tiled_min_tiles) {
-            a.S = 1; a.part = nullptr; a.counters = nullptr;
+    const bool narrow = (EPI == EPI_RESID || (EPI == EPI_QKV && a.hd <= 64 && 64 % a.hd == 0 && a.N % 64 == 0)) && a.ssq_sub == 4 && MT == 1 &&
+                        force_S <= 0 && a.KS <= 64;
+    if constexpr (EPI != EPI_ROUTER) {
+        const BlockPlan bp = plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->wk.part_floats);
+        const double old_us = narrow ? narrow_us(ntiles, EPI == EPI_QKV) : stream_us(a.N, a.KS, MT, zg, force_S > 0 ? force_S : choose_split(a.N, a.KS, zg));
+        const bool forced = c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8;   // tests cover it at small sizes
+        if (c->block_gemm > 0 && ntiles > 1 && (forced || bp.us < 0.97 * old_us)) {
+            a.S = bp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
+            const int nrb = (ntiles + BK_RT - 1) / BK_RT, ncb = (a.N + 64 * bp.NB - 1) / (64 * bp.NB), band = block_band(nrb);
+            const dim3 g((unsigned)block_grid(ncb * a.S, nrb));
             ProfScope ps(c, 0, (double)a.N * K * 2.0);
-            hipLaunchKernelGGL((k_gemm_tiled<EPI>), dim3((unsigned)tiled_blocks(ntiles, ncg)), dim3(512), 0, c->stream, a, ncg, ntiles);
-            LAUNCHCHK(c, "k_gemm_tiled");
+            if (bp.NB == 4) hipLaunchKernelGGL((k_gemm_block<4, 4, EPI>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            else if (bp.deep) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            else hipLaunchKernelGGL((k_gemm_block<2, 4, EPI>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            LAUNCHCHK(c, "k_gemm_block");
             return DEER_OK;
         }
     }
-    if ((EPI == EPI_RESID || (EPI == EPI_QKV && a.hd <= 64 && 64 % a.hd == 0 && a.N % 64 == 0)) && a.ssq_sub == 4 && MT == 1 &&
-        force_S <= 0 && a.KS <= 64) {
+    if (narrow) {
         // an unsplit GEMM of a small model: one workgroup per row tile and 32-column weight block (residual GEMM) or
         // 64-column pair of blocks (QKV: whole heads)
         a.S = 1; a.part = nullptr; a.counters = nullptr;
@@ -1077,7 +1119,7 @@ int deer_debug_stream_read(deer_ctx *c, const void *buf_dev, size_t bytes, int32
 int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles) {
     if (!c) return DEER_EINVAL;
     if (min_tiles < 0) return fail(c, DEER_EINVAL, "min_tiles must not be negative");
-    c->tiled_min_tiles = min_tiles;
+    c->block_gemm = min_tiles;
     return DEER_OK;
 }
 

@@ -1,0 +1,486 @@
+// LDS-blocked GEMMs for passes of several row tiles (batches, prompts), two workgroups per compute unit.
+//
+// A workgroup of four waves owns 128 rows x 64 NB columns; wave (wr, wc) multiplies rows 64 wr .. + 63 and columns
+// 32 NB wc .. of them (two row tiles x NB column tiles).  Both operands travel to LDS with direct-to-LDS loads, one
+// k-step of 16 per stage in a ring of NST stages (a fragment is a plain 1 KB copy: operands are stored in MFMA
+// register order).  Two workgroups share a compute unit, so that the barrier, the first loads and the epilogue of one run
+// under the products of the other.  With S > 1 the workgroups of a tile take shares of K; their accumulators meet
+// through memory as they lie in the registers, and the last to arrive sums the shares in order and runs the epilogue.
+//
+// Bound: the matrix cores for many row tiles (128 of them, 8B gate/up: 1.28 PFLOP/s issued, what the largest plain bf16
+// product reaches on this card is 1.36; LM head of 16: 1.6 PFLOP/s), the L2 -> LDS path for few (a k-step of NB = 4 brings
+// 16 KB; a compute unit gets 27 to 34 bytes per clock, 512 cycles of products need 32).  A 64 x 128 wave tile reads 8 KB of
+// LDS per 16 products, which leaves the LDS half idle; 128 x 256 per workgroup needs 16 KB from L2 per 64 products
+// against 32 KB in the streaming kernel's pairs of row tiles.  Measured against the kernels that did this work before
+// (one 256 x 256 tile per 512 threads in lockstep; the streaming kernel), microseconds per launch, 8B widths: gate/up at
+// 4 / 7 / 16 / 32 / 128 row tiles 83 / 142 / 227 / 454 / 1369 -> 70 / 112 / 187 / 330 / 1270, QKV at 16 / 64 / 128
+// 81 / 255 / 531 -> 64 / 185 / 333, down at 24 / 64 200 / 648 -> 165 / 325, LM head at 16 (with 151936 columns) 1348 -> 760.
+#pragma once
+#include "deer_kernels.hpp"
+
+namespace deer {
+
+constexpr int BK_RT = 4;     // row tiles per workgroup
+// With 64 columns per wave the accumulators are added to a second set every BK_FOLD k-steps.  A matrix instruction adds its
+// products to the running sum with a rounding of its own, and over a whole K of 256 to 768 k-steps in one chain (twice
+// that many additions: hi and lo) these add up to twice the error of the streaming kernel, whose eight waves hold an eighth
+// of K each (16 sequences, 12 layers of the 8B shape: logits 1.24e-4 off the 64-bit reference against 6.1e-5; folded:
+// 4.0e-5).  128 columns per wave leave no registers for a second set.
+constexpr int BK_FOLD = 32;
+constexpr int BT_STRIDE = 132;   // padded LDS row stride (floats) of a wave's 32 x 128 epilogue tile
+
+// LDS byte address of a __shared__ object
+__device__ __forceinline__ uint32_t lds_addr32(const void *p) {
+    return (uint32_t)(size_t)(const void __attribute__((address_space(3))) *)p;
+}
+template <int OFF>
+__device__ __forceinline__ void lds_frag(u32x4 &v, uint32_t addr) {
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(v) : "v"(addr), "n"(OFF));
+}
+
+template <int NB>
+struct BlockFrags { u32x4 w[NB], xh[2], xl[2]; };   // one k-step of a wave
+
+template <int NB>
+__device__ __forceinline__ void block_read(BlockFrags<NB> &f, uint32_t sbw, uint32_t sbx) {
+    lds_frag<0>(f.xh[0], sbx); lds_frag<1024>(f.xh[1], sbx);
+    lds_frag<0>(f.w[0], sbw); lds_frag<1024>(f.w[1], sbw);
+    if constexpr (NB == 4) { lds_frag<2048>(f.w[2], sbw); lds_frag<3072>(f.w[3], sbw); }
+    lds_frag<BK_RT * 1024>(f.xl[0], sbx); lds_frag<BK_RT * 1024 + 1024>(f.xl[1], sbx);
+}
+// the fragments are valid after this point (they pass through the wait as operands)
+template <int NB>
+__device__ __forceinline__ void block_wait(BlockFrags<NB> &f) {
+    if constexpr (NB == 4)
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(f.w[0]), "+v"(f.w[1]), "+v"(f.w[2]), "+v"(f.w[3]), "+v"(f.xh[0]), "+v"(f.xh[1]), "+v"(f.xl[0]), "+v"(f.xl[1])
+                     :: "memory");
+    else
+        asm volatile("s_waitcnt lgkmcnt(0)"
+                     : "+v"(f.w[0]), "+v"(f.w[1]), "+v"(f.xh[0]), "+v"(f.xh[1]), "+v"(f.xl[0]), "+v"(f.xl[1]) :: "memory");
+}
+
+template <int NB, int NST>
+struct BlockSmem {
+    static constexpr int FRAGS = 2 * NB + 2 * BK_RT;   // per stage: weight column tiles, row tiles hi, row tiles lo
+    union {
+        uint4 st[NST][FRAGS * 64];
+        float tile[4][32 * BT_STRIDE];                 // epilogue: one 32 x 128 tile per wave
+    };
+    int last;
+};
+
+// The K loop.  base[i] + vo[i]: where a lane's 16 bytes of this wave's i-th fragment of k-step 0 lie (k-steps are 1 KB
+// apart); n k-steps.  Ends with this wave's LDS reads done and none of its loads in flight.
+// Schedule of k-step it (its fragments are in registers): wait until k-step it + 1 has landed | barrier: everybody's share
+// of it has, and everybody has read k-step it | read the fragments of it + 1 | multiply it, and between the products
+// request k-step it + NST into the buffer of k-step it.
+// What is not a product has to be short or stand between products: a matrix instruction occupies its pipe for 32 cycles
+// and the wave's other instructions issue meanwhile.  The steady state therefore runs without any condition (NST k-steps
+// per trip, buffers at constant offsets); the last up to 2 NST - 1 k-steps take the general form.
+template <int NB, int NST, int LPW>
+__device__ __forceinline__ void block_loop(f32x16 (&acc)[2][NB], const char *(&base)[LPW], const uint32_t (&vo)[LPW],
+                                           BlockSmem<NB, NST> &sm, int n, int w, int lane) {
+    constexpr int SB = BlockSmem<NB, NST>::FRAGS * 1024;
+    static_assert((NST == 4 || NST == 8) && (NST - 1) * LPW <= 63, "the loops below are written for these; the counter of loads in flight has six bits");
+    const uint32_t s0 = lds_addr32(sm.st[0]) + lane * 16;
+    const uint32_t ow = s0 + (w & 1) * NB * 1024, ox = s0 + (2 * NB + (w >> 1) * 2) * 1024;
+    // this wave's i-th fragment of the next k-step to be requested
+    auto request1 = [&](int buf, int i) {
+        asm volatile("" : "+s"(base[i]));   // stays a scalar address
+        __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(base[i] + vo[i]),
+                                         (void __attribute__((address_space(3))) *)(sm.st[buf] + (w * LPW + i) * 64), 16, 0, 0);
+        base[i] += 1024;
+    };
+    f32x16 sum[2][NB];   // NB == 2 only
+    auto mul = [&](const BlockFrags<NB> &f, int j) {   // product j of 4 NB: all row and column tiles with hi, then with lo
+        const int mt = (j / NB) & 1, nb = j % NB;
+        acc[mt][nb] = mfma32(j < 2 * NB ? f.xh[mt] : f.xl[mt], f.w[nb], acc[mt][nb]);
+    };
+    BlockFrags<NB> fa, fb;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[mt][nb][r] = 0.f;
+#pragma unroll
+    for (int k = 0; k < NST; ++k)
+        if (k < n) {
+#pragma unroll
+            for (int i = 0; i < LPW; ++i) request1(k, i);
+        }
+    if (n >= NST) wait_loads<(NST - 1) * LPW>(); else wait_loads<0>();
+    barrier_keep_loads();
+    block_read<NB>(fa, ow, ox);
+    block_wait<NB>(fa);
+    auto step = [&](BlockFrags<NB> &cur, BlockFrags<NB> &next, auto buf_c) {   // steady state
+        constexpr int buf = decltype(buf_c)::value, nbuf = (buf + 1) % NST;
+        wait_loads<(NST - 2) * LPW>();
+        barrier_keep_loads();
+        block_read<NB>(next, ow + nbuf * SB, ox + nbuf * SB);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 4 * NB; ++j) {
+            mul(cur, j);
+            if (j % NB == NB - 1 && j / NB < 3) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = j / NB; i < LPW; i += 3) request1(buf, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        block_wait<NB>(next);
+    };
+    int it = 0, fold = BK_FOLD;
+    for (; it < n - 2 * NST + 1; it += NST) {
+        if constexpr (NB == 2) {
+            if (it >= fold) {
+                fold += BK_FOLD;
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) { sum[mt][nb][r] += acc[mt][nb][r]; acc[mt][nb][r] = 0.f; }
+            }
+        }
+        step(fa, fb, std::integral_constant<int, 0>{}); step(fb, fa, std::integral_constant<int, 1>{});
+        step(fa, fb, std::integral_constant<int, 2>{}); step(fb, fa, std::integral_constant<int, 3>{});
+        if constexpr (NST == 8) {
+            step(fa, fb, std::integral_constant<int, 4>{}); step(fb, fa, std::integral_constant<int, 5>{});
+            step(fa, fb, std::integral_constant<int, 6>{}); step(fb, fa, std::integral_constant<int, 7>{});
+        }
+    }
+    auto last_steps = [&](BlockFrags<NB> &cur, BlockFrags<NB> &next) {
+        const bool more = it + 1 < n;
+        if (more) {
+            if (n - 2 - it >= NST - 2) wait_loads<(NST - 2) * LPW>(); else wait_loads<0>();
+            barrier_keep_loads();
+            const int buf = it & (NST - 1), nbuf = (it + 1) & (NST - 1);
+            if (it + NST < n) {
+#pragma unroll
+                for (int i = 0; i < LPW; ++i) request1(buf, i);
+            }
+            block_read<NB>(next, ow + nbuf * SB, ox + nbuf * SB);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 4 * NB; ++j) mul(cur, j);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) block_wait<NB>(next);
+        ++it;
+    };
+    while (it < n) {
+        last_steps(fa, fb);
+        if (it < n) last_steps(fb, fa);
+    }
+    if constexpr (NB == 2) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[mt][nb][r] += sum[mt][nb][r];
+    }
+}
+
+// rstd of row (lane & 31) of the 32 rows that start at grow0, in both halves of the wave
+__device__ __forceinline__ float wave_rstd(const float *ssq, size_t row, int half, int ncg, int d, float eps) {
+    const float *p = ssq + row * ncg;
+    float s = 0.f;
+    int g = half;
+    for (; g + 6 < ncg; g += 8) {
+        const float v0 = p[g], v1 = p[g + 2], v2 = p[g + 4], v3 = p[g + 6];
+        s += v0; s += v1; s += v2; s += v3;
+    }
+    for (; g < ncg; g += 2) s += p[g];
+    s += shx(s, 32);
+    return rsqrtf(s / (float)d + eps);
+}
+
+// LDS writes of this wave are readable by its other lanes behind this point
+__device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Accumulators of one row tile into a 32 x 128 tile (columns col0 ..), MFMA register layout -> row-major
+template <int NB>
+__device__ __forceinline__ void wave_park(const f32x16 (&acc)[NB], float *tile, int col0, int lane) {
+    const int half = lane >> 5, cl = lane & 31;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) tile[mfma_row(r, half) * BT_STRIDE + col0 + nb * 32 + cl] = acc[nb][r];
+}
+
+// The epilogues of deer_kernels.hpp for one wave and one 32 x 128 tile: row tile t of the pass (ct of the launch), column
+// group cg.  No barriers: every wave runs its own.
+template <int EPI>
+__device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, int cg, int ct, int t) {
+    const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
+    const size_t grow = (size_t)t * 32 + row;
+    float rs = 0.f;
+    if (EPI != EPI_RESID) rs = wave_rstd(a.ssq_in, grow, half, a.ncg_in, a.d_in, a.eps);
+    if (EPI == EPI_SWIGLU) {
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {   // octets of 8 channels
+            const int oct = 2 * i + half;
+            const float *g = tile + row * BT_STRIDE + oct * 8, *u = g + 64;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float ge = g[e] * rs;
+                v[e] = ge / (1.f + expf(-ge)) * (u[e] * rs);
+            }
+            uint4 hi, lo;
+            pack8_split(v, hi, lo);
+            const size_t vec = (size_t)t * (a.F / 16) * 64 + frag_vec(row, cg * 8 + oct);
+            a.ahi[vec] = hi;
+            a.alo[vec] = lo;
+        }
+    } else if (EPI == EPI_RESID) {
+        const int N = a.N, c4 = row * 4;
+        float *hp = a.h + ((size_t)t * 32 + half) * N + (size_t)cg * CG + c4;
+        float4 hv[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) hv[i] = *(const float4 *)(hp + (size_t)(2 * i) * N);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {   // rows 2 i + half
+            float4 *tp = (float4 *)(tile + (2 * i + half) * BT_STRIDE + c4);
+            const float4 y = *tp;
+            const float4 v = make_float4(hv[i].x + y.x, hv[i].y + y.y, hv[i].z + y.z, hv[i].w + y.w);
+            *(float4 *)(hp + (size_t)(2 * i) * N) = v;
+            *tp = v;
+        }
+        wave_lds_sync();
+        float ss[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {   // 32-column blocks: octets 4 b .. 4 b + 3, two per half
+            ss[b] = 0.f;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int oct = 4 * b + 2 * j + half;
+                const float *tp = tile + row * BT_STRIDE + oct * 8;
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { v[e] = tp[e]; ss[b] += v[e] * v[e]; }
+                uint4 hi, lo;
+                pack8_split(v, hi, lo);
+                const size_t vec = (size_t)t * (N / 16) * 64 + frag_vec(row, cg * 16 + oct);
+                a.xhi_out[vec] = hi;
+                a.xlo_out[vec] = lo;
+            }
+            ss[b] += shx(ss[b], 32);
+        }
+        if (half == 0) {
+            if (a.ssq_sub == 4) *(float4 *)(a.ssq_out + grow * (N / 32) + cg * 4) = make_float4(ss[0], ss[1], ss[2], ss[3]);
+            else a.ssq_out[grow * (N / CG) + cg] = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+        }
+    } else if (EPI == EPI_QKV) {
+        const int hd = a.hd, Hq = a.Hq, Hkv = a.Hkv, half_hd = hd >> 1;
+        const int b = a.rm.tile_seq[t], slot = a.rm.slot[grow];
+#pragma unroll 1
+        for (int i = 0; i < 8; ++i) {
+            const int oct = 2 * i + half, col0 = cg * CG + oct * 8;   // first of 8 columns, all in one head
+            const int kind = col0 < Hq * hd ? 0 : (col0 < (Hq + Hkv) * hd ? 1 : 2);
+            const int hc = col0 - (kind == 0 ? 0 : (kind == 1 ? Hq * hd : (Hq + Hkv) * hd));
+            const int head = hc / hd, i0 = hc % hd;
+            const float *x = tile + row * BT_STRIDE + oct * 8;
+            float v[8];
+            if (kind < 2) {
+                const float *xp = x + ((i0 < half_hd) ? half_hd : -half_hd);
+                const float2 *cs = a.cs + grow * half_hd + (i0 < half_hd ? i0 : i0 - half_hd);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float2 c = cs[e];
+                    v[e] = (i0 < half_hd) ? x[e] * rs * c.x - xp[e] * rs * c.y : x[e] * rs * c.x + xp[e] * rs * c.y;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = x[e] * rs;
+            }
+            if (kind == 0) {
+                uint4 hi, lo;
+                pack8_split(v, hi, lo);
+                const size_t vec = ((size_t)(t * Hq + head) * (hd / 16)) * 64 + frag_vec(row, i0 >> 3);
+                a.qhi[vec] = hi;
+                a.qlo[vec] = lo;
+            } else if (slot >= 0) {
+                const size_t kvb = (size_t)b * a.kv.seq_stride + (size_t)head * a.kv.head_stride;
+                if (kind == 1) {
+                    *(uint4 *)(a.kv.k + kvb + k_cache_off(slot, i0 >> 3, hd)) = pack8(v);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) a.kv.vt[kvb + v_cache_off(slot, i0 + e, hd)] = (uint16_t)f2bf(v[e]);
+                }
+            }
+        }
+    } else if (EPI == EPI_LMHEAD) {
+        const int V = a.N, k = a.k, sub = lane & 7;   // 8 lanes per row, 16 columns each; 8 rows at a time
+        const float T = a.T, invT = T > 0.f ? 1.f / T : 1.f;
+#pragma unroll 1
+        for (int r0 = 0; r0 < 32; r0 += 8) {
+            const int lr = r0 + (lane >> 3);
+            const float sc = __int_as_float(__builtin_amdgcn_ds_bpermute(lr << 2, __float_as_int(rs)));
+            const bool live = lr < k && lr >= a.k_lo;
+            float m = -INFINITY, gm = -INFINITY, se = 0.f;
+            int idx = 0x7fffffff, gidx = 0x7fffffff;
+            float z[16];
+            if (live) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) z[e] = tile[lr * BT_STRIDE + sub * 16 + e] * sc;
+                if (a.logits) {
+                    float *q = a.logits + ((size_t)ct * k + lr) * V + (size_t)cg * CG + sub * 16;
+#pragma unroll
+                    for (int e = 0; e < 16; e += 4) *(float4 *)(q + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
+                }
+                const bool draw = T > 0.f && a.draw;
+                uint64_t key = 0;
+                if (draw) key = row_key(a.seed, TAG_DRAFT, (uint64_t)a.rm.tile_seq[t], (uint64_t)a.rm.pos[t * 32 + lr]);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int v = cg * CG + sub * 16 + e;
+                    argmax_merge(m, idx, z[e], v);
+                    if (draw) argmax_merge(gm, gidx, z[e] * invT + gumbel(key, (uint64_t)v), v);
+                }
+            }
+#pragma unroll
+            for (int off = 1; off < 8; off <<= 1) {
+                const float m2 = shx(m, off); const int i2 = shx(idx, off);
+                argmax_merge(m, idx, m2, i2);
+                const float g2 = shx(gm, off); const int gi2 = shx(gidx, off);
+                argmax_merge(gm, gidx, g2, gi2);
+            }
+            if (live && T > 0.f) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) se += expf((z[e] - m) * invT);
+            }
+#pragma unroll
+            for (int off = 1; off < 8; off <<= 1) se += shx(se, off);
+            if (live && sub == 0) a.stat[((size_t)ct * k + lr) * a.ncg_v + cg] = RowStat{m, idx, se, gm, gidx};
+        }
+    }
+}
+
+// Workgroup id -> (column block and K share p, row block).  Ids 8 apart share an XCD; every XCD gets one contiguous run
+// of the order (band of up to 8 row blocks, p, row block in the band), so that the workgroups it runs together read few
+// weight columns and few rows.
+struct BlockItem { int p, rb; bool valid; };
+__device__ __forceinline__ BlockItem block_item(int lin, int P, int nrb, int band) {
+    const int nb = (nrb + band - 1) / opaque_s(band), total = nb * band * P, per = (total + 7) >> 3;
+    const int i = (lin & 7) * per + (lin >> 3);
+    const int bd = i / opaque_s(band * P), r = i - bd * band * P;
+    BlockItem it;
+    it.p = r / opaque_s(band);
+    it.rb = bd * band + (r - it.p * band);
+    it.valid = (lin >> 3) < per && i < total && it.rb < nrb;
+    return it;
+}
+inline int block_band(int nrb) { const int bands = (nrb + 7) / 8; return (nrb + bands - 1) / bands; }
+inline int block_grid(int P, int nrb) {
+    const int band = block_band(nrb), nb = (nrb + band - 1) / band;
+    return 8 * ((nb * band * P + 7) / 8);
+}
+
+// ncb: column blocks of 64 NB columns; nrt: row tiles (tile ct = 0 .. nrt - 1 is pass tile a.mt0 + ct * a.mt_stride)
+template <int NB, int NST, int EPI>
+__global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 1) void k_gemm_block(const GemmArgs a, int ncb, int nrt, int band) {
+    constexpr int LPW = BlockSmem<NB, NST>::FRAGS / 4;
+    __shared__ __attribute__((aligned(16))) BlockSmem<NB, NST> sm;
+    const int tidx = opaque_tid();
+    const int w = __builtin_amdgcn_readfirstlane(tidx >> 6), lane = tidx & 63;
+    const int wr = w >> 1, wc = w & 1;
+    const int nrb = (nrt + BK_RT - 1) / BK_RT;
+    const BlockItem bi = block_item(blockIdx.x, ncb * a.S, nrb, band);
+    if (!bi.valid) return;
+    const int s = bi.p / opaque_s(ncb), cb = bi.p - s * ncb, rb = bi.rb;
+    const int KS = a.KS, per = (KS + a.S - 1) / opaque_s(a.S);
+    const int ks0 = s * per, n = min(KS, ks0 + per) - ks0;   // the host keeps every share non-empty
+    const int nmt = max(0, min(2, nrt - (rb * BK_RT + wr * 2)));
+    const char *base[LPW];
+    uint32_t vo[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {   // fragments past the matrix repeat the last ones (their products are not used)
+        const int f = w * LPW + i;
+        const uint4 *p;
+        if (f < 2 * NB) p = a.W + ((size_t)min(cb * 2 * NB + f, a.N / 32 - 1) * KS + ks0) * 64;
+        else {
+            const int x = f - 2 * NB, ct = min(rb * BK_RT + (x & (BK_RT - 1)), nrt - 1);
+            p = (x < BK_RT ? a.Xhi : a.Xlo) + ((size_t)(a.mt0 + ct * a.mt_stride) * KS + ks0) * 64;
+        }
+        base[i] = (const char *)p;
+        vo[i] = lane * 16;
+    }
+    f32x16 acc[2][NB];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
+    block_loop<NB, NST, LPW>(acc, base, vo, sm, n, w, lane);
+
+    if (a.S > 1) {
+        // shares meet through memory: [share][row block][column block][wave][(mt, nb, quad)][lane] x 16 bytes
+        const size_t sstride = (size_t)nrb * ncb * 4 * (2 * NB * 4 * 256);
+        float *p0 = a.part + (((size_t)rb * ncb + cb) * 4 + w) * (2 * NB * 4 * 256) + lane * 4;
+        float *pw = p0 + s * sstride;
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+            if (mt < nmt)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        store16_agent(pw + ((mt * NB + nb) * 4 + q) * 256, acc[mt][nb][4 * q], acc[mt][nb][4 * q + 1], acc[mt][nb][4 * q + 2], acc[mt][nb][4 * q + 3]);
+        if (!arrive_last(a.counters + (size_t)rb * ncb + cb, a.S, &sm.last)) return;
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+            if (mt < nmt)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const float *pr = p0 + (mt * NB + nb) * 4 * 256;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
+                    for (int u0 = 0; u0 < a.S; u0 += 4) {   // four shares' loads in flight, summed in order
+                        u32x4 v[4][4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) load16_agent_async(v[u][q], pr + min(u0 + u, a.S - 1) * sstride + q * 256);
+                        wait_loads<0>();
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                tie(v[u][q]);
+                                if (u0 + u < a.S)
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) acc[mt][nb][4 * q + e] += __uint_as_float(v[u][q][e]);
+                            }
+                    }
+                }
+    } else {
+        __syncthreads();   // every wave has read the ring: the epilogue tiles reuse it
+    }
+    if constexpr (NB == 4) {
+        const int cg = cb * 2 + wc;
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const int ct = rb * BK_RT + wr * 2 + mt;
+            if (mt >= nmt || cg * CG >= a.N) continue;
+            wave_park<NB>(acc[mt], sm.tile[w], 0, lane);
+            wave_lds_sync();
+            wave_epilogue<EPI>(a, sm.tile[w], cg, ct, a.mt0 + ct * a.mt_stride);
+            wave_lds_sync();
+        }
+    } else {   // a column group is made by the two waves of a row pair: wave wc finishes row tile wc
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) wave_park<NB>(acc[mt], sm.tile[wr * 2 + mt], wc * 64, lane);
+        __syncthreads();
+        const int ct = rb * BK_RT + wr * 2 + wc;
+        if (wc < nmt) wave_epilogue<EPI>(a, sm.tile[wr * 2 + wc], cb, ct, a.mt0 + ct * a.mt_stride);
+    }
+}
+
+}  // namespace deer
