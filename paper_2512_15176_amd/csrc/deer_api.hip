@@ -35,10 +35,7 @@ thread_local std::string g_init_error;
 
 
 constexpr int STAMP_MAX_BLOCKS = 4096;   // workgroups whose stamps deer_debug_gemm_stamps can record (8 stamps each)
-// rows of a prefill chunk / 32: dense models take 4096 rows per pass through the blocked GEMM, mixtures 512
-// (their grouped expert buffers grow with the rows of a pass)
-constexpr int PREFILL_TILES_DENSE = 128, PREFILL_TILES_MOE = 16;
-int prefill_tiles(const deer_init_params &p) { return (p.target.n_experts || p.drafter.n_experts) ? PREFILL_TILES_MOE : PREFILL_TILES_DENSE; }
+constexpr int PREFILL_TILES = 128;       // most row tiles of a prefill pass (4096 rows: every pass streams the weights once)
 constexpr int PART_TILES_MIN = 16;   // split-K partials exist for passes of up to max(2 * batch, 16) row tiles
 constexpr int MAX_NS = 32;          // key-range splits of block attention
 constexpr int NARROW_MAX_D = 1024;  // residual width up to which a dense model's O projection runs in 32-column workgroups
@@ -79,10 +76,10 @@ struct Work {   // carved from the workspace
     AcceptOut ao{};
     int *ids = nullptr;                // prompt staging [max_seq]
     // mixture-of-experts routing and staging (target only)
-    int *route_e = nullptr, *exp_cnt = nullptr, *pair_row = nullptr, *pair_slot = nullptr;
+    int *route_e = nullptr, *exp_cnt = nullptr, *pair_row = nullptr, *pair_slot = nullptr, *tile_off = nullptr, *items = nullptr;
     float *route_w = nullptr, *moe_out = nullptr;
     unsigned long long *moe_touched = nullptr;   // (layer, expert) pairs streamed since the last read
-    uint4 *act_hi = nullptr, *act_lo = nullptr;
+    uint4 *act_hi = nullptr, *act_lo = nullptr, *xg_hi = nullptr, *xg_lo = nullptr;   // per expert: FFN activations, gathered input rows
     int *gemm_cnt = nullptr, *attn_cnt = nullptr;   // arrival counters, zero between kernels
     size_t cnt_bytes = 0; char *cnt_base = nullptr;
     double *theta[2] = {nullptr, nullptr};
@@ -241,7 +238,7 @@ void plan_model(ModelRT &m, const deer_model_cfg &c, int max_batch, int max_seq)
 // Carves the workspace; with base == nullptr only computes the size.
 void plan_work(Work &w, const deer_init_params &p, char *base) {
     const int B = p.max_batch;
-    const int MAXT = std::max(2 * B, prefill_tiles(p)), MAXR = MAXT * 32;
+    const int MAXT = std::max(2 * B, PREFILL_TILES), MAXR = MAXT * 32;
     const int PARTR = std::max(2 * B, PART_TILES_MIN) * 32;
     const deer_model_cfg &t = p.target, &d = p.drafter;
     const size_t dmax = std::max(t.d_model, d.d_model);
@@ -276,12 +273,14 @@ void plan_work(Work &w, const deer_init_params &p, char *base) {
     w.pf_desc = (int4 *)take((size_t)MAXT * sizeof(int4));
     for (const deer_model_cfg *mc : {&t, &d}) {
         if (!mc->n_experts || w.route_e) continue;
-        const size_t chunks = MAXT;   // 32-pair chunks per expert: at most every row of the pass
+        const size_t tiles = 128 + (size_t)MAXR * 8 / 32, n_items = 128 + (size_t)MAXR * 8 / 64;   // 32-pair tiles and 64-pair items: the last of an expert may be short
         w.route_e = (int *)take((size_t)MAXR * 8 * 4); w.route_w = (float *)take((size_t)MAXR * 8 * 4);
         w.exp_cnt = (int *)take(128 * 4); w.moe_touched = (unsigned long long *)take(8);
         w.pair_row = (int *)take((size_t)128 * MAXR * 4); w.pair_slot = (int *)take((size_t)128 * MAXR * 4);
         w.moe_out = (float *)take((size_t)MAXR * 8 * dmax * 4);
-        w.act_hi = (uint4 *)take((size_t)128 * chunks * (fmax / 16) * 1024); w.act_lo = (uint4 *)take((size_t)128 * chunks * (fmax / 16) * 1024);
+        w.tile_off = (int *)take(128 * 4); w.items = (int *)take((2 + 2 * n_items) * 4);
+        w.act_hi = (uint4 *)take(tiles * (fmax / 16) * 1024); w.act_lo = (uint4 *)take(tiles * (fmax / 16) * 1024);
+        w.xg_hi = (uint4 *)take(tiles * (dmax / 16) * 1024); w.xg_lo = (uint4 *)take(tiles * (dmax / 16) * 1024);
     }
     {
         const size_t ng = (size_t)(std::max(std::max(t.d_model, d.d_model), 4 * (int)fmax) / CG + 64) * MAXT, na = (size_t)MAXT * hq;
@@ -359,12 +358,13 @@ double narrow_us(int ntiles, bool qkv) {
 // Blocked kernel: NB = 4 (128 x 256 per workgroup, two on a compute unit: 0.34 us per k-step each up to two of them, 0.40
 // when all are busy for long) or NB = 2 (128 x 128; 0.245 us alone on its compute unit, 0.225 otherwise).
 struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; };
-BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, size_t part_floats) {
+BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size_t part_floats) {
     BlockPlan best;
     const int nrb = (ntiles + BK_RT - 1) / BK_RT;
     // 128 columns per wave keep K in one chain of sums (see BK_FOLD): only where the error enters once and last (the LM head:
-    // no difference measured) or in large launches (1024 rows on, 128 blocks of 256 x 256), where no kernel here folds
-    const bool wide_ok = lm_head || (ntiles >= 32 && ((ntiles + 7) / 8) * ((N / CG + 1) / 2) >= 128);
+    // no difference measured) or in large launches (1024 rows on, 128 blocks of 256 x 256), where it is the chip's rate that
+    // counts; not beside a mixture, where a rounding can send a row to another expert
+    const bool wide_ok = lm_head || (!mixture && ntiles >= 32 && ((ntiles + 7) / 8) * ((N / CG + 1) / 2) >= 128);
     for (int NB = wide_ok ? 4 : 2; NB >= 2; NB -= 2) {
         const int ncb = (N + 64 * NB - 1) / (64 * NB);
         for (int S = 1; S <= (lm_head ? 1 : 8); ++S) {
@@ -403,7 +403,7 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     const bool narrow = (EPI == EPI_RESID || (EPI == EPI_QKV && a.hd <= 64 && 64 % a.hd == 0 && a.N % 64 == 0)) && a.ssq_sub == 4 && MT == 1 &&
                         force_S <= 0 && a.KS <= 64;
     if constexpr (EPI != EPI_ROUTER) {
-        const BlockPlan bp = plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->wk.part_floats);
+        const BlockPlan bp = plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);
         const double old_us = narrow ? narrow_us(ntiles, EPI == EPI_QKV) : stream_us(a.N, a.KS, MT, zg, force_S > 0 ? force_S : choose_split(a.N, a.KS, zg));
         const bool forced = c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8;   // tests cover it at small sizes
         if (c->block_gemm > 0 && ntiles > 1 && (forced || bp.us < 0.97 * old_us)) {
@@ -482,6 +482,10 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
     }
     return DEER_OK;
 }
+
+// Gate/up of a mixture runs blocked (rows gathered per expert first) from 12 pairs per expert on: 6 row tiles of a layer of
+// 128 experts, top 8, take 172 against 177 us, 8 row tiles 174 against 198, 4 row tiles 170 against 162.
+constexpr int MOE_BLOCK_PAIRS = 12;
 
 // One forward pass of `model` over the rows described by the row metadata (ntiles tiles).
 // rows: the pass's rows are described by a PassRows (draft, verify): one launch works them out, gathers the embeddings
@@ -604,29 +608,38 @@ int run_pass(deer_ctx *c, int model, int ntiles, int max_limit, const LmPlan &lm
             a.route_spread = (c->route_spread && (mc.n_experts & (mc.n_experts - 1)) == 0) ? l + 1 : 0;
             rc = launch_gemm<EPI_ROUTER>(c, a, d, ntiles, 0);
             if (rc) return rc;
-            const int cap = rows, chunks = ntiles;
+            const int cap = rows;
             prof_close(c);
-            hipLaunchKernelGGL(k_moe_group, dim3(1), dim3(256), 0, s, w.route_e, w.rm.slot, rows, mc.top_k, mc.n_experts, cap,
-                               w.exp_cnt, w.pair_row, w.pair_slot, w.moe_touched);
+            hipLaunchKernelGGL(k_moe_group, dim3(1), dim3(1024), 0, s, w.route_e, w.rm.slot, rows, mc.top_k, mc.n_experts, cap,
+                               w.exp_cnt, w.pair_row, w.pair_slot, w.tile_off, w.items, w.moe_touched);
             LAUNCHCHK(c, "k_moe_group");
             MoeArgs ma{};
-            ma.cap = cap; ma.chunks = chunks; ma.cnt = w.exp_cnt; ma.pair_row = w.pair_row; ma.pair_slot = w.pair_slot;
+            ma.cap = cap; ma.cnt = w.exp_cnt; ma.pair_row = w.pair_row; ma.pair_slot = w.pair_slot; ma.tile_off = w.tile_off; ma.items = w.items;
             ma.ssq_in = w.ssq; ma.ncg_in = ncg_d; ma.d_in = d; ma.eps = mc.rms_eps;
             ma.ahi = w.act_hi; ma.alo = w.act_lo; ma.Fe = m.F; ma.route_w = w.route_w; ma.moe_out = w.moe_out; ma.d = d;
             ma.W = (const uint4 *)(lw + m.lo_gu); ma.wexp_stride = m.exp_gu_bytes / 16; ma.Xhi = w.xa_hi; ma.Xlo = w.xa_lo;
             ma.N = 2 * m.F; ma.KS = d / 16;
+            const bool blocked = c->block_gemm > 0 && rows * mc.top_k >= MOE_BLOCK_PAIRS * mc.n_experts;
+            const size_t max_items = (size_t)std::min(mc.n_experts, rows * mc.top_k) + (size_t)rows * mc.top_k / 64;
+            auto block_grid_x = [&](int N) { return dim3((unsigned)(8 * ((max_items * ((N + 255) / 256) + 7) / 8))); };
+            if (blocked) {
+                hipLaunchKernelGGL(k_moe_gather, dim3(ncg_d, (unsigned)max_items), dim3(256), 0, s, w.h, ma, w.xg_hi, w.xg_lo);
+                LAUNCHCHK(c, "k_moe_gather");
+                ma.Xhi = w.xg_hi; ma.Xlo = w.xg_lo;
+            }
             {
                 ProfScope ps(c, 0, 0.0);
-                hipLaunchKernelGGL(k_gemm_moe<MOE_GATEUP>, dim3((2 * m.F / CG + MOE_CGS - 1) / MOE_CGS, mc.n_experts, chunks), dim3(512), 0, s, ma);
+                if (blocked) hipLaunchKernelGGL(k_moe_block<MOE_GATEUP>, block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
+                else hipLaunchKernelGGL(k_gemm_moe, dim3((ma.N / CG + MOE_CGS - 1) / MOE_CGS, mc.n_experts, ntiles), dim3(512), 0, s, ma);
             }
-            LAUNCHCHK(c, "k_gemm_moe gate/up");
+            LAUNCHCHK(c, "grouped gate/up");
             ma.W = (const uint4 *)(lw + m.lo_d); ma.wexp_stride = m.exp_d_bytes / 16; ma.Xhi = w.act_hi; ma.Xlo = w.act_lo;
             ma.N = d; ma.KS = m.F / 16;
             {
                 ProfScope ps(c, 0, 0.0);
-                hipLaunchKernelGGL(k_gemm_moe<MOE_DOWN>, dim3((d / CG + MOE_CGS - 1) / MOE_CGS, mc.n_experts, chunks), dim3(512), 0, s, ma);
+                hipLaunchKernelGGL(k_moe_block<MOE_DOWN>, block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
             }
-            LAUNCHCHK(c, "k_gemm_moe down");
+            LAUNCHCHK(c, "grouped down");
             prof_close(c);
             hipLaunchKernelGGL(k_moe_combine, dim3(ncg_d, ntiles), dim3(256), 0, s, w.moe_out, w.rm.slot, mc.top_k, w.h, w.xa_hi,
                                w.xa_lo, w.ssq, d);
@@ -726,7 +739,7 @@ int deer_init_models(const deer_init_params *p, const deer_buffers *bufs, const 
         c->m[i].kv = (uint16_t *)bufs->kv[i];
     }
     plan_work(c->wk, *p, (char *)bufs->workspace);
-    c->max_tiles = std::max(2 * p->max_batch, prefill_tiles(*p));
+    c->max_tiles = std::max(2 * p->max_batch, PREFILL_TILES);
     // caches must hold finite values everywhere: masked keys are multiplied by zero weights
     for (int i = 0; i < 2; ++i) {
         e = hipMemsetAsync(bufs->kv[i], 0, need.kv[i], c->stream);
@@ -825,7 +838,7 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
     // Passes of up to cap tiles; a pass takes the next rows of as many sequences as fit, each sequence's rows in
     // whole tiles (rows of one sequence that are split over passes continue in the next pass, over the keys the
     // earlier pass has written).  The descriptor lists stay alive until the stream has been waited for.
-    const int cap = prefill_tiles(c->p);
+    const int cap = PREFILL_TILES;
     std::vector<std::vector<int4>> kept;
     for (int model = 0; model < 2; ++model) {
         std::vector<int4> desc;

@@ -20,13 +20,13 @@
 
 namespace deer {
 
-constexpr int BK_RT = 4;     // row tiles per workgroup
+constexpr int BK_RT = 4;     // row tiles per workgroup of k_gemm_block
 // With 64 columns per wave the accumulators are added to a second set every BK_FOLD k-steps.  A matrix instruction adds its
 // products to the running sum with a rounding of its own, and over a whole K of 256 to 768 k-steps in one chain (twice
 // that many additions: hi and lo) these add up to twice the error of the streaming kernel, whose eight waves hold an eighth
 // of K each (16 sequences, 12 layers of the 8B shape: logits 1.24e-4 off the 64-bit reference against 6.1e-5; folded:
 // 4.0e-5).  128 columns per wave leave no registers for a second set.
-constexpr int BK_FOLD = 32;
+constexpr int BK_FOLD = 16;
 constexpr int BT_STRIDE = 132;   // padded LDS row stride (floats) of a wave's 32 x 128 epilogue tile
 
 // LDS byte address of a __shared__ object
@@ -41,12 +41,12 @@ __device__ __forceinline__ void lds_frag(u32x4 &v, uint32_t addr) {
 template <int NB>
 struct BlockFrags { u32x4 w[NB], xh[2], xl[2]; };   // one k-step of a wave
 
-template <int NB>
+template <int NB, int RT>   // RT: row tiles of the workgroup; their lo planes follow the hi planes
 __device__ __forceinline__ void block_read(BlockFrags<NB> &f, uint32_t sbw, uint32_t sbx) {
     lds_frag<0>(f.xh[0], sbx); lds_frag<1024>(f.xh[1], sbx);
     lds_frag<0>(f.w[0], sbw); lds_frag<1024>(f.w[1], sbw);
     if constexpr (NB == 4) { lds_frag<2048>(f.w[2], sbw); lds_frag<3072>(f.w[3], sbw); }
-    lds_frag<BK_RT * 1024>(f.xl[0], sbx); lds_frag<BK_RT * 1024 + 1024>(f.xl[1], sbx);
+    lds_frag<RT * 1024>(f.xl[0], sbx); lds_frag<RT * 1024 + 1024>(f.xl[1], sbx);
 }
 // the fragments are valid after this point (they pass through the wait as operands)
 template <int NB>
@@ -60,9 +60,10 @@ __device__ __forceinline__ void block_wait(BlockFrags<NB> &f) {
                      : "+v"(f.w[0]), "+v"(f.w[1]), "+v"(f.xh[0]), "+v"(f.xh[1]), "+v"(f.xl[0]), "+v"(f.xl[1]) :: "memory");
 }
 
-template <int NB, int NST>
+// WC: waves side by side.  The workgroup's row tiles are 2 * 4 / WC, its column tiles NB * WC.
+template <int NB, int NST, int WC = 2>
 struct BlockSmem {
-    static constexpr int FRAGS = 2 * NB + 2 * BK_RT;   // per stage: weight column tiles, row tiles hi, row tiles lo
+    static constexpr int RT = 8 / WC, CT = NB * WC, FRAGS = CT + 2 * RT;   // per stage: weight column tiles, row tiles hi, row tiles lo
     union {
         uint4 st[NST][FRAGS * 64];
         float tile[4][32 * BT_STRIDE];                 // epilogue: one 32 x 128 tile per wave
@@ -78,13 +79,14 @@ struct BlockSmem {
 // What is not a product has to be short or stand between products: a matrix instruction occupies its pipe for 32 cycles
 // and the wave's other instructions issue meanwhile.  The steady state therefore runs without any condition (NST k-steps
 // per trip, buffers at constant offsets); the last up to 2 NST - 1 k-steps take the general form.
-template <int NB, int NST, int LPW>
+template <int NB, int NST, int WC, int LPW>
 __device__ __forceinline__ void block_loop(f32x16 (&acc)[2][NB], const char *(&base)[LPW], const uint32_t (&vo)[LPW],
-                                           BlockSmem<NB, NST> &sm, int n, int w, int lane) {
-    constexpr int SB = BlockSmem<NB, NST>::FRAGS * 1024;
+                                           BlockSmem<NB, NST, WC> &sm, int n, int w, int lane) {
+    using SM = BlockSmem<NB, NST, WC>;
+    constexpr int SB = SM::FRAGS * 1024;
     static_assert((NST == 4 || NST == 8) && (NST - 1) * LPW <= 63, "the loops below are written for these; the counter of loads in flight has six bits");
     const uint32_t s0 = lds_addr32(sm.st[0]) + lane * 16;
-    const uint32_t ow = s0 + (w & 1) * NB * 1024, ox = s0 + (2 * NB + (w >> 1) * 2) * 1024;
+    const uint32_t ow = s0 + (w % WC) * NB * 1024, ox = s0 + (SM::CT + (w / WC) * 2) * 1024;
     // this wave's i-th fragment of the next k-step to be requested
     auto request1 = [&](int buf, int i) {
         asm volatile("" : "+s"(base[i]));   // stays a scalar address
@@ -112,13 +114,13 @@ __device__ __forceinline__ void block_loop(f32x16 (&acc)[2][NB], const char *(&b
         }
     if (n >= NST) wait_loads<(NST - 1) * LPW>(); else wait_loads<0>();
     barrier_keep_loads();
-    block_read<NB>(fa, ow, ox);
+    block_read<NB, SM::RT>(fa, ow, ox);
     block_wait<NB>(fa);
     auto step = [&](BlockFrags<NB> &cur, BlockFrags<NB> &next, auto buf_c) {   // steady state
         constexpr int buf = decltype(buf_c)::value, nbuf = (buf + 1) % NST;
         wait_loads<(NST - 2) * LPW>();
         barrier_keep_loads();
-        block_read<NB>(next, ow + nbuf * SB, ox + nbuf * SB);
+        block_read<NB, SM::RT>(next, ow + nbuf * SB, ox + nbuf * SB);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 4 * NB; ++j) {
@@ -163,7 +165,7 @@ __device__ __forceinline__ void block_loop(f32x16 (&acc)[2][NB], const char *(&b
 #pragma unroll
                 for (int i = 0; i < LPW; ++i) request1(buf, i);
             }
-            block_read<NB>(next, ow + nbuf * SB, ox + nbuf * SB);
+            block_read<NB, SM::RT>(next, ow + nbuf * SB, ox + nbuf * SB);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
-    block_loop<NB, NST, LPW>(acc, base, vo, sm, n, w, lane);
+    block_loop<NB, NST, 2, LPW>(acc, base, vo, sm, n, w, lane);
 
     if (a.S > 1) {
         // shares meet through memory: [share][row block][column block][wave][(mt, nb, quad)][lane] x 16 bytes
@@ -480,6 +482,120 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
         __syncthreads();
         const int ct = rb * BK_RT + wr * 2 + wc;
         if (wc < nmt) wave_epilogue<EPI>(a, sm.tile[wr * 2 + wc], cb, ct, a.mt0 + ct * a.mt_stride);
+    }
+}
+
+// The rows of the pairs, gathered into tiles of their expert for the blocked gate/up GEMM: (item, 128-column group) per
+// workgroup, from the fp32 residual stream (row-major: 512 contiguous bytes per row; the same hi and lo planes as in the
+// pass's own fragments, where a pair's row is 16 bytes of every 128-byte line: read from there, the GEMM moved eight
+// times the bytes, 590 us for 2048 rows of the 128-expert layer).  Rows past the last pair of a tile repeat it.
+__global__ __launch_bounds__(256) void k_moe_gather(const float *__restrict__ h, const MoeArgs a, uint4 *__restrict__ xhi, uint4 *__restrict__ xlo) {
+    const int item = blockIdx.y, cg = blockIdx.x;
+    if (item >= a.items[0]) return;
+    const int ex = a.items[2 + 2 * item], first = a.items[3 + 2 * item], n = min(64, a.cnt[ex] - first);
+    const int at = a.tile_off[ex] + (first >> 5), rows = ((n + 31) >> 5) << 5;
+    const int *prow = a.pair_row + (size_t)ex * a.cap + first;
+    for (int e = threadIdx.x; e < rows * 16; e += 256) {   // (octet pair, tile, octet, row): a wave reads 64 and writes 1024 bytes per row / fragment
+        const int row = e & 31, tile = rows == 64 ? (e >> 6) & 1 : 0, oct = 2 * (rows == 64 ? e >> 7 : e >> 6) + ((e >> 5) & 1);
+        const int r = prow[min(tile * 32 + row, n - 1)];
+        const float4 *p = (const float4 *)(h + (size_t)r * a.d_in + cg * CG + oct * 8);
+        const float4 v0 = p[0], v1 = p[1];
+        const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        uint4 hi, lo;
+        pack8_split(v, hi, lo);
+        const size_t vec = (size_t)(at + tile) * (a.d_in / 16) * 64 + frag_vec(row, cg * 16 + oct);
+        xhi[vec] = hi;
+        xlo[vec] = lo;
+    }
+}
+
+// Grouped expert GEMMs: the down projection of every pass, gate/up of passes with several rows per expert.  A workgroup
+// owns up to 64 (row, expert) pairs of one expert and 256 columns (four waves side by side, 64 columns each); work items
+// (k_moe_group) are blocks of 64 pairs.  64 rows rather than 128: the pairs of an expert are few and uneven, and rows past
+// them are multiplied for nothing.  Consecutive workgroups of an XCD take the column blocks of one item, then the expert's
+// next item, whose weights are then in that L2.
+// Bound: HBM (the expert weights) up to a few rows per expert, then the matrix cores.  Layer of 128 experts, top 8,
+// d = 2048, expert width 768, microseconds at 1 / 8 / 16 / 64 / 128 row tiles against the streaming kernel with its
+// 32-pair chunks: down 69 / 80 / 92 / 157 / 264 for 75 / 97 / 137 / 429 / 826, gate/up with the gather before it 155 / 174 /
+// 210 / 323 / 516 for 129 / 198 / 314 / 1217 / 2642.
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) {
+    constexpr int NB = 2, NST = 4, WC = 4;
+    using SM = BlockSmem<NB, NST, WC>;
+    constexpr int LPW = SM::FRAGS / 4;
+    __shared__ __attribute__((aligned(16))) SM sm;
+    const int total = a.items[0] * ncb, per8 = (total + 7) >> 3;   // items[0]: number of items, then (expert, first pair) each
+    const int lin = blockIdx.x, i = (lin & 7) * per8 + (lin >> 3);
+    if ((lin >> 3) >= per8 || i >= total) return;
+    const int item = i / opaque_s(ncb), cb = i - item * ncb;
+    const int ex = a.items[2 + 2 * item], first = a.items[3 + 2 * item];
+    const int n = min(64, a.cnt[ex] - first);          // pairs of this item
+    const int at = a.tile_off[ex] + (first >> 5);      // its first activation tile
+    const int tidx = opaque_tid();
+    const int w = __builtin_amdgcn_readfirstlane(tidx >> 6), lane = tidx & 63, half = lane >> 5;
+    const int KS = a.KS;
+    const int *prow = a.pair_row + (size_t)ex * a.cap + first, *pslot = a.pair_slot + (size_t)ex * a.cap + first;
+    const char *base[LPW];
+    uint32_t vo[LPW];
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+        const int f = w * LPW + j;
+        vo[j] = lane * 16;
+        if (f < SM::CT) base[j] = (const char *)(a.W + (size_t)ex * a.wexp_stride + (size_t)min(cb * SM::CT + f, a.N / 32 - 1) * KS * 64);
+        else {
+            const int x = f - SM::CT, rt = min(x & (SM::RT - 1), (n - 1) >> 5);   // a row tile without pairs repeats the first one
+            base[j] = (const char *)((x < SM::RT ? a.Xhi : a.Xlo) + (size_t)(at + rt) * KS * 64);
+        }
+    }
+    f32x16 acc[2][NB];
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
+    block_loop<NB, NST, WC, LPW>(acc, base, vo, sm, KS, w, lane);
+    __syncthreads();   // every wave has read the ring: the epilogue tiles reuse it
+    // two waves make a column group: tile (group w >> 1, row tile mt); wave w finishes row tile w & 1 of its group
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) wave_park<NB>(acc[mt], sm.tile[(w >> 1) * 2 + mt], (w & 1) * 64, lane);
+    __syncthreads();
+    const int mt = w & 1, cg = cb * 2 + (w >> 1), row = lane & 31;
+    if (mt * 32 >= n || cg * CG >= a.N) return;
+    const float *tile = sm.tile[w];
+    if (MODE == MOE_GATEUP) {
+        const float rs = wave_rstd(a.ssq_in, prow[min(mt * 32 + row, n - 1)], half, a.ncg_in, a.d_in, a.eps);
+#pragma unroll 1
+        for (int j = 0; j < 4; ++j) {
+            const int oct = 2 * j + half;
+            const float *g = tile + row * BT_STRIDE + oct * 8, *u = g + 64;
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float ge = g[e] * rs;
+                v[e] = ge / (1.f + expf(-ge)) * (u[e] * rs);
+            }
+            uint4 hi, lo;
+            pack8_split(v, hi, lo);
+            const size_t vec = (size_t)(at + mt) * (a.Fe / 16) * 64 + frag_vec(row, cg * 8 + oct);
+            a.ahi[vec] = hi;
+            a.alo[vec] = lo;
+        }
+    } else {
+        // lane l knows pair l & 31 of the tile; rows 2 j + half, 512 bytes each
+        const int q = mt * 32 + row;
+        const int pr = q < n ? prow[q] : -1, sl = q < n ? pslot[q] : 0;
+        const float wgt = q < n ? a.route_w[pr * 8 + sl] : 0.f;
+        const int c4 = row * 4;
+#pragma unroll 4
+        for (int j = 0; j < 16; ++j) {
+            const int r = 2 * j + half;
+            const int p = __builtin_amdgcn_ds_bpermute(r << 2, pr), s = __builtin_amdgcn_ds_bpermute(r << 2, sl);
+            const float g = __int_as_float(__builtin_amdgcn_ds_bpermute(r << 2, __float_as_int(wgt)));
+            if (p < 0) continue;
+            const float4 y = *(const float4 *)(tile + r * BT_STRIDE + c4);
+            *(float4 *)(a.moe_out + ((size_t)p * 8 + s) * a.d + (size_t)cg * CG + c4) = make_float4(y.x * g, y.y * g, y.z * g, y.w * g);
+        }
     }
 }
 

@@ -1342,28 +1342,51 @@ __global__ __launch_bounds__(512) void k_gemm_narrow(const GemmArgs a, int ngrp,
 }
 
 // ------------------------------------------------------------------------------------------
-// one block: cnt[e], and for pair i of expert e the pass row and its routing slot
-__global__ __launch_bounds__(256) void k_moe_group(const int *__restrict__ route_e, const int *__restrict__ row_slot,
-                                                   int rows, int top_k, int n_experts, int cap, int *__restrict__ cnt,
-                                                   int *__restrict__ pair_row, int *__restrict__ pair_slot,
-                                                   unsigned long long *__restrict__ touched_total) {
-    __shared__ int s_cnt[128];
-    if (threadIdx.x < 128) s_cnt[threadIdx.x] = 0;
+// One block: cnt[e]; for pair i of expert e the pass row and its routing slot; tile_off[e]: the 32-pair activation tiles of
+// the experts before e; items: [0] number of 64-pair work items, from [2] on (expert, first pair) of each.
+// One row per thread and trip: a pass of 2048 rows takes two trips of eight LDS atomics per thread.
+__global__ __launch_bounds__(1024) void k_moe_group(const int *__restrict__ route_e, const int *__restrict__ row_slot,
+                                                    int rows, int top_k, int n_experts, int cap, int *__restrict__ cnt,
+                                                    int *__restrict__ pair_row, int *__restrict__ pair_slot,
+                                                    int *__restrict__ tile_off, int *__restrict__ items,
+                                                    unsigned long long *__restrict__ touched_total) {
+    __shared__ int s_cnt[128], s_tiles[128], s_items[128];
+    const int tid = threadIdx.x;
+    if (tid < 128) s_cnt[tid] = 0;
     __syncthreads();
-    for (int p = threadIdx.x; p < rows * top_k; p += 256) {
-        const int row = p / top_k, j = p % top_k;
+    for (int row = tid; row < rows; row += 1024) {
         if (row_slot[row] < 0) continue;                 // unused rows of a tile route nowhere
-        const int e = route_e[row * 8 + j];
-        const int i = atomicAdd(&s_cnt[e], 1);           // order inside an expert does not affect results
-        pair_row[e * cap + i] = row;
-        pair_slot[e * cap + i] = j;
+        const int4 e0 = *(const int4 *)(route_e + row * 8), e1 = *(const int4 *)(route_e + row * 8 + 4);
+        const int ev[8] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y, e1.z, e1.w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (j >= top_k) break;
+            const int e = ev[j];
+            const int i = atomicAdd(&s_cnt[e], 1);       // order inside an expert does not affect results
+            pair_row[e * cap + i] = row;
+            pair_slot[e * cap + i] = j;
+        }
     }
     __syncthreads();
-    if (threadIdx.x < n_experts) {
-        cnt[threadIdx.x] = s_cnt[threadIdx.x];
-        // running count of (layer, expert) pairs whose weights a pass has to stream (for byte accounting)
-        if (s_cnt[threadIdx.x] > 0) atomicAdd(touched_total, 1ULL);
+    const int n = tid < n_experts ? s_cnt[tid] : 0;
+    if (tid < 128) { s_tiles[tid] = (n + 31) >> 5; s_items[tid] = (n + 63) >> 6; }
+    __syncthreads();
+    for (int off = 1; off < 128; off <<= 1) {            // running sums over the experts
+        int a = 0, b = 0;
+        if (tid < 128 && tid >= off) { a = s_tiles[tid - off]; b = s_items[tid - off]; }
+        __syncthreads();
+        if (tid < 128) { s_tiles[tid] += a; s_items[tid] += b; }
+        __syncthreads();
     }
+    if (tid < n_experts) {
+        cnt[tid] = n;
+        tile_off[tid] = s_tiles[tid] - ((n + 31) >> 5);
+        const int k = (n + 63) >> 6, first = s_items[tid] - k;
+        for (int j = 0; j < k; ++j) { items[2 + 2 * (first + j)] = tid; items[3 + 2 * (first + j)] = j * 64; }
+        // running count of (layer, expert) pairs whose weights a pass has to stream (for byte accounting)
+        if (n > 0) atomicAdd(touched_total, 1ULL);
+    }
+    if (tid == 127) items[0] = s_items[127];
 }
 
 enum { MOE_GATEUP = 0, MOE_DOWN = 1 };
@@ -1371,27 +1394,24 @@ enum { MOE_GATEUP = 0, MOE_DOWN = 1 };
 struct MoeArgs {
     const uint4 *W; size_t wexp_stride;      // expert e's matrix at W + e * wexp_stride (16-byte units)
     const uint4 *Xhi, *Xlo;                  // GATEUP: the pass's fragments of h; DOWN: activation tiles
-    int N, KS, cap, chunks;
-    const int *cnt, *pair_row, *pair_slot;
+    int N, KS, cap;
+    const int *cnt, *pair_row, *pair_slot, *tile_off, *items;
     const float *ssq_in; int ncg_in, d_in; float eps;   // GATEUP: RMSNorm scale of each pair's row
-    uint4 *ahi, *alo; int Fe;                // GATEUP out: activation tile (e*chunks + chunk), Fe/16 k-steps
+    uint4 *ahi, *alo; int Fe;                // GATEUP out: activation tile tile_off[e] + chunk, Fe/16 k-steps
     const float *route_w; float *moe_out; int d;        // DOWN out: moe_out[row][slot][d] = w * y
 };
 
-#ifndef DEER_MOE_CGS
-#define DEER_MOE_CGS 2
-#endif
-constexpr int MOE_CGS = DEER_MOE_CGS;   // column groups per workgroup of the grouped expert GEMMs
+constexpr int MOE_CGS = 2;   // column groups per workgroup of the streaming gate/up GEMM
+// Gate/up of passes with few rows per expert (see k_moe_block for the others and for the down projection).
 // grid: x = MOE_CGS column groups, y = expert, z = chunk of 32 pairs.  Same streaming loop and wave tree as k_gemm.
 // A workgroup does MOE_CGS column groups one after the other and requests the first k-steps of the next before it
 // sums and stores the current one: with one workgroup per CU at a time, a launch of many short work items otherwise
 // leaves the memory pipe idle during every item's wave sum, epilogue and first-load latency.
-template <int MODE>
 __global__ __launch_bounds__(512) void k_gemm_moe(const MoeArgs a) {
     __shared__ float red[8 * 32 * 128];
     __shared__ float tile[32 * RED_STRIDE];
     __shared__ float s_rstd[32];
-    __shared__ int s_row[32], s_slot[32];
+    __shared__ int s_row[32];
     const int ex = blockIdx.y, chunk = blockIdx.z;
     const int n = a.cnt[ex] - chunk * 32;
     if (n <= 0) return;
@@ -1401,10 +1421,9 @@ __global__ __launch_bounds__(512) void k_gemm_moe(const MoeArgs a) {
     if (threadIdx.x < 32) {
         const bool v = threadIdx.x < n;
         s_row[threadIdx.x] = v ? a.pair_row[ex * a.cap + chunk * 32 + threadIdx.x] : -1;
-        s_slot[threadIdx.x] = v ? a.pair_slot[ex * a.cap + chunk * 32 + threadIdx.x] : 0;
     }
     __syncthreads();
-    if (MODE == MOE_GATEUP && threadIdx.x < 32) {   // RMSNorm factor of each pair's row
+    if (threadIdx.x < 32) {   // RMSNorm factor of each pair's row
         float sc = 0.f;
         const int r = s_row[threadIdx.x];
         if (r >= 0) {
@@ -1419,16 +1438,10 @@ __global__ __launch_bounds__(512) void k_gemm_moe(const MoeArgs a) {
     const int per = (KS + 7) / 8;
     const int ks0 = w * per, ks1 = min(KS, ks0 + per);
     const size_t wstride = (size_t)KS * 64;
-    // activation fragment of this lane: GATEUP gathers the pair's own row out of the pass's tiles
-    const uint4 *xh, *xl;
-    if (MODE == MOE_GATEUP) {
-        const int r = myrow < 0 ? 0 : myrow;
-        const size_t off = ((size_t)(r >> 5) * KS) * 64 + (r & 31) + 32 * half;
-        xh = a.Xhi + off; xl = a.Xlo + off;
-    } else {
-        const size_t off = ((size_t)(ex * a.chunks + chunk) * KS) * 64 + lane;
-        xh = a.Xhi + off; xl = a.Xlo + off;
-    }
+    // activation fragment of this lane: the pair's own row, gathered out of the pass's tiles
+    const int xr = myrow < 0 ? 0 : myrow;
+    const size_t xoff = ((size_t)(xr >> 5) * KS) * 64 + (xr & 31) + 32 * half;
+    const uint4 *xh = a.Xhi + xoff, *xl = a.Xlo + xoff;
     const bool live = myrow >= 0;
     const u32x4 z4 = {0u, 0u, 0u, 0u};
     // D k-steps of loads in flight, issued and waited for by hand (see gemm_block)
@@ -1480,33 +1493,20 @@ __global__ __launch_bounds__(512) void k_gemm_moe(const MoeArgs a) {
         }
         if (it + 1 < MOE_CGS && cg + 1 < ncg) first_loads(cg + 1);   // on their way during the sum and the epilogue below
         reduce_waves_to_tile(acc, red, tile, w, lane);
-        if (MODE == MOE_GATEUP) {
-            for (int item = threadIdx.x; item < 256; item += blockDim.x) {
-                const int row = item & 31, oct = item >> 5;
-                float v[8];
+        for (int item = threadIdx.x; item < 256; item += blockDim.x) {
+            const int row = item & 31, oct = item >> 5;
+            float v[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    float g = tile[row * RED_STRIDE + oct * 8 + e] * s_rstd[row];
-                    float u = tile[row * RED_STRIDE + 64 + oct * 8 + e] * s_rstd[row];
-                    v[e] = g / (1.f + expf(-g)) * u;
-                }
-                uint4 hi, lo;
-                pack8_split(v, hi, lo);
-                size_t vec = (size_t)(ex * a.chunks + chunk) * (a.Fe / 16) * 64 + frag_vec(row, cg * 8 + oct);
-                a.ahi[vec] = hi;
-                a.alo[vec] = lo;
+            for (int e = 0; e < 8; ++e) {
+                float g = tile[row * RED_STRIDE + oct * 8 + e] * s_rstd[row];
+                float u = tile[row * RED_STRIDE + 64 + oct * 8 + e] * s_rstd[row];
+                v[e] = g / (1.f + expf(-g)) * u;
             }
-        } else {
-            for (int e = threadIdx.x; e < 32 * 32; e += blockDim.x) {
-                const int row = e >> 5, c4 = (e & 31) * 4;
-                const int pr = s_row[row];
-                if (pr < 0) continue;
-                const int slot = s_slot[row];
-                const float wgt = a.route_w[pr * 8 + slot];
-                const float *tp = tile + row * RED_STRIDE + c4;
-                *(float4 *)(a.moe_out + ((size_t)pr * 8 + slot) * a.d + cg * CG + c4) =
-                    make_float4(tp[0] * wgt, tp[1] * wgt, tp[2] * wgt, tp[3] * wgt);
-            }
+            uint4 hi, lo;
+            pack8_split(v, hi, lo);
+            size_t vec = (size_t)(a.tile_off[ex] + chunk) * (a.Fe / 16) * 64 + frag_vec(row, cg * 8 + oct);
+            a.ahi[vec] = hi;
+            a.alo[vec] = lo;
         }
         __syncthreads();   // the tile is read: the next column group's sum may overwrite it
     }

@@ -59,3 +59,29 @@ def test_blocked_and_streaming_kernels_agree(engine, lens, k):
     for a, b in ((zd0, zd1), (zt0, zt1), (zd0, zd2), (zt0, zt2)):
         off = np.linalg.norm(a - b, axis=-1) / np.linalg.norm(a, axis=-1)   # per row
         assert np.isfinite(b).all() and float(off.max()) < TOL, (lens, float(off.max()))
+
+
+@pytest.mark.parametrize("lens", [[7], [65], [190, 3], [700, 33, 1]])
+def test_grouped_gemms_of_a_mixture(lens):
+    """Experts with fewer and more than 32 and 64 pairs, 384 = one and a half 256-column blocks, an expert width of three
+    64-channel groups: gathered rows and blocked gate/up (from 12 pairs per expert on) against the streaming gate/up and
+    the oracle."""
+    import torch
+    from gpu_common import make_pair
+    t = di.ModelShape(2, 384, 6, 3, 64, 0, 1024, n_experts=12, top_k=3, d_ff_expert=192, rope_base=1e4)
+    d, k = di.CONFIGS["tiny"]["drafter"], 8
+    wt, wd = StoredWeights(t, di.TARGET_SEED, "bf16"), StoredWeights(d, di.DRAFTER_SEED, "bf16")
+    eng = make_engine(t, d, wt, wd, len(lens), 1024, k)
+    prompts = [di.prompt_ids(t.vocab, n, seq=20 + b) for b, n in enumerate(lens)]
+    blocks = np.random.default_rng(2).integers(0, t.vocab, (len(lens), k)).astype(np.int32)
+    got = []
+    for mode in (0, 128):
+        eng.debug_gemm_tiled(mode)
+        got.append(_pass(eng, prompts, k, 0.0, blocks, torch)[1])
+    for b, prompt in enumerate(prompts):
+        pair = make_pair(t, d, wt, wd, 1024)
+        pair.prefill(prompt)
+        z = pair.verify_logits([int(v) for v in blocks[b]])
+        for g in got:
+            assert np.abs(g[b] - z).max() < 2e-3, (lens, b, np.abs(g[b] - z).max())   # the small mixture's bound in the lock-step test
+    eng.close()
