@@ -470,9 +470,10 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
         LAUNCHCHK(c, "k_attn_head");
         return DEER_OK;
     }
-    hipLaunchKernelGGL(k_attn<HD>, dim3(mc.n_kv_heads * NS, ntiles), dim3(512), 0, c->stream, w.q_hi, w.q_lo, K, Vt,
-                       m.kv_seq_stride, m.kv_head_stride, c->p.max_seq, w.rm.tile_seq, w.rm.limit, w.opart,
-                       mc.n_q_heads, mc.n_kv_heads, NS, scale_log2e, w.xb_hi, w.xb_lo);
+    const int HG = (mc.n_q_heads / mc.n_kv_heads + ATT_HEADS - 1) / ATT_HEADS;
+    hipLaunchKernelGGL(k_attn<HD>, dim3(mc.n_kv_heads * HG * NS, ntiles), dim3(256), 0, c->stream, w.q_hi, w.q_lo, K, Vt,
+                       m.kv_seq_stride, m.kv_head_stride, w.rm.tile_seq, w.rm.limit, w.opart,
+                       mc.n_q_heads, mc.n_kv_heads, HG, NS, scale_log2e, w.xb_hi, w.xb_lo);
     LAUNCHCHK(c, "k_attn");
     if (NS > 1) {
         const int n_items = ntiles * mc.n_q_heads * (HD / 32) * 2;
@@ -514,10 +515,11 @@ int run_pass(deer_ctx *c, int model, int ntiles, int max_limit, const LmPlan &lm
         LAUNCHCHK(c, "k_rope_table");
     }
     const int nkt = (max_limit + 31) / 32;
-    // key-range splits: aim at one workgroup per compute unit; a split holds at least one staged chunk of 4 key
-    // tiles; ntiles * NS never exceeds the partial buffer (max(64, most tiles of a pass) tile slots)
+    // key-range splits: aim at two workgroups per compute unit; a split holds at least four key tiles; ntiles * NS never
+    // exceeds the partial buffer (max(64, most tiles of a pass) tile slots)
     constexpr int ns_target = 256;
-    int NS = (ns_target + mc.n_kv_heads * ntiles - 1) / (mc.n_kv_heads * ntiles);
+    const int attn_items = mc.n_kv_heads * ((mc.n_q_heads / mc.n_kv_heads + ATT_HEADS - 1) / ATT_HEADS) * ntiles;
+    int NS = (2 * ns_target + attn_items - 1) / attn_items;
     NS = std::max(1, std::min({NS, MAX_NS, std::max(1, std::max(64, c->max_tiles) / ntiles), (nkt + 3) / 4}));
     // Passes of few tiles (decoding) run attention per query head: (tile, head, key range) workgroups, about one per
     // compute unit, as long as a wave then has at most ATT_HEAD_MAX_TILES key tiles of its range to go through

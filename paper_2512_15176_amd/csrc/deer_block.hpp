@@ -29,15 +29,6 @@ constexpr int BK_RT = 4;     // row tiles per workgroup of k_gemm_block
 constexpr int BK_FOLD = 16;
 constexpr int BT_STRIDE = 132;   // padded LDS row stride (floats) of a wave's 32 x 128 epilogue tile
 
-// LDS byte address of a __shared__ object
-__device__ __forceinline__ uint32_t lds_addr32(const void *p) {
-    return (uint32_t)(size_t)(const void __attribute__((address_space(3))) *)p;
-}
-template <int OFF>
-__device__ __forceinline__ void lds_frag(u32x4 &v, uint32_t addr) {
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(v) : "v"(addr), "n"(OFF));
-}
-
 template <int NB>
 struct BlockFrags { u32x4 w[NB], xh[2], xl[2]; };   // one k-step of a wave
 

@@ -15,6 +15,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <type_traits>
+#include <utility>
 #include <stdint.h>
 
 namespace deer {
@@ -126,6 +127,23 @@ __device__ __forceinline__ void wait_steps(int steps) {
     else wait_loads<4 * PER>();
 }
 __device__ __forceinline__ void tie(u32x4 &r) { asm volatile("" : "+v"(r)); }
+
+// Fragments that direct-to-LDS loads have put into LDS are read with instructions the compiler does not see as LDS reads:
+// before one of those, of memory that such loads may write, it waits for ALL loads in flight, the ones requested ahead
+// included.  The caller's counted waits and barriers order the reads after their own loads, and a fragment is valid after
+// wait_lds<N>() (at most N younger LDS reads outstanding) and tie().
+// LDS byte address of a __shared__ object
+__device__ __forceinline__ uint32_t lds_addr32(const void *p) {
+    return (uint32_t)(size_t)(const void __attribute__((address_space(3))) *)p;
+}
+template <int OFF>
+__device__ __forceinline__ void lds_frag(u32x4 &v, uint32_t addr) {
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(v) : "v"(addr), "n"(OFF));
+}
+template <int N>
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }
+template <int OFF, int... I>
+__device__ __forceinline__ void lds_frags(u32x4 *v, uint32_t addr, std::integer_sequence<int, I...>) { (lds_frag<OFF + 1024 * I>(v[I], addr), ...); }
 
 // Workgroup barrier for loops that keep direct-to-LDS loads in flight across it: __syncthreads() waits for every
 // outstanding vector memory operation of the wave (its fence covers the LDS writes of those loads), which would
@@ -1671,241 +1689,201 @@ __device__ __forceinline__ void attn_write_frag(const f32x16 *o, float inv, int 
 }
 
 // ------------------------------------------------------------------------------------------
-// Block attention item for a whole workgroup of 8 waves: passes of many row tiles or long key ranges (k_attn).
-//  - one (row tile, kv head, key-range split) item per workgroup; wave w serves query head (w & 3) of the
-//    GQA group on the key tiles of parity (w >> 2) of each staged chunk, so two waves per SIMD overlap;
-//  - the K and V fragments of a chunk of ATT_CH 32-key tiles are requested by the eight waves together (every
-//    fragment fetched once per workgroup instead of once per query head) and land in LDS in fragment order
-//    (direct-to-LDS loads, no registers held while they travel); ATT_NBUF chunk buffers form a ring, so
-//    ATT_NBUF - 1 chunks are on their way while one is multiplied, with one barrier per chunk;
-//  - Q fragments stay in registers, loaded by every wave for its own head;
-//  - the two key parities of a head are combined through LDS, then the result goes to the output
-//    projection's input (NS == 1) or to an un-normalised partial (M, L, O) for the merge.
-// b: the tile's sequence; lim: the key limit of this lane's query row.
+// Block attention of passes of many row tiles or long key ranges: one (row tile, up to four query heads of a kv head, key
+// range) item per workgroup of four waves, two workgroups per compute unit.
+//  - wave = query head: every key tile of the range goes through all four waves, so that a tile's K and V fragments are
+//    fetched once per workgroup.  They land in LDS in fragment order (direct-to-LDS loads, no registers held while they
+//    travel), two tiles at a time: one pair is on its way while the other is multiplied, with one barrier per pair;
+//  - a pair shares one softmax step (one maximum over 64 keys, one rescale of O), and the products of its two tiles, and of
+//    the O^T tiles, are interleaved chains;
+//  - Q fragments stay in registers;
+//  - the two workgroups of a compute unit share nothing and drift apart, so that the products of one run under the softmax
+//    of the other;
+//  - the result goes to the output projection's input (NS == 1) or to an un-normalised partial (M, L, O) for the merge.
+// Bound: the chain products -> softmax -> products of two waves per SIMD, at the clock that is left when matrix cores and
+// HBM are both busy (counted: 1.84 GHz and the matrix pipe busy 58 % of a long-context launch).  Microseconds per launch
+// against one workgroup of eight waves, two per head, behind one barrier: 8B heads, 16 sequences x 32768 keys 565 -> 536
+// (4.0 TB/s of K and V), prompt of 4096 341 -> 268, batch of prompts (104 tiles) 73 -> 51; drafter, prompt of 4096
+// 138 -> 96.  A ring of four single tiles took 544 and 290 (drafter 114).
 // ------------------------------------------------------------------------------------------
 #ifndef DEER_ATT_P_LO
 #define DEER_ATT_P_LO 1
 #endif
 constexpr bool ATT_P_LO = DEER_ATT_P_LO != 0;   // the low-order bf16 plane of the softmax weights enters P V
-constexpr int ATT_CH = 2;     // key tiles per staged chunk: one per key parity
-constexpr int ATT_NBUF = 4;   // chunk buffers: ATT_NBUF - 1 chunks (96 KB) are on their way while one is multiplied
+constexpr int ATT_HEADS = 4;                    // query heads per workgroup
+template <int HD>
 struct AttnSmem {
-    uint4 buf[ATT_NBUF][ATT_CH * 16 * 64];   // [tile][fragment: K k-steps, then V (tile, half) pairs][lane]; 4 x 32 KB
-    float2 ml[4 * 64];                       // parked (m, l) of the odd-parity waves
+    static constexpr int FPT = HD / 8;   // fragments of 1 KB per key tile (K k-steps, then V (tile, half) pairs)
+    uint4 buf[2][2][FPT * 64];           // two pairs of key tiles
 };
 
-// FRAGS_EARLY: all K fragments of a tile are requested from LDS before the first product and the V fragments
-// before the softmax, so the matrix pipe does not wait for one LDS read per two products.
-template <int HD, bool FRAGS_EARLY = false>
-__device__ __forceinline__ void attn_item(const uint4 *Qhi, const uint4 *Qlo, const uint16_t *__restrict__ Kc,
-                                          const uint16_t *__restrict__ Vt, size_t seq_stride, size_t head_stride,
-                                          int max_seq, int b, int lim, float *part, int Hq, int Hkv, int NS,
-                                          float scale_log2e, uint4 *xhi, uint4 *xlo, AttnSmem &as, int kvh, int split, int t) {
-    constexpr int KSQ = HD / 16, HT = HD / 32, FPT = KSQ + 2 * HT;   // fragments per tile
-    constexpr int LPW = ATT_CH * FPT / 8;                            // staging loads per wave and chunk
+// grid: x = kv_head + Hkv * (group of four heads + HG * split), y = pass tile counted from the last (prompts: the longest
+// key ranges start first); 256 threads
+template <int HD>
+__global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, const uint4 *__restrict__ Qlo,
+                                                 const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Vt,
+                                                 size_t seq_stride, size_t head_stride,
+                                                 const int *__restrict__ tile_seq, const int *__restrict__ row_limit,
+                                                 float *__restrict__ part, int Hq, int Hkv, int HG, int NS, float scale_log2e,
+                                                 uint4 *__restrict__ xhi, uint4 *__restrict__ xlo) {
+    using SM = AttnSmem<HD>;
+    constexpr int KSQ = HD / 16, HT = HD / 32, FPT = SM::FPT, LPW = FPT / 4;
     constexpr int PF = AttnPartial<HD>::FLOATS;
+    __shared__ __attribute__((aligned(16))) SM as;
     const int tidx = opaque_tid();
     const int w = __builtin_amdgcn_readfirstlane(tidx >> 6), lane = tidx & 63;   // the wave index as a scalar
-    const int G = Hq / opaque_s(Hkv);
-    // up to four query heads per kv head: wave = (head, key-tile parity); more: wave = head, every key tile, so
-    // that eight heads share one pass over the keys instead of two
-    const bool wide = G > 4;
-    const int g = wide ? w : (w & 3), par = wide ? 0 : (w >> 2);
-    const int npar = wide ? 1 : 2, hpr = wide ? 8 : 4;   // key parities; heads per round
     const int half = lane >> 5, qrow = lane & 31;
+    const int t = gridDim.y - 1 - blockIdx.y;
+    const int kvh = blockIdx.x % opaque_s(Hkv), xr = blockIdx.x / opaque_s(Hkv), hg = xr % opaque_s(HG), split = xr / opaque_s(HG);
+    const int G = Hq / opaque_s(Hkv), g = hg * ATT_HEADS + w;
+    const bool active = g < G;
+    const int head = kvh * G + min(g, G - 1);
+    const int b = tile_seq[t], lim = row_limit[t * 32 + qrow];   // lim: the key limit of this lane's query row
     int maxlim = lim, minlim = lim;
 #pragma unroll
     for (int off = 1; off < 32; off <<= 1) {
         maxlim = max(maxlim, shx(maxlim, off));
         minlim = min(minlim, shx(minlim, off));
     }
+    maxlim = __builtin_amdgcn_readfirstlane(maxlim);
+    minlim = __builtin_amdgcn_readfirstlane(minlim);
     const int nkt = (maxlim + 31) >> 5;
     const int per = (nkt + NS - 1) / opaque_s(NS);
-    const int kt0 = split * per, kt1 = min(nkt, kt0 + per);
-    const int nchunks = kt1 > kt0 ? (kt1 - kt0 + ATT_CH - 1) / ATT_CH : 0;
-    const uint16_t *Kp = Kc + (size_t)b * seq_stride + (size_t)kvh * head_stride;
-    const uint16_t *Vp = Vt + (size_t)b * seq_stride + (size_t)kvh * head_stride;
-
-    // Requests this wave's share of a chunk (fragment f = w + 8 * i) straight into LDS: a 16-byte
-    // direct-to-LDS load writes lane l's vector at (uniform base) + 16 * l, which is the fragment order, and
-    // needs no registers while it travels.  Tiles past the range repeat the last one (not used).
-    auto stage = [&](uint4 *dst, int c0) {
-        const int ntile = min(ATT_CH, kt1 - c0);
-        // the lane offset (elements) is rebuilt here from a small value, so that 64-bit addresses per lane do not
-        // live (spilled) across the whole item
-        int lo8 = lane * 8;
-        asm volatile("" : "+v"(lo8));
+    const int kt0 = split * per, n = max(0, min(nkt, kt0 + per) - kt0);
+    const char *Kp = (const char *)(Kc + (size_t)b * seq_stride + (size_t)kvh * head_stride) + (size_t)kt0 * (64 * HD);
+    const char *Vp = (const char *)(Vt + (size_t)b * seq_stride + (size_t)kvh * head_stride) + (size_t)kt0 * (64 * HD);
+    // this wave's share of a key tile: fragments w LPW .. + LPW - 1, straight into LDS (lane l's 16 bytes land at base + 16 l).
+    // Half of the waves fetch K, half V.  A pair's second tile past the range repeats the last one (finite values, weight 0).
+    const char *src = (w < 2 ? Kp : Vp) + (w & 1) * LPW * 1024 + lane * 16;
+    auto stage = [&](int buf, int pair) {
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            const int f = w + 8 * i, tl = f / FPT, fi = f % FPT;
-            const int kt = c0 + min(tl, ntile - 1);
-            const uint16_t *src;   // both caches hold a key tile as HD / 16 fragments of 1 KB
-            if (fi < KSQ) src = Kp + (lo8 + kt * (32 * HD) + fi * 512);
-            else src = Vp + (lo8 + kt * (32 * HD) + (fi - KSQ) * 512);
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)src,
-                                             (void __attribute__((address_space(3))) *)(dst + f * 64), 16, 0, 0);
+        for (int j = 0; j < 2; ++j) {
+            const char *p = src + (size_t)min(2 * pair + j, n - 1) * (64 * HD);
+#pragma unroll
+            for (int f = 0; f < LPW; ++f)
+                __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(p + f * 1024),
+                                                 (void __attribute__((address_space(3))) *)(as.buf[buf][j] + (w * LPW + f) * 64), 16, 0, 0);
         }
     };
-
-    for (int g0 = 0; g0 < G; g0 += hpr) {
-        const bool active = g0 + g < G;
-        const int head = kvh * G + min(g0 + g, G - 1);
-        f32x16 oacc[HT];
+    const uint32_t ring = lds_addr32(as.buf[0][0]) + lane * 16;
+    f32x16 oacc[HT];
 #pragma unroll
-        for (int tt = 0; tt < HT; ++tt)
+    for (int tt = 0; tt < HT; ++tt)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[tt][r] = 0.f;
-        float m_run = -INFINITY, l_run = 0.f;
-
-        if (nchunks > 0) {
-            uint4 qh[KSQ], ql[KSQ];
-            __syncthreads();   // the previous head round or item has been read
-            {   // this wave's Q fragments (requested first: every later wait covers them)
-                const size_t qb = ((size_t)(t * Hq + head) * KSQ) * 64 + lane;
+        for (int r = 0; r < 16; ++r) oacc[tt][r] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    if (n > 0) {
+        const int np = (n + 1) >> 1;
+        uint4 qh[KSQ], ql[KSQ];
+        {   // this wave's Q fragments (requested first: every later wait covers them)
+            const size_t qb = ((size_t)(t * Hq + head) * KSQ) * 64 + lane;
 #pragma unroll
-                for (int s = 0; s < KSQ; ++s) { qh[s] = Qhi[qb + (size_t)s * 64]; ql[s] = Qlo[qb + (size_t)s * 64]; }
-            }
+            for (int s = 0; s < KSQ; ++s) { qh[s] = Qhi[qb + (size_t)s * 64]; ql[s] = Qlo[qb + (size_t)s * 64]; }
+        }
+        stage(0, 0);
+        for (int i = 0; i < np; ++i) {
+            wait_loads<0>();
+            barrier_keep_loads();   // every wave's share of pair i is in LDS, and pair i - 1 has been read by all
+            if (i + 1 < np) stage((i + 1) & 1, i + 1);
+            if (!active) continue;
+            const uint32_t fr = ring + (i & 1) * (2 * FPT * 1024);
+            // S^T of both tiles: one chain of products per tile, interleaved
+            f32x16 sacc[2];
 #pragma unroll
-            for (int c = 0; c < ATT_NBUF - 1; ++c)
-                if (c < nchunks) stage(as.buf[c], kt0 + c * ATT_CH);
-
-            for (int ci = 0; ci < nchunks; ++ci) {
-                const int c0 = kt0 + ci * ATT_CH;
-                const int ntile = min(ATT_CH, kt1 - c0);
-                // chunk ci has landed once at most the loads of the chunks requested after it are outstanding
-                const int later = min(ATT_NBUF - 2, nchunks - 1 - ci);
-                if (later >= 2) wait_loads<2 * LPW>(); else if (later == 1) wait_loads<LPW>(); else wait_loads<0>();
-                barrier_keep_loads();   // every wave's share of chunk ci is in LDS, and chunk ci - 1 has been read by all
-                if (ci + ATT_NBUF - 1 < nchunks) stage(as.buf[(ci + ATT_NBUF - 1) % ATT_NBUF], c0 + (ATT_NBUF - 1) * ATT_CH);
-                if (active)
-                for (int tl = par; tl < ntile; tl += npar) {
-                    const int kt = c0 + tl;
-                    const uint4 *fr = as.buf[ci % ATT_NBUF] + (size_t)(tl * FPT) * 64 + lane;
-                    f32x16 sacc;
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
-                    uint4 kf[KSQ], vfr[HT * 2];
-                    if (FRAGS_EARLY) {
+                for (int r = 0; r < 16; ++r) sacc[j][r] = 0.f;
+            u32x4 kf[2][2][KSQ / 2];   // [half of the k-steps][tile]
+            lds_frags<0>(kf[0][0], fr, std::make_integer_sequence<int, KSQ / 2>{});
+            lds_frags<FPT * 1024>(kf[0][1], fr, std::make_integer_sequence<int, KSQ / 2>{});
+            lds_frags<KSQ / 2 * 1024>(kf[1][0], fr, std::make_integer_sequence<int, KSQ / 2>{});
+            lds_frags<FPT * 1024 + KSQ / 2 * 1024>(kf[1][1], fr, std::make_integer_sequence<int, KSQ / 2>{});
 #pragma unroll
-                        for (int s = 0; s < KSQ; ++s) kf[s] = fr[s * 64];
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+            for (int h2 = 0; h2 < 2; ++h2) {
+                if (h2 == 0) wait_lds<KSQ>(); else wait_lds<0>();
 #pragma unroll
-                    for (int s = 0; s < KSQ; ++s) {
-                        if (!FRAGS_EARLY) kf[s] = fr[s * 64];
-                        sacc = mfma32(kf[s], qh[s], sacc);
-                        sacc = mfma32(kf[s], ql[s], sacc);
-                    }
-                    if (FRAGS_EARLY) {
-#pragma unroll
-                        for (int i = 0; i < HT * 2; ++i) vfr[i] = fr[(KSQ + i) * 64];
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    // lane holds keys kt*32 + 16*half + r, r = 0..15, for query row qrow
-                    const int key0 = kt * 32 + 16 * half;
-                    if (kt * 32 + 32 > minlim) {   // only tiles that reach some row's limit need the mask
-#pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            if (key0 + r >= lim) sacc[r] = -INFINITY;
-                    }
-                    float mx = sacc[0];
-#pragma unroll
-                    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
-                    mx = fmaxf(mx, shx(mx, 32));
-                    const float m_new = fmaxf(m_run, mx);
-                    float pr[16];
-                    if (m_new == -INFINITY) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) pr[r] = 0.f;
-                    } else {
-                        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);   // m_run = -inf -> 0
-                        const float mb = m_new * scale_log2e;
-                        float ls = 0.f;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) { pr[r] = __builtin_amdgcn_exp2f(sacc[r] * scale_log2e - mb); ls += pr[r]; }
-                        l_run = l_run * alpha + ls;
-                        m_run = m_new;
-                        if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {   // the running max moved for some row
-#pragma unroll
-                            for (int tt = 0; tt < HT; ++tt)
-#pragma unroll
-                                for (int r = 0; r < 16; ++r) oacc[tt][r] *= alpha;
-                        }
-                    }
-                    uint4 ph[2], pl[2];
-                    pack8_split(pr, ph[0], pl[0]);
-                    pack8_split(pr + 8, ph[1], pl[1]);
-#pragma unroll
-                    for (int tt = 0; tt < HT; ++tt)
-#pragma unroll
-                        for (int s2 = 0; s2 < 2; ++s2) {
-                            const uint4 vf = FRAGS_EARLY ? vfr[tt * 2 + s2] : fr[(KSQ + tt * 2 + s2) * 64];
-                            oacc[tt] = mfma32(vf, ph[s2], oacc[tt]);
-                            if (ATT_P_LO) oacc[tt] = mfma32(vf, pl[s2], oacc[tt]);
-                        }
+                for (int s = 0; s < KSQ / 2; ++s) {
+                    const int ss = h2 * (KSQ / 2) + s;
+                    tie(kf[h2][0][s]); tie(kf[h2][1][s]);
+                    sacc[0] = mfma32(kf[h2][0][s], qh[ss], sacc[0]);
+                    sacc[1] = mfma32(kf[h2][1][s], qh[ss], sacc[1]);
+                    sacc[0] = mfma32(kf[h2][0][s], ql[ss], sacc[0]);
+                    sacc[1] = mfma32(kf[h2][1][s], ql[ss], sacc[1]);
                 }
             }
-            __syncthreads();   // the buffers have been read: the parity merge below reuses them
-        } else {
-            __syncthreads();   // the previous head round or item has been read
-        }
-        // combine the two key parities of each head: odd-parity waves park (m, l, O), even-parity waves merge
-        float4 *ox = (float4 *)as.buf[0];
-        if (par == 1) {   // never in the one-wave-per-head arrangement
-            as.ml[g * 64 + lane] = make_float2(m_run, l_run);
+            u32x4 vf[2 * HT];   // the first tile's V, on its way during the softmax
+            lds_frags<KSQ * 1024>(vf, fr, std::make_integer_sequence<int, 2 * HT>{});
+            // a lane holds keys kt*32 + 16*half + r, r = 0..15, of both tiles for query row qrow
+            const int kt = kt0 + 2 * i, key0 = kt * 32 + 16 * half;
+            const int lim1 = 2 * i + 1 < n ? lim : 0;   // the second tile of the last pair may lie past the range
+            if (kt * 32 + 64 > minlim || 2 * i + 1 >= n) {   // only tiles that reach some row's limit need the mask
 #pragma unroll
-            for (int tt = 0; tt < HT; ++tt)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    ox[((g * HT + tt) * 4 + q) * 64 + lane] = make_float4(oacc[tt][4 * q], oacc[tt][4 * q + 1], oacc[tt][4 * q + 2], oacc[tt][4 * q + 3]);
-        }
-        __syncthreads();
-        if (par == 0 && active) {
-            if (!wide) {
-                const float2 o_ml = as.ml[g * 64 + lane];
-                const float M = fmaxf(m_run, o_ml.x);
-                const float f0 = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((m_run - M) * scale_log2e);
-                const float f1 = (o_ml.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((o_ml.x - M) * scale_log2e);
-                l_run = f0 * l_run + f1 * o_ml.y;
-                m_run = M;
-#pragma unroll
-                for (int tt = 0; tt < HT; ++tt)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 v = ox[((g * HT + tt) * 4 + q) * 64 + lane];
-                        oacc[tt][4 * q] = f0 * oacc[tt][4 * q] + f1 * v.x;
-                        oacc[tt][4 * q + 1] = f0 * oacc[tt][4 * q + 1] + f1 * v.y;
-                        oacc[tt][4 * q + 2] = f0 * oacc[tt][4 * q + 2] + f1 * v.z;
-                        oacc[tt][4 * q + 3] = f0 * oacc[tt][4 * q + 3] + f1 * v.w;
-                    }
+                for (int r = 0; r < 16; ++r) {
+                    if (key0 + r >= lim) sacc[0][r] = -INFINITY;
+                    if (key0 + 32 + r >= lim1) sacc[1][r] = -INFINITY;
+                }
             }
-            const float l_tot = l_run + shx(l_run, 32);
-            if (NS == 1) {
-                attn_write_frag<HD, true>(oacc, l_tot > 0.f ? 1.f / l_tot : 0.f, t, head, Hq, lane, xhi, xlo);
-            } else {
-                float *pp = part + ((size_t)(t * Hq + head) * NS + split) * PF;
+            float mx = fmaxf(sacc[0][0], sacc[1][0]);
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(sacc[0][r], sacc[1][r]));
+            mx = fmaxf(mx, shx(mx, 32));
+            const float m_new = fmaxf(m_run, mx);
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;   // a row without visible keys so far: every weight is exp2(-inf) = 0
+            const float alpha = __builtin_amdgcn_exp2f((m_run - m_use) * scale_log2e);   // m_run = -inf -> 0
+            const float mb = m_use * scale_log2e;
+            float ls0 = 0.f, ls1 = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                sacc[0][r] = __builtin_amdgcn_exp2f(sacc[0][r] * scale_log2e - mb); ls0 += sacc[0][r];
+                sacc[1][r] = __builtin_amdgcn_exp2f(sacc[1][r] * scale_log2e - mb); ls1 += sacc[1][r];
+            }
+            l_run = l_run * alpha + (ls0 + ls1);
+            m_run = m_new;
+            if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {   // the running max moved for some row
 #pragma unroll
                 for (int tt = 0; tt < HT; ++tt)
 #pragma unroll
-                    for (int r2 = 0; r2 < 8; ++r2) st_agent2(pp + ((tt * 8 + r2) * 64 + lane) * 2, oacc[tt][2 * r2], oacc[tt][2 * r2 + 1]);
-                if (half == 0) st_agent2(pp + 32 * HD + 2 * qrow, m_run, l_tot);
+                    for (int r = 0; r < 16; ++r) oacc[tt][r] *= alpha;
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                float pr[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) pr[r] = sacc[j][r];
+                uint4 ph[2], pl[2];
+                pack8_split(pr, ph[0], pl[0]);
+                pack8_split(pr + 8, ph[1], pl[1]);
+                wait_lds<0>();
+#pragma unroll
+                for (int v = 0; v < 2 * HT; ++v) tie(vf[v]);
+                // the O^T tiles' chains interleaved
+#pragma unroll
+                for (int s2 = 0; s2 < 2; ++s2) {
+#pragma unroll
+                    for (int tt = 0; tt < HT; ++tt) oacc[tt] = mfma32(vf[tt * 2 + s2], ph[s2], oacc[tt]);
+                    if (ATT_P_LO)
+#pragma unroll
+                        for (int tt = 0; tt < HT; ++tt) oacc[tt] = mfma32(vf[tt * 2 + s2], pl[s2], oacc[tt]);
+                }
+                if (j == 0) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    lds_frags<(FPT + KSQ) * 1024>(vf, fr, std::make_integer_sequence<int, 2 * HT>{});
+                }
             }
         }
     }
-}
-
-// grid: x = kv_head + Hkv * split, y = pass tile (32 query rows of one sequence); 512 threads
-template <int HD>
-__global__ __launch_bounds__(512) void k_attn(const uint4 *__restrict__ Qhi, const uint4 *__restrict__ Qlo,
-                                              const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Vt,
-                                              size_t seq_stride, size_t head_stride, int max_seq,
-                                              const int *__restrict__ tile_seq, const int *__restrict__ row_limit,
-                                              float *__restrict__ part, int Hq, int Hkv, int NS, float scale_log2e,
-                                              uint4 *__restrict__ xhi, uint4 *__restrict__ xlo) {
-    __shared__ __attribute__((aligned(16))) AttnSmem as;
-    const int t = blockIdx.y;
-    attn_item<HD, true>(Qhi, Qlo, Kc, Vt, seq_stride, head_stride, max_seq, tile_seq[t], row_limit[t * 32 + (threadIdx.x & 31)],
-                        part, Hq, Hkv, NS, scale_log2e, xhi, xlo, as, blockIdx.x % Hkv, blockIdx.x / Hkv, t);
+    if (!active) return;
+    const float l_tot = l_run + shx(l_run, 32);
+    if (NS == 1) {
+        attn_write_frag<HD, false>(oacc, l_tot > 0.f ? 1.f / l_tot : 0.f, t, head, Hq, lane, xhi, xlo);
+    } else {
+        float *pp = part + ((size_t)(t * Hq + head) * NS + split) * PF;
+#pragma unroll
+        for (int tt = 0; tt < HT; ++tt)
+#pragma unroll
+            for (int r2 = 0; r2 < 8; ++r2) st_agent2(pp + ((tt * 8 + r2) * 64 + lane) * 2, oacc[tt][2 * r2], oacc[tt][2 * r2 + 1]);
+        if (half == 0) st_agent2(pp + 32 * HD + 2 * qrow, m_run, l_tot);
+    }
 }
 
 // Writes registers 8*hh .. 8*hh+7 of O^T tile tt (held in o[0..7], scaled by inv) into the output projection's
