@@ -254,7 +254,8 @@ void plan_work(Work &w, const deer_init_params &p, char *base) {
     w.st.len = (int *)take(B * 4); w.st.dr_len = (int *)take(B * 4); w.st.pending = (int *)take(B * 4);
     w.st.ing_n = (int *)take(B * 4); w.st.finished = (int *)take(B * 4); w.st.ing_tok = (int *)take((size_t)B * 32 * 4);
     w.rm.tok = (int *)take(MAXR * 4); w.rm.pos = (int *)take(MAXR * 4); w.rm.limit = (int *)take(MAXR * 4);
-    w.rm.slot = (int *)take(MAXR * 4); w.rm.tile_seq = (int *)take(MAXT * 4);
+    w.rm.slot = (int *)take(MAXR * 4); w.rm.seq = (int *)take(MAXR * 4); w.rm.qrow = (int *)take(MAXR * 4); w.rm.grow = (int *)take(MAXR * 4);
+    w.rm.tile_seq = (int *)take(MAXT * 4);
     w.cs = (float2 *)take((size_t)MAXR * 64 * sizeof(float2));
     w.theta[0] = (double *)take(64 * 8); w.theta[1] = (double *)take(64 * 8);
     w.h = (float *)take((size_t)MAXR * dmax * 4);
@@ -453,7 +454,7 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
 
 // draw: the pass samples its rows' tokens (Gumbel-max over the perturbed logits): the drafter's pass at T > 0; the target's
 // rows only need the maximum and the sum of exponentials
-struct LmPlan { bool on; int mt0, mt_stride, n_tiles, k; float T; uint64_t seed; int k_lo = 0; bool draw = false; };
+struct LmPlan { bool on; int n_lm, k; float T; uint64_t seed; int k_lo = 0; bool draw = false; };   // n_lm rows with logits, k per sequence
 
 template <int HD>
 int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_head, float scale_log2e, double kv_bytes,
@@ -465,19 +466,19 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
     ProfScope ps(c, 1, kv_bytes);
     if (NS_head > 0) {   // few tiles: one workgroup per (tile, query head, key range), merged by the last to arrive
         hipLaunchKernelGGL(k_attn_head<HD>, dim3(mc.n_q_heads * NS_head, ntiles), dim3(512), 0, c->stream, w.q_hi, w.q_lo, K, Vt,
-                           m.kv_seq_stride, m.kv_head_stride, w.rm.tile_seq, w.rm.limit, w.opart, w.attn_cnt,
+                           m.kv_seq_stride, m.kv_head_stride, w.rm.tile_seq, w.rm.limit, w.rm.grow, w.opart, w.attn_cnt,
                            mc.n_q_heads, mc.n_kv_heads, NS_head, scale_log2e, w.xb_hi, w.xb_lo, nx);
         LAUNCHCHK(c, "k_attn_head");
         return DEER_OK;
     }
     const int HG = (mc.n_q_heads / mc.n_kv_heads + ATT_HEADS - 1) / ATT_HEADS;
     hipLaunchKernelGGL(k_attn<HD>, dim3(mc.n_kv_heads * HG * NS, ntiles), dim3(256), 0, c->stream, w.q_hi, w.q_lo, K, Vt,
-                       m.kv_seq_stride, m.kv_head_stride, w.rm.tile_seq, w.rm.limit, w.opart,
+                       m.kv_seq_stride, m.kv_head_stride, w.rm.tile_seq, w.rm.limit, w.rm.grow, w.opart,
                        mc.n_q_heads, mc.n_kv_heads, HG, NS, scale_log2e, w.xb_hi, w.xb_lo);
     LAUNCHCHK(c, "k_attn");
     if (NS > 1) {
         const int n_items = ntiles * mc.n_q_heads * (HD / 32) * 2;
-        hipLaunchKernelGGL(k_attn_merge<HD>, dim3((n_items + 3) / 4), dim3(256), 0, c->stream, w.opart, NS, mc.n_q_heads, n_items,
+        hipLaunchKernelGGL(k_attn_merge<HD>, dim3((n_items + 3) / 4), dim3(256), 0, c->stream, w.opart, w.rm.grow, NS, mc.n_q_heads, n_items,
                            scale_log2e, w.xb_hi, w.xb_lo);
         LAUNCHCHK(c, "k_attn_merge");
     }
@@ -488,10 +489,10 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
 // 128 experts, top 8, take 172 against 177 us, 8 row tiles 174 against 198, 4 row tiles 170 against 162.
 constexpr int MOE_BLOCK_PAIRS = 12;
 
-// One forward pass of `model` over the rows described by the row metadata (ntiles tiles).
+// One forward pass of `model` over the rows described by the row metadata: ntiles tiles of GEMM rows, n_attn attention tiles.
 // rows: the pass's rows are described by a PassRows (draft, verify): one launch works them out, gathers the embeddings
 // and fills the RoPE table; null: the row metadata is in place already (prefill).
-int run_pass(deer_ctx *c, int model, int ntiles, int max_limit, const LmPlan &lm, double kv_keys_total = 0.0,
+int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, const LmPlan &lm, double kv_keys_total = 0.0,
              const PassRows *rows_desc = nullptr) {
     ModelRT &m = c->m[model];
     Work &w = c->wk;
@@ -503,8 +504,8 @@ int run_pass(deer_ctx *c, int model, int ntiles, int max_limit, const LmPlan &lm
     if (c->stamp_launch >= 0 && model == c->stamp_model) (void)hipMemsetAsync(w.stamps, 0, (size_t)STAMP_MAX_BLOCKS * 64, s);
     prof_close(c);
     if (rows_desc) {
-        hipLaunchKernelGGL(k_pass_begin, dim3(ncg_d + 1, ntiles), dim3(256), 0, s, *rows_desc, w.rm, (const uint16_t *)(m.w + m.off_embed),
-                           w.h, w.xa_hi, w.xa_lo, w.ssq, d, ncg_d, m.ssq_sub, m.theta, w.cs, hd / 2);
+        hipLaunchKernelGGL(k_pass_begin, dim3(ncg_d + 2, std::max(ntiles, n_attn)), dim3(256), 0, s, *rows_desc, w.rm, (const uint16_t *)(m.w + m.off_embed),
+                           w.h, w.xa_hi, w.xa_lo, w.ssq, d, ncg_d, m.ssq_sub, m.theta, w.cs, hd / 2, ntiles, n_attn);
         LAUNCHCHK(c, "k_pass_begin");
     } else {
         hipLaunchKernelGGL(k_embed, dim3(ncg_d, ntiles), dim3(256), 0, s, (const uint16_t *)(m.w + m.off_embed), w.rm.tok, w.h,
@@ -515,25 +516,24 @@ int run_pass(deer_ctx *c, int model, int ntiles, int max_limit, const LmPlan &lm
         LAUNCHCHK(c, "k_rope_table");
     }
     const int nkt = (max_limit + 31) / 32;
-    // key-range splits: aim at two workgroups per compute unit; a split holds at least four key tiles; ntiles * NS never
+    // key-range splits: aim at two workgroups per compute unit; a split holds at least four key tiles; n_attn * NS never
     // exceeds the partial buffer (max(64, most tiles of a pass) tile slots)
     constexpr int ns_target = 256;
-    const int attn_items = mc.n_kv_heads * ((mc.n_q_heads / mc.n_kv_heads + ATT_HEADS - 1) / ATT_HEADS) * ntiles;
+    const int attn_items = mc.n_kv_heads * ((mc.n_q_heads / mc.n_kv_heads + ATT_HEADS - 1) / ATT_HEADS) * n_attn;
     int NS = (2 * ns_target + attn_items - 1) / attn_items;
-    NS = std::max(1, std::min({NS, MAX_NS, std::max(1, std::max(64, c->max_tiles) / ntiles), (nkt + 3) / 4}));
+    NS = std::max(1, std::min({NS, MAX_NS, std::max(1, std::max(64, c->max_tiles) / n_attn), (nkt + 3) / 4}));
     // Passes of few tiles (decoding) run attention per query head: (tile, head, key range) workgroups, about one per
     // compute unit, as long as a wave then has at most ATT_HEAD_MAX_TILES key tiles of its range to go through
     int NS_head = 0;
-    if (ntiles * mc.n_q_heads <= ns_target) {
-        int ns = ns_target / (ntiles * mc.n_q_heads);
-        ns = std::max(1, std::min({ns, MAX_NS, std::max(1, std::max(64, c->max_tiles) / ntiles), (nkt + 7) / 8}));
+    if (n_attn * mc.n_q_heads <= ns_target) {
+        int ns = ns_target / (n_attn * mc.n_q_heads);
+        ns = std::max(1, std::min({ns, MAX_NS, std::max(1, std::max(64, c->max_tiles) / n_attn), (nkt + 7) / 8}));
         const int per = (nkt + ns - 1) / ns;
         if ((per + 7) / 8 <= ATT_HEAD_MAX_TILES) NS_head = ns;
     }
     const float scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
     const double kv_bytes = kv_keys_total * mc.n_kv_heads * hd * 2.0 * 2.0;   // K and V rows read per layer
     GemmArgs base{};
-    base.mt0 = 0; base.mt_stride = 1;
     base.ssq_in = w.ssq; base.ncg_in = ncg_d * m.ssq_sub; base.d_in = d; base.eps = mc.rms_eps;
     base.ssq_sub = m.ssq_sub;
     base.cs = w.cs; base.rm = w.rm; base.qhi = w.q_hi; base.qlo = w.q_lo;
@@ -582,9 +582,9 @@ int run_pass(deer_ctx *c, int model, int ntiles, int max_limit, const LmPlan &lm
         int rc = launch_gemm<EPI_QKV>(c, a, d, ntiles, 0);
         if (rc) return rc;
         const NextWeights nx_o = fetch_ahead_narrow ? next_plan_narrow(lw + m.lo_o, d, m.kattn, 1) : next_plan(lw + m.lo_o, d, m.kattn);
-        if (hd == 128) rc = launch_attn<128>(c, m, l, ntiles, NS, NS_head, scale_log2e, kv_bytes, nx_o);
-        else if (hd == 64) rc = launch_attn<64>(c, m, l, ntiles, NS, NS_head, scale_log2e, kv_bytes, nx_o);
-        else rc = launch_attn<32>(c, m, l, ntiles, NS, NS_head, scale_log2e, kv_bytes, nx_o);
+        if (hd == 128) rc = launch_attn<128>(c, m, l, n_attn, NS, NS_head, scale_log2e, kv_bytes, nx_o);
+        else if (hd == 64) rc = launch_attn<64>(c, m, l, n_attn, NS, NS_head, scale_log2e, kv_bytes, nx_o);
+        else rc = launch_attn<32>(c, m, l, n_attn, NS, NS_head, scale_log2e, kv_bytes, nx_o);
         if (rc) return rc;
         a = base;
         a.W = (const uint4 *)(lw + m.lo_o); a.Xhi = w.xb_hi; a.Xlo = w.xb_lo; a.N = d;
@@ -652,13 +652,12 @@ int run_pass(deer_ctx *c, int model, int ntiles, int max_limit, const LmPlan &lm
         const int V = mc.vocab;
         GemmArgs a = base;
         a.W = (const uint4 *)(m.w + m.off_lm); a.Xhi = w.xa_hi; a.Xlo = w.xa_lo; a.N = V;
-        a.mt0 = lm.mt0; a.mt_stride = lm.mt_stride;
-        a.k = lm.k; a.k_lo = lm.k_lo; a.T = lm.T; a.seed = lm.seed; a.draw = lm.draw ? 1 : 0; a.stat = w.stat; a.ncg_v = V / CG;
+        a.k = lm.k; a.n_lm = lm.n_lm; a.k_lo = lm.k_lo; a.T = lm.T; a.seed = lm.seed; a.draw = lm.draw ? 1 : 0; a.stat = w.stat; a.ncg_v = V / CG;
         a.logits = (c->p.keep_logits || lm.T > 0.f) ? w.logits[model] : nullptr;
-        int rc = launch_gemm<EPI_LMHEAD>(c, a, d, lm.n_tiles, 1);
+        int rc = launch_gemm<EPI_LMHEAD>(c, a, d, (lm.n_lm + 31) / 32, 1);
         if (rc) return rc;
         prof_close(c);
-        hipLaunchKernelGGL(k_rowstat_final, dim3(lm.n_tiles * lm.k), dim3(256), 0, s, w.stat, V / CG, lm.T, w.res[model], lm.k, lm.k_lo);
+        hipLaunchKernelGGL(k_rowstat_final, dim3(lm.n_lm), dim3(256), 0, s, w.stat, V / CG, lm.T, w.res[model], lm.k, lm.k_lo);
         LAUNCHCHK(c, "k_rowstat_final");
     }
     prof_close(c);
@@ -837,40 +836,41 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
         pend[b] = ids[total - 1];
     }
     HIPCHK(c, hipMemcpyAsync(w.ids, ids, total * 4, hipMemcpyHostToDevice, c->stream));
-    // Passes of up to cap tiles; a pass takes the next rows of as many sequences as fit, each sequence's rows in
-    // whole tiles (rows of one sequence that are split over passes continue in the next pass, over the keys the
-    // earlier pass has written).  The descriptor lists stay alive until the stream has been waited for.
-    const int cap = PREFILL_TILES;
+    // Passes of up to cap tiles; a pass takes the next rows of as many sequences as fit: its GEMM rows follow each other
+    // without gaps, its attention tiles hold up to 32 rows of one sequence (rows of one sequence that are split over passes
+    // continue in the next pass, over the keys the earlier pass has written).  The descriptor lists stay alive until the
+    // stream has been waited for.
+    const int cap = std::max(2 * c->p.max_batch, PREFILL_TILES);
     std::vector<std::vector<int4>> kept;
     for (int model = 0; model < 2; ++model) {
         std::vector<int4> desc;
-        int maxlim = 0;
+        int maxlim = 0, n_rows = 0;
         auto flush = [&]() -> int {
             if (desc.empty()) return DEER_OK;
             kept.push_back(desc);
             const std::vector<int4> &dsc = kept.back();
-            const int ntiles = (int)dsc.size();
+            const int n_attn = (int)dsc.size(), ntiles = (n_rows + 31) / 32;
             HIPCHK(c, hipMemcpyAsync(w.pf_desc, dsc.data(), dsc.size() * sizeof(int4), hipMemcpyHostToDevice, c->stream));
-            hipLaunchKernelGGL(k_rows_prefill, dim3(ntiles), dim3(32), 0, c->stream, w.rm, w.ids, w.pf_desc);
+            hipLaunchKernelGGL(k_rows_prefill, dim3(n_attn + 1), dim3(32), 0, c->stream, w.rm, w.ids, w.pf_desc, n_attn, n_rows, ntiles);
             LAUNCHCHK(c, "k_rows_prefill");
-            LmPlan lm{false, 0, 1, 0, 0, 0.f, 0};
-            int rc = run_pass(c, model, ntiles, maxlim, lm);
+            LmPlan lm{false, 0, 0, 0.f, 0};
+            int rc = run_pass(c, model, ntiles, n_attn, maxlim, lm);
             desc.clear();
             maxlim = 0;
+            n_rows = 0;
             return rc;
         };
         for (int b = 0; b < batch; ++b) {
             const int nrows = (model == DEER_TARGET) ? lens[b] - 1 : lens[b];   // the last token stays pending for the target
             int c0 = 0;
             while (c0 < nrows) {
-                if ((int)desc.size() == cap)
+                if ((int)desc.size() == cap || n_rows == cap * 32)
                     if (int rc = flush()) return rc;
-                const int room = cap - (int)desc.size();
-                const int take = std::min(nrows - c0, room * 32);
-                for (int i = 0; i < take; i += 32)
-                    desc.push_back(make_int4(b, c0 + i, std::min(32, take - i), (int)(offs[b] + c0 + i)));
+                const int take = std::min({nrows - c0, 32, cap * 32 - n_rows});
+                desc.push_back(make_int4(b, c0, take | n_rows << 6, (int)(offs[b] + c0)));
                 maxlim = std::max(maxlim, c0 + take);
                 c0 += take;
+                n_rows += take;
             }
         }
         if (int rc = flush()) return rc;
@@ -897,11 +897,12 @@ int deer_draft_block_multipass(deer_ctx *c, int32_t k, float T, uint64_t seed, i
     if (c->state != ST_PREFILLED) return fail(c, DEER_ESTATE, "draft_block needs a prefilled or committed state");
     if (k + c->bonus > 32) return fail(c, DEER_EINVAL, "with the bonus token on, k must be at most 31 (k + 1 rows per tile)");
     const int B = c->batch;
-    int maxlim = 0, any_ing = 0;
+    int maxlim = 0, n_ing = 0, max_ing = 0;
     for (int b = 0; b < B; ++b) {
         if (c->h_len[b] + k > c->p.max_seq) return fail(c, DEER_ECAPACITY, "sequence %d: length %d + k exceeds max_seq", b, c->h_len[b]);
         maxlim = std::max(maxlim, c->h_len[b] + k);
-        any_ing |= c->h_ing_n[b] > 0;
+        n_ing += c->h_ing_n[b];
+        max_ing = std::max(max_ing, c->h_ing_n[b]);
     }
     Work &w = c->wk;
     double keys = 0;
@@ -911,16 +912,15 @@ int deer_draft_block_multipass(deer_ctx *c, int32_t k, float T, uint64_t seed, i
     for (int s = 1; s <= n_passes; ++s) {
         const int lo = (k * (s - 1) + n_passes - 1) / n_passes, hi = (k * s + n_passes - 1) / n_passes;
         if (hi == lo) continue;
-        const int tps = any_ing ? 2 : 1;
         PassRows pr{};
         pr.draft_pass = 1; pr.st = w.st; pr.tokens = draft_dev; pr.k = k; pr.nrows = 0; pr.vocab = c->p.drafter.vocab;
-        pr.mask_id = c->p.mask_token_id; pr.tiles_per_seq = tps; pr.n_fixed = lo;
-        LmPlan lm{true, 0, tps, B, k, T, seed, lo, T > 0.f};
-        int rc = run_pass(c, DEER_DRAFTER, B * tps, maxlim, lm, keys, &pr);
+        pr.mask_id = c->p.mask_token_id; pr.n_fixed = lo; pr.B = B; pr.n_ingest = n_ing; pr.share = k + max_ing <= 32;
+        LmPlan lm{true, B * k, k, T, seed, lo, T > 0.f};
+        int rc = run_pass(c, DEER_DRAFTER, (B * k + n_ing + 31) / 32, n_ing > 0 && !pr.share ? 2 * B : B, maxlim, lm, keys, &pr);
         if (rc) return rc;
         hipLaunchKernelGGL(k_draft_finish, dim3(B), dim3(32), 0, c->stream, w.st, w.res[DEER_DRAFTER], draft_dev, k, lo);
         LAUNCHCHK(c, "k_draft_finish");
-        any_ing = 0;   // the device-side counts were cleared by k_draft_finish
+        n_ing = max_ing = 0;   // the device-side counts were cleared by k_draft_finish
     }
     std::fill(c->h_ing_n.begin(), c->h_ing_n.end(), 0);
     c->cur_k = k;
@@ -945,11 +945,11 @@ int deer_verify_block(deer_ctx *c, int32_t k, float T, const int32_t *draft_dev)
     Work &w = c->wk;
     PassRows pr{};
     pr.draft_pass = 0; pr.st = w.st; pr.tokens = draft_dev; pr.k = k; pr.nrows = nrows; pr.vocab = c->p.target.vocab;
-    pr.tiles_per_seq = 1;
-    LmPlan lm{true, 0, 1, B, nrows, T, 0};
+    pr.B = B;
+    LmPlan lm{true, B * nrows, nrows, T, 0};
     double keys = 0;
     for (int b = 0; b < B; ++b) keys += c->h_len[b] - 1 + nrows;
-    int rc = run_pass(c, DEER_TARGET, B, maxlim, lm, keys, &pr);
+    int rc = run_pass(c, DEER_TARGET, (B * nrows + 31) / 32, B, maxlim, lm, keys, &pr);
     if (rc) return rc;
     c->wk_draft = draft_dev;
     c->state = ST_VERIFIED;

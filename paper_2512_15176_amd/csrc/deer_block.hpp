@@ -206,10 +206,9 @@ __device__ __forceinline__ void wave_park(const f32x16 (&acc)[NB], float *tile, 
         for (int r = 0; r < 16; ++r) tile[mfma_row(r, half) * BT_STRIDE + col0 + nb * 32 + cl] = acc[nb][r];
 }
 
-// The epilogues of deer_kernels.hpp for one wave and one 32 x 128 tile: row tile t of the pass (ct of the launch), column
-// group cg.  No barriers: every wave runs its own.
+// The epilogues of deer_kernels.hpp for one wave and one 32 x 128 tile: row tile t, column group cg.  No barriers: every wave runs its own.
 template <int EPI>
-__device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, int cg, int ct, int t) {
+__device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, int cg, int t) {
     const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
     const size_t grow = (size_t)t * 32 + row;
     float rs = 0.f;
@@ -271,7 +270,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
         }
     } else if (EPI == EPI_QKV) {
         const int hd = a.hd, Hq = a.Hq, Hkv = a.Hkv, half_hd = hd >> 1;
-        const int b = a.rm.tile_seq[t], slot = a.rm.slot[grow];
+        const int b = a.rm.seq[grow], slot = a.rm.slot[grow], qr = a.rm.qrow[grow];
 #pragma unroll 1
         for (int i = 0; i < 8; ++i) {
             const int oct = 2 * i + half, col0 = cg * CG + oct * 8;   // first of 8 columns, all in one head
@@ -295,9 +294,11 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
             if (kind == 0) {
                 uint4 hi, lo;
                 pack8_split(v, hi, lo);
-                const size_t vec = ((size_t)(t * Hq + head) * (hd / 16)) * 64 + frag_vec(row, i0 >> 3);
-                a.qhi[vec] = hi;
-                a.qlo[vec] = lo;
+                if (qr >= 0) {
+                    const size_t vec = ((size_t)((qr >> 5) * Hq + head) * (hd / 16)) * 64 + frag_vec(qr & 31, i0 >> 3);
+                    a.qhi[vec] = hi;
+                    a.qlo[vec] = lo;
+                }
             } else if (slot >= 0) {
                 const size_t kvb = (size_t)b * a.kv.seq_stride + (size_t)head * a.kv.head_stride;
                 if (kind == 1) {
@@ -309,13 +310,14 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
             }
         }
     } else if (EPI == EPI_LMHEAD) {
-        const int V = a.N, k = a.k, sub = lane & 7;   // 8 lanes per row, 16 columns each; 8 rows at a time
+        const int V = a.N, sub = lane & 7;   // 8 lanes per row, 16 columns each; 8 rows at a time
         const float T = a.T, invT = T > 0.f ? 1.f / T : 1.f;
 #pragma unroll 1
         for (int r0 = 0; r0 < 32; r0 += 8) {
             const int lr = r0 + (lane >> 3);
             const float sc = __int_as_float(__builtin_amdgcn_ds_bpermute(lr << 2, __float_as_int(rs)));
-            const bool live = lr < k && lr >= a.k_lo;
+            const size_t lm = (size_t)t * 32 + lr;
+            const bool live = (int)lm < a.n_lm && (int)lm % opaque_s(a.k) >= a.k_lo;
             float m = -INFINITY, gm = -INFINITY, se = 0.f;
             int idx = 0x7fffffff, gidx = 0x7fffffff;
             float z[16];
@@ -323,13 +325,13 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
 #pragma unroll
                 for (int e = 0; e < 16; ++e) z[e] = tile[lr * BT_STRIDE + sub * 16 + e] * sc;
                 if (a.logits) {
-                    float *q = a.logits + ((size_t)ct * k + lr) * V + (size_t)cg * CG + sub * 16;
+                    float *q = a.logits + lm * V + (size_t)cg * CG + sub * 16;
 #pragma unroll
                     for (int e = 0; e < 16; e += 4) *(float4 *)(q + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
                 }
                 const bool draw = T > 0.f && a.draw;
                 uint64_t key = 0;
-                if (draw) key = row_key(a.seed, TAG_DRAFT, (uint64_t)a.rm.tile_seq[t], (uint64_t)a.rm.pos[t * 32 + lr]);
+                if (draw) key = row_key(a.seed, TAG_DRAFT, (uint64_t)a.rm.seq[lm], (uint64_t)a.rm.pos[lm]);
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int v = cg * CG + sub * 16 + e;
@@ -350,7 +352,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
             }
 #pragma unroll
             for (int off = 1; off < 8; off <<= 1) se += shx(se, off);
-            if (live && sub == 0) a.stat[((size_t)ct * k + lr) * a.ncg_v + cg] = RowStat{m, idx, se, gm, gidx};
+            if (live && sub == 0) a.stat[lm * a.ncg_v + cg] = RowStat{m, idx, se, gm, gidx};
         }
     }
 }
@@ -375,7 +377,7 @@ inline int block_grid(int P, int nrb) {
     return 8 * ((nb * band * P + 7) / 8);
 }
 
-// ncb: column blocks of 64 NB columns; nrt: row tiles (tile ct = 0 .. nrt - 1 is pass tile a.mt0 + ct * a.mt_stride)
+// ncb: column blocks of 64 NB columns; nrt: row tiles
 template <int NB, int NST, int EPI>
 __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 1) void k_gemm_block(const GemmArgs a, int ncb, int nrt, int band) {
     constexpr int LPW = BlockSmem<NB, NST>::FRAGS / 4;
@@ -399,7 +401,7 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
         if (f < 2 * NB) p = a.W + ((size_t)min(cb * 2 * NB + f, a.N / 32 - 1) * KS + ks0) * 64;
         else {
             const int x = f - 2 * NB, ct = min(rb * BK_RT + (x & (BK_RT - 1)), nrt - 1);
-            p = (x < BK_RT ? a.Xhi : a.Xlo) + ((size_t)(a.mt0 + ct * a.mt_stride) * KS + ks0) * 64;
+            p = (x < BK_RT ? a.Xhi : a.Xlo) + ((size_t)ct * KS + ks0) * 64;
         }
         base[i] = (const char *)p;
         vo[i] = lane * 16;
@@ -464,7 +466,7 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
             if (mt >= nmt || cg * CG >= a.N) continue;
             wave_park<NB>(acc[mt], sm.tile[w], 0, lane);
             wave_lds_sync();
-            wave_epilogue<EPI>(a, sm.tile[w], cg, ct, a.mt0 + ct * a.mt_stride);
+            wave_epilogue<EPI>(a, sm.tile[w], cg, ct);
             wave_lds_sync();
         }
     } else {   // a column group is made by the two waves of a row pair: wave wc finishes row tile wc
@@ -472,7 +474,7 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
         for (int mt = 0; mt < 2; ++mt) wave_park<NB>(acc[mt], sm.tile[wr * 2 + mt], wc * 64, lane);
         __syncthreads();
         const int ct = rb * BK_RT + wr * 2 + wc;
-        if (wc < nmt) wave_epilogue<EPI>(a, sm.tile[wr * 2 + wc], cb, ct, a.mt0 + ct * a.mt_stride);
+        if (wc < nmt) wave_epilogue<EPI>(a, sm.tile[wr * 2 + wc], cb, ct);
     }
 }
 

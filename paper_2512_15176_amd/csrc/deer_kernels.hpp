@@ -333,67 +333,115 @@ struct SeqState {       // device arrays, one entry per sequence
     int *finished;      // EOS seen
 };
 
-struct RowMeta {        // device arrays over the rows of a pass
-    int *tok, *pos, *limit, *slot;   // [rows]; slot < 0: do not write K,V
-    int *tile_seq;                   // [tiles]
+// The rows of a pass have two numberings.  GEMM rows are packed: the rows of all sequences follow each other without gaps,
+// so that no row tile is multiplied for padding but the end of the last one.  Attention works on tiles of 32 query rows
+// of one sequence; attention row = 32 * attention tile + r.  The QKV epilogue writes a row's Q fragments at its attention
+// row, the attention kernels write their result at the GEMM row.
+struct RowMeta {
+    int *tok, *pos, *slot, *seq, *qrow;   // [GEMM rows]; slot < 0: do not write K,V; qrow: the attention row, < 0: none (padding)
+    int *limit, *grow;                    // [attention rows]: visible keys (0: no such row), GEMM row (< 0: none)
+    int *tile_seq;                        // [attention tiles]
 };
 
-// verify rows of sequence b: tile b; row i < nrows: [x_j, y^_1 .. y^_{nrows-1}] at positions j-1+i, with
-// nrows = k, or k + 1 when the bonus token is on (the last draft is a row too)
 // token ids that reach the embedding gather are forced into [0, vocab): drafts come from caller memory
 __device__ __forceinline__ int safe_tok(int t, int vocab) { return (t < 0 || t >= vocab) ? 0 : t; }
 
 // Rows of a verify or draft pass (Alg. 1: one pass per model and iteration).
-//   verify: tile b = sequence b, nrows rows [x_j, y^_1 .. ]: row i at position j - 1 + i, causal over the cache.
-//   draft: sequence b has tiles_per_seq tiles; tile 0 = k MASK rows at positions j..j+k-1 (they see the cache, the
-//   ingested rows and every MASK row; their K,V land in slots past the cached length and are never kept); tile 1 = the
-//   m not-yet-cached committed tokens, causal.  The first n_fixed block rows hold the tokens fixed[b][0 .. n_fixed)
-//   instead of the MASK id (a partially filled block: a later pass of a multi-pass draft).
+//   verify: sequence b has nrows GEMM rows [x_j, y^_1 .. y^_{nrows-1}] from b * nrows on and attention tile b; row i at
+//   position j - 1 + i, causal over the cache.  nrows = k, or k + 1 when the bonus token is on (the last draft is a row too).
+//   draft: first the k MASK rows of every sequence (GEMM rows b * k ..; positions j..j+k-1; they see the cache, the ingested
+//   rows and every MASK row; their K,V land in slots past the cached length and are never kept), then the not-yet-cached
+//   committed tokens of all sequences, causal.  Attention tile b holds the MASK rows; the committed tokens of b follow them
+//   there if they fit for every sequence (share), else they have the tile B + b.  The first n_fixed block rows hold the
+//   tokens fixed[b][0 .. n_fixed) instead of the MASK id (a partially filled block: a later pass of a multi-pass draft).
 struct PassRows {
     int draft_pass;                  // 0: verify, 1: draft
     SeqState st;
     const int *tokens;               // verify: the draft tokens [B][k]; draft: the fixed tokens [B][k] (n_fixed > 0)
     int k, nrows, vocab;             // nrows: verify rows per sequence
-    int mask_id, tiles_per_seq, n_fixed;
+    int mask_id, n_fixed;
+    int B, share, n_ingest;          // sequences; draft: committed tokens in all that the drafter has not cached
 };
-struct RowDesc { int tok, pos, slot, limit; };
+struct RowDesc { int tok, pos, slot, seq, qrow; };
 
-__device__ __forceinline__ RowDesc pass_row(const PassRows &p, int tile, int r, int &b) {
-    RowDesc d{0, 0, -1, 0};
-    if (!p.draft_pass) {
-        b = tile;
-        if (r < p.nrows) {
-            const int pos = p.st.len[b] - 1 + r;
-            d.tok = safe_tok(r == 0 ? p.st.pending[b] : p.tokens[b * p.k + r - 1], p.vocab);
-            d.pos = pos; d.slot = pos; d.limit = pos + 1;
+// running sums of the sequences' counts of not-yet-cached tokens: pref[b] = those before b, pref[B] = all; 256 threads
+__device__ __forceinline__ void ingest_prefix(const PassRows &p, int *pref) {
+    for (int b = threadIdx.x; b < p.B; b += 256) pref[b + 1] = p.st.ing_n[b];
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int per = (p.B + 63) >> 6, b0 = min(p.B, (int)threadIdx.x * per), b1 = min(p.B, b0 + per);
+        int sum = 0;
+        for (int b = b0; b < b1; ++b) { sum += pref[b + 1]; pref[b + 1] = sum; }
+        int run = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __builtin_amdgcn_ds_bpermute(((int)threadIdx.x - off) << 2, run);
+            if ((int)threadIdx.x >= off) run += v;
         }
-    } else {
-        b = tile / p.tiles_per_seq;
-        const int t = tile - b * p.tiles_per_seq;
-        if (t == 0 && r < p.k) {
-            const int j = p.st.len[b];
-            d.tok = r < p.n_fixed ? safe_tok(p.tokens[b * p.k + r], p.vocab) : p.mask_id;
-            d.pos = j + r; d.slot = j + r; d.limit = j + p.k;
-        } else if (t == 1 && r < p.st.ing_n[b]) {
-            const int dl = p.st.dr_len[b];
-            d.tok = safe_tok(p.st.ing_tok[b * 32 + r], p.vocab);
-            d.pos = dl + r; d.slot = dl + r; d.limit = dl + r + 1;
+        for (int b = b0; b < b1; ++b) pref[b + 1] += run - sum;
+        if (threadIdx.x == 0) pref[0] = 0;
+    }
+    __syncthreads();
+}
+
+// GEMM row g
+__device__ __forceinline__ RowDesc pass_row(const PassRows &p, const int *pref, int g) {
+    RowDesc d{0, 0, -1, 0, -1};
+    if (!p.draft_pass) {
+        const int b = g / p.nrows, r = g - b * p.nrows;
+        if (b < p.B) {
+            const int pos = p.st.len[b] - 1 + r;
+            d = RowDesc{safe_tok(r == 0 ? p.st.pending[b] : p.tokens[b * p.k + r - 1], p.vocab), pos, pos, b, b * 32 + r};
+        }
+        return d;
+    }
+    const int b = g / p.k, r = g - b * p.k;
+    if (b < p.B) {
+        const int j = p.st.len[b];
+        d = RowDesc{r < p.n_fixed ? safe_tok(p.tokens[b * p.k + r], p.vocab) : p.mask_id, j + r, j + r, b, b * 32 + r};
+    } else if (p.n_ingest > 0) {
+        const int q = g - p.B * p.k;
+        if (q < pref[p.B]) {
+            int lo = 0, hi = p.B - 1;   // the sequence with pref[lo] <= q < pref[lo + 1]
+            while (lo < hi) { const int mid = (lo + hi) >> 1; if (q < pref[mid + 1]) hi = mid; else lo = mid + 1; }
+            const int i = q - pref[lo], pos = p.st.dr_len[lo] + i;
+            d = RowDesc{safe_tok(p.st.ing_tok[lo * 32 + i], p.vocab), pos, pos, lo, p.share ? lo * 32 + p.k + i : (p.B + lo) * 32 + i};
         }
     }
     return d;
 }
 
-// prefill pass: tile t holds desc[t].z rows of sequence desc[t].x, causal, at positions desc[t].y + r, whose token
-// ids start at ids[desc[t].w].  A pass may hold tiles of several sequences (each sequence's rows in whole tiles).
-__global__ void k_rows_prefill(RowMeta rm, const int *__restrict__ ids, const int4 *__restrict__ desc) {
-    const int4 dsc = desc[blockIdx.x];
-    const int r = threadIdx.x, row = blockIdx.x * 32 + r;
-    if (r == 0) rm.tile_seq[blockIdx.x] = dsc.x;
-    if (r < dsc.z) {
-        rm.tok[row] = ids[dsc.w + r]; rm.pos[row] = dsc.y + r; rm.slot[row] = dsc.y + r; rm.limit[row] = dsc.y + r + 1;
-    } else {
-        rm.tok[row] = 0; rm.pos[row] = 0; rm.slot[row] = -1; rm.limit[row] = 0;
+// attention row r of tile t: its key limit and GEMM row; b: the tile's sequence
+__device__ __forceinline__ void pass_attn_row(const PassRows &p, const int *pref, int t, int r, int &b, int &limit, int &grow) {
+    b = t < p.B ? t : t - p.B;
+    limit = 0; grow = -1;
+    if (!p.draft_pass) {
+        if (r < p.nrows) { limit = p.st.len[b] + r; grow = b * p.nrows + r; }
+        return;
     }
+    if (t < p.B && r < p.k) { limit = p.st.len[b] + p.k; grow = b * p.k + r; return; }
+    if (p.n_ingest == 0) return;
+    const int i = t < p.B ? (p.share ? r - p.k : 32) : r;
+    if (i < pref[b + 1] - pref[b]) { limit = p.st.dr_len[b] + i + 1; grow = p.B * p.k + pref[b] + i; }
+}
+
+// prefill pass: attention tile t holds desc[t].z & 63 rows of sequence desc[t].x, causal, at positions desc[t].y + r, whose
+// token ids start at ids[desc[t].w]; they are the GEMM rows from desc[t].z >> 6 on (packed over all sequences of the pass).
+// The last block marks the padding rows n_rows .. 32 * ntiles - 1.
+__global__ void k_rows_prefill(RowMeta rm, const int *__restrict__ ids, const int4 *__restrict__ desc, int n_desc, int n_rows, int ntiles) {
+    const int r = threadIdx.x;
+    if ((int)blockIdx.x == n_desc) {
+        const int g = n_rows + r;
+        if (g < ntiles * 32) { rm.tok[g] = 0; rm.pos[g] = 0; rm.slot[g] = -1; rm.seq[g] = 0; rm.qrow[g] = -1; }
+        return;
+    }
+    const int4 dsc = desc[blockIdx.x];
+    const int a = blockIdx.x * 32 + r, n = dsc.z & 63, g = (dsc.z >> 6) + r;
+    if (r == 0) rm.tile_seq[blockIdx.x] = dsc.x;
+    const bool live = r < n;
+    rm.limit[a] = live ? dsc.y + r + 1 : 0;
+    rm.grow[a] = live ? g : -1;
+    if (live) { rm.tok[g] = ids[dsc.w + r]; rm.pos[g] = dsc.y + r; rm.slot[g] = dsc.y + r; rm.seq[g] = dsc.x; rm.qrow[g] = a; }
 }
 
 // cos/sin of pos * theta_i, evaluated in double, stored fp32: cs[row][i] = (cos, sin)
@@ -453,27 +501,35 @@ __global__ __launch_bounds__(256) void k_embed(const uint16_t *__restrict__ E, c
 }
 
 // The start of a draft or verify pass in one launch: every block works out its tile's rows (pass_row), then blocks
-// x < ncg gather the embeddings of column group x, block x == ncg writes the row metadata and the tile's RoPE table.
-// (Three launches of a few microseconds each left the GPU waiting for the host at the start of every pass.)
+// x < ncg gather the embeddings of column group x, block x == ncg writes the row metadata and the tile's RoPE table; block
+// x == ncg + 1 writes the metadata of attention tile y.  (Three launches of a few microseconds each left the GPU waiting
+// for the host at the start of every pass.)
 __global__ __launch_bounds__(256) void k_pass_begin(PassRows p, RowMeta rm, const uint16_t *__restrict__ E, float *__restrict__ h,
                                                     uint4 *__restrict__ xhi, uint4 *__restrict__ xlo, float *__restrict__ ssq,
                                                     int d, int ncg, int ssq_sub, const double *__restrict__ theta,
-                                                    float2 *__restrict__ cs, int half) {
+                                                    float2 *__restrict__ cs, int half, int ntiles, int n_attn) {
     __shared__ float tile[32 * RED_STRIDE];
-    __shared__ int s_tok[32], s_pos[32];
+    __shared__ int s_tok[32], s_pos[32], s_pref[1025];
     const int t = blockIdx.y;
-    if (threadIdx.x < 32) {
-        int b;
-        const RowDesc r = pass_row(p, t, threadIdx.x, b);
-        s_tok[threadIdx.x] = r.tok; s_pos[threadIdx.x] = r.pos;
-        if (blockIdx.x == ncg) {
-            const int row = t * 32 + threadIdx.x;
-            rm.tok[row] = r.tok; rm.pos[row] = r.pos; rm.slot[row] = r.slot; rm.limit[row] = r.limit;
+    if (t >= ((int)blockIdx.x == ncg + 1 ? n_attn : ntiles)) return;
+    if (p.draft_pass && p.n_ingest > 0) ingest_prefix(p, s_pref);
+    if ((int)blockIdx.x == ncg + 1) {
+        if (threadIdx.x < 32) {
+            int b, limit, grow;
+            pass_attn_row(p, s_pref, t, threadIdx.x, b, limit, grow);
+            rm.limit[t * 32 + threadIdx.x] = limit; rm.grow[t * 32 + threadIdx.x] = grow;
             if (threadIdx.x == 0) rm.tile_seq[t] = b;
         }
+        return;
+    }
+    if (threadIdx.x < 32) {
+        const int row = t * 32 + threadIdx.x;
+        const RowDesc r = pass_row(p, s_pref, row);
+        s_tok[threadIdx.x] = r.tok; s_pos[threadIdx.x] = r.pos;
+        if ((int)blockIdx.x == ncg) { rm.tok[row] = r.tok; rm.pos[row] = r.pos; rm.slot[row] = r.slot; rm.seq[row] = r.seq; rm.qrow[row] = r.qrow; }
     }
     __syncthreads();
-    if (blockIdx.x < ncg) {
+    if ((int)blockIdx.x < ncg) {
         embed_tile(tile, E, s_tok, h, xhi, xlo, ssq, d, ncg, ssq_sub, blockIdx.x, t);
     } else {
         for (int idx = threadIdx.x; idx < 32 * half; idx += 256) {
@@ -494,7 +550,7 @@ __global__ __launch_bounds__(256) void k_pass_begin(PassRows p, RowMeta rm, cons
 //   fixed tree.  S == 1: the epilogue runs on the tile in LDS.  S > 1: the tile goes to a partial
 //   buffer and the block that arrives last at the group's counter sums the S partials in order
 //   s = 0..S-1 and runs the epilogue, so results do not depend on arrival order.
-//   Tiles of the launch: tile(ct) = mt0 + ct * mt_stride, ct = z*MT + mt.
+//   Row tiles of the launch: z*MT + mt.
 // ------------------------------------------------------------------------------------------
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3, EPI_ROUTER = 4 };
 
@@ -609,7 +665,7 @@ struct GemmArgs {
     int kv_fetch_bytes;   // QKV launch before a per-head attention launch over one sequence: bytes of each kv head's K (and V^T) blocks to pull in, or 0
     const uint4 *W, *Xhi, *Xlo;
     float *part; int *counters;
-    int N, KS, S, mt0, mt_stride, rows_total;
+    int N, KS, S, rows_total;
     // RMSNorm of the GEMM input rows: rstd from per-group sums of squares (QKV, SWIGLU, LMHEAD)
     const float *ssq_in; int ncg_in, d_in; float eps;
     // QKV: RoPE, Q fragments, cache writes
@@ -620,7 +676,7 @@ struct GemmArgs {
     // SWIGLU: activation fragments over F channels
     uint4 *ahi, *alo; int F;
     // LMHEAD: logits, per-group row statistics
-    int k; float *logits; float T; uint64_t seed; RowStat *stat; int ncg_v;
+    int k, n_lm; float *logits; float T; uint64_t seed; RowStat *stat; int ncg_v;   // n_lm: rows with logits, k of each sequence, the first GEMM rows of the pass
     int draw;   // T > 0: also the Gumbel-max of the perturbed logits (a pass that samples its rows' tokens)
     unsigned long long *stamps;   // debugging: [workgroup][8] device-clock stamps of this launch, or null
     int k_lo;   // rows below k_lo keep the logits and statistics of an earlier pass (multi-pass draft)
@@ -647,14 +703,13 @@ __device__ __forceinline__ void tile_rstd(const float *ssq, float *rstd, int gro
 // The tile holds columns cg * WIDTH .. + WIDTH - 1 with row stride STRIDE.  WIDTH is a multiple of head_dim, so that
 // a head, and with it every rotation pair, lies inside one tile.
 // pre (optional): what qkv_prefetch loaded for this thread's item while the tile was still being summed.
-constexpr int QKV_PRE = 18;   // 8 (cos, sin) pairs, the row's cache slot, the tile's sequence
+constexpr int QKV_PRE = 19;   // 8 (cos, sin) pairs, the row's cache slot, its sequence, its attention row
 template <bool COH, int WIDTH = CG, int STRIDE = RED_STRIDE, bool PRE = false>
 __device__ __forceinline__ void epi_qkv(const GemmArgs &a, const float *tile, const float *rstd, int cg, int t,
                                         const float (&pre)[QKV_PRE]) {
     const int tidx = opaque_tid();
     const int hd = a.hd, Hq = a.Hq, Hkv = a.Hkv;
     const int half_hd = hd >> 1;
-    const int b = PRE ? __float_as_int(pre[17]) : a.rm.tile_seq[t];
     constexpr int RED_STRIDE = STRIDE;   // the row stride of this tile
     for (int item = tidx; item < 4 * WIDTH; item += 512) {   // GEMM workgroups have 512 threads
         const int row = item & 31, oct = item >> 5;
@@ -681,12 +736,16 @@ __device__ __forceinline__ void epi_qkv(const GemmArgs &a, const float *tile, co
         if (kind == 0) {
             uint4 hi, lo;
             pack8_split(v, hi, lo);
-            size_t vec = ((size_t)(t * Hq + head) * (hd / 16)) * 64 + frag_vec(row, i0 >> 3);
-            st16<COH>(a.qhi + vec, hi);
-            st16<COH>(a.qlo + vec, lo);
+            const int qr = PRE ? __float_as_int(pre[18]) : a.rm.qrow[grow];
+            if (qr >= 0) {
+                size_t vec = ((size_t)((qr >> 5) * Hq + head) * (hd / 16)) * 64 + frag_vec(qr & 31, i0 >> 3);
+                st16<COH>(a.qhi + vec, hi);
+                st16<COH>(a.qlo + vec, lo);
+            }
         } else {
             const int slot = PRE ? __float_as_int(pre[16]) : a.rm.slot[grow];
             if (slot >= 0) {
+                const int b = PRE ? __float_as_int(pre[17]) : a.rm.seq[grow];
                 size_t base = (size_t)b * a.kv.seq_stride + (size_t)head * a.kv.head_stride;
                 if (kind == 1) {
                     st16<COH>((uint4 *)(a.kv.k + base + k_cache_off(slot, i0 >> 3, hd)), pack8(v));
@@ -721,8 +780,8 @@ __device__ __forceinline__ void qkv_prefetch(const GemmArgs &a, float (&pre)[QKV
             pre[2 * e] = c.x; pre[2 * e + 1] = c.y;
         }
     }
-    if (kind >= 1) pre[16] = __int_as_float(a.rm.slot[grow]);
-    pre[17] = __int_as_float(a.rm.tile_seq[t]);
+    if (kind >= 1) { pre[16] = __int_as_float(a.rm.slot[grow]); pre[17] = __int_as_float(a.rm.seq[grow]); }
+    else pre[18] = __int_as_float(a.rm.qrow[grow]);
 }
 
 // O-proj / down-proj epilogue: h += y; new fragment planes of h; per-group sum of squares.
@@ -804,15 +863,16 @@ __device__ __forceinline__ void epi_swiglu(const GemmArgs &a, const float *tile,
 }
 
 // LM-head epilogue: RMSNorm scale, optional logits store, per-(row, group) argmax / sumexp / Gumbel-max.
-// LM rows are the first k rows of the tile; lm_row = ct*k + i.
+// LM rows are the first n_lm GEMM rows of the pass, k of each sequence.
 template <bool COH>
-__device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile, const float *rstd, int cg, int ct, int t) {
+__device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile, const float *rstd, int cg, int t) {
     const int tidx = opaque_tid();
     if (tidx >= 256) return;
-    const int V = a.N, k = a.k;
+    const int V = a.N;
     const float T = a.T;
     const int row = tidx >> 3, sub = tidx & 7;   // 8 threads per row, 16 columns each
-    const bool live = row < k && row >= a.k_lo;
+    const size_t lm = (size_t)t * 32 + row;
+    const bool live = (int)lm < a.n_lm && (int)lm % opaque_s(a.k) >= a.k_lo;
     float m = -INFINITY, gm = -INFINITY, se = 0.f;
     int idx = 0x7fffffff, gidx = 0x7fffffff;
     float z[16];
@@ -822,13 +882,13 @@ __device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile,
 #pragma unroll
         for (int e = 0; e < 16; ++e) z[e] = tile[row * RED_STRIDE + sub * 16 + e] * sc;
         if (a.logits) {
-            float *q = a.logits + ((size_t)ct * k + row) * V + (size_t)cg * CG + sub * 16;
+            float *q = a.logits + lm * V + (size_t)cg * CG + sub * 16;
 #pragma unroll
             for (int e = 0; e < 16; e += 4) *(float4 *)(q + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
         }
         uint64_t key = 0;
         const bool draw = T > 0.f && a.draw;
-        if (draw) key = row_key(a.seed, TAG_DRAFT, (uint64_t)a.rm.tile_seq[t], (uint64_t)a.rm.pos[t * 32 + row]);
+        if (draw) key = row_key(a.seed, TAG_DRAFT, (uint64_t)a.rm.seq[lm], (uint64_t)a.rm.pos[lm]);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             int v = cg * CG + sub * 16 + e;
@@ -850,7 +910,7 @@ __device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile,
 #pragma unroll
     for (int off = 1; off < 8; off <<= 1) se += shx(se, off);
     if (live && sub == 0) {
-        RowStat *sp = a.stat + ((size_t)ct * k + row) * a.ncg_v + cg;
+        RowStat *sp = a.stat + lm * a.ncg_v + cg;
         stf<COH>(&sp->m, m); sti<COH>(&sp->idx, idx); stf<COH>(&sp->sumexp, se); stf<COH>(&sp->gm, gm); sti<COH>(&sp->gidx, gidx);
     }
 }
@@ -915,9 +975,8 @@ __device__ __forceinline__ void epi_router(const GemmArgs &a, const float *tile,
 // RSTD_READY: `rstd` already holds the tile's factors (tile_rstd ran before a barrier the caller has passed).
 template <int EPI, bool COH, bool RSTD_READY = false>
 __device__ __forceinline__ void run_epilogue(const GemmArgs &a, float *tile, float *rstd, float *scratch,
-                                             const float (&hreg)[8], int cg, int ct) {
+                                             const float (&hreg)[8], int cg, int t) {
     // caller has synchronised after filling `tile`
-    const int t = a.mt0 + ct * a.mt_stride;
     if (EPI != EPI_RESID && !RSTD_READY) {
         tile_rstd<COH>(a.ssq_in, rstd, t * 32, a.ncg_in, a.d_in, a.eps);
         __syncthreads();
@@ -930,7 +989,7 @@ __device__ __forceinline__ void run_epilogue(const GemmArgs &a, float *tile, flo
     else if (EPI == EPI_RESID) epi_resid<COH>(a, tile, scratch, hreg, cg, t);
     else if (EPI == EPI_SWIGLU) epi_swiglu<COH>(a, tile, rstd, cg, t);
     else if (EPI == EPI_ROUTER) epi_router(a, tile, rstd, t);
-    else epi_lmhead<COH>(a, tile, rstd, cg, ct, t);
+    else epi_lmhead<COH>(a, tile, rstd, cg, t);
 }
 
 // Sum of the 8 waves' accumulators (one 32 x 128 tile each, MFMA register layout) in the fixed order
@@ -986,7 +1045,7 @@ __device__ __forceinline__ void gemm_finish(const GemmArgs &a, GemmSmem &sm, int
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int ct = z * MT + mt;
-        if (EPI == EPI_RESID) resid_prefetch<COH>(a, hreg[mt], cg, a.mt0 + ct * a.mt_stride);
+        if (EPI == EPI_RESID) resid_prefetch<COH>(a, hreg[mt], cg, ct);
         const size_t sstride = (size_t)a.rows_total * N;
         const float *p[2];
 #pragma unroll
@@ -1069,7 +1128,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &a, GemmSmem &sm, int 
     const uint4 *xh[MT], *xl[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        size_t tl = (size_t)(a.mt0 + (z * MT + mt) * a.mt_stride);
+        size_t tl = (size_t)(z * MT + mt);
         xh[mt] = a.Xhi + tl * KS * 64 + lane;
         xl[mt] = a.Xlo + tl * KS * 64 + lane;
     }
@@ -1094,7 +1153,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &a, GemmSmem &sm, int 
     if (RSTD_EARLY) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const float *sp = a.ssq_in + (size_t)((a.mt0 + (z * MT + mt) * a.mt_stride) * 32 + (tidx >> 4)) * a.ncg_in;
+            const float *sp = a.ssq_in + (size_t)((z * MT + mt) * 32 + (tidx >> 4)) * a.ncg_in;
 #pragma unroll
             for (int i = 0; i < RSQ; ++i)
                 if (i < nsq) load4_async(sq[mt][i], sp + min((tidx & 15) + 16 * i, a.ncg_in - 1));
@@ -1170,7 +1229,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &a, GemmSmem &sm, int 
     for (int mt = 0; mt < MT; ++mt) {
         const int ct = z * MT + mt;
         if (mt > 0) __syncthreads();
-        if (EPI == EPI_RESID && S == 1) resid_prefetch<COH>(a, hreg, cg, a.mt0 + ct * a.mt_stride);
+        if (EPI == EPI_RESID && S == 1) resid_prefetch<COH>(a, hreg, cg, ct);
         reduce_waves_to_tile(acc[mt], red, tile, w, lane);
         if (S == 1) {
             run_epilogue<EPI, COH, RSTD_EARLY>(a, tile, s_rstd + 32 * mt, red, hreg, cg, ct);
@@ -1252,7 +1311,7 @@ __global__ __launch_bounds__(512) void k_gemm_narrow(const GemmArgs a, int ngrp,
     const int tidx = opaque_tid();
     const int w = __builtin_amdgcn_readfirstlane(tidx >> 6), lane = tidx & 63;
     const int N = a.N, KS = a.KS;
-    const int t = a.mt0 + z * a.mt_stride;
+    const int t = z;
     const int slin = z * ngrp + p;   // stamps: 0 start, 1 this wave's k-steps multiplied, 2 epilogue done
     gemm_stamp(a, slin, 0);
     const uint4 *wp = a.W + (size_t)(p * NB) * KS * 64 + lane;
@@ -1653,13 +1712,13 @@ struct AttnPartial {   // per (tile, head, split): O in register layout [HD/32][
 };
 
 template <int HD, bool COH>
-__device__ __forceinline__ void attn_write_frag(const f32x16 *o, float inv, int t, int head, int Hq, int lane,
+__device__ __forceinline__ void attn_write_frag(const f32x16 *o, float inv, int grow, int head, int Hq, int lane,
                                                 uint4 *__restrict__ xhi, uint4 *__restrict__ xlo, int tt0 = 0,
                                                 int ntt = HD / 32) {
-    // o[i] holds O^T tile tt0 + i
+    // o[i] holds O^T tile tt0 + i; grow: the GEMM row of this lane's query row, < 0: none
     // lane (qrow, half) holds dims 32*tt + 8*q + 4*half + 0..3 in regs 4q..4q+3; the partner lane (other
     // half) holds the other 4 dims of the octet.  Half 0 writes octets with even q, half 1 odd q.
-    const int half = lane >> 5, qrow = lane & 31;
+    const int half = lane >> 5;
     const int KS = Hq * HD / 16;
 #pragma unroll
     for (int ti = 0; ti < HD / 32; ++ti) {
@@ -1674,13 +1733,13 @@ __device__ __forceinline__ void attn_write_frag(const f32x16 *o, float inv, int 
                 other[e] = shx(mine[e], 32);
             }
             // octet (tt, q): dims 32*tt + 8*q + 0..7 = half-0 lane's 4 values then half-1 lane's 4 values
-            if ((q & 1) == half) {
+            if ((q & 1) == half && grow >= 0) {
                 float v[8];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { v[e] = half ? other[e] : mine[e]; v[4 + e] = half ? mine[e] : other[e]; }
                 uint4 hi, lo;
                 pack8_split(v, hi, lo);
-                size_t vec = (size_t)t * KS * 64 + frag_vec(qrow, head * (HD / 8) + tt * 4 + q);
+                size_t vec = (size_t)(grow >> 5) * KS * 64 + frag_vec(grow & 31, head * (HD / 8) + tt * 4 + q);
                 st16<COH>(xhi + vec, hi);
                 st16<COH>(xlo + vec, lo);
             }
@@ -1724,7 +1783,7 @@ __global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, 
                                                  const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Vt,
                                                  size_t seq_stride, size_t head_stride,
                                                  const int *__restrict__ tile_seq, const int *__restrict__ row_limit,
-                                                 float *__restrict__ part, int Hq, int Hkv, int HG, int NS, float scale_log2e,
+                                                 const int *__restrict__ row_grow, float *__restrict__ part, int Hq, int Hkv, int HG, int NS, float scale_log2e,
                                                  uint4 *__restrict__ xhi, uint4 *__restrict__ xlo) {
     using SM = AttnSmem<HD>;
     constexpr int KSQ = HD / 16, HT = HD / 32, FPT = SM::FPT, LPW = FPT / 4;
@@ -1875,7 +1934,7 @@ __global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, 
     if (!active) return;
     const float l_tot = l_run + shx(l_run, 32);
     if (NS == 1) {
-        attn_write_frag<HD, false>(oacc, l_tot > 0.f ? 1.f / l_tot : 0.f, t, head, Hq, lane, xhi, xlo);
+        attn_write_frag<HD, false>(oacc, l_tot > 0.f ? 1.f / l_tot : 0.f, row_grow[t * 32 + qrow], head, Hq, lane, xhi, xlo);
     } else {
         float *pp = part + ((size_t)(t * Hq + head) * NS + split) * PF;
 #pragma unroll
@@ -1889,9 +1948,9 @@ __global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, 
 // Writes registers 8*hh .. 8*hh+7 of O^T tile tt (held in o[0..7], scaled by inv) into the output projection's
 // input fragments: octets q = 2*hh and 2*hh + 1 (see attn_write_frag for the lane pairing).
 template <int HD>
-__device__ __forceinline__ void attn_store_slice(const float (&o)[8], float inv, int Hq, int head, int t, int tt, int hh,
+__device__ __forceinline__ void attn_store_slice(const float (&o)[8], float inv, int Hq, int head, int grow, int tt, int hh,
                                                  int lane, uint4 *xhi, uint4 *xlo) {
-    const int half = lane >> 5, qrow = lane & 31;
+    const int half = lane >> 5;
     const int KS = Hq * HD / 16;
 #pragma unroll
     for (int qq = 0; qq < 2; ++qq) {
@@ -1899,13 +1958,13 @@ __device__ __forceinline__ void attn_store_slice(const float (&o)[8], float inv,
         float mine[4], other[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) { mine[e] = o[4 * qq + e] * inv; other[e] = shx(mine[e], 32); }
-        if ((q & 1) == half) {
+        if ((q & 1) == half && grow >= 0) {
             float v8[8];
 #pragma unroll
             for (int e = 0; e < 4; ++e) { v8[e] = half ? other[e] : mine[e]; v8[4 + e] = half ? mine[e] : other[e]; }
             uint4 hi, lo;
             pack8_split(v8, hi, lo);
-            const size_t vec = (size_t)t * KS * 64 + frag_vec(qrow, head * (HD / 8) + tt * 4 + q);
+            const size_t vec = (size_t)(grow >> 5) * KS * 64 + frag_vec(grow & 31, head * (HD / 8) + tt * 4 + q);
             st16<true>(xhi + vec, hi);
             st16<true>(xlo + vec, lo);
         }
@@ -1918,7 +1977,7 @@ __device__ __forceinline__ void attn_store_slice(const float (&o)[8], float inv,
 // EARLY (the merge kernel, which has the registers for it): the first 16 partial outputs are requested together
 // with the (M, L) pairs, which makes it two round trips.
 template <int HD, bool EARLY = false>
-__device__ __forceinline__ void attn_merge_item(const float *part, int NS, int Hq, float scale_log2e, uint4 *xhi, uint4 *xlo,
+__device__ __forceinline__ void attn_merge_item(const float *part, const int *row_grow, int NS, int Hq, float scale_log2e, uint4 *xhi, uint4 *xlo,
                                                 int head, int t, int tt, int hh, int lane) {
     constexpr int PF = AttnPartial<HD>::FLOATS;
     const int half = lane >> 5, qrow = lane & 31;
@@ -1959,18 +2018,18 @@ __device__ __forceinline__ void attn_merge_item(const float *part, int NS, int H
                 for (int r2 = 0; r2 < 4; ++r2) { o[2 * r2] += f[s0 + u] * v[u][r2].x; o[2 * r2 + 1] += f[s0 + u] * v[u][r2].y; }
         }
     }
-    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, t, tt, hh, lane, xhi, xlo);
+    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, row_grow[t * 32 + qrow], tt, hh, lane, xhi, xlo);
 }
 
 // grid: one wave per (tile, head, O^T tile, half): 256 threads = 4 wave items per block
 template <int HD>
-__global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ part, int NS, int Hq, int n_items,
+__global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ part, const int *__restrict__ row_grow, int NS, int Hq, int n_items,
                                                     float scale_log2e, uint4 *__restrict__ xhi, uint4 *__restrict__ xlo) {
     constexpr int HT = HD / 32;
     const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (j >= n_items) return;
     const int hh = j & 1, tt = (j >> 1) % HT, head = (j / (2 * HT)) % Hq, t = j / (2 * HT * Hq);
-    attn_merge_item<HD, true>(part, NS, Hq, scale_log2e, xhi, xlo, head, t, tt, hh, threadIdx.x & 63);
+    attn_merge_item<HD, true>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, tt, hh, threadIdx.x & 63);
 }
 
 // Merge of the NS key-range partials of one (tile, head) written by attn_head_item: wave item (tt, hh) owns registers
@@ -1978,7 +2037,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
 // outputs of the first 8 ranges (16 with head_dim <= 64) are requested together: one round trip for that many ranges;
 // ranges are combined in order s = 0..NS-1.  NS <= 32.
 template <int HD>
-__device__ __forceinline__ void attn_head_merge(const float *part, int NS, int Hq, float scale_log2e, uint4 *xhi, uint4 *xlo,
+__device__ __forceinline__ void attn_head_merge(const float *part, const int *row_grow, int NS, int Hq, float scale_log2e, uint4 *xhi, uint4 *xlo,
                                                 int head, int t, int tt, int hh, int lane) {
     constexpr int PF = AttnPartial<HD>::FLOATS;
     const int qrow = lane & 31;
@@ -2029,7 +2088,7 @@ __device__ __forceinline__ void attn_head_merge(const float *part, int NS, int H
                 }
         }
     }
-    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, t, tt, hh, lane, xhi, xlo);
+    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, row_grow[t * 32 + qrow], tt, hh, lane, xhi, xlo);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2059,7 +2118,7 @@ struct AttnHeadSmem {
 template <int HD>
 __device__ __forceinline__ void attn_head_item(const uint4 *Qhi, const uint4 *Qlo, const uint16_t *__restrict__ Kc,
                                                const uint16_t *__restrict__ Vt, size_t seq_stride, size_t head_stride,
-                                               int b, int lim, float *part, int *counters, int Hq, int Hkv, int NS,
+                                               int b, int lim, const int *row_grow, float *part, int *counters, int Hq, int Hkv, int NS,
                                                float scale_log2e, uint4 *xhi, uint4 *xlo, AttnHeadSmem<HD> &as, int head,
                                                int split, int t, const NextWeights &nx) {
     constexpr int HT = HD / 32, KSQ = HD / 16, FPT = KSQ + 2 * HT;   // fragments (1 KB each) per key tile
@@ -2244,7 +2303,7 @@ __device__ __forceinline__ void attn_head_item(const uint4 *Qhi, const uint4 *Ql
             o[4] += f[u] * a1.x; o[5] += f[u] * a1.y; o[6] += f[u] * a1.z; o[7] += f[u] * a1.w;
         }
         if (NS == 1) {
-            attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, t, tt, hh, lane, xhi, xlo);
+            attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, row_grow[t * 32 + qrow], tt, hh, lane, xhi, xlo);
         } else {
             // this range's partial: O as [(tt, hh)][register quad j][lane][4] (a wave writes 1 KB at a time), then
             // (M, L)[32 rows]
@@ -2257,7 +2316,7 @@ __device__ __forceinline__ void attn_head_item(const uint4 *Qhi, const uint4 *Ql
     if (NS == 1) return;
     // the key range that arrives last at the head's counter merges all of them
     if (!arrive_last(counters + t * Hq + head, NS, &as.last)) { prefetch_next(nx, as.slot); return; }
-    if (w < 2 * HT) attn_head_merge<HD>(part, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
+    if (w < 2 * HT) attn_head_merge<HD>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
 }
 
 // grid: x = kv_head + Hkv * (head in group + G * split), y = pass tile; 512 threads
@@ -2266,13 +2325,13 @@ __global__ __launch_bounds__(512) void k_attn_head(const uint4 *__restrict__ Qhi
                                                    const uint16_t *__restrict__ Kc, const uint16_t *__restrict__ Vt,
                                                    size_t seq_stride, size_t head_stride,
                                                    const int *__restrict__ tile_seq, const int *__restrict__ row_limit,
-                                                   float *__restrict__ part, int *__restrict__ counters, int Hq, int Hkv,
+                                                   const int *__restrict__ row_grow, float *__restrict__ part, int *__restrict__ counters, int Hq, int Hkv,
                                                    int NS, float scale_log2e, uint4 *__restrict__ xhi,
                                                    uint4 *__restrict__ xlo, const NextWeights nx) {
     __shared__ __attribute__((aligned(16))) AttnHeadSmem<HD> as;
     const int t = blockIdx.y;
     const int G = Hq / Hkv, kvh = blockIdx.x % Hkv, r = blockIdx.x / Hkv;
-    attn_head_item<HD>(Qhi, Qlo, Kc, Vt, seq_stride, head_stride, tile_seq[t], row_limit[t * 32 + (threadIdx.x & 31)], part,
+    attn_head_item<HD>(Qhi, Qlo, Kc, Vt, seq_stride, head_stride, tile_seq[t], row_limit[t * 32 + (threadIdx.x & 31)], row_grow, part,
                        counters, Hq, Hkv, NS, scale_log2e, xhi, xlo, as, kvh * G + r % G, r / G, t, nx);
 }
 
@@ -2327,7 +2386,7 @@ __global__ void k_accept_greedy(SeqState st, AcceptOut out, const int *__restric
 // row; the candidates of the ACC_NB shares meet through memory and the workgroup that arrives last picks the
 // winner (largest perturbed weight, lowest index on ties: the same token whatever the split) and commits.
 // The kernel reads nothing that it writes before all shares have arrived: the committed length j comes from
-// the verify pass's row metadata (row 0 of the sequence's tile sits at position j - 1), every share arrives
+// the verify pass's row metadata (the sequence's first row sits at position j - 1), every share arrives
 // on every path (finished sequence, all k drafts accepted, a draw), and only the last arrival touches the
 // per-sequence state and resets the counter.
 constexpr int ACC_NB = 32;
@@ -2347,7 +2406,7 @@ __global__ __launch_bounds__(1024) void k_accept_sample(SeqState st, AcceptOut o
     const bool finished = st.finished[b] != 0;   // written only by the last arrival, after this read
     const int *d = draft + b * k;
     const int kt = k + bonus;           // target rows per sequence
-    const int j = verify_pos[b * 32] + 1;
+    const int j = verify_pos[b * kt] + 1;
     const float invT = 1.f / T;
     if (threadIdx.x < 64) {   // the k tests at once (each has its own uniform and rows), then the first rejection
         const int i = threadIdx.x;
