@@ -915,60 +915,69 @@ __device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile,
     }
 }
 
-// router epilogue: logits over the experts -> softmax -> top_k (lowest index on ties) -> weights
-// renormalised to sum 1.  8 threads per row, 16 experts each.
+// Value of the lane that differs in the lane index by the pattern of one data-parallel-primitive control: 0xB1 xor 1,
+// 0x4E xor 2, 0x141 mirrored in its 8 lanes, 0x140 mirrored in its 16.  A reduction that takes these four steps in order has
+// the same result in all 16 lanes of a row; a step costs two instructions, an exchange through LDS over a hundred cycles.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true); }
+template <int CTRL>
+__device__ __forceinline__ float dppf(float v) { return __uint_as_float(dpp<CTRL>(__float_as_uint(v))); }
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp64_max(uint64_t v) {
+    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(v >> 32)) << 32) | dpp<CTRL>((uint32_t)v);
+    return o > v ? o : v;
+}
+
+// router epilogue: logits over the experts -> softmax -> top_k (lowest index on ties) -> weights renormalised to sum 1.
+// 16 threads per row, 8 experts each.  A candidate is one 64-bit key, the bits of its (non-negative) weight above
+// 128 - index, so that a comparison decides value and tie at once.  (Two values per candidate and exchanges through LDS
+// took 12 of the launch's 20 us.)
 __device__ __forceinline__ void epi_router(const GemmArgs &a, const float *tile, const float *rstd, int t) {
     const int tidx = opaque_tid();
-    if (tidx >= 256) return;
-    const int row = tidx >> 3, sub = tidx & 7;
+    const int row = tidx >> 4, sub = tidx & 15;
     const int grow = t * 32 + row;
-    float z[16];
+    float z[8];
     float m = -INFINITY;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int ex = sub * 16 + e;
+    for (int e = 0; e < 8; ++e) {
+        const int ex = sub * 8 + e;
         z[e] = ex < a.n_experts ? tile[row * RED_STRIDE + ex] * rstd[row] : -INFINITY;
         m = fmaxf(m, z[e]);
     }
-#pragma unroll
-    for (int off = 1; off < 8; off <<= 1) m = fmaxf(m, shx(m, off));
+    m = fmaxf(m, dppf<0xB1>(m)); m = fmaxf(m, dppf<0x4E>(m)); m = fmaxf(m, dppf<0x141>(m)); m = fmaxf(m, dppf<0x140>(m));
     float se = 0.f;
+    uint64_t key[8];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) { z[e] = expf(z[e] - m); se += z[e]; }   // exp(-inf) = 0 for padding
-#pragma unroll
-    for (int off = 1; off < 8; off <<= 1) se += shx(se, off);
-    float wsel[8]; int esel[8];
-    float wsum = 0.f;
-    for (int j = 0; j < a.top_k; ++j) {
-        float bv = -1.f; int bi = 0x7fffffff;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) argmax_merge(bv, bi, z[e], sub * 16 + e);
-#pragma unroll
-        for (int off = 1; off < 8; off <<= 1) {
-            float v2 = shx(bv, off); int i2 = shx(bi, off);
-            argmax_merge(bv, bi, v2, i2);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) if (sub * 16 + e == bi) z[e] = -1.f;   // taken
-        wsel[j] = bv / se; esel[j] = bi;
-        wsum += wsel[j];
+    for (int e = 0; e < 8; ++e) {
+        const float w = expf(z[e] - m);   // exp(-inf) = 0 for padding, which loses every tie
+        se += w;
+        key[e] = ((uint64_t)__float_as_uint(w) << 32) | (uint32_t)(128 - (sub * 8 + e));
     }
-    if (sub == 0) {
-        if (a.route_spread) {
-            // benchmarking stand-in for a trained router (a.route_spread - 1 = layer): every row gets top_k distinct
-            // pseudo-random experts with equal weights, so a block touches about n (1 - (1 - top_k / n)^rows) experts
-            const uint32_t base = (uint32_t)mix64(((uint64_t)a.route_spread << 32) | (uint32_t)grow);
-            const uint32_t stride = ((uint32_t)(mix64(base) >> 7) | 1u);   // odd: distinct picks when n is a power of two
-            for (int j = 0; j < a.top_k; ++j) {
-                a.route_e[grow * 8 + j] = (int)((base + (uint32_t)j * stride) % (uint32_t)a.n_experts);
-                a.route_w[grow * 8 + j] = 1.f / (float)a.top_k;
-            }
-        } else {
-            for (int j = 0; j < a.top_k; ++j) {
-                a.route_e[grow * 8 + j] = esel[j];
-                a.route_w[grow * 8 + j] = wsel[j] / wsum;
-            }
-        }
+    se += dppf<0xB1>(se); se += dppf<0x4E>(se); se += dppf<0x141>(se); se += dppf<0x140>(se);
+    float my_w = 0.f, wsum = 0.f;
+    int my_e = 0;
+    for (int j = 0; j < a.top_k; ++j) {
+        uint64_t best = key[0];
+#pragma unroll
+        for (int e = 1; e < 8; ++e) best = key[e] > best ? key[e] : best;
+        best = dpp64_max<0xB1>(best); best = dpp64_max<0x4E>(best); best = dpp64_max<0x141>(best); best = dpp64_max<0x140>(best);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) key[e] = key[e] == best ? 0 : key[e];   // taken (keys are distinct and at least 1)
+        const float w = __uint_as_float((uint32_t)(best >> 32)) / se;
+        wsum += w;
+        if (sub == j) { my_w = w; my_e = 128 - (int)(uint32_t)best; }
+    }
+    if (sub >= a.top_k) return;
+    if (a.route_spread) {
+        // benchmarking stand-in for a trained router (a.route_spread - 1 = layer): every row gets top_k distinct
+        // pseudo-random experts with equal weights, so a block touches about n (1 - (1 - top_k / n)^rows) experts
+        const uint32_t base = (uint32_t)mix64(((uint64_t)a.route_spread << 32) | (uint32_t)grow);
+        const uint32_t stride = ((uint32_t)(mix64(base) >> 7) | 1u);   // odd: distinct picks when n is a power of two
+        a.route_e[grow * 8 + sub] = (int)((base + (uint32_t)sub * stride) % (uint32_t)a.n_experts);
+        a.route_w[grow * 8 + sub] = 1.f / (float)a.top_k;
+    } else {
+        a.route_e[grow * 8 + sub] = my_e;
+        a.route_w[grow * 8 + sub] = my_w / wsum;
     }
 }
 
