@@ -176,6 +176,19 @@ __device__ __forceinline__ int opaque_s(int v) {
     return v;
 }
 
+// Value of the lane that differs in the lane index by the pattern of one data-parallel-primitive control: 0xB1 xor 1,
+// 0x4E xor 2, 0x141 mirrored in its 8 lanes, 0x140 mirrored in its 16.  A reduction that takes these four steps in order has
+// the same result in all 16 lanes of a row; a step costs two instructions, an exchange through LDS over a hundred cycles.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true); }
+template <int CTRL>
+__device__ __forceinline__ float dppf(float v) { return __uint_as_float(dpp<CTRL>(__float_as_uint(v))); }
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp64_max(uint64_t v) {
+    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(v >> 32)) << 32) | dpp<CTRL>((uint32_t)v);
+    return o > v ? o : v;
+}
+
 __device__ __forceinline__ void drain_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Row of the 32x32 MFMA result held in register r of a lane in half `half` (= lane / 32).
@@ -470,34 +483,47 @@ __device__ __forceinline__ void tile_to_frag(const float *tile, uint4 *xhi, uint
     }
 }
 
-// embedding gather of one (column group, tile): h[row] = E[tok[row]] (bf16 table), plus fragment planes and sums of
-// squares; tok: the tile's 32 token ids (global memory or LDS); 256 threads
-__device__ __forceinline__ void embed_tile(float *tile, const uint16_t *__restrict__ E, const int *tok, float *__restrict__ h,
+// embedding gather of one (column group, tile): h[row] = E[tok[row]] (bf16 table), plus fragment planes (the value itself and
+// zero: the table is bf16) and sums of squares per row and column group, or (ssq_sub == 4) per 32-column block of it;
+// tok: the tile's 32 token ids (global memory or LDS); 256 threads.  16 threads per row, 8 columns each, all in registers:
+// the launch is a chain of latencies (token, table row, stores), and a tile in LDS with one thread per row for the sums made
+// it 17 us for a prompt of 7 row tiles, 8 us for the smallest.
+__device__ __forceinline__ void embed_tile(const uint16_t *__restrict__ E, const int *tok, float *__restrict__ h,
                                            uint4 *__restrict__ xhi, uint4 *__restrict__ xlo, float *__restrict__ ssq, int d,
                                            int ncg, int ssq_sub, int cg, int t) {
-    for (int e = threadIdx.x; e < 32 * CG; e += 256) {
-        int row = e >> 7, col = e & 127;
-        int grow = t * 32 + row;
-        float v = bf2f(E[(size_t)tok[row] * d + cg * CG + col]);
-        tile[row * RED_STRIDE + col] = v;
-        h[(size_t)grow * d + cg * CG + col] = v;
+    uint4 v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int item = threadIdx.x + 256 * i, row = item >> 4, oct = item & 15;
+        v[i] = *(const uint4 *)(E + (size_t)tok[row] * d + cg * CG + oct * 8);
     }
-    __syncthreads();
-    tile_to_frag(tile, xhi, xlo, (size_t)t * (d / 16) * 64, cg * CG);
-    // sums of squares per row and column group, or (ssq_sub == 4) per 32-column block of it
-    if (threadIdx.x < 32 * ssq_sub) {
-        const int row = threadIdx.x & 31, blk = threadIdx.x >> 5, wdt = CG / ssq_sub;
-        float s = 0.f;
-        for (int c = 0; c < wdt; ++c) { float v = tile[row * RED_STRIDE + blk * wdt + c]; s += v * v; }
-        ssq[(size_t)(t * 32 + row) * (ncg * ssq_sub) + cg * ssq_sub + blk] = s;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int item = threadIdx.x + 256 * i, row = item >> 4, oct = item & 15;
+        const size_t grow = (size_t)t * 32 + row;
+        const float4 lo4 = make_float4(bf2f(v[i].x & 0xffffu), __uint_as_float(v[i].x & 0xffff0000u), bf2f(v[i].y & 0xffffu), __uint_as_float(v[i].y & 0xffff0000u));
+        const float4 hi4 = make_float4(bf2f(v[i].z & 0xffffu), __uint_as_float(v[i].z & 0xffff0000u), bf2f(v[i].w & 0xffffu), __uint_as_float(v[i].w & 0xffff0000u));
+        float4 *hp = (float4 *)(h + grow * d + cg * CG + oct * 8);
+        hp[0] = lo4;
+        hp[1] = hi4;
+        const size_t vec = (size_t)t * (d / 16) * 64 + frag_vec(row, cg * 16 + oct);
+        xhi[vec] = v[i];
+        xlo[vec] = make_uint4(0u, 0u, 0u, 0u);
+        float s = lo4.x * lo4.x + lo4.y * lo4.y + lo4.z * lo4.z + lo4.w * lo4.w + hi4.x * hi4.x + hi4.y * hi4.y + hi4.z * hi4.z + hi4.w * hi4.w;
+        s += dppf<0xB1>(s); s += dppf<0x4E>(s);   // four lanes: a 32-column block
+        if (ssq_sub == 4) {
+            if ((oct & 3) == 0) ssq[grow * (ncg * 4) + cg * 4 + (oct >> 2)] = s;
+        } else {
+            s += dppf<0x141>(s); s += dppf<0x140>(s);
+            if (oct == 0) ssq[grow * ncg + cg] = s;
+        }
     }
 }
 
 __global__ __launch_bounds__(256) void k_embed(const uint16_t *__restrict__ E, const int *__restrict__ tok,
                                                float *__restrict__ h, uint4 *__restrict__ xhi, uint4 *__restrict__ xlo,
                                                float *__restrict__ ssq, int d, int ncg, int ssq_sub) {
-    __shared__ float tile[32 * RED_STRIDE];
-    embed_tile(tile, E, tok + blockIdx.y * 32, h, xhi, xlo, ssq, d, ncg, ssq_sub, blockIdx.x, blockIdx.y);
+    embed_tile(E, tok + blockIdx.y * 32, h, xhi, xlo, ssq, d, ncg, ssq_sub, blockIdx.x, blockIdx.y);
 }
 
 // The start of a draft or verify pass in one launch: every block works out its tile's rows (pass_row), then blocks
@@ -508,7 +534,6 @@ __global__ __launch_bounds__(256) void k_pass_begin(PassRows p, RowMeta rm, cons
                                                     uint4 *__restrict__ xhi, uint4 *__restrict__ xlo, float *__restrict__ ssq,
                                                     int d, int ncg, int ssq_sub, const double *__restrict__ theta,
                                                     float2 *__restrict__ cs, int half, int ntiles, int n_attn) {
-    __shared__ float tile[32 * RED_STRIDE];
     __shared__ int s_tok[32], s_pos[32], s_pref[1025];
     const int t = blockIdx.y;
     if (t >= ((int)blockIdx.x == ncg + 1 ? n_attn : ntiles)) return;
@@ -530,7 +555,7 @@ __global__ __launch_bounds__(256) void k_pass_begin(PassRows p, RowMeta rm, cons
     }
     __syncthreads();
     if ((int)blockIdx.x < ncg) {
-        embed_tile(tile, E, s_tok, h, xhi, xlo, ssq, d, ncg, ssq_sub, blockIdx.x, t);
+        embed_tile(E, s_tok, h, xhi, xlo, ssq, d, ncg, ssq_sub, blockIdx.x, t);
     } else {
         for (int idx = threadIdx.x; idx < 32 * half; idx += 256) {
             const int row = idx / half, i = idx - row * half;
@@ -913,19 +938,6 @@ __device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile,
         RowStat *sp = a.stat + lm * a.ncg_v + cg;
         stf<COH>(&sp->m, m); sti<COH>(&sp->idx, idx); stf<COH>(&sp->sumexp, se); stf<COH>(&sp->gm, gm); sti<COH>(&sp->gidx, gidx);
     }
-}
-
-// Value of the lane that differs in the lane index by the pattern of one data-parallel-primitive control: 0xB1 xor 1,
-// 0x4E xor 2, 0x141 mirrored in its 8 lanes, 0x140 mirrored in its 16.  A reduction that takes these four steps in order has
-// the same result in all 16 lanes of a row; a step costs two instructions, an exchange through LDS over a hundred cycles.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true); }
-template <int CTRL>
-__device__ __forceinline__ float dppf(float v) { return __uint_as_float(dpp<CTRL>(__float_as_uint(v))); }
-template <int CTRL>
-__device__ __forceinline__ uint64_t dpp64_max(uint64_t v) {
-    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(v >> 32)) << 32) | dpp<CTRL>((uint32_t)v);
-    return o > v ? o : v;
 }
 
 // router epilogue: logits over the experts -> softmax -> top_k (lowest index on ties) -> weights renormalised to sum 1.
