@@ -38,6 +38,7 @@ constexpr int STAMP_MAX_BLOCKS = 4096;   // workgroups whose stamps deer_debug_g
 constexpr int PREFILL_TILES = 128;       // most row tiles of a prefill pass (4096 rows: every pass streams the weights once)
 constexpr int PART_TILES_MIN = 16;   // split-K partials exist for passes of up to max(2 * batch, 16) row tiles
 constexpr int MAX_NS = 32;          // key-range splits of block attention
+constexpr size_t H_UP_MAX = 1 << 20;  // most page-locked host memory of a context for uploads
 constexpr int NARROW_MAX_D = 1024;  // residual width up to which a dense model's O projection runs in 32-column workgroups
 constexpr int NEXT_SPAN_BYTES = 16 << 10;      // fetched ahead per 32-column block of a next-launch workgroup (4 blocks: 8 loads per thread)
 constexpr int KV_FETCH_MAX_BYTES = 1 << 20;    // fetched ahead per kv head of K and of V^T: a share of one XCD's 4 MB L2
@@ -85,7 +86,9 @@ struct Work {   // carved from the workspace
     double *theta[2] = {nullptr, nullptr};
     size_t part_floats = 0;   // capacity of `part`
     AccPart *acc_part = nullptr; int *acc_cnt = nullptr;   // sampling acceptance: per-share candidates, arrival counters
-    int4 *pf_desc = nullptr;  // prefill: per-tile (sequence, first position, rows, offset into ids)
+    int4 *pf_desc[2] = {nullptr, nullptr};   // prefill, per model: the pass's attention tiles (see PassRows)
+    char *up = nullptr;       // start of the block that the host uploads; offsets of the descriptors and the prompts in it
+    size_t up_desc = 0, up_ids = 0;
     unsigned long long *stamps = nullptr;   // [STAMP_MAX_BLOCKS][8], written on request (deer_debug_gemm_stamps)
     size_t bytes = 0;
 };
@@ -115,6 +118,10 @@ struct deer_ctx {
     std::vector<char> h_ao;          // host staging of the acceptance results (pageable; used only if pinning failed)
     char *h_pin = nullptr;           // the same, page-locked: the copy lands without an intermediate staging copy
     size_t h_pin_bytes = 0;
+    char *h_pin_dev = nullptr;       // its device address: the acceptance kernels write their results there
+    char *h_up = nullptr;            // page-locked image of what the host uploads (prompts beyond it: h_up_vec)
+    size_t h_up_bytes = 0;
+    std::vector<char> h_up_vec;
     std::string err;
     // optional per-launch timing (deer_debug_profile)
     bool prof_on = false;
@@ -251,8 +258,16 @@ void plan_work(Work &w, const deer_init_params &p, char *base) {
     const size_t lmrows = (size_t)B * 32;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return base ? base + o : nullptr; };
+    // what the host uploads when sequences enter lies together, for one copy: the state, the tile descriptors of the first
+    // prefill pass of each model, the prompts
+    w.up = take(0);
     w.st.len = (int *)take(B * 4); w.st.dr_len = (int *)take(B * 4); w.st.pending = (int *)take(B * 4);
-    w.st.ing_n = (int *)take(B * 4); w.st.finished = (int *)take(B * 4); w.st.ing_tok = (int *)take((size_t)B * 32 * 4);
+    w.st.ing_n = (int *)take(B * 4); w.st.finished = (int *)take(B * 4);
+    w.up_desc = off;
+    w.pf_desc[0] = (int4 *)take((size_t)MAXT * sizeof(int4)); w.pf_desc[1] = (int4 *)take((size_t)MAXT * sizeof(int4));
+    w.up_ids = off;
+    w.ids = (int *)take((size_t)B * p.max_seq * 4);
+    w.st.ing_tok = (int *)take((size_t)B * 32 * 4);
     w.rm.tok = (int *)take(MAXR * 4); w.rm.pos = (int *)take(MAXR * 4); w.rm.limit = (int *)take(MAXR * 4);
     w.rm.slot = (int *)take(MAXR * 4); w.rm.seq = (int *)take(MAXR * 4); w.rm.qrow = (int *)take(MAXR * 4); w.rm.grow = (int *)take(MAXR * 4);
     w.rm.tile_seq = (int *)take(MAXT * 4);
@@ -270,8 +285,6 @@ void plan_work(Work &w, const deer_init_params &p, char *base) {
     w.res[0] = (RowResult *)take(lmrows * sizeof(RowResult)); w.res[1] = (RowResult *)take(lmrows * sizeof(RowResult));
     w.ao.accept_len = (int *)take(B * 4); w.ao.n_committed = (int *)take(B * 4); w.ao.committed = (int *)take((size_t)B * 32 * 4);
     w.acc_part = (AccPart *)take((size_t)B * ACC_NB * sizeof(AccPart));
-    w.ids = (int *)take((size_t)B * p.max_seq * 4);
-    w.pf_desc = (int4 *)take((size_t)MAXT * sizeof(int4));
     for (const deer_model_cfg *mc : {&t, &d}) {
         if (!mc->n_experts || w.route_e) continue;
         const size_t tiles = 128 + (size_t)MAXR * 8 / 32, n_items = 128 + (size_t)MAXR * 8 / 64;   // 32-pair tiles and 64-pair items: the last of an expert may be short
@@ -490,10 +503,9 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
 constexpr int MOE_BLOCK_PAIRS = 12;
 
 // One forward pass of `model` over the rows described by the row metadata: ntiles tiles of GEMM rows, n_attn attention tiles.
-// rows: the pass's rows are described by a PassRows (draft, verify): one launch works them out, gathers the embeddings
-// and fills the RoPE table; null: the row metadata is in place already (prefill).
-int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, const LmPlan &lm, double kv_keys_total = 0.0,
-             const PassRows *rows_desc = nullptr) {
+// rows_desc: how the first launch finds the pass's rows.
+int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, const LmPlan &lm, double kv_keys_total,
+             const PassRows &rows_desc) {
     ModelRT &m = c->m[model];
     Work &w = c->wk;
     const deer_model_cfg &mc = m.c;
@@ -503,18 +515,9 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
     hipStream_t s = c->stream;
     if (c->stamp_launch >= 0 && model == c->stamp_model) (void)hipMemsetAsync(w.stamps, 0, (size_t)STAMP_MAX_BLOCKS * 64, s);
     prof_close(c);
-    if (rows_desc) {
-        hipLaunchKernelGGL(k_pass_begin, dim3(ncg_d + 2, std::max(ntiles, n_attn)), dim3(256), 0, s, *rows_desc, w.rm, (const uint16_t *)(m.w + m.off_embed),
-                           w.h, w.xa_hi, w.xa_lo, w.ssq, d, ncg_d, m.ssq_sub, m.theta, w.cs, hd / 2, ntiles, n_attn);
-        LAUNCHCHK(c, "k_pass_begin");
-    } else {
-        hipLaunchKernelGGL(k_embed, dim3(ncg_d, ntiles), dim3(256), 0, s, (const uint16_t *)(m.w + m.off_embed), w.rm.tok, w.h,
-                           w.xa_hi, w.xa_lo, w.ssq, d, ncg_d, m.ssq_sub);
-        LAUNCHCHK(c, "k_embed");
-        int n = rows * (hd / 2);
-        hipLaunchKernelGGL(k_rope_table, dim3((n + 255) / 256), dim3(256), 0, s, w.rm.pos, m.theta, w.cs, hd / 2, rows);
-        LAUNCHCHK(c, "k_rope_table");
-    }
+    hipLaunchKernelGGL(k_pass_begin, dim3(ncg_d + 2, std::max(ntiles, n_attn)), dim3(256), 0, s, rows_desc, w.rm, (const uint16_t *)(m.w + m.off_embed),
+                       w.h, w.xa_hi, w.xa_lo, w.ssq, d, ncg_d, m.ssq_sub, m.theta, w.cs, hd / 2, ntiles, n_attn);
+    LAUNCHCHK(c, "k_pass_begin");
     const int nkt = (max_limit + 31) / 32;
     // key-range splits: aim at two workgroups per compute unit; a split holds at least four key tiles; n_attn * NS never
     // exceeds the partial buffer (max(64, most tiles of a pass) tile slots)
@@ -664,21 +667,28 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
     return DEER_OK;
 }
 
-int upload_state(deer_ctx *c, int B, const int *len, const int *dr_len, const int *pending) {
-    Work &w = c->wk;
-    std::vector<int> zeros(B, 0);
-    HIPCHK(c, hipMemcpyAsync(w.st.len, len, B * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(w.st.dr_len, dr_len, B * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(w.st.pending, pending, B * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(w.st.ing_n, zeros.data(), B * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(w.st.finished, zeros.data(), B * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+// Host image of the block at Work::up: page-locked where it fits (hipMemcpyAsync then needs no copy of its own), valid until
+// the stream has been waited for.
+char *upload_image(deer_ctx *c, size_t bytes) {
+    if (c->h_up && bytes <= c->h_up_bytes) return c->h_up;
+    c->h_up_vec.resize(bytes);
+    return c->h_up_vec.data();
+}
+void fill_state(deer_ctx *c, char *img, int B, const int *len, const int *dr_len, const int *pending) {
+    const char *up = c->wk.up;
+    memcpy(img + ((char *)c->wk.st.len - up), len, (size_t)B * 4);
+    memcpy(img + ((char *)c->wk.st.dr_len - up), dr_len, (size_t)B * 4);
+    memcpy(img + ((char *)c->wk.st.pending - up), pending, (size_t)B * 4);
+    memset(img + ((char *)c->wk.st.ing_n - up), 0, (size_t)B * 4);
+    memset(img + ((char *)c->wk.st.finished - up), 0, (size_t)B * 4);
+}
+// the host's mirror once the device state is in place
+void set_state(deer_ctx *c, int B, const int *len) {
     c->batch = B;
     c->h_len.assign(len, len + B);
     c->h_ing_n.assign(B, 0);
     c->h_finished.assign(B, 0);
     c->state = ST_PREFILLED;
-    return DEER_OK;
 }
 
 }  // namespace
@@ -760,7 +770,13 @@ int deer_init_models(const deer_init_params *p, const deer_buffers *bufs, const 
     {   // a few KB of page-locked host memory for the acceptance results (host memory: the device buffers stay the caller's)
         const size_t bytes = (size_t)((const char *)c->wk.ao.committed - (const char *)c->wk.ao.accept_len) + (size_t)p->max_batch * 32 * 4;
         void *hp = nullptr;
-        if (hipHostMalloc(&hp, bytes, hipHostMallocDefault) == hipSuccess) { c->h_pin = (char *)hp; c->h_pin_bytes = bytes; }
+        if (hipHostMalloc(&hp, bytes, hipHostMallocDefault) == hipSuccess) {
+            void *dp = nullptr;
+            c->h_pin = (char *)hp; c->h_pin_bytes = bytes;
+            if (hipHostGetDevicePointer(&dp, hp, 0) == hipSuccess) c->h_pin_dev = (char *)dp; else (void)hipGetLastError();
+        } else (void)hipGetLastError();
+        const size_t up_bytes = std::min<size_t>(c->wk.up_ids + (size_t)p->max_batch * p->max_seq * 4, H_UP_MAX);
+        if (hipHostMalloc(&hp, up_bytes, hipHostMallocDefault) == hipSuccess) { c->h_up = (char *)hp; c->h_up_bytes = up_bytes; }
         else (void)hipGetLastError();
     }
     *out = c;
@@ -835,48 +851,49 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
         total += lens[b];
         pend[b] = ids[total - 1];
     }
-    HIPCHK(c, hipMemcpyAsync(w.ids, ids, total * 4, hipMemcpyHostToDevice, c->stream));
     // Passes of up to cap tiles; a pass takes the next rows of as many sequences as fit: its GEMM rows follow each other
     // without gaps, its attention tiles hold up to 32 rows of one sequence (rows of one sequence that are split over passes
-    // continue in the next pass, over the keys the earlier pass has written).  The descriptor lists stay alive until the
-    // stream has been waited for.
-    const int cap = std::max(2 * c->p.max_batch, PREFILL_TILES);
-    std::vector<std::vector<int4>> kept;
-    for (int model = 0; model < 2; ++model) {
-        std::vector<int4> desc;
-        int maxlim = 0, n_rows = 0;
-        auto flush = [&]() -> int {
-            if (desc.empty()) return DEER_OK;
-            kept.push_back(desc);
-            const std::vector<int4> &dsc = kept.back();
-            const int n_attn = (int)dsc.size(), ntiles = (n_rows + 31) / 32;
-            HIPCHK(c, hipMemcpyAsync(w.pf_desc, dsc.data(), dsc.size() * sizeof(int4), hipMemcpyHostToDevice, c->stream));
-            hipLaunchKernelGGL(k_rows_prefill, dim3(n_attn + 1), dim3(32), 0, c->stream, w.rm, w.ids, w.pf_desc, n_attn, n_rows, ntiles);
-            LAUNCHCHK(c, "k_rows_prefill");
-            LmPlan lm{false, 0, 0, 0.f, 0};
-            int rc = run_pass(c, model, ntiles, n_attn, maxlim, lm);
-            desc.clear();
-            maxlim = 0;
-            n_rows = 0;
-            return rc;
-        };
+    // continue in the next pass, over the keys the earlier pass has written).
+    struct Pass { std::vector<int4> desc; int n_rows = 0, maxlim = 0; };
+    const int cap = c->max_tiles;
+    std::vector<Pass> passes[2];
+    for (int model = 0; model < 2; ++model)
         for (int b = 0; b < batch; ++b) {
             const int nrows = (model == DEER_TARGET) ? lens[b] - 1 : lens[b];   // the last token stays pending for the target
-            int c0 = 0;
-            while (c0 < nrows) {
-                if ((int)desc.size() == cap || n_rows == cap * 32)
-                    if (int rc = flush()) return rc;
-                const int take = std::min({nrows - c0, 32, cap * 32 - n_rows});
-                desc.push_back(make_int4(b, c0, take | n_rows << 6, (int)(offs[b] + c0)));
-                maxlim = std::max(maxlim, c0 + take);
+            for (int c0 = 0; c0 < nrows;) {
+                std::vector<Pass> &ps = passes[model];
+                if (ps.empty() || (int)ps.back().desc.size() == cap || ps.back().n_rows == cap * 32) ps.emplace_back();
+                Pass &pa = ps.back();
+                const int take = std::min({nrows - c0, 32, cap * 32 - pa.n_rows});
+                pa.desc.push_back(make_int4(b, c0, take | pa.n_rows << 6, (int)(offs[b] + c0)));
+                pa.maxlim = std::max(pa.maxlim, c0 + take);
                 c0 += take;
-                n_rows += take;
+                pa.n_rows += take;
             }
         }
-        if (int rc = flush()) return rc;
-    }
+    // one copy for the state, the first pass's descriptors of each model and the prompts (five copies and a second wait made
+    // a short request's prefill 60 us longer)
+    const size_t up_bytes = w.up_ids + total * 4;
+    char *img = upload_image(c, up_bytes);
+    fill_state(c, img, batch, lens, lens, pend.data());
+    for (int model = 0; model < 2; ++model)
+        if (!passes[model].empty())
+            memcpy(img + ((char *)w.pf_desc[model] - w.up), passes[model][0].desc.data(), passes[model][0].desc.size() * sizeof(int4));
+    memcpy(img + w.up_ids, ids, total * 4);
+    HIPCHK(c, hipMemcpyAsync(w.up, img, up_bytes, hipMemcpyHostToDevice, c->stream));
+    for (int model = 0; model < 2; ++model)
+        for (size_t i = 0; i < passes[model].size(); ++i) {
+            const Pass &pa = passes[model][i];
+            if (i > 0)   // (the lists live until the stream has been waited for)
+                HIPCHK(c, hipMemcpyAsync(w.pf_desc[model], pa.desc.data(), pa.desc.size() * sizeof(int4), hipMemcpyHostToDevice, c->stream));
+            PassRows pr{};
+            pr.kind = ROWS_PREFILL; pr.desc = w.pf_desc[model]; pr.ids = w.ids; pr.n_desc = (int)pa.desc.size();
+            const LmPlan lm{false, 0, 0, 0.f, 0};
+            if (int rc = run_pass(c, model, (pa.n_rows + 31) / 32, pr.n_desc, pa.maxlim, lm, 0.0, pr)) return rc;
+        }
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    return upload_state(c, batch, lenv.data(), lenv.data(), pend.data());
+    set_state(c, batch, lenv.data());
+    return DEER_OK;
 }
 
 int deer_set_prefilled(deer_ctx *c, int32_t batch, const int32_t *lens, const int32_t *last) {
@@ -887,7 +904,13 @@ int deer_set_prefilled(deer_ctx *c, int32_t batch, const int32_t *lens, const in
         if (lens[b] + c->p.max_k > c->p.max_seq) return fail(c, DEER_ECAPACITY, "sequence %d exceeds max_seq", b);
         if (last[b] < 0 || last[b] >= c->p.target.vocab) return fail(c, DEER_EINVAL, "token id outside the vocabulary");
     }
-    return upload_state(c, batch, lens, lens, last);
+    const size_t bytes = c->wk.up_desc;
+    char *img = upload_image(c, bytes);
+    fill_state(c, img, batch, lens, lens, last);
+    HIPCHK(c, hipMemcpyAsync(c->wk.up, img, bytes, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    set_state(c, batch, lens);
+    return DEER_OK;
 }
 
 int deer_draft_block_multipass(deer_ctx *c, int32_t k, float T, uint64_t seed, int32_t n_passes, int32_t *draft_dev) {
@@ -913,10 +936,10 @@ int deer_draft_block_multipass(deer_ctx *c, int32_t k, float T, uint64_t seed, i
         const int lo = (k * (s - 1) + n_passes - 1) / n_passes, hi = (k * s + n_passes - 1) / n_passes;
         if (hi == lo) continue;
         PassRows pr{};
-        pr.draft_pass = 1; pr.st = w.st; pr.tokens = draft_dev; pr.k = k; pr.nrows = 0; pr.vocab = c->p.drafter.vocab;
+        pr.kind = ROWS_DRAFT; pr.st = w.st; pr.tokens = draft_dev; pr.k = k; pr.nrows = 0; pr.vocab = c->p.drafter.vocab;
         pr.mask_id = c->p.mask_token_id; pr.n_fixed = lo; pr.B = B; pr.n_ingest = n_ing; pr.share = k + max_ing <= 32;
         LmPlan lm{true, B * k, k, T, seed, lo, T > 0.f};
-        int rc = run_pass(c, DEER_DRAFTER, (B * k + n_ing + 31) / 32, n_ing > 0 && !pr.share ? 2 * B : B, maxlim, lm, keys, &pr);
+        int rc = run_pass(c, DEER_DRAFTER, (B * k + n_ing + 31) / 32, n_ing > 0 && !pr.share ? 2 * B : B, maxlim, lm, keys, pr);
         if (rc) return rc;
         hipLaunchKernelGGL(k_draft_finish, dim3(B), dim3(32), 0, c->stream, w.st, w.res[DEER_DRAFTER], draft_dev, k, lo);
         LAUNCHCHK(c, "k_draft_finish");
@@ -944,12 +967,12 @@ int deer_verify_block(deer_ctx *c, int32_t k, float T, const int32_t *draft_dev)
     for (int b = 0; b < B; ++b) maxlim = std::max(maxlim, c->h_len[b] - 1 + nrows);
     Work &w = c->wk;
     PassRows pr{};
-    pr.draft_pass = 0; pr.st = w.st; pr.tokens = draft_dev; pr.k = k; pr.nrows = nrows; pr.vocab = c->p.target.vocab;
+    pr.kind = ROWS_VERIFY; pr.st = w.st; pr.tokens = draft_dev; pr.k = k; pr.nrows = nrows; pr.vocab = c->p.target.vocab;
     pr.B = B;
     LmPlan lm{true, B * nrows, nrows, T, 0};
     double keys = 0;
     for (int b = 0; b < B; ++b) keys += c->h_len[b] - 1 + nrows;
-    int rc = run_pass(c, DEER_TARGET, (B * nrows + 31) / 32, B, maxlim, lm, keys, &pr);
+    int rc = run_pass(c, DEER_TARGET, (B * nrows + 31) / 32, B, maxlim, lm, keys, pr);
     if (rc) return rc;
     c->wk_draft = draft_dev;
     c->state = ST_VERIFIED;
@@ -976,16 +999,21 @@ static int accept_impl(deer_ctx *c, int32_t k, float T, uint64_t seed, int32_t *
         c->h_ao.resize(bytes);
         host = c->h_ao.data();
     }
+    // the kernels write their few results straight into page-locked host memory where there is some (a copy behind them is one
+    // more launch of a few microseconds per iteration)
+    const bool direct = host == c->h_pin && c->h_pin_dev;
+    AcceptOut ao = w.ao;
+    if (direct) ao = AcceptOut{(int *)c->h_pin_dev, (int *)(c->h_pin_dev + o_n), (int *)(c->h_pin_dev + o_c)};
     if (T == 0.f)
-        hipLaunchKernelGGL(k_accept_greedy, dim3(B), dim3(64), 0, c->stream, w.st, w.ao, c->wk_draft, w.res[DEER_TARGET], k,
+        hipLaunchKernelGGL(k_accept_greedy, dim3(B), dim3(64), 0, c->stream, w.st, ao, c->wk_draft, w.res[DEER_TARGET], k,
                            c->p.eos_token_id, c->bonus);
     else
-        hipLaunchKernelGGL(k_accept_sample, dim3(B, ACC_NB), dim3(1024), 0, c->stream, w.st, w.ao, c->wk_draft, w.res[DEER_TARGET],
+        hipLaunchKernelGGL(k_accept_sample, dim3(B, ACC_NB), dim3(1024), 0, c->stream, w.st, ao, c->wk_draft, w.res[DEER_TARGET],
                            w.res[DEER_DRAFTER], w.logits[DEER_TARGET], w.logits[DEER_DRAFTER], k, V, T, seed, c->p.eos_token_id,
                            c->bonus, acc_part, acc_cnt, w.rm.pos);
     LAUNCHCHK(c, "k_accept");
-    // the three result arrays lie one after the other in the workspace: one copy instead of three
-    HIPCHK(c, hipMemcpyAsync(host, d0, bytes, hipMemcpyDeviceToHost, c->stream));
+    // (the three result arrays lie one after the other in the workspace: one copy)
+    if (!direct) HIPCHK(c, hipMemcpyAsync(host, d0, bytes, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     memcpy(acc, host, (size_t)B * 4);
     memcpy(ncom, host + o_n, (size_t)B * 4);
@@ -1031,6 +1059,7 @@ int deer_destroy(deer_ctx *c) {
     (void)hipStreamSynchronize(c->stream);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     if (c->h_pin) (void)hipHostFree(c->h_pin);
+    if (c->h_up) (void)hipHostFree(c->h_up);
     delete c;
     return DEER_OK;
 }

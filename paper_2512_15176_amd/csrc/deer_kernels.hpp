@@ -367,13 +367,17 @@ __device__ __forceinline__ int safe_tok(int t, int vocab) { return (t < 0 || t >
 //   committed tokens of all sequences, causal.  Attention tile b holds the MASK rows; the committed tokens of b follow them
 //   there if they fit for every sequence (share), else they have the tile B + b.  The first n_fixed block rows hold the
 //   tokens fixed[b][0 .. n_fixed) instead of the MASK id (a partially filled block: a later pass of a multi-pass draft).
+//   prefill: attention tile t holds desc[t].z & 63 rows of sequence desc[t].x, causal, at positions desc[t].y + r, whose token
+//   ids start at ids[desc[t].w]; they are the GEMM rows from desc[t].z >> 6 on (packed over all sequences of the pass).
+enum { ROWS_VERIFY = 0, ROWS_DRAFT = 1, ROWS_PREFILL = 2 };
 struct PassRows {
-    int draft_pass;                  // 0: verify, 1: draft
+    int kind;
     SeqState st;
     const int *tokens;               // verify: the draft tokens [B][k]; draft: the fixed tokens [B][k] (n_fixed > 0)
     int k, nrows, vocab;             // nrows: verify rows per sequence
     int mask_id, n_fixed;
     int B, share, n_ingest;          // sequences; draft: committed tokens in all that the drafter has not cached
+    const int4 *desc; const int *ids; int n_desc;   // prefill
 };
 struct RowDesc { int tok, pos, slot, seq, qrow; };
 
@@ -400,7 +404,19 @@ __device__ __forceinline__ void ingest_prefix(const PassRows &p, int *pref) {
 // GEMM row g
 __device__ __forceinline__ RowDesc pass_row(const PassRows &p, const int *pref, int g) {
     RowDesc d{0, 0, -1, 0, -1};
-    if (!p.draft_pass) {
+    if (p.kind == ROWS_PREFILL) {
+        // tiles hold at most 32 rows, so row g lies in tile g / 32 (every tile before it is full) or a later one
+        int lo = min(g >> 5, p.n_desc - 1), hi = p.n_desc - 1;
+        int4 c = p.desc[lo];
+        if (g - (c.z >> 6) >= (c.z & 63)) {
+            while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if ((p.desc[mid].z >> 6) <= g) lo = mid; else hi = mid - 1; }
+            c = p.desc[lo];
+        }
+        const int r = g - (c.z >> 6);
+        if (r < (c.z & 63)) d = RowDesc{p.ids[c.w + r], c.y + r, c.y + r, c.x, lo * 32 + r};
+        return d;
+    }
+    if (p.kind == ROWS_VERIFY) {
         const int b = g / p.nrows, r = g - b * p.nrows;
         if (b < p.B) {
             const int pos = p.st.len[b] - 1 + r;
@@ -426,9 +442,15 @@ __device__ __forceinline__ RowDesc pass_row(const PassRows &p, const int *pref, 
 
 // attention row r of tile t: its key limit and GEMM row; b: the tile's sequence
 __device__ __forceinline__ void pass_attn_row(const PassRows &p, const int *pref, int t, int r, int &b, int &limit, int &grow) {
-    b = t < p.B ? t : t - p.B;
     limit = 0; grow = -1;
-    if (!p.draft_pass) {
+    if (p.kind == ROWS_PREFILL) {
+        const int4 c = p.desc[t];
+        b = c.x;
+        if (r < (c.z & 63)) { limit = c.y + r + 1; grow = (c.z >> 6) + r; }
+        return;
+    }
+    b = t < p.B ? t : t - p.B;
+    if (p.kind == ROWS_VERIFY) {
         if (r < p.nrows) { limit = p.st.len[b] + r; grow = b * p.nrows + r; }
         return;
     }
@@ -436,36 +458,6 @@ __device__ __forceinline__ void pass_attn_row(const PassRows &p, const int *pref
     if (p.n_ingest == 0) return;
     const int i = t < p.B ? (p.share ? r - p.k : 32) : r;
     if (i < pref[b + 1] - pref[b]) { limit = p.st.dr_len[b] + i + 1; grow = p.B * p.k + pref[b] + i; }
-}
-
-// prefill pass: attention tile t holds desc[t].z & 63 rows of sequence desc[t].x, causal, at positions desc[t].y + r, whose
-// token ids start at ids[desc[t].w]; they are the GEMM rows from desc[t].z >> 6 on (packed over all sequences of the pass).
-// The last block marks the padding rows n_rows .. 32 * ntiles - 1.
-__global__ void k_rows_prefill(RowMeta rm, const int *__restrict__ ids, const int4 *__restrict__ desc, int n_desc, int n_rows, int ntiles) {
-    const int r = threadIdx.x;
-    if ((int)blockIdx.x == n_desc) {
-        const int g = n_rows + r;
-        if (g < ntiles * 32) { rm.tok[g] = 0; rm.pos[g] = 0; rm.slot[g] = -1; rm.seq[g] = 0; rm.qrow[g] = -1; }
-        return;
-    }
-    const int4 dsc = desc[blockIdx.x];
-    const int a = blockIdx.x * 32 + r, n = dsc.z & 63, g = (dsc.z >> 6) + r;
-    if (r == 0) rm.tile_seq[blockIdx.x] = dsc.x;
-    const bool live = r < n;
-    rm.limit[a] = live ? dsc.y + r + 1 : 0;
-    rm.grow[a] = live ? g : -1;
-    if (live) { rm.tok[g] = ids[dsc.w + r]; rm.pos[g] = dsc.y + r; rm.slot[g] = dsc.y + r; rm.seq[g] = dsc.x; rm.qrow[g] = a; }
-}
-
-// cos/sin of pos * theta_i, evaluated in double, stored fp32: cs[row][i] = (cos, sin)
-__global__ void k_rope_table(const int *__restrict__ pos, const double *__restrict__ theta, float2 *__restrict__ cs,
-                             int half, int rows) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= rows * half) return;
-    int row = idx / half, i = idx % half;
-    double s, c;
-    sincos((double)pos[row] * theta[i], &s, &c);
-    cs[idx] = make_float2((float)c, (float)s);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -509,24 +501,22 @@ __device__ __forceinline__ void embed_tile(const uint16_t *__restrict__ E, const
         const size_t vec = (size_t)t * (d / 16) * 64 + frag_vec(row, cg * 16 + oct);
         xhi[vec] = v[i];
         xlo[vec] = make_uint4(0u, 0u, 0u, 0u);
-        float s = lo4.x * lo4.x + lo4.y * lo4.y + lo4.z * lo4.z + lo4.w * lo4.w + hi4.x * hi4.x + hi4.y * hi4.y + hi4.z * hi4.z + hi4.w * hi4.w;
-        s += dppf<0xB1>(s); s += dppf<0x4E>(s);   // four lanes: a 32-column block
-        if (ssq_sub == 4) {
-            if ((oct & 3) == 0) ssq[grow * (ncg * 4) + cg * 4 + (oct >> 2)] = s;
-        } else {
-            s += dppf<0x141>(s); s += dppf<0x140>(s);
-            if (oct == 0) ssq[grow * ncg + cg] = s;
+        // the squares in column order: the running sum moves from a row's lane to the next (row_shr:1), so that after as many
+        // steps as a block has lanes its last lane has the whole sum
+        const float x[8] = {lo4.x, lo4.y, lo4.z, lo4.w, hi4.x, hi4.y, hi4.z, hi4.w};
+        const int lanes = 16 / ssq_sub, at = oct & (lanes - 1);
+        float s = 0.f;
+        for (int step = 0; step < lanes; ++step) {
+            const float before = dppf<0x111>(s);
+            s = at == 0 ? 0.f : before;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s = fmaf(x[e], x[e], s);
         }
+        if (at == lanes - 1) ssq[grow * (ncg * ssq_sub) + cg * ssq_sub + (ssq_sub == 4 ? oct >> 2 : 0)] = s;
     }
 }
 
-__global__ __launch_bounds__(256) void k_embed(const uint16_t *__restrict__ E, const int *__restrict__ tok,
-                                               float *__restrict__ h, uint4 *__restrict__ xhi, uint4 *__restrict__ xlo,
-                                               float *__restrict__ ssq, int d, int ncg, int ssq_sub) {
-    embed_tile(E, tok + blockIdx.y * 32, h, xhi, xlo, ssq, d, ncg, ssq_sub, blockIdx.x, blockIdx.y);
-}
-
-// The start of a draft or verify pass in one launch: every block works out its tile's rows (pass_row), then blocks
+// The start of a pass in one launch: every block works out its tile's rows (pass_row), then blocks
 // x < ncg gather the embeddings of column group x, block x == ncg writes the row metadata and the tile's RoPE table; block
 // x == ncg + 1 writes the metadata of attention tile y.  (Three launches of a few microseconds each left the GPU waiting
 // for the host at the start of every pass.)
@@ -537,7 +527,7 @@ __global__ __launch_bounds__(256) void k_pass_begin(PassRows p, RowMeta rm, cons
     __shared__ int s_tok[32], s_pos[32], s_pref[1025];
     const int t = blockIdx.y;
     if (t >= ((int)blockIdx.x == ncg + 1 ? n_attn : ntiles)) return;
-    if (p.draft_pass && p.n_ingest > 0) ingest_prefix(p, s_pref);
+    if (p.kind == ROWS_DRAFT && p.n_ingest > 0) ingest_prefix(p, s_pref);
     if ((int)blockIdx.x == ncg + 1) {
         if (threadIdx.x < 32) {
             int b, limit, grow;
@@ -2359,7 +2349,7 @@ __global__ __launch_bounds__(512) void k_attn_head(const uint4 *__restrict__ Qhi
 // ------------------------------------------------------------------------------------------
 // acceptance and commit, one block per sequence
 // ------------------------------------------------------------------------------------------
-struct AcceptOut { int *accept_len, *n_committed, *committed; };   // device [B], [B], [B][k + bonus]
+struct AcceptOut { int *accept_len, *n_committed, *committed; };   // [B], [B], [B][k + bonus]: page-locked host memory (written, never read)
 
 // bonus = 1: the target pass had k + 1 rows and `corr` is also the extra token after k accepted drafts
 __device__ __forceinline__ void commit_tokens(SeqState st, AcceptOut out, int b, int k, int a, int corr, const int *d,
@@ -2367,9 +2357,9 @@ __device__ __forceinline__ void commit_tokens(SeqState st, AcceptOut out, int b,
     // thread 0 only
     const int cs = k + bonus;
     int n = (a < k) ? a + 1 : cs;
-    int fin = 0;
+    int fin = 0, tok = corr;
     for (int i = 0; i < n; ++i) {
-        int tok = (i < a) ? d[i] : corr;
+        tok = (i < a) ? d[i] : corr;
         out.committed[b * cs + i] = tok;
         st.ing_tok[b * 32 + i] = tok;
         if (eos >= 0 && tok == eos) { n = i + 1; fin = 1; break; }
@@ -2378,7 +2368,7 @@ __device__ __forceinline__ void commit_tokens(SeqState st, AcceptOut out, int b,
     out.n_committed[b] = n;
     st.ing_n[b] = n;
     st.len[b] += n;
-    st.pending[b] = out.committed[b * cs + n - 1];
+    st.pending[b] = tok;
     if (fin) st.finished[b] = 1;
 }
 
