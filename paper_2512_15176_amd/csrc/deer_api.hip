@@ -369,8 +369,8 @@ double stream_us(int N, int KS, int MT, int zg, int S) {
 double narrow_us(int ntiles, bool qkv) {
     return qkv ? 8.0 + 6.2 * std::max(0.0, ntiles * 24 / 256.0 - 1.0) : 6.0 + 9.0 * std::max(0.0, ntiles * 32 / 512.0 - 0.5);
 }
-// Blocked kernel: NB = 4 (128 x 256 per workgroup, two on a compute unit: 0.34 us per k-step each up to two of them, 0.40
-// when all are busy for long) or NB = 2 (128 x 128; 0.245 us alone on its compute unit, 0.225 otherwise).
+// Blocked kernel: NB = 4 (128 x 256 per workgroup: 0.3 to 0.4 us per k-step, the more the busier the chip) or NB = 2
+// (128 x 128: 0.16 us with 64 workgroups, 0.24 with one per compute unit, 0.225 with more).
 struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; };
 BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size_t part_floats) {
     BlockPlan best;
@@ -389,8 +389,10 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
             // rounds of workgroups: two share a compute unit and fill each other's gaps
             const double q = (double)nrb * ncb * S / 256.0;
             const double units = q <= 1.0 ? 1.0 : q > 2.0 ? 0.5 * (q + std::ceil(q)) : NB == 4 ? 2.0 : 1.45 + 0.5 * (q - 1.0);
-            const double step = NB == 4 ? (q <= 2.0 ? 0.34 : 0.40) : (q <= 1.0 ? 0.245 : 0.225);
-            const double us = 10.0 + units * per * step + (S > 1 ? 4.0 + 2.0 * tile_bytes / 4e6 : 0.0);
+            // fewer workgroups get more of the L2s each
+            const double step = NB == 4 ? (q <= 1.0 ? 0.30 + 0.09 * q : q <= 2.0 ? 0.36 : 0.40) : (q <= 1.0 ? 0.15 + 0.09 * q : 0.225);
+            const double mb = tile_bytes * 1e-6;   // shares that meet through memory: cheap while the L2s hold them
+            const double us = 10.0 + units * per * step + (S > 1 ? S + (mb <= 20.0 ? 0.2 * mb : 4.0 + 0.55 * (mb - 20.0)) : 0.0);
             if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0, us};
         }
     }

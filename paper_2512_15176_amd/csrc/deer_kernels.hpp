@@ -1717,7 +1717,7 @@ __global__ void k_draft_finish(SeqState st, const RowResult *__restrict__ res, i
 //   trips to memory on one workgroup).
 // ------------------------------------------------------------------------------------------
 template <int HD>
-struct AttnPartial {   // per (tile, head, split): O in register layout [HD/32][8 reg pairs][64 lanes][2], then (M, L)[32]
+struct AttnPartial {   // per (tile, head, split): O in register layout [HD/32][4 register quads][64 lanes][4], then (M, L)[32]
     static constexpr int O_FLOATS = 32 * HD;
     static constexpr int FLOATS = 32 * HD + 64;
 };
@@ -1951,8 +1951,9 @@ __global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, 
 #pragma unroll
         for (int tt = 0; tt < HT; ++tt)
 #pragma unroll
-            for (int r2 = 0; r2 < 8; ++r2) st_agent2(pp + ((tt * 8 + r2) * 64 + lane) * 2, oacc[tt][2 * r2], oacc[tt][2 * r2 + 1]);
-        if (half == 0) st_agent2(pp + 32 * HD + 2 * qrow, m_run, l_tot);
+            for (int q = 0; q < 4; ++q)
+                *(float4 *)(pp + ((tt * 4 + q) * 64 + lane) * 4) = make_float4(oacc[tt][4 * q], oacc[tt][4 * q + 1], oacc[tt][4 * q + 2], oacc[tt][4 * q + 3]);
+        if (half == 0) *(float2 *)(pp + 32 * HD + 2 * qrow) = make_float2(m_run, l_tot);
     }
 }
 
@@ -1982,37 +1983,38 @@ __device__ __forceinline__ void attn_store_slice(const float (&o)[8], float inv,
     }
 }
 
-// Merge of the NS key-range partials of one (tile, head): wave item (tt, hh) owns register pairs 4*hh .. 4*hh+3
-// of O^T tile tt.  All (M, L) pairs are requested at once, then the partial outputs 16 splits at a time, so a
-// merge of 32 splits is three memory round trips.  Splits are combined in order s = 0..NS-1.  NS <= 32.
-// EARLY (the merge kernel, which has the registers for it): the first 16 partial outputs are requested together
-// with the (M, L) pairs, which makes it two round trips.
-template <int HD, bool EARLY = false>
-__device__ __forceinline__ void attn_merge_item(const float *part, const int *row_grow, int NS, int Hq, float scale_log2e, uint4 *xhi, uint4 *xlo,
-                                                int head, int t, int tt, int hh, int lane) {
-    constexpr int PF = AttnPartial<HD>::FLOATS;
-    const int half = lane >> 5, qrow = lane & 31;
+// Merge of the NS key-range partials that k_attn left: one wave per (tile, head, O^T tile tt, register half hh).  The (M, L)
+// pairs and the first 16 partial outputs (two register quads of 1 KB per wave each) are requested together; ranges are
+// combined in order s = 0..NS-1.  NS <= 32.  Producer and consumer are separated by a kernel boundary: plain 16-byte
+// accesses (8-byte ones that bypass the L2, as between workgroups of one launch, took 20 us for 16 tiles x 32 heads x 4
+// ranges).  grid: 256 threads = 4 wave items per block
+template <int HD>
+__global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ part, const int *__restrict__ row_grow, int NS, int Hq, int n_items,
+                                                    float scale_log2e, uint4 *__restrict__ xhi, uint4 *__restrict__ xlo) {
+    constexpr int HT = HD / 32, PF = AttnPartial<HD>::FLOATS, CH = 16;
+    const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, qrow = lane & 31;
+    if (j >= n_items) return;
+    const int hh = j & 1, tt = (j >> 1) % HT, head = (j / (2 * HT)) % Hq, t = j / (2 * HT * Hq);
     const float *p0 = part + (size_t)(t * Hq + head) * NS * PF;
-    float f[32];
-    float M = -INFINITY, L = 0.f;
-    float2 v[16][4];
-    auto load_half = [&](int s0) {
+    const float4 *po = (const float4 *)(p0 + ((tt * 2 + hh) * 2 * 64 + lane) * 4);
+    const int grow = row_grow[t * 32 + qrow];
+    float4 v[CH][2];
+    auto request = [&](int s0) {
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-#pragma unroll
-            for (int r2 = 0; r2 < 4; ++r2)
-                v[u][r2] = ld_agent2(p0 + (size_t)min(s0 + u, NS - 1) * PF + ((tt * 8 + 4 * hh + r2) * 64 + lane) * 2);
+        for (int u = 0; u < CH; ++u)
+            if (s0 + u < NS) { v[u][0] = po[(size_t)(s0 + u) * (PF / 4)]; v[u][1] = po[(size_t)(s0 + u) * (PF / 4) + 64]; }
     };
-    if (EARLY) load_half(0);
+    request(0);
+    float f[32], M = -INFINITY, L = 0.f;
     {
         float2 ml[32];
 #pragma unroll
-        for (int s = 0; s < 32; ++s) ml[s] = ld_agent2(p0 + (size_t)min(s, NS - 1) * PF + 32 * HD + 2 * qrow);
+        for (int s = 0; s < 32; ++s) ml[s] = s < NS ? *(const float2 *)(p0 + (size_t)s * PF + 32 * HD + 2 * qrow) : make_float2(-INFINITY, 0.f);
 #pragma unroll
-        for (int s = 0; s < 32; ++s) if (s < NS) M = fmaxf(M, ml[s].x);
+        for (int s = 0; s < 32; ++s) M = fmaxf(M, ml[s].x);
 #pragma unroll
         for (int s = 0; s < 32; ++s) {
-            f[s] = (s >= NS || ml[s].x == -INFINITY) ? 0.f : exp2f((ml[s].x - M) * scale_log2e);
+            f[s] = ml[s].x == -INFINITY ? 0.f : exp2f((ml[s].x - M) * scale_log2e);
             L += f[s] * ml[s].y;
         }
     }
@@ -2020,27 +2022,17 @@ __device__ __forceinline__ void attn_merge_item(const float *part, const int *ro
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = 0.f;
 #pragma unroll
-    for (int s0 = 0; s0 < 32; s0 += 16) {
-        if (s0 < NS) {
-            if (!(EARLY && s0 == 0)) load_half(s0);
+    for (int s0 = 0; s0 < 32; s0 += CH) {
+        if (s0 >= NS) break;
+        if (s0 > 0) request(s0);
 #pragma unroll
-            for (int u = 0; u < 16; ++u)
-#pragma unroll
-                for (int r2 = 0; r2 < 4; ++r2) { o[2 * r2] += f[s0 + u] * v[u][r2].x; o[2 * r2 + 1] += f[s0 + u] * v[u][r2].y; }
-        }
+        for (int u = 0; u < CH; ++u)
+            if (s0 + u < NS) {
+                o[0] += f[s0 + u] * v[u][0].x; o[1] += f[s0 + u] * v[u][0].y; o[2] += f[s0 + u] * v[u][0].z; o[3] += f[s0 + u] * v[u][0].w;
+                o[4] += f[s0 + u] * v[u][1].x; o[5] += f[s0 + u] * v[u][1].y; o[6] += f[s0 + u] * v[u][1].z; o[7] += f[s0 + u] * v[u][1].w;
+            }
     }
-    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, row_grow[t * 32 + qrow], tt, hh, lane, xhi, xlo);
-}
-
-// grid: one wave per (tile, head, O^T tile, half): 256 threads = 4 wave items per block
-template <int HD>
-__global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ part, const int *__restrict__ row_grow, int NS, int Hq, int n_items,
-                                                    float scale_log2e, uint4 *__restrict__ xhi, uint4 *__restrict__ xlo) {
-    constexpr int HT = HD / 32;
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (j >= n_items) return;
-    const int hh = j & 1, tt = (j >> 1) % HT, head = (j / (2 * HT)) % Hq, t = j / (2 * HT * Hq);
-    attn_merge_item<HD, true>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, tt, hh, threadIdx.x & 63);
+    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, grow, tt, hh, lane, xhi, xlo);
 }
 
 // Merge of the NS key-range partials of one (tile, head) written by attn_head_item: wave item (tt, hh) owns registers
