@@ -584,7 +584,7 @@ def main():
                              "GBs": a_bytes / max(a_ms * 1e-3, 1e-12) / 1e9},
     }
     if not long_prefix and not args.skip_prefill:
-        # prefill of the prefix through the same kernels, 512 rows per chunk: algorithmic flops 2 * rows * parameters
+        # prefill of the prefix through the same kernels, 4096 rows per pass: algorithmic flops 2 * rows * parameters
         # of the layers (the LM head is not evaluated during prefill), both models
         def layer_params(sh):
             a = sh.d_model * (sh.n_q_heads + 2 * sh.n_kv_heads) * sh.head_dim + sh.n_q_heads * sh.head_dim * sh.d_model

@@ -13,7 +13,7 @@
 // LDS per 16 products, which leaves the LDS half idle; 128 x 256 per workgroup needs 16 KB from L2 per 64 products
 // against 32 KB in the streaming kernel's pairs of row tiles.  Measured against the kernels that did this work before
 // (one 256 x 256 tile per 512 threads in lockstep; the streaming kernel), microseconds per launch, 8B widths: gate/up at
-// 4 / 7 / 16 / 32 / 128 row tiles 83 / 142 / 227 / 454 / 1369 -> 70 / 112 / 187 / 330 / 1270, QKV at 16 / 64 / 128
+// 4 / 7 / 16 / 32 / 128 row tiles 83 / 142 / 227 / 454 / 1369 -> 70 / 112 / 190 / 330 / 1270, QKV at 16 / 64 / 128
 // 81 / 255 / 531 -> 64 / 185 / 333, down at 24 / 64 200 / 648 -> 165 / 325, LM head at 16 (with 151936 columns) 1348 -> 760.
 #pragma once
 #include "deer_kernels.hpp"
@@ -24,8 +24,9 @@ constexpr int BK_RT = 4;     // row tiles per workgroup of k_gemm_block
 // With 64 columns per wave the accumulators are added to a second set every BK_FOLD k-steps.  A matrix instruction adds its
 // products to the running sum with a rounding of its own, and over a whole K of 256 to 768 k-steps in one chain (twice
 // that many additions: hi and lo) these add up to twice the error of the streaming kernel, whose eight waves hold an eighth
-// of K each (16 sequences, 12 layers of the 8B shape: logits 1.24e-4 off the 64-bit reference against 6.1e-5; folded:
-// 4.0e-5).  128 columns per wave leave no registers for a second set.
+// of K each (16 sequences, 12 layers of the 8B shape: logits 1.24e-4 off the 64-bit reference against 6.1e-5; folded, the
+// two kernels' errors differ by less than those of two sets of weights).  16 costs no measurable time (8: 3 %).  128 columns
+// per wave leave no registers for a second set.
 constexpr int BK_FOLD = 16;
 constexpr int BT_STRIDE = 132;   // padded LDS row stride (floats) of a wave's 32 x 128 epilogue tile
 
