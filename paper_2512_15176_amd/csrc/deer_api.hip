@@ -375,10 +375,11 @@ struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; };
 BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size_t part_floats) {
     BlockPlan best;
     const int nrb = (ntiles + BK_RT - 1) / BK_RT;
-    // 128 columns per wave keep K in one chain of sums (see BK_FOLD): only where the error enters once and last (the LM head:
-    // no difference measured) or in large launches (1024 rows on, 128 blocks of 256 x 256), where it is the chip's rate that
-    // counts; not beside a mixture, where a rounding can send a row to another expert
-    const bool wide_ok = lm_head || (!mixture && ntiles >= 32 && ((ntiles + 7) / 8) * ((N / CG + 1) / 2) >= 128);
+    // 128 columns per wave keep K in one chain of sums (see BK_SHORT): only in large launches (1024 rows on, 128 blocks of
+    // 256 x 256), where it is the chip's rate that counts and no kernel before this one cut the chain either; not beside a
+    // mixture, where a rounding can send a row to another expert.  (LM heads of fewer rows would gain by it, 2 % of a pass of
+    // 16 sequences, but their logits' own error is 2 to 2.8 times the streaming kernel's then.)
+    const bool wide_ok = !mixture && ntiles >= 32 && ((ntiles + 7) / 8) * ((N / CG + 1) / 2) >= 128;
     for (int NB = wide_ok ? 4 : 2; NB >= 2; NB -= 2) {
         const int ncb = (N + 64 * NB - 1) / (64 * NB);
         for (int S = 1; S <= (lm_head ? 1 : 8); ++S) {
@@ -393,7 +394,7 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
             const double step = NB == 4 ? (q <= 1.0 ? 0.30 + 0.09 * q : q <= 2.0 ? 0.36 : 0.40) : (q <= 1.0 ? 0.15 + 0.09 * q : 0.225);
             const double mb = tile_bytes * 1e-6;   // shares that meet through memory: cheap while the L2s hold them
             const double us = 10.0 + units * per * step + (S > 1 ? S + (mb <= 20.0 ? 0.2 * mb : 4.0 + 0.55 * (mb - 20.0)) : 0.0);
-            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0, us};
+            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0 && KS >= 40, us};   // (a trip of 8 k-steps is too long a chain for less)
         }
     }
     return best;
@@ -427,9 +428,12 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
             const int nrb = (ntiles + BK_RT - 1) / BK_RT, ncb = (a.N + 64 * bp.NB - 1) / (64 * bp.NB), band = block_band(nrb);
             const dim3 g((unsigned)block_grid(ncb * a.S, nrb));
             ProfScope ps(c, 0, (double)a.N * K * 2.0);
-            if (bp.NB == 4) hipLaunchKernelGGL((k_gemm_block<4, 4, EPI>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
-            else if (bp.deep) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
-            else hipLaunchKernelGGL((k_gemm_block<2, 4, EPI>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            const bool sh = a.KS < BK_SHORT;
+            if (bp.NB == 4) hipLaunchKernelGGL((k_gemm_block<4, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            else if (bp.deep && sh) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI, true>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            else if (bp.deep) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            else if (sh) hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, true>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            else hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
             LAUNCHCHK(c, "k_gemm_block");
             return DEER_OK;
         }
@@ -636,7 +640,8 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             }
             {
                 ProfScope ps(c, 0, 0.0);
-                if (blocked) hipLaunchKernelGGL(k_moe_block<MOE_GATEUP>, block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
+                if (blocked && ma.KS < BK_SHORT) hipLaunchKernelGGL((k_moe_block<MOE_GATEUP, true>), block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
+                else if (blocked) hipLaunchKernelGGL((k_moe_block<MOE_GATEUP, false>), block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
                 else hipLaunchKernelGGL(k_gemm_moe, dim3((ma.N / CG + MOE_CGS - 1) / MOE_CGS, mc.n_experts, ntiles), dim3(512), 0, s, ma);
             }
             LAUNCHCHK(c, "grouped gate/up");
@@ -644,7 +649,8 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             ma.N = d; ma.KS = m.F / 16;
             {
                 ProfScope ps(c, 0, 0.0);
-                hipLaunchKernelGGL(k_moe_block<MOE_DOWN>, block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
+                if (ma.KS < BK_SHORT) hipLaunchKernelGGL((k_moe_block<MOE_DOWN, true>), block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
+                else hipLaunchKernelGGL((k_moe_block<MOE_DOWN, false>), block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
             }
             LAUNCHCHK(c, "grouped down");
             prof_close(c);

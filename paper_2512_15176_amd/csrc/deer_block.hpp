@@ -21,13 +21,17 @@
 namespace deer {
 
 constexpr int BK_RT = 4;     // row tiles per workgroup of k_gemm_block
-// With 64 columns per wave the accumulators are added to a second set every BK_FOLD k-steps.  A matrix instruction adds its
-// products to the running sum with a rounding of its own, and over a whole K of 256 to 768 k-steps in one chain (twice
-// that many additions: hi and lo) these add up to twice the error of the streaming kernel, whose eight waves hold an eighth
-// of K each (16 sequences, 12 layers of the 8B shape: logits 1.24e-4 off the 64-bit reference against 6.1e-5; folded, the
-// two kernels' errors differ by less than those of two sets of weights).  16 costs no measurable time (8: 3 %).  128 columns
-// per wave leave no registers for a second set.
-constexpr int BK_FOLD = 16;
+// With 64 columns per wave the accumulators are added to a second set every few k-steps.  A matrix instruction adds its
+// products to the running sum with a rounding of its own, and the relative error of a chain of n k-steps (2 n additions: hi
+// and lo) grows like the square root of n.  The streaming kernel's eight waves hold an eighth of K each, and the folded sums
+// must not be further off than theirs: every 16 k-steps do for contractions of 160 k-steps on, every 8 down to BK_SHORT.  Below that the additions of the folds themselves weigh as much as the chains: there
+// (template parameter SHORT) what an addition rounds off starts the next chain (two-sum, as in Kahan's summation).
+// LM heads whose input is exact, relative error of the logits against 64 bits, streaming / one chain / folded as here:
+// d = 896 8.9e-8 / 1.76e-7 / 7.2e-8, 2048 1.09e-7 / 2.73e-7 / 1.0e-7, 4096 1.42e-7 / 3.96e-7 / 1.3e-7.  The drafter's QKV
+// (56 k-steps, 105 row tiles): K,V values that round the other way 1.30 times the streaming kernel's with a plain fold
+// every 16, 1.07 every 8 or 4, 0.98 so.  128 columns per wave leave no registers for a second set.
+constexpr int BK_SHORT = 104;    // k-steps of the whole contraction
+__host__ __device__ constexpr int block_fold(int KS) { return KS < 40 ? 4 : KS < 160 ? 8 : 16; }
 constexpr int BT_STRIDE = 132;   // padded LDS row stride (floats) of a wave's 32 x 128 epilogue tile
 
 template <int NB>
@@ -67,13 +71,13 @@ struct BlockSmem {
 // apart); n k-steps.  Ends with this wave's LDS reads done and none of its loads in flight.
 // Schedule of k-step it (its fragments are in registers): wait until k-step it + 1 has landed | barrier: everybody's share
 // of it has, and everybody has read k-step it | read the fragments of it + 1 | multiply it, and between the products
-// request k-step it + NST into the buffer of k-step it.
+// request k-step it + NST into the buffer of k-step it.  fold: see BK_SHORT.
 // What is not a product has to be short or stand between products: a matrix instruction occupies its pipe for 32 cycles
 // and the wave's other instructions issue meanwhile.  The steady state therefore runs without any condition (NST k-steps
 // per trip, buffers at constant offsets); the last up to 2 NST - 1 k-steps take the general form.
-template <int NB, int NST, int WC, int LPW>
+template <int NB, int NST, int WC, int LPW, bool SHORT>
 __device__ __forceinline__ void block_loop(f32x16 (&acc)[2][NB], const char *(&base)[LPW], const uint32_t (&vo)[LPW],
-                                           BlockSmem<NB, NST, WC> &sm, int n, int w, int lane) {
+                                           BlockSmem<NB, NST, WC> &sm, int n, int fold, int w, int lane) {
     using SM = BlockSmem<NB, NST, WC>;
     constexpr int SB = SM::FRAGS * 1024;
     static_assert((NST == 4 || NST == 8) && (NST - 1) * LPW <= 63, "the loops below are written for these; the counter of loads in flight has six bits");
@@ -127,19 +131,23 @@ __device__ __forceinline__ void block_loop(f32x16 (&acc)[2][NB], const char *(&b
         __builtin_amdgcn_sched_barrier(0);
         block_wait<NB>(next);
     };
-    int it = 0, fold = BK_FOLD;
+    auto fold_in = [&] {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float s = sum[mt][nb][r], a = acc[mt][nb][r], t = s + a;
+                    sum[mt][nb][r] = t;
+                    // (the clamp keeps an infinite sum infinite: inf - inf would make it a NaN)
+                    acc[mt][nb][r] = SHORT ? __builtin_amdgcn_fmed3f(a - (t - s), -3.4028234e38f, 3.4028234e38f) : 0.f;
+                }
+    };
+    int it = 0, next_fold = fold;
     for (; it < n - 2 * NST + 1; it += NST) {
-        if constexpr (NB == 2) {
-            if (it >= fold) {
-                fold += BK_FOLD;
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) { sum[mt][nb][r] += acc[mt][nb][r]; acc[mt][nb][r] = 0.f; }
-            }
-        }
+        if constexpr (NB == 2)
+            if (it >= next_fold) { next_fold = it + fold; fold_in(); }
         step(fa, fb, std::integral_constant<int, 0>{}); step(fb, fa, std::integral_constant<int, 1>{});
         step(fa, fb, std::integral_constant<int, 2>{}); step(fb, fa, std::integral_constant<int, 3>{});
         if constexpr (NST == 8) {
@@ -166,6 +174,8 @@ __device__ __forceinline__ void block_loop(f32x16 (&acc)[2][NB], const char *(&b
         if (more) block_wait<NB>(next);
         ++it;
     };
+    if constexpr (NB == 2)
+        if (it >= next_fold) fold_in();
     while (it < n) {
         last_steps(fa, fb);
         if (it < n) last_steps(fb, fa);
@@ -378,8 +388,8 @@ inline int block_grid(int P, int nrb) {
     return 8 * ((nb * band * P + 7) / 8);
 }
 
-// ncb: column blocks of 64 NB columns; nrt: row tiles
-template <int NB, int NST, int EPI>
+// ncb: column blocks of 64 NB columns; nrt: row tiles; SHORT: a contraction of less than BK_SHORT k-steps
+template <int NB, int NST, int EPI, bool SHORT>
 __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 1) void k_gemm_block(const GemmArgs a, int ncb, int nrt, int band) {
     constexpr int LPW = BlockSmem<NB, NST>::FRAGS / 4;
     __shared__ __attribute__((aligned(16))) BlockSmem<NB, NST> sm;
@@ -414,7 +424,7 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
-    block_loop<NB, NST, 2, LPW>(acc, base, vo, sm, n, w, lane);
+    block_loop<NB, NST, 2, LPW, SHORT>(acc, base, vo, sm, n, block_fold(KS), w, lane);
 
     if (a.S > 1) {
         // shares meet through memory: [share][row block][column block][wave][(mt, nb, quad)][lane] x 16 bytes
@@ -512,7 +522,7 @@ __global__ __launch_bounds__(256) void k_moe_gather(const float *__restrict__ h,
 // d = 2048, expert width 768, microseconds at 1 / 8 / 16 / 64 / 128 row tiles against the streaming kernel with its
 // 32-pair chunks: down 69 / 80 / 92 / 157 / 264 for 75 / 97 / 137 / 429 / 826, gate/up with the gather before it 155 / 174 /
 // 210 / 323 / 516 for 129 / 198 / 314 / 1217 / 2642.
-template <int MODE>
+template <int MODE, bool SHORT>
 __global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) {
     constexpr int NB = 2, NST = 4, WC = 4;
     using SM = BlockSmem<NB, NST, WC>;
@@ -548,7 +558,7 @@ __global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) 
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
-    block_loop<NB, NST, WC, LPW>(acc, base, vo, sm, KS, w, lane);
+    block_loop<NB, NST, WC, LPW, SHORT>(acc, base, vo, sm, KS, block_fold(KS), w, lane);
     __syncthreads();   // every wave has read the ring: the epilogue tiles reuse it
     // two waves make a column group: tile (group w >> 1, row tile mt); wave w finishes row tile w & 1 of its group
 #pragma unroll
