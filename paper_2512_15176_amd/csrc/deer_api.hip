@@ -690,6 +690,33 @@ void fill_state(deer_ctx *c, char *img, int B, const int *len, const int *dr_len
     memset(img + ((char *)c->wk.st.ing_n - up), 0, (size_t)B * 4);
     memset(img + ((char *)c->wk.st.finished - up), 0, (size_t)B * 4);
 }
+struct PrefillPass { std::vector<int4> desc; int n_rows = 0, maxlim = 0; };   // attention tiles (see PassRows), GEMM rows, most visible keys
+// The uploads and passes of a prefill; passes[model] and ids must live until the stream has been waited for.
+int enqueue_prefill(deer_ctx *c, int batch, const int *ids, const int *lens, const int *pending, size_t total,
+                    const std::vector<PrefillPass> (&passes)[2]) {
+    Work &w = c->wk;
+    // one copy for the state, the first pass's descriptors of each model and the prompts (five copies and a second wait made
+    // a short request's prefill 60 us longer)
+    const size_t up_bytes = w.up_ids + total * 4;
+    char *img = upload_image(c, up_bytes);
+    fill_state(c, img, batch, lens, lens, pending);
+    for (int model = 0; model < 2; ++model)
+        if (!passes[model].empty())
+            memcpy(img + ((char *)w.pf_desc[model] - w.up), passes[model][0].desc.data(), passes[model][0].desc.size() * sizeof(int4));
+    memcpy(img + w.up_ids, ids, total * 4);
+    HIPCHK(c, hipMemcpyAsync(w.up, img, up_bytes, hipMemcpyHostToDevice, c->stream));
+    for (int model = 0; model < 2; ++model)
+        for (size_t i = 0; i < passes[model].size(); ++i) {
+            const PrefillPass &pa = passes[model][i];
+            if (i > 0)
+                HIPCHK(c, hipMemcpyAsync(w.pf_desc[model], pa.desc.data(), pa.desc.size() * sizeof(int4), hipMemcpyHostToDevice, c->stream));
+            PassRows pr{};
+            pr.kind = ROWS_PREFILL; pr.desc = w.pf_desc[model]; pr.ids = w.ids; pr.n_desc = (int)pa.desc.size();
+            const LmPlan lm{false, 0, 0, 0.f, 0};
+            if (int rc = run_pass(c, model, (pa.n_rows + 31) / 32, pr.n_desc, pa.maxlim, lm, 0.0, pr)) return rc;
+        }
+    return DEER_OK;
+}
 // the host's mirror once the device state is in place
 void set_state(deer_ctx *c, int B, const int *len) {
     c->batch = B;
@@ -848,7 +875,6 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
         if (lens[b] < 1) return fail(c, DEER_EINVAL, "prompt %d is empty", b);
         if (lens[b] + c->p.max_k > c->p.max_seq) return fail(c, DEER_ECAPACITY, "prompt %d: %d tokens + one block exceed max_seq %d", b, lens[b], c->p.max_seq);
     }
-    Work &w = c->wk;
     std::vector<int> pend(batch), lenv(lens, lens + batch);
     std::vector<size_t> offs(batch);
     size_t total = 0;
@@ -862,16 +888,15 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
     // Passes of up to cap tiles; a pass takes the next rows of as many sequences as fit: its GEMM rows follow each other
     // without gaps, its attention tiles hold up to 32 rows of one sequence (rows of one sequence that are split over passes
     // continue in the next pass, over the keys the earlier pass has written).
-    struct Pass { std::vector<int4> desc; int n_rows = 0, maxlim = 0; };
     const int cap = c->max_tiles;
-    std::vector<Pass> passes[2];
+    std::vector<PrefillPass> passes[2];
     for (int model = 0; model < 2; ++model)
         for (int b = 0; b < batch; ++b) {
             const int nrows = (model == DEER_TARGET) ? lens[b] - 1 : lens[b];   // the last token stays pending for the target
             for (int c0 = 0; c0 < nrows;) {
-                std::vector<Pass> &ps = passes[model];
+                std::vector<PrefillPass> &ps = passes[model];
                 if (ps.empty() || (int)ps.back().desc.size() == cap || ps.back().n_rows == cap * 32) ps.emplace_back();
-                Pass &pa = ps.back();
+                PrefillPass &pa = ps.back();
                 const int take = std::min({nrows - c0, 32, cap * 32 - pa.n_rows});
                 pa.desc.push_back(make_int4(b, c0, take | pa.n_rows << 6, (int)(offs[b] + c0)));
                 pa.maxlim = std::max(pa.maxlim, c0 + take);
@@ -879,27 +904,11 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
                 pa.n_rows += take;
             }
         }
-    // one copy for the state, the first pass's descriptors of each model and the prompts (five copies and a second wait made
-    // a short request's prefill 60 us longer)
-    const size_t up_bytes = w.up_ids + total * 4;
-    char *img = upload_image(c, up_bytes);
-    fill_state(c, img, batch, lens, lens, pend.data());
-    for (int model = 0; model < 2; ++model)
-        if (!passes[model].empty())
-            memcpy(img + ((char *)w.pf_desc[model] - w.up), passes[model][0].desc.data(), passes[model][0].desc.size() * sizeof(int4));
-    memcpy(img + w.up_ids, ids, total * 4);
-    HIPCHK(c, hipMemcpyAsync(w.up, img, up_bytes, hipMemcpyHostToDevice, c->stream));
-    for (int model = 0; model < 2; ++model)
-        for (size_t i = 0; i < passes[model].size(); ++i) {
-            const Pass &pa = passes[model][i];
-            if (i > 0)   // (the lists live until the stream has been waited for)
-                HIPCHK(c, hipMemcpyAsync(w.pf_desc[model], pa.desc.data(), pa.desc.size() * sizeof(int4), hipMemcpyHostToDevice, c->stream));
-            PassRows pr{};
-            pr.kind = ROWS_PREFILL; pr.desc = w.pf_desc[model]; pr.ids = w.ids; pr.n_desc = (int)pa.desc.size();
-            const LmPlan lm{false, 0, 0, 0.f, 0};
-            if (int rc = run_pass(c, model, (pa.n_rows + 31) / 32, pr.n_desc, pa.maxlim, lm, 0.0, pr)) return rc;
-        }
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    c->state = ST_INIT;   // no sequences until all of the call has worked: the device state may be of the new ones, the host's of the old
+    int rc = enqueue_prefill(c, batch, ids, lens, pend.data(), total, passes);
+    const hipError_t e = hipStreamSynchronize(c->stream);   // after an error too: the next call writes to the same staging memory
+    if (rc) return rc;
+    if (e != hipSuccess) return fail(c, DEER_EHIP, "prefill: %s", hipGetErrorString(e));
     set_state(c, batch, lenv.data());
     return DEER_OK;
 }
@@ -915,8 +924,9 @@ int deer_set_prefilled(deer_ctx *c, int32_t batch, const int32_t *lens, const in
     const size_t bytes = c->wk.up_desc;
     char *img = upload_image(c, bytes);
     fill_state(c, img, batch, lens, lens, last);
-    HIPCHK(c, hipMemcpyAsync(c->wk.up, img, bytes, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    c->state = ST_INIT;   // (see deer_prefill)
+    const hipError_t e = hipMemcpyAsync(c->wk.up, img, bytes, hipMemcpyHostToDevice, c->stream), e2 = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess || e2 != hipSuccess) return fail(c, DEER_EHIP, "state: %s", hipGetErrorString(e != hipSuccess ? e : e2));
     set_state(c, batch, lens);
     return DEER_OK;
 }
