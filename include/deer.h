@@ -251,9 +251,16 @@ int deer_debug_gemm_stamps(deer_ctx *c, int model, int launch, uint64_t *stamps_
 
 /* GEMMs of passes of several row tiles run blocked (128 x 128 or 128 x 256 tiles through LDS) where that is estimated
  * to be faster than the weight-streaming kernel (min_tiles = 128, the default; larger values: the same).  0 switches the
- * blocked kernel off; 1 .. 127 make every GEMM of a pass with at least 256 rows take it (tests cover it at small sizes).
- * Results agree within rounding (different summation order over K). */
+ * blocked kernel off, also for the gate/up projections of a mixture's experts (their down projections always run blocked);
+ * 1 .. 127 make every dense GEMM of a pass with at least 8 row tiles take it.  Results agree within rounding (different
+ * summation order over K). */
 int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles);
+
+/* Test aid: makes every dense GEMM of a pass of at least two row tiles run in one form of the blocked kernel (unless
+ * deer_debug_gemm_tiled has switched it off): workgroups of 64 * nb columns (nb = 2 or 4) with `ring` k-steps on their way
+ * (4, with nb = 2 also 8) and K in `splits` shares (1 .. 8; fewer where a share would be empty or the partial sums would not
+ * fit; LM heads: 1).  nb = 0: back to the estimate.  DEER_EINVAL for a form that does not exist. */
+int deer_debug_gemm_block(deer_ctx *c, int nb, int ring, int splits);
 
 /* Current committed length j per sequence (host mirror). */
 int deer_get_lengths(const deer_ctx *c, int32_t *len_host);

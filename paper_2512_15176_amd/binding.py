@@ -18,7 +18,7 @@ EXPORTS = ["deer_query_sizes", "deer_init_models", "deer_load_tensor", "deer_pre
            "deer_draft_block", "deer_verify_block", "deer_accept_and_commit", "deer_accept_and_commit_static", "deer_destroy", "deer_last_error",
            "deer_debug_get_logits", "deer_get_lengths", "deer_get_kv_layout", "deer_debug_profile",
            "deer_debug_profile_read", "deer_debug_force_commit", "deer_debug_load_kv", "deer_set_bonus_token",
-           "deer_draft_block_multipass", "deer_debug_gemm_tiled",
+           "deer_draft_block_multipass", "deer_debug_gemm_tiled", "deer_debug_gemm_block",
            "deer_debug_gemm_stamps", "deer_debug_experts_streamed", "deer_debug_route_spread",
            "deer_debug_stream_read"]
 
@@ -92,6 +92,7 @@ def load_library(path: str = LIB_PATH):
     lib.deer_debug_force_commit.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32]
     lib.deer_debug_load_kv.argtypes = [C.c_void_p, C.c_int, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
     lib.deer_debug_gemm_tiled.argtypes = [C.c_void_p, C.c_int]
+    lib.deer_debug_gemm_block.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int]
     lib.deer_debug_profile_read.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.POINTER(C.c_double)]
     _lib = lib
     return lib
@@ -289,6 +290,10 @@ class DeerEngine:
 
     def debug_gemm_tiled(self, min_tiles):
         self._check(self.lib.deer_debug_gemm_tiled(self.ctx, int(min_tiles)))
+
+    def debug_gemm_block(self, nb, ring=4, splits=1):
+        """Forces one form of the blocked GEMM; nb = 0: back to the estimate."""
+        self._check(self.lib.deer_debug_gemm_block(self.ctx, nb, ring, splits))
 
     def debug_force_commit(self, tokens):
         """Commits tokens[b] (a list per sequence, possibly empty) instead of running the acceptance rule."""

@@ -108,6 +108,7 @@ struct deer_ctx {
     float cur_T = 0.f;
     int max_tiles = 0;
     int block_gemm = 128;            // deer_debug_gemm_tiled: 0 never blocked; 128 where it is estimated to be faster; less: from 8 row tiles on
+    int force_nb = 0, force_ring = 0, force_S = 0;   // deer_debug_gemm_block; force_nb 0: off
     // deer_debug_gemm_stamps: which streaming-GEMM launch of which model's passes records its stamps
     int stamp_model = 0, stamp_launch = -1, stamp_blocks = 0, gemm_launch_idx = 0, cur_pass_model = 0;
     int route_spread = 0;            // deer_debug_route_spread: synthetic uniform routing for mixture models
@@ -400,6 +401,14 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
     return best;
 }
 
+// deer_debug_gemm_block: the given form, with as many of the K shares as have k-steps and fit the partials' buffer
+BlockPlan forced_block(const deer_ctx *c, int N, int KS, int ntiles, bool lm_head) {
+    BlockPlan bp{c->force_nb, lm_head ? 1 : c->force_S, c->force_nb == 2 && c->force_ring == 8, 0.0};
+    const size_t tile_floats = (size_t)((ntiles + BK_RT - 1) / BK_RT) * ((N + 64 * bp.NB - 1) / (64 * bp.NB)) * 128 * 64 * bp.NB;
+    while (bp.S > 1 && ((bp.S - 1) * ((KS + bp.S - 1) / bp.S) >= KS || bp.S * tile_floats > c->wk.part_floats)) --bp.S;
+    return bp;
+}
+
 template <int EPI>
 int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     a.KS = K / 16;
@@ -420,9 +429,10 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     const bool narrow = (EPI == EPI_RESID || (EPI == EPI_QKV && a.hd <= 64 && 64 % a.hd == 0 && a.N % 64 == 0)) && a.ssq_sub == 4 && MT == 1 &&
                         force_S <= 0 && a.KS <= 64;
     if constexpr (EPI != EPI_ROUTER) {
-        const BlockPlan bp = plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);
+        const BlockPlan bp = c->force_nb ? forced_block(c, a.N, a.KS, ntiles, EPI == EPI_LMHEAD)
+                                         : plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);
         const double old_us = narrow ? narrow_us(ntiles, EPI == EPI_QKV) : stream_us(a.N, a.KS, MT, zg, force_S > 0 ? force_S : choose_split(a.N, a.KS, zg));
-        const bool forced = c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8;   // tests cover it at small sizes
+        const bool forced = c->force_nb || (c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8);   // tests cover it at small sizes
         if (c->block_gemm > 0 && ntiles > 1 && (forced || bp.us < 0.97 * old_us)) {
             a.S = bp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
             const int nrb = (ntiles + BK_RT - 1) / BK_RT, ncb = (a.N + 64 * bp.NB - 1) / (64 * bp.NB), band = block_band(nrb);
@@ -1182,6 +1192,14 @@ int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles) {
     if (!c) return DEER_EINVAL;
     if (min_tiles < 0) return fail(c, DEER_EINVAL, "min_tiles must not be negative");
     c->block_gemm = min_tiles;
+    return DEER_OK;
+}
+
+int deer_debug_gemm_block(deer_ctx *c, int nb, int ring, int splits) {
+    if (!c) return DEER_EINVAL;
+    if (nb != 0 && !((nb == 2 && (ring == 4 || ring == 8)) || (nb == 4 && ring == 4))) return fail(c, DEER_EINVAL, "no such form of the blocked GEMM");
+    if (nb != 0 && (splits < 1 || splits > 8)) return fail(c, DEER_EINVAL, "splits must be in 1..8");
+    c->force_nb = nb; c->force_ring = ring; c->force_S = splits;
     return DEER_OK;
 }
 

@@ -1,0 +1,81 @@
+"""Which GEMM kernels the host side launches for a prompt or a batch (a stand-in for the HIP runtime records them, no GPU):
+that the forms the parity tests compare are the ones that run there, and that every form is reached by a test."""
+import os
+import sys
+
+import pytest
+
+sys.path.insert(0, os.path.join(os.path.dirname(os.path.abspath(__file__)), "hip_stub"))
+from host_engine import run_script   # noqa: E402
+
+SCRIPT = """
+import re
+import deer_inputs as di
+def engine(t, d, batch, max_seq):
+    return HostEngine(t, d, batch, max_seq)
+def gemms(e, call):
+    e.stub.stub_reset()
+    assert call() == 0
+    out = set()
+    for name, grid in e.launches():
+        m = re.search("k_gemm_blockILi(\\\\d)ELi(\\\\d)ELi(\\\\d)ELb(\\\\d)E", name)
+        if m: out.add("block<%s,%s,%s,%s>" % m.groups())
+        elif "k_moe_block" in name: out.add("moe_block")
+        elif "k_gemm" in name: out.add(re.search("k_gemm(_rows|_narrow|_moe)?", name)[0])
+    return out
+"""
+QKV, RESID, SWIGLU, LM = range(4)
+
+
+def routes(tmp_path, body):
+    return eval(run_script(tmp_path, SCRIPT + body))
+
+
+def test_wide_prompts_reach_the_256_column_form(tmp_path):
+    """The prompts of test_gpu_block_forms.py::test_wide_prompts_agree, with the estimate's own choice."""
+    got = routes(tmp_path, """
+t8, t4 = (di.scaled(di.CONFIGS[c]["target"], n_layers=2, vocab=16384) for c in ("qwen3_8b", "qwen3_4b"))
+d = di.scaled(di.DRAFTER_05B, n_layers=2, vocab=16384)
+print([gemms(e, lambda: e.prefill([[3] * n])) for e, n in ((engine(t8, d, 1, 2176), 2100), (engine(t4, d, 1, 3392), 3329))])
+""")
+    assert {f"block<4,4,{e},0>" for e in (QKV, RESID, SWIGLU)} <= got[0], got[0]
+    assert {f"block<4,4,{e},0>" for e in (RESID, SWIGLU)} <= got[1], got[1]
+
+
+@pytest.mark.parametrize("form,names", [((2, 4), ["2,4"]), ((2, 8), ["2,8"]), ((4, 4), ["4,4"])])
+def test_the_forced_form_runs_in_every_dense_gemm(tmp_path, form, names):
+    got = routes(tmp_path, f"""
+t = di.ModelShape(1, 384, 6, 3, 64, 640, 1152, rope_base=1e4)
+e = engine(t, t, 3, 512)
+assert e.lib.deer_debug_gemm_block(e.ctx, {form[0]}, {form[1]}, 3) == 0
+a = gemms(e, lambda: e.prefill([[3] * 290, [4] * 33, [5] * 200]))
+b = gemms(e, lambda: e.draft_block(32))
+assert e.lib.deer_debug_gemm_block(e.ctx, 0, 0, 0) == 0 and e.lib.deer_debug_gemm_tiled(e.ctx, 0) == 0
+c = gemms(e, lambda: e.verify_block(32))
+bad = [e.lib.deer_debug_gemm_block(e.ctx, *f) for f in ((4, 8, 1), (3, 4, 1), (2, 4, 0), (2, 4, 9), (2, 5, 1))]
+print((a, b, c, bad))
+""")
+    short = "0" if form[0] == 4 else "1"
+    assert got[0] == {f"block<{names[0]},{e},{short}>" for e in (QKV, RESID, SWIGLU)}, got[0]
+    assert got[1] == got[0] | {f"block<{names[0]},{LM},{short}>"}, got[1]
+    assert not any("block" in n for n in got[2]), got[2]
+    assert got[3] == [-1] * 5
+
+
+def test_rows_of_the_block_gemm_tests_take_the_blocked_kernel(tmp_path):
+    """The cases of test_gpu_block_gemm.py with the estimate's choice (its other two settings switch the kernel off and
+    force it): from 5 row tiles on some GEMM of the prompt runs blocked."""
+    got = routes(tmp_path, """
+t = di.scaled(di.CONFIGS["qwen3_8b"]["target"], n_layers=2, vocab=16384)
+d = di.scaled(di.DRAFTER_05B, n_layers=2, vocab=16384)
+e = engine(t, d, 9, 1536)
+out = []
+for lens, k in (([97], 32), ([161, 33], 5), ([225], 1), ([511], 17), ([40, 300, 77, 129, 65, 31, 2, 1, 200], 32), ([1200], 32)):
+    a = gemms(e, lambda: e.prefill([[3] * n for n in lens]))
+    out.append((a, gemms(e, lambda: e.draft_block(k)) | gemms(e, lambda: e.verify_block(k))))
+print(out)
+""")
+    for i, (prompt, block) in enumerate(got):
+        print(i, sorted(prompt), sorted(block))
+    assert all(any(n.startswith("block") for n in prompt) for prompt, _ in got)
+    assert any(n.startswith("block<2") and n.split(",")[2] == str(LM) for n in got[4][1])
