@@ -35,7 +35,7 @@ thread_local std::string g_init_error;
 
 
 constexpr int STAMP_MAX_BLOCKS = 4096;   // workgroups whose stamps deer_debug_gemm_stamps can record (8 stamps each)
-constexpr int PREFILL_TILES = 128;       // most row tiles of a prefill pass (4096 rows: every pass streams the weights once)
+constexpr int PREFILL_TILES = 128;   // row tiles that a prefill pass may have at any batch size (4096 rows: every pass streams the weights once)
 constexpr int PART_TILES_MIN = 16;   // split-K partials exist for passes of up to max(2 * batch, 16) row tiles
 constexpr int MAX_NS = 32;          // key-range splits of block attention
 constexpr size_t H_UP_MAX = 1 << 20;  // most page-locked host memory of a context for uploads
@@ -895,9 +895,10 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
         total += lens[b];
         pend[b] = ids[total - 1];
     }
-    // Passes of up to cap tiles; a pass takes the next rows of as many sequences as fit: its GEMM rows follow each other
-    // without gaps, its attention tiles hold up to 32 rows of one sequence (rows of one sequence that are split over passes
-    // continue in the next pass, over the keys the earlier pass has written).
+    // Passes of up to cap attention tiles, each up to 32 rows of one sequence; a pass takes the next tiles of as many sequences
+    // as fit, and its GEMM rows follow each other without gaps (rows of one sequence that are split over passes continue in
+    // the next pass, over the keys the earlier pass has written).  The buffers hold PREFILL_TILES tiles, and what a draft pass
+    // of max_batch sequences needs: many short prompts of a large batch then go through in fewer passes.
     const int cap = c->max_tiles;
     std::vector<PrefillPass> passes[2];
     for (int model = 0; model < 2; ++model)
@@ -905,9 +906,9 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
             const int nrows = (model == DEER_TARGET) ? lens[b] - 1 : lens[b];   // the last token stays pending for the target
             for (int c0 = 0; c0 < nrows;) {
                 std::vector<PrefillPass> &ps = passes[model];
-                if (ps.empty() || (int)ps.back().desc.size() == cap || ps.back().n_rows == cap * 32) ps.emplace_back();
+                if (ps.empty() || (int)ps.back().desc.size() == cap) ps.emplace_back();
                 PrefillPass &pa = ps.back();
-                const int take = std::min({nrows - c0, 32, cap * 32 - pa.n_rows});
+                const int take = std::min(nrows - c0, 32);
                 pa.desc.push_back(make_int4(b, c0, take | pa.n_rows << 6, (int)(offs[b] + c0)));
                 pa.maxlim = std::max(pa.maxlim, c0 + take);
                 c0 += take;
