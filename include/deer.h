@@ -260,7 +260,7 @@ int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles);
 
 /* Test aid: makes every dense GEMM of a pass of at least two row tiles run in one form of the blocked kernel (unless
  * deer_debug_gemm_tiled has switched it off): workgroups of 64 * nb columns (nb = 2 or 4) with `ring` k-steps on their way
- * (4, with nb = 2 also 8) and K in `splits` shares (1 .. 8; fewer where a share would be empty or the partial sums would not
+ * (4; with nb = 2 also 8, which contractions of less than 104 k-steps take as 4) and K in `splits` shares (1 .. 8; fewer where a share would be empty or the partial sums would not
  * fit; LM heads: 1).  nb = 0: back to the estimate.  DEER_EINVAL for a form that does not exist. */
 int deer_debug_gemm_block(deer_ctx *c, int nb, int ring, int splits);
 

@@ -366,9 +366,13 @@ double stream_us(int N, int KS, int MT, int zg, int S) {
     const double rounds = std::ceil((double)(N / CG) * S * zg / 256.0);
     return 5.0 + rounds * (MT == 2 ? 5.0 + 0.125 * KS / S : 4.0 + (zg > 16 ? 0.1 : 0.07) * KS / S) + (S > 1 ? 6.0 : 0.0);
 }
-// narrow workgroups of a small model (drafter: O 6 us up to 8 tiles, 10.6 at 16, 64 at 105; QKV 8, 14 and 61)
-double narrow_us(int ntiles, bool qkv) {
-    return qkv ? 8.0 + 6.2 * std::max(0.0, ntiles * 24 / 256.0 - 1.0) : 6.0 + 9.0 * std::max(0.0, ntiles * 32 / 512.0 - 0.5);
+// Narrow workgroups of a small model: rounds of them (ids are padded to 8 column groups, see k_gemm_narrow) on 256 compute
+// units.  Fitted to O projections of N = 256 .. 1024, K = 256 .. 1024 and QKV of N = 512 .. 3072 over 1 .. 105 row tiles;
+// d = 896: O 5.1 us at 1 tile, 9.3 at 16, 17 at 31, 67 at 105, QKV 7.3, 11.4, 18.4 and 58; d = 256: O 4.1, 4.5, 6.1 and 12.4;
+// d = 1024 with 16 kv heads: QKV 7.4, 18, 40 and 127.
+double narrow_us(int N, int KS, int ntiles, bool qkv) {
+    const double r = (N / (qkv ? 64 : 32) + 7) / 8 * 8 * ntiles / 256.0;
+    return qkv ? 5.6 + 0.04 * KS + (3.2 + 0.05 * KS) * std::max(0.0, r - 1.0) : 4.0 + 0.035 * KS + (1.6 + 0.067 * KS) * std::max(0.0, r - 1.5);
 }
 // Blocked kernel: NB = 4 (128 x 256 per workgroup: 0.3 to 0.4 us per k-step, the more the busier the chip) or NB = 2
 // (128 x 128: 0.16 us with 64 workgroups, 0.24 with one per compute unit, 0.225 with more).
@@ -395,7 +399,7 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
             const double step = NB == 4 ? (q <= 1.0 ? 0.30 + 0.09 * q : q <= 2.0 ? 0.36 : 0.40) : (q <= 1.0 ? 0.15 + 0.09 * q : 0.225);
             const double mb = tile_bytes * 1e-6;   // shares that meet through memory: cheap while the L2s hold them
             const double us = 10.0 + units * per * step + (S > 1 ? S + (mb <= 20.0 ? 0.2 * mb : 4.0 + 0.55 * (mb - 20.0)) : 0.0);
-            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0 && KS >= 40, us};   // (a trip of 8 k-steps is too long a chain for less)
+            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0 && KS >= BK_SHORT, us};   // (short contractions: the ring of 8 takes 2 us more)
         }
     }
     return best;
@@ -403,7 +407,7 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
 
 // deer_debug_gemm_block: the given form, with as many of the K shares as have k-steps and fit the partials' buffer
 BlockPlan forced_block(const deer_ctx *c, int N, int KS, int ntiles, bool lm_head) {
-    BlockPlan bp{c->force_nb, lm_head ? 1 : c->force_S, c->force_nb == 2 && c->force_ring == 8, 0.0};
+    BlockPlan bp{c->force_nb, lm_head ? 1 : c->force_S, c->force_nb == 2 && c->force_ring == 8 && KS >= BK_SHORT, 0.0};
     const size_t tile_floats = (size_t)((ntiles + BK_RT - 1) / BK_RT) * ((N + 64 * bp.NB - 1) / (64 * bp.NB)) * 128 * 64 * bp.NB;
     while (bp.S > 1 && ((bp.S - 1) * ((KS + bp.S - 1) / bp.S) >= KS || bp.S * tile_floats > c->wk.part_floats)) --bp.S;
     return bp;
@@ -431,7 +435,7 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     if constexpr (EPI != EPI_ROUTER) {
         const BlockPlan bp = c->force_nb ? forced_block(c, a.N, a.KS, ntiles, EPI == EPI_LMHEAD)
                                          : plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);
-        const double old_us = narrow ? narrow_us(ntiles, EPI == EPI_QKV) : stream_us(a.N, a.KS, MT, zg, force_S > 0 ? force_S : choose_split(a.N, a.KS, zg));
+        const double old_us = narrow ? narrow_us(a.N, a.KS, ntiles, EPI == EPI_QKV) : stream_us(a.N, a.KS, MT, zg, force_S > 0 ? force_S : choose_split(a.N, a.KS, zg));
         const bool forced = c->force_nb || (c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8);   // tests cover it at small sizes
         if (c->block_gemm > 0 && ntiles > 1 && (forced || bp.us < 0.97 * old_us)) {
             a.S = bp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
@@ -440,7 +444,6 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
             ProfScope ps(c, 0, (double)a.N * K * 2.0);
             const bool sh = a.KS < BK_SHORT;
             if (bp.NB == 4) hipLaunchKernelGGL((k_gemm_block<4, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
-            else if (bp.deep && sh) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI, true>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
             else if (bp.deep) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
             else if (sh) hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, true>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
             else hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);

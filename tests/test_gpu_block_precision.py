@@ -17,8 +17,8 @@ BOUND = 1.03
 
 @pytest.mark.parametrize("d,vocab", [
     (256, 2048), (512, 4096),      # 16 and 32 k-steps
-    (896, 2048), (896, 16384),     # 56: the deep ring (64 workgroups) and the usual one
-    (1536, 16384), (1664, 2048),   # 96 and 104: either side of the two ways to fold
+    (896, 2048), (896, 16384),     # 56; 64 and 512 workgroups
+    (1536, 16384), (1664, 2048),   # 96 and 104: either side of the two ways to fold (and, with 64 workgroups, of the ring of 8)
     (2560, 16384),                 # 160
     (4096, 2048), (4096, 16384),   # 256
 ])

@@ -42,10 +42,11 @@ print([gemms(e, lambda: e.prefill([[3] * n])) for e, n in ((engine(t8, d, 1, 217
     assert {f"block<4,4,{e},0>" for e in (RESID, SWIGLU)} <= got[1], got[1]
 
 
-@pytest.mark.parametrize("form,names", [((2, 4), ["2,4"]), ((2, 8), ["2,8"]), ((4, 4), ["4,4"])])
-def test_the_forced_form_runs_in_every_dense_gemm(tmp_path, form, names):
+@pytest.mark.parametrize("d,form,ring", [(384, (2, 4), 4), (384, (2, 8), 4), (384, (4, 4), 4), (1664, (2, 4), 4), (1664, (2, 8), 8)])
+def test_the_forced_form_runs_in_every_dense_gemm(tmp_path, d, form, ring):
+    """d = 1664: every contraction has 104 k-steps, the shortest that folds plainly and may have the ring of 8."""
     got = routes(tmp_path, f"""
-t = di.ModelShape(1, 384, 6, 3, 64, 640, 1152, rope_base=1e4)
+t = di.ModelShape(1, {d}, {d // 64}, {d // 128}, 64, {d}, 1152, rope_base=1e4)
 e = engine(t, t, 3, 512)
 assert e.lib.deer_debug_gemm_block(e.ctx, {form[0]}, {form[1]}, 3) == 0
 a = gemms(e, lambda: e.prefill([[3] * 290, [4] * 33, [5] * 200]))
@@ -55,9 +56,9 @@ c = gemms(e, lambda: e.verify_block(32))
 bad = [e.lib.deer_debug_gemm_block(e.ctx, *f) for f in ((4, 8, 1), (3, 4, 1), (2, 4, 0), (2, 4, 9), (2, 5, 1))]
 print((a, b, c, bad))
 """)
-    short = "0" if form[0] == 4 else "1"
-    assert got[0] == {f"block<{names[0]},{e},{short}>" for e in (QKV, RESID, SWIGLU)}, got[0]
-    assert got[1] == got[0] | {f"block<{names[0]},{LM},{short}>"}, got[1]
+    name = lambda e: f"block<{form[0]},{ring},{e},{int(form[0] == 2 and d < 1664)}>"   # noqa: E731
+    assert got[0] == {name(e) for e in (QKV, RESID, SWIGLU)}, got[0]
+    assert got[1] == got[0] | {name(LM)}, got[1]
     assert not any("block" in n for n in got[2]), got[2]
     assert got[3] == [-1] * 5
 
@@ -79,3 +80,21 @@ print(out)
         print(i, sorted(prompt), sorted(block))
     assert all(any(n.startswith("block") for n in prompt) for prompt, _ in got)
     assert any(n.startswith("block<2") and n.split(",")[2] == str(LM) for n in got[4][1])
+
+
+def test_small_models_take_the_kernel_that_is_faster_there(tmp_path):
+    """Narrow workgroups against the blocked kernel, by the matrices' sizes.  Microseconds, narrow / blocked: O of d = 256 at 63
+    row tiles 8.4 / 11.5, of d = 896 at 31 17.0 / 19.1 and at 63 41 / 20; QKV of d = 1024 with 16 kv heads at 31 40 / 26, of
+    d = 512 with 2 at 31 10.8 / 19.0."""
+    got = routes(tmp_path, """
+out = []
+for d, hq, hkv, tiles in ((256, 4, 2, 63), (896, 14, 2, 31), (896, 14, 2, 63), (1024, 16, 16, 31), (512, 8, 2, 31)):
+    t = di.ModelShape(1, d, hq, hkv, 64, 2048, 1024, rope_base=1e4)
+    e = engine(t, t, 1, 2112)
+    e.stub.stub_reset()
+    assert e.prefill([[3] * 32 * tiles]) == 0
+    names = [n for n, _ in e.launches() if "k_gemm" in n]
+    out.append(["block" in names[0], "block" in names[1]])   # QKV, O
+print(out)
+""")
+    assert got[0][1] is False and got[1][1] is False and got[2][1] is True and got[3][0] is True and got[4][0] is False, got
