@@ -1774,7 +1774,8 @@ __device__ __forceinline__ void attn_write_frag(const f32x16 *o, float inv, int 
 // HBM are both busy (counted: 1.84 GHz and the matrix pipe busy 58 % of a long-context launch).  Microseconds per launch
 // against one workgroup of eight waves, two per head, behind one barrier: 8B heads, 16 sequences x 32768 keys 565 -> 536
 // (4.0 TB/s of K and V), prompt of 4096 341 -> 268, batch of prompts (104 tiles) 73 -> 51; drafter, prompt of 4096
-// 138 -> 96.  A ring of four single tiles took 544 and 290 (drafter 114).
+// 138 -> 96.  A ring of four single tiles took 544 and 290 (drafter 114).  Tiles of fewer than 32 rows skip the mask and the
+// rescale like full ones (16 sequences x 8192 keys, 31 / 16 / 4 rows: 162 / 158 / 139 -> 153 / 153 / 132; 32 rows: 154).
 // ------------------------------------------------------------------------------------------
 #ifndef DEER_ATT_P_LO
 #define DEER_ATT_P_LO 1
@@ -1809,7 +1810,7 @@ __global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, 
     const bool active = g < G;
     const int head = kvh * G + min(g, G - 1);
     const int b = tile_seq[t], lim = row_limit[t * 32 + qrow];   // lim: the key limit of this lane's query row
-    int maxlim = lim, minlim = lim;
+    int maxlim = lim, minlim = lim > 0 ? lim : 0x7fffffff;   // rows that do not exist set no limit: their results, whatever they are, go nowhere
 #pragma unroll
     for (int off = 1; off < 32; off <<= 1) {
         maxlim = max(maxlim, shx(maxlim, off));
@@ -1841,7 +1842,9 @@ __global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, 
     for (int tt = 0; tt < HT; ++tt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[tt][r] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
+    // The lowest finite number, not -inf: a row that has seen no key yet keeps it as its maximum, with every weight exp2(-inf) = 0
+    // and the factor of O exp2(0) = 1, so that it needs no case of its own and no rescale.
+    float m_run = -3.4028234e38f, l_run = 0.f;
     if (n > 0) {
         const int np = (n + 1) >> 1;
         uint4 qh[KSQ], ql[KSQ];
@@ -1898,9 +1901,8 @@ __global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, 
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(sacc[0][r], sacc[1][r]));
             mx = fmaxf(mx, shx(mx, 32));
             const float m_new = fmaxf(m_run, mx);
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;   // a row without visible keys so far: every weight is exp2(-inf) = 0
-            const float alpha = __builtin_amdgcn_exp2f((m_run - m_use) * scale_log2e);   // m_run = -inf -> 0
-            const float mb = m_use * scale_log2e;
+            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
+            const float mb = m_new * scale_log2e;
             float ls0 = 0.f, ls1 = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {

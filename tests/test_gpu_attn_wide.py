@@ -39,3 +39,33 @@ def test_wide_attention(hq, hkv, hd, lens):
         want = pair.verify_logits([int(v) for v in blocks[b]])
         assert np.abs(z[b] - want).max() < 2e-3, (b, np.abs(z[b] - want).max())   # the tiny shapes' bound elsewhere
     eng.close()
+
+
+@pytest.mark.parametrize("k", [1, 5, 31, 32])
+def test_blocks_of_fewer_rows_than_a_tile(k):
+    """A batch's verify pass (9 tiles of 32 heads): tiles of which some rows do not exist, key ranges split over workgroups, of
+    which the short sequences have none in the later ranges, beside ranges that end inside a tile."""
+    import torch
+    t = di.ModelShape(1, 256, 32, 8, 128, 512, 1024, rope_base=1e4)
+    d, lens = di.CONFIGS["tiny"]["drafter"], [700, 3, 33, 64, 129, 1, 290, 511, 96]
+    assert len(lens) * t.n_q_heads > 256
+    wt, wd = StoredWeights(t, di.TARGET_SEED, "bf16"), StoredWeights(d, di.DRAFTER_SEED, "bf16")
+    eng = make_engine(t, d, wt, wd, len(lens), 768, 32)
+    eng._workspace.fill_(255)          # NaN patterns where no pass writes, in the memory that the next engine gets
+    at = eng._workspace.data_ptr()
+    eng.close()
+    del eng
+    eng = make_engine(t, d, wt, wd, len(lens), 768, 32)
+    assert eng._workspace.data_ptr() == at
+    prompts = [di.prompt_ids(t.vocab, n, seq=80 + b) for b, n in enumerate(lens)]
+    blocks = np.random.default_rng(5).integers(0, t.vocab, (len(lens), k)).astype(np.int32)
+    eng.prefill(prompts)
+    eng.draft_block(k, 0.0, 0)
+    eng.verify_block(k, 0.0, torch.from_numpy(blocks).cuda())
+    z = eng.debug_get_logits(0, k)
+    for b, prompt in enumerate(prompts):
+        pair = make_pair(t, d, wt, wd, 768)
+        pair.prefill(prompt)
+        want = pair.verify_logits([int(v) for v in blocks[b]])
+        assert np.abs(z[b] - want).max() < 2e-3, (b, np.abs(z[b] - want).max())
+    eng.close()
