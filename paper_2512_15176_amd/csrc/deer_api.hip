@@ -269,7 +269,7 @@ void plan_work(Work &w, const deer_init_params &p, char *base) {
     w.up_ids = off;
     w.ids = (int *)take((size_t)B * p.max_seq * 4);
     w.st.ing_tok = (int *)take((size_t)B * 32 * 4);
-    w.rm.tok = (int *)take(MAXR * 4); w.rm.pos = (int *)take(MAXR * 4); w.rm.limit = (int *)take(MAXR * 4);
+    w.rm.pos = (int *)take(MAXR * 4); w.rm.limit = (int *)take(MAXR * 4);
     w.rm.slot = (int *)take(MAXR * 4); w.rm.seq = (int *)take(MAXR * 4); w.rm.qrow = (int *)take(MAXR * 4); w.rm.grow = (int *)take(MAXR * 4);
     w.rm.tile_seq = (int *)take(MAXT * 4);
     w.cs = (float2 *)take((size_t)MAXR * 64 * sizeof(float2));

@@ -24,7 +24,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;   // a 16-byte operand fragment held in registers
 
-constexpr int TILE_M = 32;       // rows per tile
 constexpr int CG = 128;          // columns per column group (4 MFMA column blocks)
 constexpr int RED_STRIDE = 136;  // padded LDS row stride (floats) of a 32x128 tile
 
@@ -43,12 +42,6 @@ __device__ __forceinline__ float bf2f(uint32_t b) { return __uint_as_float(b << 
 __device__ __forceinline__ uint32_t f2bf2(float a, float b) {
     f32x2 v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// x ~= hi + lo, both bf16
-__device__ __forceinline__ void split_bf(float x, uint32_t &hi, uint32_t &lo) {
-    hi = f2bf(x);
-    lo = f2bf(x - bf2f(hi));
 }
 
 __device__ __forceinline__ uint4 pack8(const float *v) {
@@ -78,21 +71,14 @@ __device__ __forceinline__ f32x16 mfma32(u32x4 a, uint4 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// A 16-byte load of data that is read exactly once per pass (weights, the prefix K/V rows): marked
-// non-temporal so that the stream does not push activations, partial sums and the kernel's own
-// instructions out of L2.
-__device__ __forceinline__ uint4 ld16_stream(const uint4 *p) {
-    const u32x4 v = __builtin_nontemporal_load((const u32x4 *)p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 // Hand-scheduled loads (used where the compiler's wait-count insertion would drain every outstanding
 // load at a loop header): the load is issued here and its result may only be read after wait_loads<N>()
 // (at most N younger loads still outstanding; loads return in order) followed by tie() on the register.
 __device__ __forceinline__ void load16_async(u32x4 &dst, const void *p) {
     asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(dst) : "v"(p) : "memory");
 }
-// the same, marked non-temporal (data read once per pass: weights)
+// the same, marked non-temporal: data read exactly once per pass (weights), which should not push activations, partial sums
+// and the kernel's own instructions out of L2
 __device__ __forceinline__ void load16_stream_async(u32x4 &dst, const void *p) {
     asm volatile("global_load_dwordx4 %0, %1, off nt" : "=&v"(dst) : "v"(p) : "memory");
 }
@@ -188,8 +174,6 @@ __device__ __forceinline__ uint64_t dpp64_max(uint64_t v) {
     const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(v >> 32)) << 32) | dpp<CTRL>((uint32_t)v);
     return o > v ? o : v;
 }
-
-__device__ __forceinline__ void drain_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Row of the 32x32 MFMA result held in register r of a lane in half `half` (= lane / 32).
 __device__ __forceinline__ int mfma_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
@@ -351,7 +335,7 @@ struct SeqState {       // device arrays, one entry per sequence
 // of one sequence; attention row = 32 * attention tile + r.  The QKV epilogue writes a row's Q fragments at its attention
 // row, the attention kernels write their result at the GEMM row.
 struct RowMeta {
-    int *tok, *pos, *slot, *seq, *qrow;   // [GEMM rows]; slot < 0: do not write K,V; qrow: the attention row, < 0: none (padding)
+    int *pos, *slot, *seq, *qrow;         // [GEMM rows]; slot < 0: do not write K,V; qrow: the attention row, < 0: none (padding)
     int *limit, *grow;                    // [attention rows]: visible keys (0: no such row), GEMM row (< 0: none)
     int *tile_seq;                        // [attention tiles]
 };
@@ -541,7 +525,7 @@ __global__ __launch_bounds__(256) void k_pass_begin(PassRows p, RowMeta rm, cons
         const int row = t * 32 + threadIdx.x;
         const RowDesc r = pass_row(p, s_pref, row);
         s_tok[threadIdx.x] = r.tok; s_pos[threadIdx.x] = r.pos;
-        if ((int)blockIdx.x == ncg) { rm.tok[row] = r.tok; rm.pos[row] = r.pos; rm.slot[row] = r.slot; rm.seq[row] = r.seq; rm.qrow[row] = r.qrow; }
+        if ((int)blockIdx.x == ncg) { rm.pos[row] = r.pos; rm.slot[row] = r.slot; rm.seq[row] = r.seq; rm.qrow[row] = r.qrow; }
     }
     __syncthreads();
     if ((int)blockIdx.x < ncg) {
@@ -1718,29 +1702,25 @@ __global__ void k_draft_finish(SeqState st, const RowResult *__restrict__ res, i
 // ------------------------------------------------------------------------------------------
 template <int HD>
 struct AttnPartial {   // per (tile, head, split): O in register layout [HD/32][4 register quads][64 lanes][4], then (M, L)[32]
-    static constexpr int O_FLOATS = 32 * HD;
     static constexpr int FLOATS = 32 * HD + 64;
 };
 
-template <int HD, bool COH>
+// o: O^T of one head, scaled by inv, into the output projection's input; grow: the GEMM row of this lane's query row, < 0: none
+template <int HD>
 __device__ __forceinline__ void attn_write_frag(const f32x16 *o, float inv, int grow, int head, int Hq, int lane,
-                                                uint4 *__restrict__ xhi, uint4 *__restrict__ xlo, int tt0 = 0,
-                                                int ntt = HD / 32) {
-    // o[i] holds O^T tile tt0 + i; grow: the GEMM row of this lane's query row, < 0: none
+                                                uint4 *__restrict__ xhi, uint4 *__restrict__ xlo) {
     // lane (qrow, half) holds dims 32*tt + 8*q + 4*half + 0..3 in regs 4q..4q+3; the partner lane (other
     // half) holds the other 4 dims of the octet.  Half 0 writes octets with even q, half 1 odd q.
     const int half = lane >> 5;
     const int KS = Hq * HD / 16;
 #pragma unroll
-    for (int ti = 0; ti < HD / 32; ++ti) {
-        if (ti >= ntt) break;
-        const int tt = tt0 + ti;
+    for (int tt = 0; tt < HD / 32; ++tt)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             float mine[4], other[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                mine[e] = o[ti][4 * q + e] * inv;
+                mine[e] = o[tt][4 * q + e] * inv;
                 other[e] = shx(mine[e], 32);
             }
             // octet (tt, q): dims 32*tt + 8*q + 0..7 = half-0 lane's 4 values then half-1 lane's 4 values
@@ -1750,12 +1730,11 @@ __device__ __forceinline__ void attn_write_frag(const f32x16 *o, float inv, int 
                 for (int e = 0; e < 4; ++e) { v[e] = half ? other[e] : mine[e]; v[4 + e] = half ? mine[e] : other[e]; }
                 uint4 hi, lo;
                 pack8_split(v, hi, lo);
-                size_t vec = (size_t)(grow >> 5) * KS * 64 + frag_vec(grow & 31, head * (HD / 8) + tt * 4 + q);
-                st16<COH>(xhi + vec, hi);
-                st16<COH>(xlo + vec, lo);
+                const size_t vec = (size_t)(grow >> 5) * KS * 64 + frag_vec(grow & 31, head * (HD / 8) + tt * 4 + q);
+                xhi[vec] = hi;
+                xlo[vec] = lo;
             }
         }
-    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1947,7 +1926,7 @@ __global__ __launch_bounds__(256, 2) void k_attn(const uint4 *__restrict__ Qhi, 
     if (!active) return;
     const float l_tot = l_run + shx(l_run, 32);
     if (NS == 1) {
-        attn_write_frag<HD, false>(oacc, l_tot > 0.f ? 1.f / l_tot : 0.f, row_grow[t * 32 + qrow], head, Hq, lane, xhi, xlo);
+        attn_write_frag<HD>(oacc, l_tot > 0.f ? 1.f / l_tot : 0.f, row_grow[t * 32 + qrow], head, Hq, lane, xhi, xlo);
     } else {
         float *pp = part + ((size_t)(t * Hq + head) * NS + split) * PF;
 #pragma unroll
@@ -2343,7 +2322,7 @@ __global__ __launch_bounds__(512) void k_attn_head(const uint4 *__restrict__ Qhi
 // ------------------------------------------------------------------------------------------
 // acceptance and commit, one block per sequence
 // ------------------------------------------------------------------------------------------
-struct AcceptOut { int *accept_len, *n_committed, *committed; };   // [B], [B], [B][k + bonus]: page-locked host memory (written, never read)
+struct AcceptOut { int *accept_len, *n_committed, *committed; };   // [B], [B], [B][k + bonus]: written, never read (page-locked host memory, or the workspace where there is none)
 
 // bonus = 1: the target pass had k + 1 rows and `corr` is also the extra token after k accepted drafts
 __device__ __forceinline__ void commit_tokens(SeqState st, AcceptOut out, int b, int k, int a, int corr, const int *d,
