@@ -65,11 +65,11 @@ def test_8b_layer_widths_prefill_through_tiled_gemm():
 
 
 def test_batch_of_64_sequences_through_tiled_gemm():
-    """64 sequences make 2048-row verify passes and 4096-row draft passes (ingest + MASK tiles, LM head on every
-    second tile): every GEMM of both passes, the LM heads included, runs through the tiled kernel."""
+    """64 sequences with blocks of 32 make 2048-row verify passes, and draft passes of 2048 rows with the committed tokens behind
+    them (over 100 in the second iteration): every GEMM of both passes, the LM heads included, runs through the tiled kernel."""
     import torch
     cfg = di.CONFIGS["tiny"]
-    t, d, k, B = cfg["target"], cfg["drafter"], cfg["k"], 64
+    t, d, k, B = cfg["target"], cfg["drafter"], 32, 64
     wt, wd = StoredWeights(t, di.TARGET_SEED, "bf16"), StoredWeights(d, di.DRAFTER_SEED, "bf16")
     eng = make_engine(t, d, wt, wd, B, 128, k)
     eng.debug_gemm_tiled(1)

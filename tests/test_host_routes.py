@@ -98,3 +98,18 @@ for d, hq, hkv, tiles in ((256, 4, 2, 63), (896, 14, 2, 31), (896, 14, 2, 63), (
 print(out)
 """)
     assert got[0][1] is False and got[1][1] is False and got[2][1] is True and got[3][0] is True and got[4][0] is False, got
+
+
+def test_a_batch_of_64_blocks_runs_blocked_throughout(tmp_path):
+    """The passes of test_gpu_tiled_gemm.py::test_batch_of_64_sequences_through_tiled_gemm: 64 row tiles, every GEMM blocked."""
+    got = routes(tmp_path, """
+t, d = di.CONFIGS["tiny"]["target"], di.CONFIGS["tiny"]["drafter"]
+e = engine(t, d, 64, 128)
+assert e.lib.deer_debug_gemm_tiled(e.ctx, 1) == 0
+e.prefill([[3] * 40] * 64)
+a = gemms(e, lambda: e.draft_block(32))
+tiles = [g for n, g in e.launches() if "k_pass_begin" in n]
+print((a, gemms(e, lambda: e.verify_block(32)), tiles))
+""")
+    assert all(n.startswith("block") for n in got[0] | got[1]) and len(got[0]) == 4, got
+    assert got[2][0][1] == 64
