@@ -382,8 +382,9 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
     const int nrb = (ntiles + BK_RT - 1) / BK_RT;
     // 128 columns per wave keep K in one chain of sums (see BK_SHORT): only in large launches (1024 rows on, 128 blocks of
     // 256 x 256), where it is the chip's rate that counts and no kernel before this one cut the chain either; not beside a
-    // mixture, where a rounding can send a row to another expert.  (LM heads of fewer rows would gain by it, 2 % of a pass of
-    // 16 sequences, but their logits' own error is 2 to 2.8 times the streaming kernel's then.)
+    // mixture, where a rounding can send a row to another expert.  (LM heads of fewer rows would gain by it - 16 row
+    // tiles, 151936 columns, mean of d = 4096 and 896: 793 against 865 us, 2 to 3 % of an iteration of 16 sequences - but
+    // their logits' own error is 2 to 2.8 times the streaming kernel's then.)
     const bool wide_ok = !mixture && ntiles >= 32 && ((ntiles + 7) / 8) * ((N / CG + 1) / 2) >= 128;
     for (int NB = wide_ok ? 4 : 2; NB >= 2; NB -= 2) {
         const int ncb = (N + 64 * NB - 1) / (64 * NB);
@@ -517,9 +518,9 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
     return DEER_OK;
 }
 
-// Gate/up of a mixture runs blocked (rows gathered per expert first) from 12 pairs per expert on: 6 row tiles of a layer of
-// 128 experts, top 8, take 172 against 177 us, 8 row tiles 174 against 198, 4 row tiles 170 against 162.
-constexpr int MOE_BLOCK_PAIRS = 12;
+// Gate/up of a mixture runs blocked (rows gathered per expert first) from 14 pairs per expert on: 6 row tiles of a layer of
+// 128 experts, top 8, take 174 against 168 us, 7 row tiles 174 against 174, 8 row tiles 173 against 179, 16 208 against 293.
+constexpr int MOE_BLOCK_PAIRS = 14;
 
 // One forward pass of `model` over the rows described by the row metadata: ntiles tiles of GEMM rows, n_attn attention tiles.
 // rows_desc: how the first launch finds the pass's rows.

@@ -64,7 +64,7 @@ def test_blocked_and_streaming_kernels_agree(engine, lens, k):
 @pytest.mark.parametrize("lens", [[7], [65], [190, 3], [700, 33, 1]])
 def test_grouped_gemms_of_a_mixture(lens):
     """Experts with fewer and more than 32 and 64 pairs, 384 = one and a half 256-column blocks, an expert width of three
-    64-channel groups: gathered rows and blocked gate/up (from 12 pairs per expert on) against the streaming gate/up and
+    64-channel groups: gathered rows and blocked gate/up (from 14 pairs per expert on) against the streaming gate/up and
     the oracle."""
     import torch
     from gpu_common import make_pair

@@ -113,3 +113,13 @@ print((a, gemms(e, lambda: e.verify_block(32)), tiles))
 """)
     assert all(n.startswith("block") for n in got[0] | got[1]) and len(got[0]) == 4, got
     assert got[2][0][1] == 64
+
+
+def test_grouped_gate_up_runs_blocked_where_experts_have_rows_enough(tmp_path):
+    """128 experts, top 8: 12 pairs per expert at 6 row tiles, where the streaming kernel is faster, 14 at 7."""
+    got = routes(tmp_path, """
+t = di.ModelShape(1, 256, 4, 2, 32, 0, 1024, n_experts=128, top_k=8, d_ff_expert=128, rope_base=1e4)
+e = engine(t, di.CONFIGS["tiny"]["drafter"], 1, 512)
+print([gemms(e, lambda: e.prefill([[3] * (32 * n + 1)])) for n in (6, 7)])
+""")
+    assert "k_gemm_moe" in got[0] and "k_gemm_moe" not in got[1] and "moe_block" in got[0] & got[1], got
