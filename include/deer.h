@@ -121,14 +121,14 @@ int deer_load_tensor(deer_ctx *c, int model, int tensor_id, int layer, int exper
  * prompt_lens_host[b] >= 1.  Builds the target cache for x_{1:j-1} and the drafter cache for
  * x_{1:j} with causal attention, in passes that hold the rows of as many sequences as fit (each pass streams the
  * weights once): up to max(128, 2 * max_batch) tiles of 32 rows, a sequence's last tile being filled in part, i.e. up
- * to 4096 rows, or 64 * max_batch if that is more.  Waits for completion.  After an error the context holds no
- * sequences. */
+ * to 4096 rows, or 64 * max_batch if that is more.  Waits for completion.  After DEER_EHIP the context holds no
+ * sequences (refused arguments leave it as it was). */
 int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *prompt_ids_host, const int32_t *prompt_lens_host);
 
 /* Sets the state as if `lens_host[b]` tokens had been prefilled, WITHOUT running the models:
  * the caller has written cache contents itself (deer_debug_load_kv) - used where a real prefill
  * is too costly (32k-token prefixes).  last_token_host[b] = x_j, the pending token.  The drafter
- * cache is taken to hold all lens_host[b] tokens. */
+ * cache is taken to hold all lens_host[b] tokens.  Errors as for deer_prefill. */
 int deer_set_prefilled(deer_ctx *c, int32_t batch, const int32_t *lens_host, const int32_t *last_token_host);
 
 /* Drafter pass (Sec. 3.2: one pass proposes the whole block; position i's law does not depend

@@ -7,14 +7,15 @@
 // under the products of the other.  With S > 1 the workgroups of a tile take shares of K; their accumulators meet
 // through memory as they lie in the registers, and the last to arrive sums the shares in order and runs the epilogue.
 //
-// Bound: the matrix cores for many row tiles (128 of them, 8B gate/up: 1.28 PFLOP/s issued, what the largest plain bf16
-// product reaches on this card is 1.36; LM head of 16: 1.6 PFLOP/s), the L2 -> LDS path for few (a k-step of NB = 4 brings
+// Bound: the matrix cores for many row tiles (128 of them, 8B gate/up: 1.31 PFLOP/s issued, what the largest plain bf16
+// product reaches on this card is 1.36), the L2 -> LDS path for few (a k-step of NB = 4 brings
 // 16 KB; a compute unit gets 27 to 34 bytes per clock, 512 cycles of products need 32).  A 64 x 128 wave tile reads 8 KB of
 // LDS per 16 products, which leaves the LDS half idle; 128 x 256 per workgroup needs 16 KB from L2 per 64 products
 // against 32 KB in the streaming kernel's pairs of row tiles.  Measured against the kernels that did this work before
 // (one 256 x 256 tile per 512 threads in lockstep; the streaming kernel), microseconds per launch, 8B widths: gate/up at
-// 4 / 7 / 16 / 32 / 128 row tiles 83 / 142 / 227 / 454 / 1369 -> 70 / 112 / 190 / 330 / 1270, QKV at 16 / 64 / 128
-// 81 / 255 / 531 -> 64 / 185 / 333, down at 24 / 64 200 / 648 -> 165 / 325, LM head at 16 (with 151936 columns) 1348 -> 760.
+// 4 / 7 / 16 / 32 / 128 row tiles 85 / 146 / 224 / 439 / 1345 -> 71 / 117 / 192 / 326 / 1255, QKV at 16 / 64 / 128
+// 83 / 247 / 503 -> 69 / 189 / 327, down at 24 / 64 196 / 621 -> 167 / 320, LM heads of 151936 columns at 16 (mean of
+// d = 4096 and 896) 1348 -> 865.
 #pragma once
 #include "deer_kernels.hpp"
 
@@ -520,8 +521,8 @@ __global__ __launch_bounds__(256) void k_moe_gather(const float *__restrict__ h,
 // next item, whose weights are then in that L2.
 // Bound: HBM (the expert weights) up to a few rows per expert, then the matrix cores.  Layer of 128 experts, top 8,
 // d = 2048, expert width 768, microseconds at 1 / 8 / 16 / 64 / 128 row tiles against the streaming kernel with its
-// 32-pair chunks: down 69 / 80 / 92 / 157 / 264 for 75 / 97 / 137 / 429 / 826, gate/up with the gather before it 155 / 174 /
-// 210 / 323 / 516 for 129 / 198 / 314 / 1217 / 2642.
+// 32-pair chunks: down 74 / 81 / 86 / 162 / 283 for 75 / 97 / 137 / 429 / 826, gate/up with the gather before it - / 176 /
+// 208 / 325 / 549 for 129 / 181 / 293 / 1057 / 2370.
 template <int MODE, bool SHORT>
 __global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) {
     constexpr int NB = 2, NST = 4, WC = 4;

@@ -916,8 +916,8 @@ __device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile,
 
 // router epilogue: logits over the experts -> softmax -> top_k (lowest index on ties) -> weights renormalised to sum 1.
 // 16 threads per row, 8 experts each.  A candidate is one 64-bit key, the bits of its (non-negative) weight above
-// 128 - index, so that a comparison decides value and tie at once.  (Two values per candidate and exchanges through LDS
-// took 12 of the launch's 20 us.)
+// 128 - index, so that a comparison decides value and tie at once.  (With two values per candidate and exchanges
+// through LDS the launch took 20 us, now 12.5.)
 __device__ __forceinline__ void epi_router(const GemmArgs &a, const float *tile, const float *rstd, int t) {
     const int tidx = opaque_tid();
     const int row = tidx >> 4, sub = tidx & 15;
@@ -1751,8 +1751,8 @@ __device__ __forceinline__ void attn_write_frag(const f32x16 *o, float inv, int 
 //  - the result goes to the output projection's input (NS == 1) or to an un-normalised partial (M, L, O) for the merge.
 // Bound: the chain products -> softmax -> products of two waves per SIMD, at the clock that is left when matrix cores and
 // HBM are both busy (counted: 1.84 GHz and the matrix pipe busy 58 % of a long-context launch).  Microseconds per launch
-// against one workgroup of eight waves, two per head, behind one barrier: 8B heads, 16 sequences x 32768 keys 565 -> 536
-// (4.0 TB/s of K and V), prompt of 4096 341 -> 268, batch of prompts (104 tiles) 73 -> 51; drafter, prompt of 4096
+// against one workgroup of eight waves, two per head, behind one barrier: 8B heads, 16 sequences x 32768 keys 560 -> 531
+// (4.0 TB/s of K and V), prompt of 4096 341 -> 268, batch of prompts (104 tiles) 73 -> 53; drafter, prompt of 4096
 // 138 -> 96.  A ring of four single tiles took 544 and 290 (drafter 114).  Tiles of fewer than 32 rows skip the mask and the
 // rescale like full ones (16 sequences x 8192 keys, 31 / 16 / 4 rows: 162 / 158 / 139 -> 153 / 153 / 132; 32 rows: 154).
 // ------------------------------------------------------------------------------------------
