@@ -39,6 +39,7 @@ constexpr int PREFILL_TILES = 128;   // row tiles that a prefill pass may have a
 constexpr int PART_TILES_MIN = 16;   // split-K partials exist for passes of up to max(2 * batch, 16) row tiles
 constexpr int MAX_NS = 32;          // key-range splits of block attention
 constexpr size_t H_UP_MAX = 1 << 20;  // most page-locked host memory of a context for uploads
+constexpr int SLIM_MAX_D = 4096, SLIM_TILES = 4;   // passes of up to 4 row tiles of a model up to this width may use k_gemm_slim (64 sums of squares per row)
 constexpr int NARROW_MAX_D = 1024;  // residual width up to which a dense model's O projection runs in 32-column workgroups
 constexpr int NEXT_SPAN_BYTES = 16 << 10;      // fetched ahead per 32-column block of a next-launch workgroup (4 blocks: 8 loads per thread)
 constexpr int KV_FETCH_MAX_BYTES = 1 << 20;    // fetched ahead per kv head of K and of V^T: a share of one XCD's 4 MB L2
@@ -50,7 +51,7 @@ size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 struct ModelRT {
     deer_model_cfg c{};
     int n_qkv = 0, kattn = 0, F = 0;   // fused QKV width, Hq*hd, FFN width used by GEMMs
-    int ssq_sub = 1;   // sums of squares of the residual stream per 128-column group (1) or per 32-column block (4)
+    int ssq_sub = 1;   // passes of many row tiles: sums of squares of the residual stream per 128-column group (1) or per 32-column block (4)
     // weights (device)
     char *w = nullptr;
     size_t off_embed = 0, off_lm = 0, off_layers = 0, layer_bytes = 0;
@@ -111,6 +112,7 @@ struct deer_ctx {
     int force_nb = 0, force_ring = 0, force_S = 0;   // deer_debug_gemm_block; force_nb 0: off
     // deer_debug_gemm_stamps: which streaming-GEMM launch of which model's passes records its stamps
     int stamp_model = 0, stamp_launch = -1, stamp_blocks = 0, gemm_launch_idx = 0, cur_pass_model = 0;
+    bool slim = true;                // deer_debug_gemm_tiled: off where it asks for the plain streaming kernels
     int route_spread = 0;            // deer_debug_route_spread: synthetic uniform routing for mixture models
     int bonus = 0;                   // 1: verify k + 1 rows, commit one more target token after k accepted drafts
     void *static_scratch = nullptr;  // this device's copy of `scratch`
@@ -374,6 +376,33 @@ double narrow_us(int N, int KS, int ntiles, bool qkv) {
     const double r = (N / (qkv ? 64 : 32) + 7) / 8 * 8 * ntiles / 256.0;
     return qkv ? 5.6 + 0.04 * KS + (3.2 + 0.05 * KS) * std::max(0.0, r - 1.0) : 4.0 + 0.035 * KS + (1.6 + 0.067 * KS) * std::max(0.0, r - 1.5);
 }
+// Passes of up to SLIM_TILES row tiles, one round of workgroups: a fixed part and behind it the larger of HBM's time for the
+// weights (6.5 TB/s) and a compute unit's for what its workgroups draw (62 KB per microsecond).  Fitted to launches of the
+// 4B, 8B, 30B-A3B and drafter matrices over one and two row tiles (see k_gemm_slim; microseconds measured / estimated, 8B O
+// in 224 wide workgroups 13.2 / 13.4, in 256 slim ones 11.0 / 11.6, drafter down 11.7 / 11.9 and 7.4 / 7.8).
+double small_us(double base, int N, int KS, int wgs, int S, int frags) {   // frags: 1 KB fragments per k-step of a workgroup
+    const double hbm = (double)N * KS * 32.0 / 6.5e6, cu = std::ceil(wgs / 256.0) * ((double)KS / S) * frags / 62.0;
+    return base + std::max(hbm, cu);
+}
+double stream_small_us(int N, int KS, int MT, int zg, int S) {
+    return small_us(MT == 2 ? (S > 1 ? 14.0 : 12.0) : (S > 1 ? 8.2 : 5.6), N, KS, N / CG * S * zg, S, 4 + 2 * MT);
+}
+// k_gemm_slim for one GEMM of a pass; C == 0: the wide kernels
+struct SlimPlan { int C = 0, S = 1, ngrp = 0, pairs = 0; double us = 1e30; };
+SlimPlan plan_slim(int epi, int N, int KS, int ntiles, int hd, int ssq_sub, size_t part_floats) {
+    SlimPlan best;
+    // a residual GEMM leaves one sum of squares per row and workgroup: its width is what the pass keeps
+    const int C = epi == EPI_RESID ? 4 / ssq_sub : 2, ngrp = N / (32 * C);
+    if (ntiles > SLIM_TILES || C > 2 || (epi != EPI_RESID && epi != EPI_QKV && epi != EPI_SWIGLU)) return best;
+    // one workgroup per compute unit, padding of the ids included (a second one on some would take as long again); at most
+    // eight shares (they are loaded together)
+    for (int S = 1; S <= 8 && (ngrp * S + 7) / 8 * 8 * ntiles <= 256; ++S) {
+        if (S > 1 && (KS < 16 * S || (size_t)ngrp * S * ntiles * 1024 * C > part_floats)) break;
+        const double us = small_us((S > 1 ? 6.0 : 4.7) + 0.4 * (C - 1), N, KS, ngrp * S * ntiles, S, C + 2);
+        if (us < best.us) best = SlimPlan{C, S, ngrp, epi == EPI_SWIGLU || (epi == EPI_QKV && hd == 128), us};
+    }
+    return best;
+}
 // Blocked kernel: NB = 4 (128 x 256 per workgroup: 0.3 to 0.4 us per k-step, the more the busier the chip) or NB = 2
 // (128 x 128: 0.16 us with 64 workgroups, 0.24 with one per compute unit, 0.225 with more).
 struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; };
@@ -433,10 +462,14 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     a.rows_total = ntiles * 32;
     const bool narrow = (EPI == EPI_RESID || (EPI == EPI_QKV && a.hd <= 64 && 64 % a.hd == 0 && a.N % 64 == 0)) && a.ssq_sub == 4 && MT == 1 &&
                         force_S <= 0 && a.KS <= 64;
+    const int wide_S = force_S > 0 ? force_S : choose_split(a.N, a.KS, zg);
+    SlimPlan sp;
+    if (!narrow && force_S <= 0 && a.slim) sp = plan_slim(EPI, a.N, a.KS, ntiles, a.hd, a.ssq_sub, c->wk.part_floats);
+    const bool slim = sp.C > 0 && sp.us < 0.98 * stream_small_us(a.N, a.KS, MT, zg, wide_S);
     if constexpr (EPI != EPI_ROUTER) {
         const BlockPlan bp = c->force_nb ? forced_block(c, a.N, a.KS, ntiles, EPI == EPI_LMHEAD)
                                          : plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);
-        const double old_us = narrow ? narrow_us(a.N, a.KS, ntiles, EPI == EPI_QKV) : stream_us(a.N, a.KS, MT, zg, force_S > 0 ? force_S : choose_split(a.N, a.KS, zg));
+        const double old_us = narrow ? narrow_us(a.N, a.KS, ntiles, EPI == EPI_QKV) : slim ? sp.us : stream_us(a.N, a.KS, MT, zg, wide_S);
         const bool forced = c->force_nb || (c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8);   // tests cover it at small sizes
         if (c->block_gemm > 0 && ntiles > 1 && (forced || bp.us < 0.97 * old_us)) {
             a.S = bp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
@@ -466,7 +499,19 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
         LAUNCHCHK(c, "k_gemm_narrow");
         return DEER_OK;
     }
-    a.S = force_S > 0 ? force_S : choose_split(a.N, a.KS, zg);
+    if constexpr (EPI == EPI_RESID || EPI == EPI_QKV || EPI == EPI_SWIGLU)
+        if (slim) {
+            a.S = sp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
+            a.stamps = stamp_buffer(c, (size_t)sp.ngrp * sp.S * ntiles);
+            c->gemm_launch_idx++;
+            ProfScope ps(c, 0, (double)a.N * K * 2.0);
+            const dim3 g1((unsigned)((sp.ngrp * sp.S + 7) / 8 * 8 * ntiles));
+            if (sp.C == 2) hipLaunchKernelGGL((k_gemm_slim<2, EPI>), g1, dim3(512), 0, c->stream, a, sp.ngrp, ntiles, sp.pairs);
+            else if constexpr (EPI == EPI_RESID) hipLaunchKernelGGL((k_gemm_slim<1, EPI>), g1, dim3(512), 0, c->stream, a, sp.ngrp, ntiles, sp.pairs);
+            LAUNCHCHK(c, "k_gemm_slim");
+            return DEER_OK;
+        }
+    a.S = wide_S;
     while (a.S > 1 && (size_t)a.S * a.rows_total * a.N > c->wk.part_floats) --a.S;   // partials must fit their buffer
     a.part = (EPI == EPI_LMHEAD) ? nullptr : c->wk.part;
     a.counters = c->wk.gemm_cnt;
@@ -532,11 +577,14 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
     const int d = mc.d_model, hd = mc.head_dim, rows = ntiles * 32, ncg_d = d / CG;
     c->gemm_launch_idx = 0;
     c->cur_pass_model = model;
+    // not for a mixture: another order of its sums can send a row that lies between two experts to the other one
+    const bool slim = c->slim && !mc.n_experts && ntiles <= SLIM_TILES && d <= SLIM_MAX_D;
+    const int ssq_sub = m.ssq_sub == 4 ? 4 : slim ? 2 : 1;   // what the pass's residual GEMMs leave: one sum of squares per 32, 64 or 128 columns
     hipStream_t s = c->stream;
     if (c->stamp_launch >= 0 && model == c->stamp_model) (void)hipMemsetAsync(w.stamps, 0, (size_t)STAMP_MAX_BLOCKS * 64, s);
     prof_close(c);
     hipLaunchKernelGGL(k_pass_begin, dim3(ncg_d + 2, std::max(ntiles, n_attn)), dim3(256), 0, s, rows_desc, w.rm, (const uint16_t *)(m.w + m.off_embed),
-                       w.h, w.xa_hi, w.xa_lo, w.ssq, d, ncg_d, m.ssq_sub, m.theta, w.cs, hd / 2, ntiles, n_attn);
+                       w.h, w.xa_hi, w.xa_lo, w.ssq, d, ncg_d, ssq_sub, m.theta, w.cs, hd / 2, ntiles, n_attn);
     LAUNCHCHK(c, "k_pass_begin");
     const int nkt = (max_limit + 31) / 32;
     // key-range splits: aim at two workgroups per compute unit; a split holds at least four key tiles; n_attn * NS never
@@ -557,8 +605,8 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
     const float scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
     const double kv_bytes = kv_keys_total * mc.n_kv_heads * hd * 2.0 * 2.0;   // K and V rows read per layer
     GemmArgs base{};
-    base.ssq_in = w.ssq; base.ncg_in = ncg_d * m.ssq_sub; base.d_in = d; base.eps = mc.rms_eps;
-    base.ssq_sub = m.ssq_sub;
+    base.ssq_in = w.ssq; base.ncg_in = ncg_d * ssq_sub; base.d_in = d; base.eps = mc.rms_eps;
+    base.ssq_sub = ssq_sub; base.slim = slim;
     base.cs = w.cs; base.rm = w.rm; base.qhi = w.q_hi; base.qlo = w.q_lo;
     base.Hq = mc.n_q_heads; base.Hkv = mc.n_kv_heads; base.hd = hd;
     base.h = w.h; base.xhi_out = w.xa_hi; base.xlo_out = w.xa_lo; base.ssq_out = w.ssq;
@@ -571,8 +619,9 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
     // epilogue) or for gate/up, costs more than it saves.
     // A small dense model (narrow workgroups for its unsplit O and QKV projections, one or two row tiles): attention
     // fetches the output projection's 32-column blocks whole, the split down projection the next layer's QKV blocks.
-    const bool fetch_ahead = ntiles == 1 && m.ssq_sub == 1;
-    const bool fetch_ahead_narrow = ntiles <= 2 && m.ssq_sub == 4 && !mc.n_experts;
+    const bool small_dense = m.ssq_sub == 4;
+    const bool fetch_ahead = ntiles == 1 && !small_dense;
+    const bool fetch_ahead_narrow = ntiles <= 2 && small_dense && !mc.n_experts;
     auto next_plan_narrow = [&](const char *W, int N, int K, int NB) {   // NB: 1 residual GEMM, 2 QKV (whole heads)
         NextWeights nx{};
         const int KS = K / 16;
@@ -582,14 +631,17 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
         nx.block_bytes = (long long)KS * 1024; nx.narrow_nb = NB; nx.Z = ntiles;
         return nx;
     };
-    auto next_plan = [&](const char *W, int N, int K) {
+    auto next_plan = [&](const char *W, int N, int K, int epi) {
         NextWeights nx{};
         if (!fetch_ahead) return nx;
         const int KS = K / 16;
         int S = choose_split(N, KS, 1);
-        while (S > 1 && (size_t)S * 32 * N > c->wk.part_floats) --S;
+        nx.ncg = N / CG; nx.nblk = 4;
+        const SlimPlan sp = slim ? plan_slim(epi, N, KS, 1, hd, ssq_sub, c->wk.part_floats) : SlimPlan{};
+        if (sp.C > 0 && sp.us < 0.98 * stream_small_us(N, KS, 1, 1, S)) { S = sp.S; nx.ncg = sp.ngrp; nx.nblk = sp.C; nx.pairs = sp.pairs; }
+        else while (S > 1 && (size_t)S * 32 * N > c->wk.part_floats) --S;
         const int per = (KS + S * 8 - 1) / (S * 8);
-        nx.base = W; nx.ncg = N / CG; nx.nwg = nx.ncg * S; nx.span = NEXT_SPAN_BYTES;
+        nx.base = W; nx.nwg = nx.ncg * S; nx.span = NEXT_SPAN_BYTES;
         nx.block_bytes = (long long)KS * 1024; nx.split_bytes = (long long)8 * per * 1024;
         return nx;
     };
@@ -604,7 +656,7 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             a.kv_fetch_bytes = std::min(KV_FETCH_MAX_BYTES, std::max(0, (max_limit - 32) / 32) * 32 * hd * 2);
         int rc = launch_gemm<EPI_QKV>(c, a, d, ntiles, 0);
         if (rc) return rc;
-        const NextWeights nx_o = fetch_ahead_narrow ? next_plan_narrow(lw + m.lo_o, d, m.kattn, 1) : next_plan(lw + m.lo_o, d, m.kattn);
+        const NextWeights nx_o = fetch_ahead_narrow ? next_plan_narrow(lw + m.lo_o, d, m.kattn, 1) : next_plan(lw + m.lo_o, d, m.kattn, EPI_RESID);
         if (hd == 128) rc = launch_attn<128>(c, m, l, n_attn, NS, NS_head, scale_log2e, kv_bytes, nx_o);
         else if (hd == 64) rc = launch_attn<64>(c, m, l, n_attn, NS, NS_head, scale_log2e, kv_bytes, nx_o);
         else rc = launch_attn<32>(c, m, l, n_attn, NS, NS_head, scale_log2e, kv_bytes, nx_o);
@@ -622,7 +674,7 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             a.W = (const uint4 *)(lw + m.lo_d); a.Xhi = w.xb_hi; a.Xlo = w.xb_lo; a.N = d;
             if (l + 1 < mc.n_layers)
                 a.nx = fetch_ahead_narrow ? next_plan_narrow(lw + m.layer_bytes + m.lo_qkv, m.n_qkv, d, 2)
-                                          : next_plan(lw + m.layer_bytes + m.lo_qkv, m.n_qkv, d);
+                                          : next_plan(lw + m.layer_bytes + m.lo_qkv, m.n_qkv, d, EPI_QKV);
             rc = launch_gemm<EPI_RESID>(c, a, m.F, ntiles, 0);
             if (rc) return rc;
         } else {
@@ -1197,6 +1249,7 @@ int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles) {
     if (!c) return DEER_EINVAL;
     if (min_tiles < 0) return fail(c, DEER_EINVAL, "min_tiles must not be negative");
     c->block_gemm = min_tiles;
+    c->slim = min_tiles != 0;
     return DEER_OK;
 }
 

@@ -278,6 +278,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
         }
         if (half == 0) {
             if (a.ssq_sub == 4) *(float4 *)(a.ssq_out + grow * (N / 32) + cg * 4) = make_float4(ss[0], ss[1], ss[2], ss[3]);
+            else if (a.ssq_sub == 2) *(float2 *)(a.ssq_out + grow * (N / 64) + cg * 2) = make_float2(ss[0] + ss[1], ss[2] + ss[3]);
             else a.ssq_out[grow * (N / CG) + cg] = (ss[0] + ss[1]) + (ss[2] + ss[3]);
         }
     } else if (EPI == EPI_QKV) {

@@ -86,8 +86,8 @@ __device__ __forceinline__ void load4_async(float &dst, const void *p) {
     asm volatile("global_load_dword %0, %1, off" : "=&v"(dst) : "v"(p) : "memory");
 }
 __device__ __forceinline__ void tie(float &r) { asm volatile("" : "+v"(r)); }
-// at most `steps` x PER loads may still be outstanding (steps <= 4)
-template <int PER>
+// at most `steps` x PER loads may still be outstanding (steps <= MAX <= 5)
+template <int PER, int MAX = 4>
 __device__ __forceinline__ void wait_steps(int steps);
 // The same with agent scope: the load is served by memory, not by an L2 that may hold an older copy of a line
 // another XCD has written since.
@@ -103,14 +103,15 @@ __device__ __forceinline__ void store16_agent(void *p, float a, float b, float c
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-template <int PER>
+template <int PER, int MAX>
 __device__ __forceinline__ void wait_steps(int steps) {
-    static_assert(4 * PER <= 63, "the counter has six bits");
+    static_assert(MAX >= 3 && MAX <= 5 && MAX * PER <= 63, "the counter has six bits");
     if (steps <= 0) wait_loads<0>();
     else if (steps == 1) wait_loads<PER>();
     else if (steps == 2) wait_loads<2 * PER>();
-    else if (steps == 3) wait_loads<3 * PER>();
-    else wait_loads<4 * PER>();
+    else if (MAX == 3 || steps == 3) wait_loads<3 * PER>();
+    else if (MAX == 4 || steps == 4) wait_loads<4 * PER>();
+    else wait_loads<5 * PER>();
 }
 __device__ __forceinline__ void tie(u32x4 &r) { asm volatile("" : "+v"(r)); }
 
@@ -460,7 +461,7 @@ __device__ __forceinline__ void tile_to_frag(const float *tile, uint4 *xhi, uint
 }
 
 // embedding gather of one (column group, tile): h[row] = E[tok[row]] (bf16 table), plus fragment planes (the value itself and
-// zero: the table is bf16) and sums of squares per row and column group, or (ssq_sub == 4) per 32-column block of it;
+// zero: the table is bf16) and sums of squares per row and 128 / ssq_sub columns;
 // tok: the tile's 32 token ids (global memory or LDS); 256 threads.  16 threads per row, 8 columns each, all in registers:
 // the launch is a chain of latencies (token, table row, stores), and a tile in LDS with one thread per row for the sums made
 // it 17 us for a prompt of 7 row tiles, 8 us for the smallest.
@@ -496,7 +497,7 @@ __device__ __forceinline__ void embed_tile(const uint16_t *__restrict__ E, const
 #pragma unroll
             for (int e = 0; e < 8; ++e) s = fmaf(x[e], x[e], s);
         }
-        if (at == lanes - 1) ssq[grow * (ncg * ssq_sub) + cg * ssq_sub + (ssq_sub == 4 ? oct >> 2 : 0)] = s;
+        if (at == lanes - 1) ssq[grow * (ncg * ssq_sub) + cg * ssq_sub + oct / lanes] = s;
     }
 }
 
@@ -599,8 +600,9 @@ __device__ __forceinline__ void load16_discard(void *sink, const void *p) {
 // they pull it into their XCD's L2 while the launch's last workgroups finish (memory is idle then), so that the next
 // launch's first k-steps hit there.  Workgroup ids 8 apart share an XCD in both launches; workgroup j of this launch
 // fetches for workgroup j of the next.
-//   narrow_nb == 0 (k_gemm's grid order): next-launch workgroup j works on column group j % ncg and K split j / ncg;
-//     fetched: the first `span` bytes of the split's K range in each of the group's four 32-column blocks.
+//   narrow_nb == 0 (the order of k_gemm and k_gemm_slim): next-launch workgroup j works on column group j % ncg and K split
+//     j / ncg; fetched: the first `span` bytes of the split's K range in each of the group's nblk 32-column blocks, which
+//     are adjacent or (pairs) the blocks of slim_block.
 //   narrow_nb = NB > 0 (k_gemm_narrow's order): j = 8 * ((p / 8) * Z + z) + p % 8 is row tile z of the group p of NB
 //     blocks, all of K; the Z workgroups of a group read the same (contiguous) NB * block_bytes: part z of Z is fetched.
 struct NextWeights {
@@ -610,7 +612,14 @@ struct NextWeights {
     long long block_bytes;     // one 32-column block: KS * 1024
     long long split_bytes;     // a split's K range within a block
     int narrow_nb, Z;
+    int nblk, pairs;           // 32-column blocks of a column group (k_gemm: 4)
 };
+
+// First 32-column block of column group p of k_gemm_slim and the distance to its second.  pairs: blocks two apart inside a
+// group of four — a gate block and its up block, or the two halves of a 128-wide head (a rotation pair lies in both).
+__device__ __forceinline__ int slim_block(int p, int C, bool pairs, int j) {
+    return pairs ? ((p >> 1) << 2) + (p & 1) + 2 * j : p * C + j;
+}
 
 // lds: 8 KB of LDS the workgroup is done with
 __device__ __forceinline__ void prefetch_next(const NextWeights &nx, void *lds) {
@@ -633,9 +642,10 @@ __device__ __forceinline__ void prefetch_next(const NextWeights &nx, void *lds) 
         const int cg = j % nx.ncg, sp = j / nx.ncg;
         const long long s_off = sp * nx.split_bytes;
         const int len = (int)min((long long)nx.span, nx.block_bytes - s_off);   // stays inside the block
-        const char *p0 = nx.base + (long long)cg * 4 * nx.block_bytes + s_off + tid * 16;
-        for (int nb = 0; nb < 4; ++nb)
-            for (int o = tid * 16; o < len; o += 512 * 16) load16_discard(sink, p0 + nb * nx.block_bytes + (o - tid * 16));
+        for (int nb = 0; nb < nx.nblk; ++nb) {
+            const char *p0 = nx.base + (long long)slim_block(cg, nx.nblk, nx.pairs, nb) * nx.block_bytes + s_off;
+            for (int o = tid * 16; o < len; o += 512 * 16) load16_discard(sink, p0 + o);
+        }
     }
     wait_loads<0>();
 }
@@ -671,7 +681,8 @@ struct GemmArgs {
     const float2 *cs; RowMeta rm; uint4 *qhi, *qlo; KvView kv; int Hq, Hkv, hd;
     // RESID: h += y, new fragments and sums of squares of h
     float *h; uint4 *xhi_out, *xlo_out; float *ssq_out;
-    int ssq_sub;   // 1: one sum of squares per row and 128-column group; 4: one per 32-column block (narrow launches)
+    int ssq_sub;   // sums of squares per row and 128-column group: 1, 2 (passes with slim launches) or 4 (narrow launches of a small model)
+    int slim;      // the pass may use k_gemm_slim
     // SWIGLU: activation fragments over F channels
     uint4 *ahi, *alo; int F;
     // LMHEAD: logits, per-group row statistics
@@ -831,6 +842,14 @@ __device__ __forceinline__ void epi_resid(const GemmArgs &a, float *tile, float 
             const int row = tidx & 31, blk = tidx >> 5;
             stf<COH>(a.ssq_out + (size_t)(t * 32 + row) * (N / 32) + cg * 4 + blk,
                      scratch[(2 * blk) * 32 + row] + scratch[(2 * blk + 1) * 32 + row]);
+        }
+    } else if (a.ssq_sub == 2) {   // waves 4b .. 4b + 3 make 64-column block b
+        if (tidx < 64) {
+            const int row = tidx & 31, blk = tidx >> 5;
+            float s2 = 0.f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) s2 += scratch[(4 * blk + w) * 32 + row];
+            stf<COH>(a.ssq_out + (size_t)(t * 32 + row) * (N / 64) + cg * 2 + blk, s2);
         }
     } else if (tidx < 32) {
         float s2 = 0.f;
@@ -1142,7 +1161,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &a, GemmSmem &sm, int 
     // requested first and turned into factors once the first k-step has arrived, instead of as a dependent round
     // trip inside the epilogue.  Thread (row, j) = (tidx >> 4, tidx & 15) holds the groups j, j + 16, ...
     constexpr bool RSTD_EARLY = EPI != EPI_RESID;
-    constexpr int RSQ = 4;                 // groups per thread: ncg_in <= 64 (the host checks d_model <= 8192)
+    constexpr int RSQ = 4;                 // sums per thread: ncg_in <= 64 (the host sees to it)
     float sq[MT][RSQ];
     const int nsq = RSTD_EARLY ? (a.ncg_in + 15) >> 4 : 0;
     if (RSTD_EARLY) {
@@ -1411,6 +1430,241 @@ __global__ __launch_bounds__(512) void k_gemm_narrow(const GemmArgs a, int ngrp,
         if (tidx < 32) a.ssq_out[(size_t)(t * 32 + tidx) * (N / 32) + p] = sm.ssp[tidx] + sm.ssp[32 + tidx];
     }
     gemm_stamp(a, slin, 2);
+}
+
+// ------------------------------------------------------------------------------------------
+// Streaming GEMM in small workgroups, for passes of few row tiles: one row tile, C = 1 or 2 column blocks of 32, one of S
+// shares of K.  Same loop as gemm_block (eight waves take the k-steps w, w + 8, ... of the share; sums over the waves in the
+// order w = 0..7, over the shares s = 0..S-1), but what follows the stream is a quarter or half as long: the wave sum moves
+// 32 KB per block through LDS instead of 128 KB, a share's partial tile is 4 KB per block, kept in the register layout so
+// that it needs no LDS tile on its way, and the residual epilogue works on registers.
+// What bounds a launch: about 6 us of start, exchange and epilogue (4.7 without shares), and behind that HBM (6.5 TB/s) or
+// what one compute unit draws, 60 to 75 KB per microsecond of weights and activations together as long as the weights come
+// from HBM.  So: as many workgroups as compute units, each with few bytes; the host picks C and S (slim_us).
+// Back to back with rotating weights, one row tile, microseconds against k_gemm: O 4096 x 4096 13.2 -> 11.0, 4096 x 2560
+// 12.4 -> 9.4, 4096 x 2048 11.9 -> 8.6; down 9728 x 2560 18.1 -> 14.0, 4864 x 896 11.7 -> 7.4 (12288 x 4096: 22.3 and 21.6);
+// QKV 2048 x 5120 11.9 -> 9.3, gate/up 896 x 9728 10.4 -> 7.9.
+// grid: 1-D; with P = s * ngrp + p, the Z row tiles of (column group p, share s) get the ids 8 * ((P / 8) * Z + z) + P % 8
+// (one XCD).  Sums of squares are written per 32 C columns (GemmArgs::ssq_sub == 4 / C).
+// ------------------------------------------------------------------------------------------
+template <int C>
+struct GemmSlimSmem {
+    float4 red[8][C * 4][64];          // [wave][block, register quad][lane]
+    float tile[32 * (32 * C + 4)];     // QKV, SWIGLU: the finished tile, row-major
+    float rstd[32];
+    int last;
+};
+
+template <int C, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_slim(const GemmArgs a, int ngrp, int Z, int pairs) {
+    static_assert(EPI == EPI_RESID || C == 2, "QKV and gate/up need both blocks of a pair");
+    constexpr int TS = 32 * C + 4;     // row stride of the tile in LDS
+    constexpr int D = C == 1 ? 6 : 4, LPS = C + 2;   // k-steps in flight per wave, loads per k-step
+    __shared__ GemmSlimSmem<C> sm;
+    const int lin = blockIdx.x, q8 = lin >> 3;
+    const int S = a.S, z = q8 % Z, P = 8 * (q8 / Z) + (lin & 7);
+    if (P >= ngrp * S) return;
+    const int s = P / ngrp, p = P - s * ngrp;
+    const int tidx = opaque_tid();
+    const int w = __builtin_amdgcn_readfirstlane(tidx >> 6), lane = tidx & 63, half = lane >> 5, cl = lane & 31;
+    const int N = a.N, KS = a.KS;
+    const int slin = P * Z + z;        // stamps as in gemm_block
+    gemm_stamp(a, slin, 0);
+    const int per = (KS + S * 8 - 1) / (S * 8);
+    const int ks0 = s * 8 * per + w, ks1 = min(KS, (s + 1) * 8 * per);
+    const int n = ks0 < ks1 ? (ks1 - ks0 + 7) >> 3 : 0;   // this wave's k-steps: ks0, ks0 + 8, ...
+    const uint4 *wp[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) wp[j] = a.W + (size_t)slim_block(p, C, pairs, j) * KS * 64 + lane;
+    const uint4 *xh = a.Xhi + (size_t)z * KS * 64 + lane, *xl = a.Xlo + (size_t)z * KS * 64 + lane;
+    // RMSNorm factors of the input rows, requested first (see gemm_block): thread (row, j) = (tidx >> 4, tidx & 15)
+    constexpr bool RSTD = EPI != EPI_RESID;
+    constexpr int RSQ = 4;
+    float sq[RSQ];
+    const int nsq = RSTD ? (a.ncg_in + 15) >> 4 : 0;
+    if (RSTD) {
+        const float *sp = a.ssq_in + (size_t)(z * 32 + (tidx >> 4)) * a.ncg_in;
+#pragma unroll
+        for (int i = 0; i < RSQ; ++i)
+            if (i < nsq) load4_async(sq[i], sp + min((tidx & 15) + 16 * i, a.ncg_in - 1));
+    }
+    auto store_rstd = [&] {   // the sums of squares have arrived
+        float ssum = 0.f;
+#pragma unroll
+        for (int i = 0; i < RSQ; ++i)
+            if (i < nsq) { tie(sq[i]); if ((tidx & 15) + 16 * i < a.ncg_in) ssum += sq[i]; }
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) ssum += shx(ssum, off);
+        if ((tidx & 15) == 0) sm.rstd[tidx >> 4] = rsqrtf(ssum / (float)a.d_in + a.eps);
+    };
+    u32x4 wb[D][C], xhb[D], xlb[D];
+    auto request = [&](int sl, int ks) {   // sl is a constant once the callers' loops are unrolled
+#pragma unroll
+        for (int j = 0; j < C; ++j) load16_stream_async(wb[sl][j], wp[j] + (size_t)ks * 64);
+        load16_async(xhb[sl], xh + (size_t)ks * 64);
+        load16_async(xlb[sl], xl + (size_t)ks * 64);
+    };
+    f32x16 acc[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        if (d < n) request(d, ks0 + 8 * d);
+    for (int j0 = 0; j0 < n; j0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int j = j0 + d;
+            if (j < n) {
+                wait_steps<LPS, D - 1>(min(D - 1, n - 1 - j));   // loads requested after those of k-step j
+#pragma unroll
+                for (int q = 0; q < C; ++q) tie(wb[d][q]);
+                tie(xhb[d]); tie(xlb[d]);
+                if (RSTD && j == 0) store_rstd();
+#pragma unroll
+                for (int q = 0; q < C; ++q) acc[q] = mfma32(xhb[d], wb[d][q], acc[q]);
+#pragma unroll
+                for (int q = 0; q < C; ++q) acc[q] = mfma32(xlb[d], wb[d][q], acc[q]);
+                if (j + D < n) request(d, ks0 + 8 * (j + D));
+            }
+        }
+    }
+    if (RSTD && n == 0) { wait_loads<0>(); store_rstd(); }   // a wave without k-steps still owes its rows' factors
+    gemm_stamp(a, slin, 1);
+    // Wave w < 4 C finishes register quad w & 3 of block w >> 2: column cl of the block, rows 8 quad + 4 half .. + 3
+    const bool mine = w < 4 * C;
+    const int blk = slim_block(p, C, pairs, min(w >> 2, C - 1)), quad = w & 3, row0 = 8 * quad + 4 * half;
+    float *hp = a.h + (size_t)(z * 32 + row0) * N + blk * 32 + cl;   // RESID
+    float hv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (EPI == EPI_RESID && mine)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) hv[e] = hp[(size_t)e * N];
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sm.red[w][j * 4 + q][lane] = make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
+    barrier_keep_loads();
+    float y[4] = {0.f, 0.f, 0.f, 0.f};
+    if (mine) {
+        float4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = sm.red[u][w][lane];
+        y[0] = v[0].x; y[1] = v[0].y; y[2] = v[0].z; y[3] = v[0].w;
+#pragma unroll
+        for (int u = 1; u < 8; ++u) { y[0] += v[u].x; y[1] += v[u].y; y[2] += v[u].z; y[3] += v[u].w; }
+    }
+    if (S > 1) {
+        float *pt = a.part + (size_t)(p * Z + z) * S * (1024 * C) + (w * 64 + lane) * 4;   // [share][wave][lane][4]
+        if (mine) store16_agent(pt + (size_t)s * (1024 * C), y[0], y[1], y[2], y[3]);
+        const bool last = arrive_last(a.counters + p * Z + z, S, &sm.last);
+        gemm_stamp(a, slin, 3);
+        if (!last) {   // (sm.red has been read: every wave has passed arrive_last's barriers)
+            if (EPI == EPI_QKV) prefetch_kv(a.kv.k, a.kv.vt, a.kv.head_stride, a.Hkv, a.kv_fetch_bytes, sm.red);
+            else prefetch_next(a.nx, sm.red);
+            return;
+        }
+        if (mine) {
+            u32x4 v[8];   // at most eight shares, all requested together
+#pragma unroll
+            for (int u = 0; u < 8; ++u) load16_agent_async(v[u], pt + (size_t)min(u, S - 1) * (1024 * C));
+            wait_loads<0>();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                tie(v[u]);
+                if (u < S)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] += __uint_as_float(v[u][e]);
+            }
+        }
+    }
+    if (EPI == EPI_RESID) {
+        if (C == 1 && !mine) return;   // (C == 2: every wave has a quad)
+        // h += y; new fragment planes of h (two bytes per lane: eight lanes make an octet); sums of squares of the block
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float v = hv[e] + y[e];
+            hp[(size_t)e * N] = v;
+            const uint32_t hi = f2bf(v), lo = f2bf(v - bf2f(hi));
+            const size_t at = ((size_t)z * (N / 16) * 64 + frag_vec(row0 + e, blk * 4 + (cl >> 3))) * 8 + (cl & 7);
+            ((uint16_t *)a.xhi_out)[at] = (uint16_t)hi;
+            ((uint16_t *)a.xlo_out)[at] = (uint16_t)lo;
+            float ss = v * v;
+            ss += dppf<0xB1>(ss); ss += dppf<0x4E>(ss); ss += dppf<0x141>(ss); ss += dppf<0x140>(ss);
+            ss += shx(ss, 16);
+            if (cl == 0) {
+                if (C == 1) a.ssq_out[(size_t)(z * 32 + row0 + e) * (N / 32) + p] = ss;
+                else sm.tile[(w >> 2) * 32 + row0 + e] = ss;
+            }
+        }
+        if (C == 2) {   // both blocks' sums in one
+            barrier_keep_loads();
+            if (tidx < 32) a.ssq_out[(size_t)(z * 32 + tidx) * (N / 64) + p] = sm.tile[tidx] + sm.tile[32 + tidx];
+        }
+    } else {
+        if (mine)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sm.tile[(row0 + e) * TS + (w >> 2) * 32 + cl] = y[e];
+        __syncthreads();
+        if (tidx >= (EPI == EPI_QKV ? 256 : 128)) return;
+        const int row = tidx & 31, oct = tidx >> 5;
+        const float sc = sm.rstd[row];
+        const float *x = sm.tile + row * TS + oct * 8;
+        float v[8];
+        uint4 hi, lo;
+        if (EPI == EPI_SWIGLU) {   // block 0: 32 gate channels, block 1: their up channels; the group's other 32 are its neighbour's
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float g = x[e] * sc, u = x[32 + e] * sc;
+                v[e] = g / (1.f + expf(-g)) * u;
+            }
+            pack8_split(v, hi, lo);
+            const size_t vec = (size_t)z * (a.F / 16) * 64 + frag_vec(row, p * 4 + oct);
+            a.ahi[vec] = hi;
+            a.alo[vec] = lo;
+        } else {
+            const int hd = a.hd, Hq = a.Hq, Hkv = a.Hkv, half_hd = hd >> 1, grow = z * 32 + row;
+            const int col0 = slim_block(p, C, pairs, oct >> 2) * 32 + (oct & 3) * 8;   // first of 8 columns, all in one head
+            const int kind = col0 < Hq * hd ? 0 : (col0 < (Hq + Hkv) * hd ? 1 : 2);
+            const int hc = col0 - (kind == 0 ? 0 : (kind == 1 ? Hq * hd : (Hq + Hkv) * hd));
+            const int head = hc / hd, i0 = hc % hd;
+            if (kind < 2) {
+                const int po = hd == 32 ? 16 : 32;   // the rotation partner's distance in the tile: half a head, or the other block of a 128-wide head
+                const float *xp = x + (i0 < half_hd ? po : -po);
+                const float2 *cs = a.cs + (size_t)grow * half_hd + (i0 < half_hd ? i0 : i0 - half_hd);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float2 c = cs[e];
+                    const float xe = x[e] * sc, xq = xp[e] * sc;
+                    v[e] = (i0 < half_hd) ? xe * c.x - xq * c.y : xe * c.x + xq * c.y;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = x[e] * sc;
+            }
+            if (kind == 0) {
+                pack8_split(v, hi, lo);
+                const int qr = a.rm.qrow[grow];
+                if (qr >= 0) {
+                    const size_t vec = ((size_t)((qr >> 5) * Hq + head) * (hd / 16)) * 64 + frag_vec(qr & 31, i0 >> 3);
+                    a.qhi[vec] = hi;
+                    a.qlo[vec] = lo;
+                }
+            } else {
+                const int slot = a.rm.slot[grow];
+                if (slot >= 0) {
+                    const size_t base = (size_t)a.rm.seq[grow] * a.kv.seq_stride + (size_t)head * a.kv.head_stride;
+                    if (kind == 1) *(uint4 *)(a.kv.k + base + k_cache_off(slot, i0 >> 3, hd)) = pack8(v);
+                    else
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) a.kv.vt[base + v_cache_off(slot, i0 + e, hd)] = (uint16_t)f2bf(v[e]);
+                }
+            }
+        }
+    }
+    gemm_stamp(a, slin, S > 1 ? 4 : 2);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -1,0 +1,48 @@
+"""GPU parity of the small-workgroup streaming GEMMs (one or two 32-column blocks per workgroup, K in up to eight shares),
+which passes of one to four row tiles take by an estimate, against the wide streaming kernels: head dims 32, 64 and 128 (the
+blocks of a rotation pair are neighbours or two apart), contractions that leave waves without k-steps, ragged last tiles.
+test_host_routes.py checks that these shapes take them."""
+import numpy as np
+import pytest
+
+import deer_inputs as di
+from gpu_common import gpu_available
+from test_gpu_block_forms import _compare, _engine
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+SHAPES = {   # d, q heads, kv heads, head dim, d_ff
+    "hd128": (1152, 9, 3, 128, 1216),    # 72, 72 and 76 k-steps
+    "hd64": (2048, 16, 4, 64, 5632),     # 128, 64 and 352
+    "hd32": (1280, 20, 4, 32, 1344),     # 80, 40 and 84
+    "small": (384, 6, 3, 64, 2112),      # 24 and 132: one block per workgroup, beside the narrow QKV and O launches
+}
+BATCHES = [([70], 32), ([33], 5), ([40, 65, 8], 20), ([64, 31, 100], 31), ([50, 9, 128, 77], 32)]   # prefixes, k: 1, 1, 2, 3, 4 row tiles
+
+
+@pytest.mark.parametrize("name", SHAPES)
+def test_slim_launches_agree_with_the_wide_ones(name):
+    import torch
+    d, hq, hkv, hd, ff = SHAPES[name]
+    t = di.ModelShape(2, d, hq, hkv, hd, ff, 1152, rope_base=1e4)
+    eng = _engine(t, di.ModelShape(1, 384, 6, 3, 64, 2112, 1152, rope_base=1e4), 4, 256, torch)
+    for x in eng._kv:   # stand-in keys and values everywhere: N(0, 1)
+        v = x.view(torch.bfloat16)
+        v.copy_(torch.randn(v.shape, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda", dtype=torch.bfloat16))
+    for lens, k in BATCHES:
+        blocks = torch.from_numpy(np.random.default_rng(k).integers(0, t.vocab, (2, len(lens), k)).astype(np.int32)).cuda()
+        out = {}
+        for mode in (0, 128):   # wide kernels, then the estimate's choice
+            eng.debug_gemm_tiled(mode)
+            eng.set_prefilled(lens, [5] * len(lens))
+            res = []
+            for block in blocks:   # the second iteration also takes in what the first committed
+                eng.draft_block(k, 0.0, 0)
+                zd = eng.debug_get_logits(1, k)
+                eng.verify_block(k, 0.0, block)
+                res += [zd, eng.debug_get_logits(0, k)]
+                eng.debug_force_commit([[1, 2, 3]] * len(lens))
+            out[mode] = ([x.view(torch.bfloat16).clone() for x in eng._kv], res)
+        print(name, lens, k, flush=True)
+        _compare(out[0], out[128])
+    eng.close()

@@ -123,3 +123,32 @@ e = engine(t, di.CONFIGS["tiny"]["drafter"], 1, 512)
 print([gemms(e, lambda: e.prefill([[3] * (32 * n + 1)])) for n in (6, 7)])
 """)
     assert "k_gemm_moe" in got[0] and "k_gemm_moe" not in got[1] and "moe_block" in got[0] & got[1], got
+
+
+def test_shapes_of_the_slim_gemm_tests_take_it(tmp_path):
+    """The shapes and batches of test_gpu_slim_gemm.py: every form of the small-workgroup kernel runs in one of them, and none
+    where it is switched off."""
+    got = routes(tmp_path, """
+def slim(e, call):
+    e.stub.stub_reset()
+    assert call() == 0
+    return {re.search("k_gemm_slimILi(\\d)ELi(\\d)E", n).groups() for n, _ in e.launches() if "k_gemm_slim" in n}
+out = []
+for d, hq, hkv, hd, ff in ((1152, 9, 3, 128, 1216), (2048, 16, 4, 64, 5632), (1280, 20, 4, 32, 1344), (384, 6, 3, 64, 2112)):
+    t = di.ModelShape(2, d, hq, hkv, hd, ff, 1152, rope_base=1e4)
+    e = engine(t, di.ModelShape(1, 384, 6, 3, 64, 2112, 1152, rope_base=1e4), 4, 256)
+    for lens, k in (([70], 32), ([33], 5), ([40, 65, 8], 20), ([64, 31, 100], 31), ([50, 9, 128, 77], 32)):
+        for mode in (0, 128):
+            e.lib.deer_debug_gemm_tiled(e.ctx, mode)
+            e.set_prefilled(lens, [5] * len(lens))
+            out.append((hd if d > 384 else 0, len(lens), mode, slim(e, lambda: e.draft_block(k)), slim(e, lambda: e.verify_block(k))))
+print(out)
+""")
+    assert all(not d and not v for _, _, mode, d, v in got if mode == 0)
+    on = [(hd, n, v) for hd, n, mode, _, v in got if mode]   # the target's passes
+    for hd in (128, 64, 32):
+        forms = set().union(*(f for h, _, f in on if h == hd))
+        assert {("2", str(QKV)), ("2", str(RESID))} <= forms, (hd, forms)
+    assert ("1", str(RESID)) in set().union(*(f for h, _, f in on if h == 0))
+    assert ("2", str(SWIGLU)) in set().union(*(f for _, _, f in on)) and all(d for _, _, mode, d, _ in got if mode)
+    assert all(any(f for h, n, f in on if n == m) for m in (1, 3, 4)), on
