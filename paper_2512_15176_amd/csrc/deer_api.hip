@@ -597,8 +597,14 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
     // compute unit, as long as a wave then has at most ATT_HEAD_MAX_TILES key tiles of its range to go through
     int NS_head = 0;
     if (n_attn * mc.n_q_heads <= ns_target) {
-        int ns = ns_target / (n_attn * mc.n_q_heads);
-        ns = std::max(1, std::min({ns, MAX_NS, std::max(1, std::max(64, c->max_tiles) / n_attn), (nkt + 7) / 8}));
+        const int ns_max = std::max(1, std::min({ns_target / (n_attn * mc.n_q_heads), ATT_HEAD_MAX_NS, std::max(1, std::max(64, c->max_tiles) / n_attn), (nkt + 7) / 8}));
+        // a range's key tiles (0.28 us each with head_dim 128) against the merge, which one compute unit per head runs behind the
+        // last of them, about 0.2 us per range (14 heads of 64, 129 key tiles: 17 ranges, one tile per wave, 13.0 us from the
+        // launch's first workgroup to its last store, 10 ranges 9.9)
+        auto cost = [&](int n) { return (nkt + n - 1) / n * hd * 0.0022 + (n > 1 ? 1.0 + 0.2 * n : 0.0); };
+        int ns = 1;
+        for (int n = 2; n <= ns_max; ++n)
+            if (cost(n) < cost(ns)) ns = n;
         const int per = (nkt + ns - 1) / ns;
         if ((per + 7) / 8 <= ATT_HEAD_MAX_TILES) NS_head = ns;
     }

@@ -101,6 +101,9 @@ __device__ __forceinline__ void store16_agent(void *p, float a, float b, float c
     u32x4 v = {__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)};
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 2" ::"v"(p), "v"(v) : "memory");
 }
+__device__ __forceinline__ void store16_agent(uint4 *p, uint4 x) {
+    store16_agent(p, __uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w));
+}
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 template <int PER, int MAX>
@@ -1440,7 +1443,7 @@ __global__ __launch_bounds__(512) void k_gemm_narrow(const GemmArgs a, int ngrp,
 // that it needs no LDS tile on its way, and the residual epilogue works on registers.
 // What bounds a launch: about 6 us of start, exchange and epilogue (4.7 without shares), and behind that HBM (6.5 TB/s) or
 // what one compute unit draws, 60 to 75 KB per microsecond of weights and activations together as long as the weights come
-// from HBM.  So: as many workgroups as compute units, each with few bytes; the host picks C and S (slim_us).
+// from HBM.  So: as many workgroups as compute units, each with few bytes; the host picks C and S (plan_slim).
 // Back to back with rotating weights, one row tile, microseconds against k_gemm: O 4096 x 4096 13.2 -> 11.0, 4096 x 2560
 // 12.4 -> 9.4, 4096 x 2048 11.9 -> 8.6; down 9728 x 2560 18.1 -> 14.0, 4864 x 896 11.7 -> 7.4 (12288 x 4096: 22.3 and 21.6);
 // QKV 2048 x 5120 11.9 -> 9.3, gate/up 896 x 9728 10.4 -> 7.9.
@@ -2212,8 +2215,8 @@ __device__ __forceinline__ void attn_store_slice(const float (&o)[8], float inv,
             uint4 hi, lo;
             pack8_split(v8, hi, lo);
             const size_t vec = (size_t)(grow >> 5) * KS * 64 + frag_vec(grow & 31, head * (HD / 8) + tt * 4 + q);
-            st16<true>(xhi + vec, hi);
-            st16<true>(xlo + vec, lo);
+            store16_agent(xhi + vec, hi);
+            store16_agent(xlo + vec, lo);
         }
     }
 }
@@ -2272,16 +2275,21 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
 
 // Merge of the NS key-range partials of one (tile, head) written by attn_head_item: wave item (tt, hh) owns registers
 // 8*hh .. 8*hh+7 of O^T tile tt, which a partial holds as two register quads of 1 KB per wave.  All (M, L) pairs and the
-// outputs of the first 8 ranges (16 with head_dim <= 64) are requested together: one round trip for that many ranges;
-// ranges are combined in order s = 0..NS-1.  NS <= 32.
-template <int HD>
+// outputs of the first 8 ranges (16 with head_dim <= 64) are requested together; ranges are combined in order s = 0..NS-1.  NS <= MAX.  The merge is the tail of the launch and runs on one compute unit per
+// head, so nothing is loaded or computed for ranges that do not exist (loads and factors for 32 ranges, whatever their
+// number, made it 5.5 us behind the last arrival of 8), and up to 8 ranges have a short code of their own: its instructions
+// come from the L2, as nothing on the compute unit has run them in this launch (3.9 us with the code for 32 ranges, 3.0 with
+// this one; 8B heads, 129 key tiles: 17.2 -> 13.8 us from the launch's first workgroup to its last store).
+constexpr int ATT_HEAD_MAX_NS = 16;   // key ranges per head
+template <int HD, int MAX>
 __device__ __forceinline__ void attn_head_merge(const float *part, const int *row_grow, int NS, int Hq, float scale_log2e, uint4 *xhi, uint4 *xlo,
                                                 int head, int t, int tt, int hh, int lane) {
     constexpr int PF = AttnPartial<HD>::FLOATS;
     const int qrow = lane & 31;
     const float *p0 = part + (size_t)(t * Hq + head) * NS * PF;
     const float *po = p0 + ((tt * 2 + hh) * 2 * 64 + lane) * 4;
-    constexpr int CH = HD <= 64 ? 16 : 8;   // ranges whose outputs are requested together (registers: 8 per range)
+    const int grow = row_grow[t * 32 + qrow];
+    constexpr int CH = MAX > 8 && HD <= 64 ? 16 : 8;   // ranges whose outputs are requested together (registers: 8 per range)
     u32x4 v[CH][2];
     auto request = [&](int s0) {
 #pragma unroll
@@ -2291,26 +2299,29 @@ __device__ __forceinline__ void attn_head_merge(const float *part, const int *ro
                 load16_agent_async(v[u][1], po + (size_t)(s0 + u) * PF + 256);
             }
     };
-    float f[32];
+    float f[MAX];
     float M = -INFINITY, L = 0.f;
     {
-        float2 ml[32];
+        float2 ml[MAX];
 #pragma unroll
-        for (int s = 0; s < 32; ++s) ml[s] = ld_agent2(p0 + (size_t)min(s, NS - 1) * PF + 32 * HD + 2 * qrow);
+        for (int s = 0; s < MAX; ++s)
+            if (s < NS) ml[s] = ld_agent2(p0 + (size_t)s * PF + 32 * HD + 2 * qrow);
         request(0);
 #pragma unroll
-        for (int s = 0; s < 32; ++s) if (s < NS) M = fmaxf(M, ml[s].x);
+        for (int s = 0; s < MAX; ++s)
+            if (s < NS) M = fmaxf(M, ml[s].x);
 #pragma unroll
-        for (int s = 0; s < 32; ++s) {
-            f[s] = (s >= NS || ml[s].x == -INFINITY) ? 0.f : exp2f((ml[s].x - M) * scale_log2e);
-            L += f[s] * ml[s].y;
-        }
+        for (int s = 0; s < MAX; ++s)
+            if (s < NS) {
+                f[s] = ml[s].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml[s].x - M) * scale_log2e);
+                L += f[s] * ml[s].y;
+            }
     }
     float o[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = 0.f;
 #pragma unroll
-    for (int s0 = 0; s0 < 32; s0 += CH) {
+    for (int s0 = 0; s0 < MAX; s0 += CH) {
         if (s0 < NS) {
             if (s0 > 0) request(s0);
             wait_loads<0>();
@@ -2326,7 +2337,7 @@ __device__ __forceinline__ void attn_head_merge(const float *part, const int *ro
                 }
         }
     }
-    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, row_grow[t * 32 + qrow], tt, hh, lane, xhi, xlo);
+    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, grow, tt, hh, lane, xhi, xlo);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2401,7 +2412,7 @@ __device__ __forceinline__ void attn_head_item(const uint4 *Qhi, const uint4 *Ql
         for (int f = 0; f < FPT; ++f) load16_async(rf[f], frag_src(kt, f));
     };
 
-    // Q first (every later wait covers it), then this wave's first two key tiles
+    // Q first (every later wait covers it), then this wave's first two key tiles, the second behind the barrier
     {
         const size_t qb = ((size_t)(t * Hq + head) * KSQ) * 64 + lane;
         for (int f = w; f < 2 * KSQ; f += 8) {
@@ -2410,10 +2421,12 @@ __device__ __forceinline__ void attn_head_item(const uint4 *Qhi, const uint4 *Ql
                                              (void __attribute__((address_space(3))) *)(as.q + f * 64), 16, 0, 0);
         }
     }
+    // (the second tile behind the barrier: a compute unit's loads return in the order of their requests, and the waves' second
+    // tiles, 128 KB, would stand in front of the last waves' shares of Q)
     if (n > 0) issue_lds(first);
-    if (n > 1) issue_reg(first + 8);
-    if (n > 1) wait_loads<2 * FPT>(); else if (n == 1) wait_loads<FPT>(); else wait_loads<0>();
+    if (n > 0) wait_loads<FPT>(); else wait_loads<0>();
     barrier_keep_loads();   // Q of every wave's share is in LDS
+    if (n > 1) issue_reg(first + 8);
 
     f32x16 oacc[HT];
 #pragma unroll
@@ -2554,7 +2567,9 @@ __device__ __forceinline__ void attn_head_item(const uint4 *Qhi, const uint4 *Ql
     if (NS == 1) return;
     // the key range that arrives last at the head's counter merges all of them
     if (!arrive_last(counters + t * Hq + head, NS, &as.last)) { prefetch_next(nx, as.slot); return; }
-    if (w < 2 * HT) attn_head_merge<HD>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
+    if (w >= 2 * HT) return;
+    if (NS <= 8) attn_head_merge<HD, 8>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
+    else attn_head_merge<HD, ATT_HEAD_MAX_NS>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
 }
 
 // grid: x = kv_head + Hkv * (head in group + G * split), y = pass tile; 512 threads
