@@ -333,23 +333,23 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
             const bool live = (int)lm < a.n_lm && (int)lm % opaque_s(a.k) >= a.k_lo;
             float m = -INFINITY, gm = -INFINITY, se = 0.f;
             int idx = 0x7fffffff, gidx = 0x7fffffff;
-            float z[16];
+            const float4 *tp = (const float4 *)(tile + lr * BT_STRIDE + sub * 16);   // (short loops over the tile: see epi_lmhead)
             if (live) {
+                float4 *q = a.logits ? (float4 *)(a.logits + lm * V + (size_t)cg * CG + sub * 16) : nullptr;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) z[e] = tile[lr * BT_STRIDE + sub * 16 + e] * sc;
-                if (a.logits) {
-                    float *q = a.logits + lm * V + (size_t)cg * CG + sub * 16;
-#pragma unroll
-                    for (int e = 0; e < 16; e += 4) *(float4 *)(q + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
+                for (int e = 0; e < 4; ++e) {
+                    const float4 z = make_float4(tp[e].x * sc, tp[e].y * sc, tp[e].z * sc, tp[e].w * sc);
+                    if (q) q[e] = z;
+                    const int v = cg * CG + sub * 16 + 4 * e;
+                    argmax_merge(m, idx, z.x, v); argmax_merge(m, idx, z.y, v + 1); argmax_merge(m, idx, z.z, v + 2); argmax_merge(m, idx, z.w, v + 3);
                 }
-                const bool draw = T > 0.f && a.draw;
-                uint64_t key = 0;
-                if (draw) key = row_key(a.seed, TAG_DRAFT, (uint64_t)a.rm.seq[lm], (uint64_t)a.rm.pos[lm]);
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int v = cg * CG + sub * 16 + e;
-                    argmax_merge(m, idx, z[e], v);
-                    if (draw) argmax_merge(gm, gidx, z[e] * invT + gumbel(key, (uint64_t)v), v);
+                if (T > 0.f && a.draw) {
+                    const uint64_t key = row_key(a.seed, TAG_DRAFT, (uint64_t)a.rm.seq[lm], (uint64_t)a.rm.pos[lm]);
+#pragma unroll 2
+                    for (int e = 0; e < 16; ++e) {
+                        const int v = cg * CG + sub * 16 + e;
+                        argmax_merge(gm, gidx, ((const float *)tp)[e] * sc * invT + gumbel(key, (uint64_t)v), v);
+                    }
                 }
             }
 #pragma unroll
@@ -360,8 +360,8 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
                 argmax_merge(gm, gidx, g2, gi2);
             }
             if (live && T > 0.f) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) se += expf((z[e] - m) * invT);
+#pragma unroll 4
+                for (int e = 0; e < 16; ++e) se += expf((((const float *)tp)[e] * sc - m) * invT);
             }
 #pragma unroll
             for (int off = 1; off < 8; off <<= 1) se += shx(se, off);
