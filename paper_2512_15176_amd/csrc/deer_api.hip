@@ -403,9 +403,11 @@ SlimPlan plan_slim(int epi, int N, int KS, int ntiles, int hd, int ssq_sub, size
     }
     return best;
 }
+// shares that meet through memory (megabytes): cheap while the L2s hold them
+double meet_us(double mb) { return mb <= 20.0 ? 0.2 * mb : 4.0 + 0.55 * (mb - 20.0); }
 // Blocked kernel: NB = 4 (128 x 256 per workgroup: 0.3 to 0.4 us per k-step, the more the busier the chip) or NB = 2
-// (128 x 128: 0.16 us with 64 workgroups, 0.24 with one per compute unit, 0.225 with more).
-struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; };
+// (128 x 128: 0.16 us with 64 workgroups, 0.24 with one per compute unit, 0.225 to 0.235 with more).
+struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; int full = 0, G = 0, piece = 0; };   // full: blocks run whole, 0: all (see BlockDeal)
 BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size_t part_floats) {
     BlockPlan best;
     const int nrb = (ntiles + BK_RT - 1) / BK_RT;
@@ -426,10 +428,22 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
             const double q = (double)nrb * ncb * S / 256.0;
             const double units = q <= 1.0 ? 1.0 : q > 2.0 ? 0.5 * (q + std::ceil(q)) : NB == 4 ? 2.0 : 1.45 + 0.5 * (q - 1.0);
             // fewer workgroups get more of the L2s each
-            const double step = NB == 4 ? (q <= 1.0 ? 0.30 + 0.09 * q : q <= 2.0 ? 0.36 : 0.40) : (q <= 1.0 ? 0.15 + 0.09 * q : 0.225);
-            const double mb = tile_bytes * 1e-6;   // shares that meet through memory: cheap while the L2s hold them
-            const double us = 10.0 + units * per * step + (S > 1 ? S + (mb <= 20.0 ? 0.2 * mb : 4.0 + 0.55 * (mb - 20.0)) : 0.0);
+            const double step = NB == 4 ? (q <= 1.0 ? 0.30 + 0.09 * q : q <= 2.0 ? 0.36 : 0.40) : (q <= 1.0 ? 0.15 + 0.09 * q : q <= 2.0 ? 0.225 : 0.235);
+            const double us = 10.0 + units * per * step + (S > 1 ? S + meet_us(tile_bytes * 1e-6) : 0.0);
             if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0 && KS >= BK_SHORT, us};   // (short contractions: the ring of 8 takes 2 us more)
+        }
+        // More blocks than compute units: an equal number of whole blocks for each, the rest in pieces of at least an eighth
+        // of a block.  A compute unit's rate hardly depends on how many workgroups share it, so that a launch takes the k-steps
+        // of the fullest one.  Microseconds, last blocks whole / in pieces, 105 row tiles: 4B O 158 / 132, down 330 / 288 (both
+        // against the best uniform shares), gate/up 557 / 536, QKV (half of the last round is full) 198 / 206; 8B gate/up at 9
+        // tiles 170 / 142; LM head of d = 2048 at 4 tiles 182 / 190 (1187 blocks, 163 in pieces).
+        const int blocks = nrb * ncb, full = blocks / 256 * 256, rest = blocks - full;
+        if (full > 0 && rest > 0 && KS >= 32) {
+            int G = std::min(256, rest * 8);
+            const int piece = std::max(16, (rest * KS + G - 1) / G);
+            G = ((rest * KS + piece - 1) / piece + 7) / 8 * 8;
+            const double us = 10.0 + ((double)full / 256.0 * KS + piece) * (NB == 4 ? 0.40 : 0.235) + meet_us((G + rest) * 128.0 * 64 * NB * 4e-6);
+            if (2.0 * G * 128 * 64 * NB <= (double)part_floats && us < best.us) best = BlockPlan{NB, 1, false, us, full, G, piece};
         }
     }
     return best;
@@ -474,13 +488,15 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
         if (c->block_gemm > 0 && ntiles > 1 && (forced || bp.us < 0.97 * old_us)) {
             a.S = bp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
             const int nrb = (ntiles + BK_RT - 1) / BK_RT, ncb = (a.N + 64 * bp.NB - 1) / (64 * bp.NB), band = block_band(nrb);
-            const dim3 g((unsigned)block_grid(ncb * a.S, nrb));
+            const int blocks = nrb * ncb * a.S;
+            const BlockDeal deal{blocks, bp.full ? bp.full : blocks, bp.G, bp.piece, (a.KS + a.S - 1) / a.S};
+            const dim3 g((unsigned)block_grid(deal));
             ProfScope ps(c, 0, (double)a.N * K * 2.0);
             const bool sh = a.KS < BK_SHORT;
-            if (bp.NB == 4) hipLaunchKernelGGL((k_gemm_block<4, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
-            else if (bp.deep) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
-            else if (sh) hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, true>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
-            else hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band);
+            if (bp.NB == 4) hipLaunchKernelGGL((k_gemm_block<4, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal);
+            else if (bp.deep) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal);
+            else if (sh) hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, true>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal);
+            else hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal);
             LAUNCHCHK(c, "k_gemm_block");
             return DEER_OK;
         }

@@ -373,121 +373,161 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
 // Workgroup id -> (column block and K share p, row block).  Ids 8 apart share an XCD; every XCD gets one contiguous run
 // of the order (band of up to 8 row blocks, p, row block in the band), so that the workgroups it runs together read few
 // weight columns and few rows.
-struct BlockItem { int p, rb; bool valid; };
-__device__ __forceinline__ BlockItem block_item(int lin, int P, int nrb, int band) {
-    const int nb = (nrb + band - 1) / opaque_s(band), total = nb * band * P, per = (total + 7) >> 3;
-    const int i = (lin & 7) * per + (lin >> 3);
-    const int bd = i / opaque_s(band * P), r = i - bd * band * P;
+struct BlockItem { int p, rb; };
+__device__ __forceinline__ BlockItem block_at(int i, int P, int nrb, int band) {
+    int b0 = 0, rows = nrb;   // one band: no division
+    if (band < nrb) {
+        const int bd = min(i / opaque_s(band * P), (nrb - 1) / opaque_s(band));
+        b0 = bd * band;
+        rows = min(band, nrb - b0);   // the last band may be lower
+        i -= b0 * P;
+    }
     BlockItem it;
-    it.p = r / opaque_s(band);
-    it.rb = bd * band + (r - it.p * band);
-    it.valid = (lin >> 3) < per && i < total && it.rb < nrb;
+    it.p = i / opaque_s(rows);
+    it.rb = b0 + (i - it.p * rows);
     return it;
 }
 inline int block_band(int nrb) { const int bands = (nrb + 7) / 8; return (nrb + bands - 1) / bands; }
-inline int block_grid(int P, int nrb) {
-    const int band = block_band(nrb), nb = (nrb + band - 1) / band;
-    return 8 * ((nb * band * P + 7) / 8);
-}
+
+// How the blocks of a launch are dealt to workgroups.  full == blocks: one workgroup per block (and K share, GemmArgs::S).
+// full < blocks (S == 1): the last `blocks - full` blocks of the order, more than a compute unit's equal share of blocks, lie
+// end to end as one row of k-steps that G workgroups cut into pieces of `piece` k-steps; a piece is part of one block or of two
+// neighbours.  Those workgroups have the lowest ids: they start first, beside the whole blocks, and the pieces' sums meet
+// while those still run.
+struct BlockDeal { int blocks, full, G, piece, per; };   // per: k-steps of a uniform share
+inline int block_grid(const BlockDeal &d) { return d.G + 8 * ((d.full + 7) / 8); }
 
 // ncb: column blocks of 64 NB columns; nrt: row tiles; SHORT: a contraction of less than BK_SHORT k-steps
 template <int NB, int NST, int EPI, bool SHORT>
-__global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 1) void k_gemm_block(const GemmArgs a, int ncb, int nrt, int band) {
+__global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 1) void k_gemm_block(const GemmArgs a, int ncb, int nrt, int band, const BlockDeal deal) {
     constexpr int LPW = BlockSmem<NB, NST>::FRAGS / 4;
+    constexpr size_t PART = 4 * (2 * NB * 4 * 256);   // floats of a block's partial sums: [wave][(mt, nb, quad)][lane][4]
     __shared__ __attribute__((aligned(16))) BlockSmem<NB, NST> sm;
-    const int tidx = opaque_tid();
-    const int w = __builtin_amdgcn_readfirstlane(tidx >> 6), lane = tidx & 63;
+    const int w = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
     const int wr = w >> 1, wc = w & 1;
-    const int nrb = (nrt + BK_RT - 1) / BK_RT;
-    const BlockItem bi = block_item(blockIdx.x, ncb * a.S, nrb, band);
-    if (!bi.valid) return;
-    const int s = bi.p / opaque_s(ncb), cb = bi.p - s * ncb, rb = bi.rb;
-    const int KS = a.KS, per = (KS + a.S - 1) / opaque_s(a.S);
-    const int ks0 = s * per, n = min(KS, ks0 + per) - ks0;   // the host keeps every share non-empty
-    const int nmt = max(0, min(2, nrt - (rb * BK_RT + wr * 2)));
-    const char *base[LPW];
-    uint32_t vo[LPW];
-#pragma unroll
-    for (int i = 0; i < LPW; ++i) {   // fragments past the matrix repeat the last ones (their products are not used)
-        const int f = w * LPW + i;
-        const uint4 *p;
-        if (f < 2 * NB) p = a.W + ((size_t)min(cb * 2 * NB + f, a.N / 32 - 1) * KS + ks0) * 64;
-        else {
-            const int x = f - 2 * NB, ct = min(rb * BK_RT + (x & (BK_RT - 1)), nrt - 1);
-            p = (x < BK_RT ? a.Xhi : a.Xlo) + ((size_t)ct * KS + ks0) * 64;
-        }
-        base[i] = (const char *)p;
-        vo[i] = lane * 16;
-    }
-    f32x16 acc[2][NB];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
-    block_loop<NB, NST, 2, LPW, SHORT>(acc, base, vo, sm, n, block_fold(KS), w, lane);
-
-    if (a.S > 1) {
-        // shares meet through memory: [share][row block][column block][wave][(mt, nb, quad)][lane] x 16 bytes
-        const size_t sstride = (size_t)nrb * ncb * 4 * (2 * NB * 4 * 256);
-        float *p0 = a.part + (((size_t)rb * ncb + cb) * 4 + w) * (2 * NB * 4 * 256) + lane * 4;
-        float *pw = p0 + s * sstride;
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-            if (mt < nmt)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        store16_agent(pw + ((mt * NB + nb) * 4 + q) * 256, acc[mt][nb][4 * q], acc[mt][nb][4 * q + 1], acc[mt][nb][4 * q + 2], acc[mt][nb][4 * q + 3]);
-        if (!arrive_last(a.counters + (size_t)rb * ncb + cb, a.S, &sm.last)) return;
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-            if (mt < nmt)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const float *pr = p0 + (mt * NB + nb) * 4 * 256;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
-                    for (int u0 = 0; u0 < a.S; u0 += 4) {   // four shares' loads in flight, summed in order
-                        u32x4 v[4][4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) load16_agent_async(v[u][q], pr + min(u0 + u, a.S - 1) * sstride + q * 256);
-                        wait_loads<0>();
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                tie(v[u][q]);
-                                if (u0 + u < a.S)
-#pragma unroll
-                                    for (int e = 0; e < 4; ++e) acc[mt][nb][4 * q + e] += __uint_as_float(v[u][q][e]);
-                            }
-                    }
-                }
+    const int nrb = (nrt + BK_RT - 1) / BK_RT, KS = a.KS;
+    const int lin = blockIdx.x;
+    const bool pieces = lin < deal.G;
+    int at, end;                 // this workgroup's k-steps [at, end): of one block (share), or of the row of blocks cut into pieces
+    int cb, rb, s = 0, b = 0;    // column block, row block, uniform share; pieces: the block in the row
+    if (pieces) {
+        const int g = (lin & 7) * (deal.G >> 3) + (lin >> 3);
+        at = g * deal.piece; end = min((deal.blocks - deal.full) * KS, at + deal.piece);
+        b = at / opaque_s(KS);
     } else {
-        __syncthreads();   // every wave has read the ring: the epilogue tiles reuse it
+        const int l = lin - deal.G, per8 = (deal.full + 7) >> 3, i = (l & 7) * per8 + (l >> 3);
+        if ((l >> 3) >= per8 || i >= deal.full) return;
+        const BlockItem bi = block_at(i, ncb * a.S, nrb, band);   // the order runs over (share, column block) pairs
+        if (a.S > 1) s = bi.p / opaque_s(ncb);
+        cb = bi.p - s * ncb; rb = bi.rb;
+        at = s * deal.per; end = min(KS, at + deal.per);          // the host keeps every share non-empty
     }
-    if constexpr (NB == 4) {
-        const int cg = cb * 2 + wc;
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const int ct = rb * BK_RT + wr * 2 + mt;
-            if (mt >= nmt || cg * CG >= a.N) continue;
-            wave_park<NB>(acc[mt], sm.tile[w], 0, lane);
-            wave_lds_sync();
-            wave_epilogue<EPI>(a, sm.tile[w], cg, ct);
-            wave_lds_sync();
+#pragma unroll 1
+    for (bool first = true; at < end; first = false) {
+        // this workgroup's k-steps of the block, and where the block's shares lie
+        int ks0 = at, n = end - at, nsh = a.S, mine = s, g0 = 0, odd0 = 0;
+        if (pieces) {
+            const BlockItem bi = block_at(deal.full + b, ncb, nrb, band);
+            cb = bi.p; rb = bi.rb;
+            ks0 = at - b * KS; n = min(KS - ks0, end - at);
+            g0 = b * KS / opaque_s(deal.piece);                   // the first workgroup with a piece of this block
+            nsh = ((b + 1) * KS - 1) / opaque_s(deal.piece) - g0 + 1;
+            odd0 = g0 * deal.piece < b * KS ? 1 : 0;              // that workgroup began in the block before: its second piece
+            mine = at / opaque_s(deal.piece) - g0;
         }
-    } else {   // a column group is made by the two waves of a row pair: wave wc finishes row tile wc
+        // slot of share u: uniform (share, block), pieces (workgroup, first or second piece)
+        auto slot = [&](int u) -> size_t { return pieces ? (size_t)2 * (g0 + u) + (u == 0 ? odd0 : 0) : (size_t)u * nrb * ncb + (size_t)rb * ncb + cb; };
+        const int counter = pieces ? b : rb * ncb + cb;
+        at += n; ++b;
+        if (!first) __syncthreads();   // the epilogue's tiles have been read: the ring reuses them
+        const int nmt = max(0, min(2, nrt - (rb * BK_RT + wr * 2)));
+        const int ln = opaque_tid() & 63;   // (derived again behind the loop: registers)
+        const char *base[LPW];
+        uint32_t vo[LPW];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) wave_park<NB>(acc[mt], sm.tile[wr * 2 + mt], wc * 64, lane);
-        __syncthreads();
-        const int ct = rb * BK_RT + wr * 2 + wc;
-        if (wc < nmt) wave_epilogue<EPI>(a, sm.tile[wr * 2 + wc], cb, ct);
+        for (int i = 0; i < LPW; ++i) {   // fragments past the matrix repeat the last ones (their products are not used)
+            const int f = w * LPW + i;
+            const uint4 *p;
+            if (f < 2 * NB) p = a.W + ((size_t)min(cb * 2 * NB + f, a.N / 32 - 1) * KS + ks0) * 64;
+            else {
+                const int x = f - 2 * NB, ct = min(rb * BK_RT + (x & (BK_RT - 1)), nrt - 1);
+                p = (x < BK_RT ? a.Xhi : a.Xlo) + ((size_t)ct * KS + ks0) * 64;
+            }
+            base[i] = (const char *)p;
+            vo[i] = ln * 16;
+        }
+        f32x16 acc[2][NB];
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
+        block_loop<NB, NST, 2, LPW, SHORT>(acc, base, vo, sm, n, block_fold(KS), w, ln);
+
+        const int lane = opaque_tid() & 63;
+        if (nsh > 1) {
+            float *p0 = a.part + (size_t)w * (2 * NB * 4 * 256) + lane * 4;
+            float *pw = p0 + slot(mine) * PART;
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                if (mt < nmt)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            store16_agent(pw + ((mt * NB + nb) * 4 + q) * 256, acc[mt][nb][4 * q], acc[mt][nb][4 * q + 1], acc[mt][nb][4 * q + 2], acc[mt][nb][4 * q + 3]);
+            if (!arrive_last(a.counters + counter, nsh, &sm.last)) continue;
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+                if (mt < nmt)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const float *pr = p0 + (mt * NB + nb) * 4 * 256;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
+                        constexpr int U = NB == 4 ? 2 : 4;                // shares whose loads are in flight together, summed in order
+                        for (int u0 = 0; u0 < nsh; u0 += U) {
+                            u32x4 v[U][4];
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const float *pu = pr + slot(min(u0 + u, nsh - 1)) * PART;
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) load16_agent_async(v[u][q], pu + q * 256);
+                            }
+                            wait_loads<0>();
+#pragma unroll
+                            for (int u = 0; u < U; ++u)
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) {
+                                    tie(v[u][q]);
+                                    if (u0 + u < nsh)
+#pragma unroll
+                                        for (int e = 0; e < 4; ++e) acc[mt][nb][4 * q + e] += __uint_as_float(v[u][q][e]);
+                                }
+                        }
+                    }
+        } else {
+            __syncthreads();   // every wave has read the ring: the epilogue tiles reuse it
+        }
+        if constexpr (NB == 4) {
+            const int cg = cb * 2 + wc;
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+                const int ct = rb * BK_RT + wr * 2 + mt;
+                if (mt >= nmt || cg * CG >= a.N) continue;
+                wave_park<NB>(acc[mt], sm.tile[w], 0, lane);
+                wave_lds_sync();
+                wave_epilogue<EPI>(a, sm.tile[w], cg, ct);
+                wave_lds_sync();
+            }
+        } else {   // a column group is made by the two waves of a row pair: wave wc finishes row tile wc
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) wave_park<NB>(acc[mt], sm.tile[wr * 2 + mt], wc * 64, lane);
+            __syncthreads();
+            const int ct = rb * BK_RT + wr * 2 + wc;
+            if (wc < nmt) wave_epilogue<EPI>(a, sm.tile[wr * 2 + wc], cb, ct);
+        }
     }
 }
 

@@ -152,3 +152,36 @@ print(out)
     assert ("1", str(RESID)) in set().union(*(f for h, _, f in on if h == 0))
     assert ("2", str(SWIGLU)) in set().union(*(f for _, _, f in on)) and all(d for _, _, mode, d, _ in got if mode)
     assert all(any(f for h, n, f in on if n == m) for m in (1, 3, 4)), on
+
+
+def test_shapes_of_the_pieces_tests_run_in_pieces(tmp_path):
+    """The shape and prompts of test_gpu_block_pieces.py: launches of the blocked kernel whose grid is whole blocks for every
+    compute unit and pieces of the rest."""
+    got = routes(tmp_path, """
+t = di.ModelShape(2, 1152, 18, 2, 64, 8384, 16512, rope_base=1e4)
+def pieces(e, call):
+    e.stub.stub_reset()
+    assert call() == 0
+    out = set()
+    for name, grid in e.launches():
+        m = re.search("k_gemm_blockILi(\\\\d)ELi4ELi(\\\\d)E", name)
+        if m: out.add((int(m[1]), int(m[2]), grid[0]))
+    return out
+out = []
+for lens, k in (([202], 5), ([130, 40, 33, 1, 60], 32), ([3840], 32)):
+    e = engine(t, di.ModelShape(1, 384, 6, 3, 64, 640, 16512, rope_base=1e4), len(lens), -(-(max(lens) + 64) // 64) * 64)
+    a = pieces(e, lambda: e.prefill([[3] * n for n in lens]))
+    e.draft_block(k)
+    out.append((a, pieces(e, lambda: e.verify_block(k))))
+e = engine(di.scaled(di.CONFIGS["qwen3_4b"]["target"], n_layers=2, vocab=16384), di.scaled(di.DRAFTER_05B, n_layers=2, vocab=16384), 1, 3392)
+out.append((pieces(e, lambda: e.prefill([[3] * 3329])), set()))
+print(out)
+""")
+    print(got)
+    blocks = lambda nb, cols, nrb: -(-cols // (64 * nb)) * nrb   # noqa: E731
+    whole = lambda n: 8 * -(-n // 8)   # noqa: E731  (the grid without pieces)
+    assert any(e == SWIGLU and g > whole(blocks(nb, 16768, 2)) for nb, e, g in got[0][0])
+    assert any(e == LM and g > whole(blocks(nb, 16512, 2)) for nb, e, g in got[1][1])
+    assert any(e == RESID and g > whole(blocks(nb, 1152, 30)) for nb, e, g in got[2][0])
+    # and the 256-column form in the longer of the wide prompts of test_gpu_block_forms.py
+    assert any((nb, e) == (4, RESID) and g > whole(blocks(4, 2560, 27)) for nb, e, g in got[3][0])
