@@ -492,11 +492,16 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
             const BlockDeal deal{blocks, bp.full ? bp.full : blocks, bp.G, bp.piece, (a.KS + a.S - 1) / a.S};
             const dim3 g((unsigned)block_grid(deal));
             ProfScope ps(c, 0, (double)a.N * K * 2.0);
+            auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal); };
             const bool sh = a.KS < BK_SHORT;
-            if (bp.NB == 4) hipLaunchKernelGGL((k_gemm_block<4, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal);
-            else if (bp.deep) hipLaunchKernelGGL((k_gemm_block<2, 8, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal);
-            else if (sh) hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, true>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal);
-            else hipLaunchKernelGGL((k_gemm_block<2, 4, EPI, false>), g, dim3(256), 0, c->stream, a, ncb, ntiles, band, deal);
+            if (bp.G) {
+                if (bp.NB == 4) launch(k_gemm_block<4, 4, EPI, false, true>);
+                else if (sh) launch(k_gemm_block<2, 4, EPI, true, true>);
+                else launch(k_gemm_block<2, 4, EPI, false, true>);
+            } else if (bp.NB == 4) launch(k_gemm_block<4, 4, EPI, false, false>);
+            else if (bp.deep) launch(k_gemm_block<2, 8, EPI, false, false>);
+            else if (sh) launch(k_gemm_block<2, 4, EPI, true, false>);
+            else launch(k_gemm_block<2, 4, EPI, false, false>);
             LAUNCHCHK(c, "k_gemm_block");
             return DEER_OK;
         }

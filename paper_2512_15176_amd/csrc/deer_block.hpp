@@ -397,8 +397,10 @@ inline int block_band(int nrb) { const int bands = (nrb + 7) / 8; return (nrb + 
 struct BlockDeal { int blocks, full, G, piece, per; };   // per: k-steps of a uniform share
 inline int block_grid(const BlockDeal &d) { return d.G + 8 * ((d.full + 7) / 8); }
 
-// ncb: column blocks of 64 NB columns; nrt: row tiles; SHORT: a contraction of less than BK_SHORT k-steps
-template <int NB, int NST, int EPI, bool SHORT>
+// ncb: column blocks of 64 NB columns; nrt: row tiles; SHORT: a contraction of less than BK_SHORT k-steps; PIECES: deal.G > 0
+// (a form of its own: its loop keeps the arguments in scalar registers across the k-loop, which runs out of them: with one
+// form for both, launches without pieces took 2 to 7 % longer)
+template <int NB, int NST, int EPI, bool SHORT, bool PIECES>
 __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 1) void k_gemm_block(const GemmArgs a, int ncb, int nrt, int band, const BlockDeal deal) {
     constexpr int LPW = BlockSmem<NB, NST>::FRAGS / 4;
     constexpr size_t PART = 4 * (2 * NB * 4 * 256);   // floats of a block's partial sums: [wave][(mt, nb, quad)][lane][4]
@@ -407,7 +409,7 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
     const int wr = w >> 1, wc = w & 1;
     const int nrb = (nrt + BK_RT - 1) / BK_RT, KS = a.KS;
     const int lin = blockIdx.x;
-    const bool pieces = lin < deal.G;
+    const bool pieces = PIECES && lin < deal.G;
     int at, end;                 // this workgroup's k-steps [at, end): of one block (share), or of the row of blocks cut into pieces
     int cb, rb, s = 0, b = 0;    // column block, row block, uniform share; pieces: the block in the row
     if (pieces) {
@@ -415,15 +417,17 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
         at = g * deal.piece; end = min((deal.blocks - deal.full) * KS, at + deal.piece);
         b = at / opaque_s(KS);
     } else {
-        const int l = lin - deal.G, per8 = (deal.full + 7) >> 3, i = (l & 7) * per8 + (l >> 3);
+        const int l = PIECES ? lin - deal.G : lin, per8 = (deal.full + 7) >> 3, i = (l & 7) * per8 + (l >> 3);
         if ((l >> 3) >= per8 || i >= deal.full) return;
         const BlockItem bi = block_at(i, ncb * a.S, nrb, band);   // the order runs over (share, column block) pairs
         if (a.S > 1) s = bi.p / opaque_s(ncb);
         cb = bi.p - s * ncb; rb = bi.rb;
         at = s * deal.per; end = min(KS, at + deal.per);          // the host keeps every share non-empty
     }
+    bool first = true;
+    if (PIECES && at >= end) return;
 #pragma unroll 1
-    for (bool first = true; at < end; first = false) {
+    do {
         // this workgroup's k-steps of the block, and where the block's shares lie
         int ks0 = at, n = end - at, nsh = a.S, mine = s, g0 = 0, odd0 = 0;
         if (pieces) {
@@ -439,7 +443,8 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
         auto slot = [&](int u) -> size_t { return pieces ? (size_t)2 * (g0 + u) + (u == 0 ? odd0 : 0) : (size_t)u * nrb * ncb + (size_t)rb * ncb + cb; };
         const int counter = pieces ? b : rb * ncb + cb;
         at += n; ++b;
-        if (!first) __syncthreads();   // the epilogue's tiles have been read: the ring reuses them
+        if (PIECES && !first) __syncthreads();   // the epilogue's tiles have been read: the ring reuses them
+        first = false;
         const int nmt = max(0, min(2, nrt - (rb * BK_RT + wr * 2)));
         const int ln = opaque_tid() & 63;   // (derived again behind the loop: registers)
         const char *base[LPW];
@@ -528,7 +533,7 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
             const int ct = rb * BK_RT + wr * 2 + wc;
             if (wc < nmt) wave_epilogue<EPI>(a, sm.tile[wr * 2 + wc], cb, ct);
         }
-    }
+    } while (PIECES && at < end);
 }
 
 // The rows of the pairs, gathered into tiles of their expert for the blocked gate/up GEMM: (item, 128-column group) per
