@@ -18,7 +18,8 @@
  *    them to deer_init_models, and keeps them alive until deer_destroy.  (Host side, a context
  *    owns a few KB of page-locked memory through which deer_accept_and_commit's results arrive and up to 1 MB
  *    through which prompts and state leave.)
- *  - All device work is enqueued on the hipStream_t given at init.  deer_draft_block and
+ *  - All device work is enqueued on the hipStream_t given at init (a prefill's drafter passes may run beside the target's on a
+ *    stream that the context owns, between two events of that one).  deer_draft_block and
  *    deer_verify_block return without waiting; deer_accept_and_commit and deer_prefill wait for
  *    the stream before they return (they hand results to the host).
  *  - Call order per batch:  init -> load_tensor* -> prefill -> { draft -> verify -> accept }*.

@@ -65,13 +65,19 @@ struct ModelRT {
     double *theta = nullptr;           // device [hd/2]
 };
 
-struct Work {   // carved from the workspace
-    SeqState st{};
+// What a pass writes on its way.  A second set lets the drafter's prefill run beside the target's (see enqueue_prefill).
+struct PassBufs {
     RowMeta rm{};
     float2 *cs = nullptr;
-    float *h = nullptr, *ssq = nullptr, *part = nullptr;
+    float *h = nullptr, *ssq = nullptr, *part = nullptr, *opart = nullptr;
     uint4 *xa_hi = nullptr, *xa_lo = nullptr, *xb_hi = nullptr, *xb_lo = nullptr, *q_hi = nullptr, *q_lo = nullptr;
-    float *opart = nullptr;
+    int *gemm_cnt = nullptr, *attn_cnt = nullptr;   // arrival counters, zero between kernels
+    size_t part_floats = 0;   // capacity of `part`
+};
+
+struct Work : PassBufs {   // carved from the workspace
+    PassBufs beside;
+    SeqState st{};
     float *logits[2] = {nullptr, nullptr};
     RowStat *stat = nullptr;
     RowResult *res[2] = {nullptr, nullptr};
@@ -82,10 +88,8 @@ struct Work {   // carved from the workspace
     float *route_w = nullptr, *moe_out = nullptr;
     unsigned long long *moe_touched = nullptr;   // (layer, expert) pairs streamed since the last read
     uint4 *act_hi = nullptr, *act_lo = nullptr, *xg_hi = nullptr, *xg_lo = nullptr;   // per expert: FFN activations, gathered input rows
-    int *gemm_cnt = nullptr, *attn_cnt = nullptr;   // arrival counters, zero between kernels
     size_t cnt_bytes = 0; char *cnt_base = nullptr;
     double *theta[2] = {nullptr, nullptr};
-    size_t part_floats = 0;   // capacity of `part`
     AccPart *acc_part = nullptr; int *acc_cnt = nullptr;   // sampling acceptance: per-share candidates, arrival counters
     int4 *pf_desc[2] = {nullptr, nullptr};   // prefill, per model: the pass's attention tiles (see PassRows)
     char *up = nullptr;       // start of the block that the host uploads; offsets of the descriptors and the prompts in it
@@ -103,6 +107,8 @@ struct deer_ctx {
     ModelRT m[2];
     Work wk;
     hipStream_t stream = nullptr;
+    hipStream_t side = nullptr;      // the drafter's prefill passes, between the two events; null: none could be made
+    hipEvent_t fork = nullptr, join = nullptr;
     State state = ST_INIT;
     int batch = 0;
     int cur_k = 0;
@@ -245,6 +251,14 @@ void plan_model(ModelRT &m, const deer_model_cfg &c, int max_batch, int max_seq)
     m.kv_bytes = align_up(2 * m.kv_layer_stride * c.n_layers * 2);
 }
 
+// The drafter's prefill has buffers of its own, for passes of up to BESIDE_TILES row tiles.  Larger ones fill the chip by
+// themselves (105 row tiles of the 4B pair 16.28 ms one after the other, 16.08 beside each other; 128 of the 8B pair 105.0 and
+// 105.4); a drafter of fewer than BESIDE_LAYERS layers does not repay the fork and the join (the tiny pair's request: 8 us
+// longer); two mixtures share the routing buffers.
+constexpr int BESIDE_TILES = 64, BESIDE_LAYERS = 4;
+constexpr size_t BESIDE_PART_FLOATS = 16 << 20;   // split-K partials
+bool beside_ok(const deer_init_params &p) { return p.drafter.n_layers >= BESIDE_LAYERS && !(p.target.n_experts && p.drafter.n_experts); }
+
 // Carves the workspace; with base == nullptr only computes the size.
 void plan_work(Work &w, const deer_init_params &p, char *base) {
     const int B = p.max_batch;
@@ -301,11 +315,27 @@ void plan_work(Work &w, const deer_init_params &p, char *base) {
     }
     {
         const size_t ng = (size_t)(std::max(std::max(t.d_model, d.d_model), 4 * (int)fmax) / CG + 64) * MAXT, na = (size_t)MAXT * hq;
-        w.cnt_base = take((ng + na + (size_t)B) * 4);
-        w.gemm_cnt = (int *)w.cnt_base;
-        w.attn_cnt = w.gemm_cnt ? w.gemm_cnt + ng : nullptr;
-        w.acc_cnt = w.gemm_cnt ? w.gemm_cnt + ng + na : nullptr;
-        w.cnt_bytes = (ng + na + (size_t)B) * 4;
+        w.cnt_bytes = (2 * (ng + na) + (size_t)B) * 4;
+        w.cnt_base = take(w.cnt_bytes);
+        int *cnt = (int *)w.cnt_base;
+        w.gemm_cnt = cnt; w.attn_cnt = cnt ? cnt + ng : nullptr;
+        w.beside.gemm_cnt = cnt ? cnt + ng + na : nullptr; w.beside.attn_cnt = cnt ? cnt + 2 * ng + na : nullptr;
+        w.acc_cnt = cnt ? cnt + 2 * (ng + na) : nullptr;
+    }
+    if (beside_ok(p)) {   // the drafter's own set
+        PassBufs &b = w.beside;
+        const int T = BESIDE_TILES, R = T * 32;
+        const size_t dd = d.d_model, da = (size_t)d.n_q_heads * d.head_dim, db = std::max<size_t>(da, d.n_experts ? d.d_ff_expert : d.d_ff);
+        b.rm.pos = (int *)take(R * 4); b.rm.limit = (int *)take((size_t)MAXR * 4); b.rm.slot = (int *)take(R * 4); b.rm.seq = (int *)take(R * 4);
+        b.rm.qrow = (int *)take(R * 4); b.rm.grow = (int *)take((size_t)MAXR * 4); b.rm.tile_seq = (int *)take(MAXT * 4);
+        b.cs = (float2 *)take((size_t)R * 64 * sizeof(float2));
+        b.h = (float *)take((size_t)R * dd * 4);
+        b.ssq = (float *)take((size_t)R * (dd / 32) * 4);
+        b.xa_hi = (uint4 *)take((size_t)T * (dd / 16) * 1024); b.xa_lo = (uint4 *)take((size_t)T * (dd / 16) * 1024);
+        b.xb_hi = (uint4 *)take((size_t)T * (db / 16) * 1024); b.xb_lo = (uint4 *)take((size_t)T * (db / 16) * 1024);
+        b.q_hi = (uint4 *)take((size_t)MAXT * (da / 16) * 1024); b.q_lo = (uint4 *)take((size_t)MAXT * (da / 16) * 1024);
+        b.part_floats = BESIDE_PART_FLOATS; b.part = (float *)take(b.part_floats * 4);
+        b.opart = (float *)take((size_t)std::max(64, MAXT) * d.n_q_heads * (32 * d.head_dim + 64) * 4);
     }
     w.stamps = (unsigned long long *)take((size_t)STAMP_MAX_BLOCKS * 8 * 8);
     w.bytes = off;
@@ -798,7 +828,16 @@ int enqueue_prefill(deer_ctx *c, int batch, const int *ids, const int *lens, con
             memcpy(img + ((char *)w.pf_desc[model] - w.up), passes[model][0].desc.data(), passes[model][0].desc.size() * sizeof(int4));
     memcpy(img + w.up_ids, ids, total * 4);
     HIPCHK(c, hipMemcpyAsync(w.up, img, up_bytes, hipMemcpyHostToDevice, c->stream));
-    for (int model = 0; model < 2; ++model)
+    // The two models' caches do not depend on each other.  A prompt's passes leave compute units idle in every launch (its
+    // first loads, the meeting of shares, the last round of workgroups), so the drafter's run beside the target's, on a stream
+    // of their own with buffers of their own, between two events of the library's stream: 201 tokens through the 4B pair 8.06
+    // -> 7.13 ms, 2048 through 8 layers of the mixture with 4 of the drafter 7.60 -> 7.31.  (Not while launches are timed or
+    // stamped: those records are of one stream.)
+    bool fits = !passes[DEER_TARGET].empty();
+    for (const PrefillPass &pa : passes[DEER_DRAFTER]) fits = fits && (pa.n_rows + 31) / 32 <= BESIDE_TILES;
+    const bool beside = fits && c->side && !c->prof_on && c->stamp_launch < 0;
+    if (beside) HIPCHK(c, hipEventRecord(c->fork, c->stream));
+    auto run = [&](int model) -> int {
         for (size_t i = 0; i < passes[model].size(); ++i) {
             const PrefillPass &pa = passes[model][i];
             if (i > 0)
@@ -808,6 +847,20 @@ int enqueue_prefill(deer_ctx *c, int batch, const int *ids, const int *lens, con
             const LmPlan lm{false, 0, 0, 0.f, 0};
             if (int rc = run_pass(c, model, (pa.n_rows + 31) / 32, pr.n_desc, pa.maxlim, lm, 0.0, pr)) return rc;
         }
+        return DEER_OK;
+    };
+    if (int rc = run(DEER_TARGET)) return rc;
+    if (!beside) return run(DEER_DRAFTER);
+    HIPCHK(c, hipStreamWaitEvent(c->side, c->fork, 0));
+    const hipStream_t own = c->stream;
+    c->stream = c->side;
+    std::swap((PassBufs &)w, w.beside);
+    const int rc = run(DEER_DRAFTER);
+    std::swap((PassBufs &)w, w.beside);
+    c->stream = own;
+    const hipError_t e = hipEventRecord(c->join, c->side), e2 = hipStreamWaitEvent(c->stream, c->join, 0);
+    if (rc) return rc;
+    if (e != hipSuccess || e2 != hipSuccess) return fail(c, DEER_EHIP, "prefill: %s", hipGetErrorString(e != hipSuccess ? e : e2));
     return DEER_OK;
 }
 // the host's mirror once the device state is in place
@@ -907,6 +960,14 @@ int deer_init_models(const deer_init_params *p, const deer_buffers *bufs, const 
         if (hipHostMalloc(&hp, up_bytes, hipHostMallocDefault) == hipSuccess) { c->h_up = (char *)hp; c->h_up_bytes = up_bytes; }
         else (void)hipGetLastError();
     }
+    if (c->wk.beside.h) {   // (no stream: the drafter's prefill follows the target's)
+        if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) c->side = nullptr;
+        if (c->side && (hipEventCreateWithFlags(&c->fork, hipEventDisableTiming) != hipSuccess || hipEventCreateWithFlags(&c->join, hipEventDisableTiming) != hipSuccess)) {
+            (void)hipStreamDestroy(c->side);
+            c->side = nullptr;
+        }
+        (void)hipGetLastError();
+    }
     *out = c;
     return DEER_OK;
 }
@@ -1000,6 +1061,7 @@ int deer_prefill(deer_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
         }
     c->state = ST_INIT;   // no sequences until all of the call has worked: the device state may be of the new ones, the host's of the old
     int rc = enqueue_prefill(c, batch, ids, lens, pend.data(), total, passes);
+    if (rc && c->side) (void)hipStreamSynchronize(c->side);   // (without an error the library's stream waits for it)
     const hipError_t e = hipStreamSynchronize(c->stream);   // after an error too: the next call writes to the same staging memory
     if (rc) return rc;
     if (e != hipSuccess) return fail(c, DEER_EHIP, "prefill: %s", hipGetErrorString(e));
@@ -1170,6 +1232,9 @@ int deer_destroy(deer_ctx *c) {
     if (!c) return DEER_EINVAL;
     (void)hipStreamSynchronize(c->stream);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
+    if (c->side) { (void)hipStreamSynchronize(c->side); (void)hipStreamDestroy(c->side); }
+    if (c->fork) (void)hipEventDestroy(c->fork);
+    if (c->join) (void)hipEventDestroy(c->join);
     if (c->h_pin) (void)hipHostFree(c->h_pin);
     if (c->h_up) (void)hipHostFree(c->h_up);
     delete c;
