@@ -397,6 +397,53 @@ inline int block_band(int nrb) { const int bands = (nrb + 7) / 8; return (nrb + 
 struct BlockDeal { int blocks, full, G, piece, per; };   // per: k-steps of a uniform share
 inline int block_grid(const BlockDeal &d) { return d.G + 8 * ((d.full + 7) / 8); }
 
+// acc = the shares of a block in their order, the loads of U of them in flight together.
+template <int U, int NB, typename F>
+__device__ __forceinline__ void block_sum(f32x16 (&acc)[2][NB], int nmt, int nsh, F at) {
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+        if (mt < nmt)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
+                for (int u0 = 0; u0 < nsh; u0 += U) {
+                    u32x4 v[U][4];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const float *pu = at(min(u0 + u, nsh - 1)) + (mt * NB + nb) * 4 * 256;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) load16_agent_async(v[u][q], pu + q * 256);
+                    }
+                    wait_loads<0>();
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            tie(v[u][q]);
+                            if (u0 + u < nsh)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) acc[mt][nb][4 * q + e] += __uint_as_float(v[u][q][e]);
+                        }
+                }
+            }
+}
+
+// acc += the other share, its first MT row tiles' loads in flight together.
+template <int MT>
+__device__ __forceinline__ void block_add(f32x16 (&acc)[2][2], const float *po) {
+    u32x4 v[MT * 8];
+#pragma unroll
+    for (int q = 0; q < MT * 8; ++q) load16_agent_async(v[q], po + q * 256);
+    wait_loads<0>();
+#pragma unroll
+    for (int q = 0; q < MT * 8; ++q) {
+        tie(v[q]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[q >> 3][(q >> 2) & 1][4 * (q & 3) + e] += __uint_as_float(v[q][e]);
+    }
+}
+
 // ncb: column blocks of 64 NB columns; nrt: row tiles; SHORT: a contraction of less than BK_SHORT k-steps; PIECES: deal.G > 0
 // (a form of its own: its loop keeps the arguments in scalar registers across the k-loop, which runs out of them: with one
 // form for both, launches without pieces took 2 to 7 % longer)
@@ -483,35 +530,16 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
                         for (int q = 0; q < 4; ++q)
                             store16_agent(pw + ((mt * NB + nb) * 4 + q) * 256, acc[mt][nb][4 * q], acc[mt][nb][4 * q + 1], acc[mt][nb][4 * q + 2], acc[mt][nb][4 * q + 3]);
             if (!arrive_last(a.counters + counter, nsh, &sm.last)) continue;
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-                if (mt < nmt)
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        const float *pr = p0 + (mt * NB + nb) * 4 * 256;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
-                        constexpr int U = NB == 4 ? 2 : 4;                // shares whose loads are in flight together, summed in order
-                        for (int u0 = 0; u0 < nsh; u0 += U) {
-                            u32x4 v[U][4];
-#pragma unroll
-                            for (int u = 0; u < U; ++u) {
-                                const float *pu = pr + slot(min(u0 + u, nsh - 1)) * PART;
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) load16_agent_async(v[u][q], pu + q * 256);
-                            }
-                            wait_loads<0>();
-#pragma unroll
-                            for (int u = 0; u < U; ++u)
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) {
-                                    tie(v[u][q]);
-                                    if (u0 + u < nsh)
-#pragma unroll
-                                        for (int e = 0; e < 4; ++e) acc[mt][nb][4 * q + e] += __uint_as_float(v[u][q][e]);
-                                }
-                        }
-                    }
+            // What the last workgroup draws bounds this part (about 60 KB per microsecond): no share is read twice but the last of
+            // an odd number.  Of two, only the other one is read (both orders of a sum of two are the same; with 128 columns per
+            // wave there are no registers for it), more are summed in their order.  Against four at a time, a share repeated to
+            // fill them: 4B prefill of 200 ids 7119 -> 6889 us, 16 sequences of 8B and 6000 ids 8847 -> 8643.
+            auto at_share = [&](int u) { return p0 + slot(u) * PART; };
+            if constexpr (NB == 4) block_sum<2>(acc, nmt, nsh, at_share);
+            else if (nsh == 2 && nmt == 2) block_add<2>(acc, at_share(1 - mine));
+            else if (nsh == 2) { if (nmt) block_add<1>(acc, at_share(1 - mine)); }
+            else if (nsh % 4 == 0 || nsh == 7) block_sum<4>(acc, nmt, nsh, at_share);
+            else block_sum<3>(acc, nmt, nsh, at_share);
         } else {
             __syncthreads();   // every wave has read the ring: the epilogue tiles reuse it
         }
