@@ -510,12 +510,12 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     SlimPlan sp;
     if (!narrow && force_S <= 0 && a.slim) sp = plan_slim(EPI, a.N, a.KS, ntiles, a.hd, a.ssq_sub, c->wk.part_floats);
     const bool slim = sp.C > 0 && sp.us < 0.98 * stream_small_us(a.N, a.KS, MT, zg, wide_S);
-    if constexpr (EPI != EPI_ROUTER) {
+    if constexpr (EPI != EPI_ROUTER) if (c->block_gemm > 0 && ntiles > 1) {
         const BlockPlan bp = c->force_nb ? forced_block(c, a.N, a.KS, ntiles, EPI == EPI_LMHEAD)
                                          : plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);
         const double old_us = narrow ? narrow_us(a.N, a.KS, ntiles, EPI == EPI_QKV) : slim ? sp.us : stream_us(a.N, a.KS, MT, zg, wide_S);
         const bool forced = c->force_nb || (c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8);   // tests cover it at small sizes
-        if (c->block_gemm > 0 && ntiles > 1 && (forced || bp.us < 0.97 * old_us)) {
+        if (forced || bp.us < 0.97 * old_us) {
             a.S = bp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
             const int nrb = (ntiles + BK_RT - 1) / BK_RT, ncb = (a.N + 64 * bp.NB - 1) / (64 * bp.NB), band = block_band(nrb);
             const int blocks = nrb * ncb * a.S;
