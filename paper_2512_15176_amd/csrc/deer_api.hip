@@ -651,13 +651,13 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
         const int ns_max = std::max(1, std::min({ns_target / (n_attn * mc.n_q_heads), ATT_HEAD_MAX_NS, std::max(1, std::max(64, c->max_tiles) / n_attn), (nkt + 7) / 8}));
         // a range's key tiles (0.28 us each with head_dim 128) against the merge, which one compute unit per head runs behind the
         // last of them, about 0.2 us per range (14 heads of 64, 129 key tiles: 17 ranges, one tile per wave, 13.0 us from the
-        // launch's first workgroup to its last store, 10 ranges 9.9)
+        // launch's first workgroup to its last store, 10 ranges 9.9).  More than ATT_HEAD_NS ranges, which the merge takes in
+        // several goes, only where a wave would have too many tiles of fewer (14 heads of 64, one launch: 20000 keys in 16
+        // ranges 16.6 us, in 18 17.8; 52000 keys, where 16 do not go, in 18 26.6 and by the kernels for many tiles 42.9; 8 heads
+        // of 128: 24000 keys in 16 ranges 25.9, in 29 27.4; 64000 keys in 32 48.6, by the others 68.7)
         auto cost = [&](int n) { return (nkt + n - 1) / n * hd * 0.0022 + (n > 1 ? 1.0 + 0.2 * n : 0.0); };
-        int ns = 1;
-        for (int n = 2; n <= ns_max; ++n)
-            if (cost(n) < cost(ns)) ns = n;
-        const int per = (nkt + ns - 1) / ns;
-        if ((per + 7) / 8 <= ATT_HEAD_MAX_TILES) NS_head = ns;
+        for (int n = 1; n <= ns_max; ++n)
+            if ((nkt + n - 1) / n <= 8 * ATT_HEAD_MAX_TILES && (NS_head == 0 || (cost(n) < cost(NS_head) && (n <= ATT_HEAD_NS || NS_head > ATT_HEAD_NS)))) NS_head = n;
     }
     const float scale_log2e = (float)(1.4426950408889634 / std::sqrt((double)hd));
     const double kv_bytes = kv_keys_total * mc.n_kv_heads * hd * 2.0 * 2.0;   // K and V rows read per layer

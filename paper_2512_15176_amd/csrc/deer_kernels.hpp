@@ -2287,12 +2287,14 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *__restrict__ pa
 
 // Merge of the NS key-range partials of one (tile, head) written by attn_head_item: wave item (tt, hh) owns registers
 // 8*hh .. 8*hh+7 of O^T tile tt, which a partial holds as two register quads of 1 KB per wave.  All (M, L) pairs and the
-// outputs of the first 8 ranges (16 with head_dim <= 64) are requested together; ranges are combined in order s = 0..NS-1.  NS <= MAX.  The merge is the tail of the launch and runs on one compute unit per
-// head, so nothing is loaded or computed for ranges that do not exist (loads and factors for 32 ranges, whatever their
-// number, made it 5.5 us behind the last arrival of 8), and up to 8 ranges have a short code of their own: its instructions
-// come from the L2, as nothing on the compute unit has run them in this launch (3.9 us with the code for 32 ranges, 3.0 with
-// this one; 8B heads, 129 key tiles: 17.2 -> 13.8 us from the launch's first workgroup to its last store).
-constexpr int ATT_HEAD_MAX_NS = 16;   // key ranges per head
+// outputs of the first 8 ranges (16 with head_dim <= 64) are requested together; ranges are combined in order s = 0..NS-1.
+// NS <= MAX.  The merge is the tail of the launch and runs on one compute unit per head, so nothing is loaded or computed for
+// ranges that do not exist (loads and factors for 32 ranges, whatever their number, made it 5.5 us behind the last arrival of
+// 8), and up to 8 ranges have a short code of their own: its instructions come from the L2, as nothing on the compute unit has
+// run them in this launch (3.9 us with the code for 32 ranges, 3.0 with this one; 8B heads, 129 key tiles: 17.2 -> 13.8 us
+// from the launch's first workgroup to its last store).  (The factors come from the bare exp2 instruction, as in the key loop:
+// one below 2^-126 is zero, beside the factor 1 of the range that holds the maximum.)
+constexpr int ATT_HEAD_MAX_NS = 32, ATT_HEAD_NS = 16;   // key ranges per head; up to so many have all their (M, L) pairs in registers
 template <int HD, int MAX>
 __device__ __forceinline__ void attn_head_merge(const float *part, const int *row_grow, int NS, int Hq, float scale_log2e, uint4 *xhi, uint4 *xlo,
                                                 int head, int t, int tt, int hh, int lane) {
@@ -2350,6 +2352,54 @@ __device__ __forceinline__ void attn_head_merge(const float *part, const int *ro
         }
     }
     attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, grow, tt, hh, lane, xhi, xlo);
+}
+
+// The same for any number of ranges (few heads over long contexts), 8 at a time, with the sums so far rescaled in between: the
+// code above for 32 ranges does not fit the registers.
+template <int HD>
+__device__ __forceinline__ void attn_head_merge_many(const float *part, const int *row_grow, int NS, int Hq, float scale_log2e, uint4 *xhi, uint4 *xlo,
+                                                     int head, int t, int tt, int hh, int lane) {
+    constexpr int PF = AttnPartial<HD>::FLOATS;
+    const int qrow = lane & 31;
+    const float *pm = part + (size_t)(t * Hq + head) * NS * PF + 32 * HD + 2 * qrow;
+    const float *po = part + (size_t)(t * Hq + head) * NS * PF + ((tt * 2 + hh) * 2 * 64 + lane) * 4;
+    float M = -INFINITY, L = 0.f, o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = 0.f;
+#pragma unroll 1
+    for (int s0 = 0; s0 < NS; s0 += 8) {
+        float2 ml[8];
+        u32x4 v[8][2];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) ml[u] = s0 + u < NS ? ld_agent2(pm + (size_t)(s0 + u) * PF) : make_float2(-INFINITY, 0.f);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (s0 + u < NS) {
+                load16_agent_async(v[u][0], po + (size_t)(s0 + u) * PF);
+                load16_agent_async(v[u][1], po + (size_t)(s0 + u) * PF + 256);
+            }
+        const float before = M;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) M = fmaxf(M, ml[u].x);
+        const float alpha = before == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((before - M) * scale_log2e);
+        L *= alpha;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] *= alpha;
+        wait_loads<0>();
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (s0 + u < NS) {
+                const float f = ml[u].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml[u].x - M) * scale_log2e);
+                L += f * ml[u].y;
+                tie(v[u][0]); tie(v[u][1]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    o[e] += f * __uint_as_float(v[u][0][e]);
+                    o[4 + e] += f * __uint_as_float(v[u][1][e]);
+                }
+            }
+    }
+    attn_store_slice<HD>(o, L > 0.f ? 1.f / L : 0.f, Hq, head, row_grow[t * 32 + qrow], tt, hh, lane, xhi, xlo);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2581,7 +2631,8 @@ __device__ __forceinline__ void attn_head_item(const uint4 *Qhi, const uint4 *Ql
     if (!arrive_last(counters + t * Hq + head, NS, &as.last)) { prefetch_next(nx, as.slot); return; }
     if (w >= 2 * HT) return;
     if (NS <= 8) attn_head_merge<HD, 8>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
-    else attn_head_merge<HD, ATT_HEAD_MAX_NS>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
+    else if (NS <= ATT_HEAD_NS) attn_head_merge<HD, ATT_HEAD_NS>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
+    else attn_head_merge_many<HD>(part, row_grow, NS, Hq, scale_log2e, xhi, xlo, head, t, w >> 1, w & 1, lane);
 }
 
 // grid: x = kv_head + Hkv * (head in group + G * split), y = pass tile; 512 threads
