@@ -410,8 +410,9 @@ double narrow_us(int N, int KS, int ntiles, bool qkv) {
 // weights (6.5 TB/s) and a compute unit's for what its workgroups draw (62 KB per microsecond).  Fitted to launches of the
 // 4B, 8B, 30B-A3B and drafter matrices over one and two row tiles (see k_gemm_slim; microseconds measured / estimated, 8B O
 // in 224 wide workgroups 13.2 / 13.4, in 256 slim ones 11.0 / 11.6, drafter down 11.7 / 11.9 and 7.4 / 7.8).
+int share_steps(int KS, int S) { return (KS + 8 * S - 1) / (8 * S) * 8; }   // k-steps of a share: whole rounds of the eight waves
 double small_us(double base, int N, int KS, int wgs, int S, int frags) {   // frags: 1 KB fragments per k-step of a workgroup
-    const double hbm = (double)N * KS * 32.0 / 6.5e6, cu = std::ceil(wgs / 256.0) * ((double)KS / S) * frags / 62.0;
+    const double hbm = (double)N * KS * 32.0 / 6.5e6, cu = std::ceil(wgs / 256.0) * std::min(KS, share_steps(KS, S)) * frags / 62.0;
     return base + std::max(hbm, cu);
 }
 double stream_small_us(int N, int KS, int MT, int zg, int S) {
@@ -428,6 +429,7 @@ SlimPlan plan_slim(int epi, int N, int KS, int ntiles, int hd, int ssq_sub, size
     // eight shares (they are loaded together)
     for (int S = 1; S <= 8 && (ngrp * S + 7) / 8 * 8 * ntiles <= 256; ++S) {
         if (S > 1 && (KS < 16 * S || (size_t)ngrp * S * ntiles * 1024 * C > part_floats)) break;
+        if ((S - 1) * share_steps(KS, S) >= KS) continue;   // (72 k-steps: 4 shares would be 24, 24, 24 and none)
         const double us = small_us((S > 1 ? 6.0 : 4.7) + 0.4 * (C - 1), N, KS, ngrp * S * ntiles, S, C + 2);
         if (us < best.us) best = SlimPlan{C, S, ngrp, epi == EPI_SWIGLU || (epi == EPI_QKV && hd == 128), us};
     }

@@ -185,3 +185,28 @@ print(out)
     assert any(e == RESID and g > whole(blocks(nb, 1152, 30)) for nb, e, g in got[2][0])
     # and the 256-column form in the longer of the wide prompts of test_gpu_block_forms.py
     assert any((nb, e) == (4, RESID) and g > whole(blocks(4, 2560, 27)) for nb, e, g in got[3][0])
+
+
+def test_no_share_of_a_slim_gemm_is_empty(tmp_path):
+    """A share is a whole number of rounds of the eight waves: of 72 k-steps three shares have 24 each and a fourth none."""
+    got = routes(tmp_path, """
+out = []
+for d, ff in ((1152, 1088), (1152, 1152), (1152, 2304), (2048, 2304), (2560, 1344), (2560, 9728), (4096, 12288)):
+    t = di.ModelShape(1, d, 4, 2, 64, ff, 1152, rope_base=1e4)
+    e = engine(t, di.ModelShape(1, 128, 4, 2, 32, 512, 1152, rope_base=1e4), 2, 256)
+    for lens in ([70], [70, 33]):
+        e.set_prefilled(lens, [5] * len(lens))
+        assert e.draft_block(32) == 0
+        e.stub.stub_reset()
+        assert e.verify_block(32) == 0
+        name, grid = [l for l in e.launches() if "k_gemm" in l[0]][3]   # down
+        out.append((d, ff // 16, len(lens), grid[0] if "k_gemm_slim" in name else 0))
+print(out)
+""")
+    seen = 0
+    for d, ks, tiles, grid in got:
+        if grid:
+            S = next(s for s in range(1, 9) if (d // 64 * s + 7) // 8 * 8 * tiles == grid)
+            assert (S - 1) * 8 * -(-ks // (8 * S)) < ks, (d, ks, tiles, S)
+            seen += 1
+    assert seen >= 10, got
