@@ -8,6 +8,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
 
+OPS = ("launch", "copy", "sync", "record", "wait", "stream_create", "event_create")
+
 
 def run_script(tmp_path, text):
     """Runs the script in a process without torch; returns what it prints."""
@@ -64,4 +66,15 @@ class HostEngine:
         for i in range(self.stub.stub_launches()):
             g = (C.c_uint32 * 3)()
             out.append((self.stub.stub_launch(i, g).decode(), tuple(g)))
+        return out
+
+    def ops(self):
+        """(kind, stream, what) in the order of the calls since the last stub_reset: kernels (with the residual rows of the
+        pass they begin, else None), copies to the device (with their destination), waits of the host, events recorded and
+        waited for on a stream."""
+        out = []
+        for i in range(self.stub.stub_ops()):
+            stream, what = C.c_void_p(), C.c_void_p()
+            kind = OPS[self.stub.stub_op(i, C.byref(stream), C.byref(what))]
+            out.append((kind, stream.value, what.value))
         return out

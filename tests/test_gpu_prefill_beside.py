@@ -1,6 +1,8 @@
 """A prefill whose drafter passes run beside the target's, on a second stream with buffers of their own, leaves the caches that
 the same passes leave one after the other (which they do while launches are timed): bit for bit, pass after pass with new
-prompts, for dense and mixture targets, one tile to several passes, and decoding from them agrees."""
+prompts, for dense and mixture targets, from one row of the drafter to the 2048 that its second set of buffers holds (and one
+more, which goes through the first set), and decoding from them agrees.  That they run on two streams is checked without a GPU
+in test_host_prefill_beside.py."""
 import numpy as np
 import pytest
 
@@ -39,7 +41,8 @@ def test_beside_is_the_same_as_one_after_the_other(mixture):
     t = di.ModelShape(3, 512, 8, 2, 64, 0, 2048, n_experts=16, top_k=4, d_ff_expert=256, rope_base=1e4) if mixture else \
         di.ModelShape(6, 1280, 10, 2, 128, 3456, 2048, rope_base=1e4)
     eng = (_mixture if mixture else _engine)(t, d, 6, 1024, torch)
-    for rep, lens in enumerate(([5], [201], [60, 333, 7, 128, 64, 500], [2], [700, 31], [33] * 6, [960, 900])):
+    for rep, lens in enumerate(([5], [201], [60, 333, 7, 128, 64, 500], [2], [700, 31], [33] * 6, [960, 900], [700, 31, 640, 677],
+                                [700, 31, 640, 678])):
         prompts = [di.prompt_ids(t.vocab, n, seq=100 * rep + b) for b, n in enumerate(lens)]
         block = torch.from_numpy(np.random.default_rng(rep).integers(0, t.vocab, (len(lens), 16)).astype(np.int32)).cuda()
         out = []

@@ -40,7 +40,8 @@ def test_a_failed_call_leaves_no_sequences(tmp_path, call):
 
 @pytest.mark.parametrize("layers", [4, 6])
 def test_a_failed_prefill_of_both_models_at_once_leaves_no_sequences(tmp_path, layers):
-    """The same where the drafter's passes run on a stream of their own: whatever fails, both streams have been waited for."""
+    """The same where the drafter's passes run on a stream of their own (which stream is waited for, and failing events:
+    test_host_prefill_beside.py)."""
     script = SCRIPT.replace('e = HostEngine(cfg["target"], cfg["drafter"], 2, 256)', f'e = HostEngine(cfg["target"], di.scaled(cfg["drafter"], n_layers={layers}), 2, 256)')
     out = run_script(tmp_path, script.format(call="prefill([[3] * 40, [4] * 70])"))
     assert out.startswith("checked"), out
