@@ -256,7 +256,7 @@ void plan_model(ModelRT &m, const deer_model_cfg &c, int max_batch, int max_seq)
 // 105.4); a drafter of fewer than BESIDE_LAYERS layers does not repay the fork and the join (the tiny pair's request: 8 us
 // longer); two mixtures share the routing buffers.
 constexpr int BESIDE_TILES = 64, BESIDE_LAYERS = 4;
-constexpr size_t BESIDE_PART_FLOATS = 16 << 20;   // split-K partials
+constexpr size_t BESIDE_PART_FLOATS = 16 << 20;   // split-K partials, at most
 bool beside_ok(const deer_init_params &p) { return p.drafter.n_layers >= BESIDE_LAYERS && !(p.target.n_experts && p.drafter.n_experts); }
 
 // Carves the workspace; with base == nullptr only computes the size.
@@ -324,18 +324,24 @@ void plan_work(Work &w, const deer_init_params &p, char *base) {
     }
     if (beside_ok(p)) {   // the drafter's own set
         PassBufs &b = w.beside;
-        const int T = BESIDE_TILES, R = T * 32;
-        const size_t dd = d.d_model, da = (size_t)d.n_q_heads * d.head_dim, db = std::max<size_t>(da, d.n_experts ? d.d_ff_expert : d.d_ff);
-        b.rm.pos = (int *)take(R * 4); b.rm.limit = (int *)take((size_t)MAXR * 4); b.rm.slot = (int *)take(R * 4); b.rm.seq = (int *)take(R * 4);
-        b.rm.qrow = (int *)take(R * 4); b.rm.grow = (int *)take((size_t)MAXR * 4); b.rm.tile_seq = (int *)take(MAXT * 4);
+        // no more than max_batch sequences of max_seq slots ever need: T row tiles; A attention tiles, of one sequence each;
+        // AP partial tiles (a key range holds at least four key tiles); shares of K (eight at most, in blocks of 128 x 256;
+        // pieces only beside more than 256 whole blocks, which is above the cap)
+        const int key_tiles = p.max_seq / 32, T = (int)std::min<size_t>(BESIDE_TILES, (size_t)B * key_tiles), R = T * 32;
+        const size_t A = std::min<size_t>(MAXT, (size_t)B * key_tiles), AP = std::min<size_t>(std::max(64, MAXT), A * ((key_tiles + 3) / 4));
+        const size_t F = d.n_experts ? d.d_ff_expert : d.d_ff, wide = std::max<size_t>((size_t)(d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim, std::max<size_t>(2 * F, d.d_model));
+        const size_t dd = d.d_model, da = (size_t)d.n_q_heads * d.head_dim, db = std::max(da, F);
+        b.rm.pos = (int *)take(R * 4); b.rm.limit = (int *)take(A * 32 * 4); b.rm.slot = (int *)take(R * 4); b.rm.seq = (int *)take(R * 4);
+        b.rm.qrow = (int *)take(R * 4); b.rm.grow = (int *)take(A * 32 * 4); b.rm.tile_seq = (int *)take(A * 4);
         b.cs = (float2 *)take((size_t)R * 64 * sizeof(float2));
         b.h = (float *)take((size_t)R * dd * 4);
         b.ssq = (float *)take((size_t)R * (dd / 32) * 4);
         b.xa_hi = (uint4 *)take((size_t)T * (dd / 16) * 1024); b.xa_lo = (uint4 *)take((size_t)T * (dd / 16) * 1024);
         b.xb_hi = (uint4 *)take((size_t)T * (db / 16) * 1024); b.xb_lo = (uint4 *)take((size_t)T * (db / 16) * 1024);
-        b.q_hi = (uint4 *)take((size_t)MAXT * (da / 16) * 1024); b.q_lo = (uint4 *)take((size_t)MAXT * (da / 16) * 1024);
-        b.part_floats = BESIDE_PART_FLOATS; b.part = (float *)take(b.part_floats * 4);
-        b.opart = (float *)take((size_t)std::max(64, MAXT) * d.n_q_heads * (32 * d.head_dim + 64) * 4);
+        b.q_hi = (uint4 *)take(A * (da / 16) * 1024); b.q_lo = (uint4 *)take(A * (da / 16) * 1024);
+        b.part_floats = std::min<size_t>(BESIDE_PART_FLOATS, (size_t)8 * ((T + BK_RT - 1) / BK_RT * BK_RT * 32) * ((wide + 255) / 256 * 256));
+        b.part = (float *)take(b.part_floats * 4);
+        b.opart = (float *)take(AP * d.n_q_heads * (32 * d.head_dim + 64) * 4);
     }
     w.stamps = (unsigned long long *)take((size_t)STAMP_MAX_BLOCKS * 8 * 8);
     w.bytes = off;

@@ -34,15 +34,19 @@ def _mixture(t, d, batch, max_seq, torch):
     return eng
 
 
-@pytest.mark.parametrize("mixture", [False, True])
-def test_beside_is_the_same_as_one_after_the_other(mixture):
+LONG = (6, 1024, ([5], [201], [60, 333, 7, 128, 64, 500], [2], [700, 31], [33] * 6, [960, 900], [700, 31, 640, 677], [700, 31, 640, 678]))
+SHORT = (3, 64, ([32], [1, 32, 32], [32, 31, 32], [32] * 3))   # contexts whose second set has 6 row tiles and 6 attention tiles
+
+
+@pytest.mark.parametrize("mixture,size", [(False, LONG), (True, LONG), (False, SHORT), (True, SHORT)], ids=["False", "True", "short", "short-mixture"])
+def test_beside_is_the_same_as_one_after_the_other(mixture, size):
     import torch
+    batch, max_seq, sets = size
     d = di.ModelShape(4, 896, 14, 2, 64, 2432, 2048, rope_base=1e4)
     t = di.ModelShape(3, 512, 8, 2, 64, 0, 2048, n_experts=16, top_k=4, d_ff_expert=256, rope_base=1e4) if mixture else \
         di.ModelShape(6, 1280, 10, 2, 128, 3456, 2048, rope_base=1e4)
-    eng = (_mixture if mixture else _engine)(t, d, 6, 1024, torch)
-    for rep, lens in enumerate(([5], [201], [60, 333, 7, 128, 64, 500], [2], [700, 31], [33] * 6, [960, 900], [700, 31, 640, 677],
-                                [700, 31, 640, 678])):
+    eng = (_mixture if mixture else _engine)(t, d, batch, max_seq, torch)
+    for rep, lens in enumerate(sets):
         prompts = [di.prompt_ids(t.vocab, n, seq=100 * rep + b) for b, n in enumerate(lens)]
         block = torch.from_numpy(np.random.default_rng(rep).integers(0, t.vocab, (len(lens), 16)).astype(np.int32)).cuda()
         out = []

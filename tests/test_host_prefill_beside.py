@@ -103,3 +103,37 @@ for kind in ("launch", "copy", "record", "wait"):
 print(checked)
 """)
     assert int(out) >= (35 if "40" in prompts else 20), out
+
+
+def test_the_second_set_of_buffers_is_no_larger_than_the_contexts_ask_for(tmp_path):
+    """What the set adds to the workspace (drafters of 4 layers have it, of 3 not): for sequences of 64 slots less than a third of
+    what 64 row tiles need, which is the most."""
+    got = eval(run_script(tmp_path, """
+import deer_inputs as di
+def workspace(layers, batch, max_seq):
+    d = di.scaled(di.DRAFTER_05B, n_layers=layers)
+    return HostEngine.binding.query_sizes(HostEngine.binding.init_params(di.CONFIGS["qwen3_8b"]["target"], d, batch, max_seq, 32, 5)).workspace
+print([workspace(4, b, s) - workspace(3, b, s) for b, s in ((1, 64), (1, 512), (1, 2048), (1, 8192), (16, 2048))])
+"""))
+    assert got[0] < got[1] < got[2] <= got[3] == got[4] and 3 * got[0] < got[3] < 160e6, got
+
+
+def test_timed_passes_take_the_forms_of_the_others(tmp_path):
+    """While launches are timed the drafter's passes use the target's buffers, which hold more partial sums: the same kernels and
+    grids all the same, for drafters as wide as targets are."""
+    out = run_script(tmp_path, """
+import deer_inputs as di
+t = di.CONFIGS["tiny"]["target"]
+for d, hq, hkv, hd, ff in ((896, 14, 2, 64, 4864), (2560, 32, 8, 128, 9728), (4096, 32, 8, 128, 12288), (5120, 40, 8, 128, 25600), (8192, 64, 8, 128, 28672)):
+    e = HostEngine(t, di.ModelShape(4, d, hq, hkv, hd, ff, t.vocab, rope_base=1e4), 1, 2112)
+    for n in (20, 70, 130, 200, 400, 500, 900, 1024, 1500, 2048):
+        runs = []
+        for timed in (0, 1):
+            assert e.lib.deer_debug_profile(e.ctx, timed) == 0
+            e.stub.stub_reset()
+            assert e.prefill([[3] * n]) == 0
+            runs.append(e.launches())
+        assert runs[0] == runs[1], (d, n)
+print("checked")
+""")
+    assert out == "checked\n"
