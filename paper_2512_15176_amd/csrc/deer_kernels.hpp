@@ -229,31 +229,6 @@ __device__ __forceinline__ bool arrive_last(int *cnt, int expected, int *s_flag)
     return *s_flag != 0;
 }
 
-// Stores of results that other workgroups read.  COH = true: agent-scope (write-through) stores, for data that
-// crosses workgroups inside one kernel (they may sit on XCDs with separate L2s); COH = false: plain stores
-// (producer and consumer are separated by a kernel boundary).
-template <bool COH> __device__ __forceinline__ void stf(float *p, float v) {
-    if (COH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *p = v;
-}
-template <bool COH> __device__ __forceinline__ void sti(int *p, int v) {
-    if (COH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *p = v;
-}
-template <bool COH> __device__ __forceinline__ void st16(uint4 *p, uint4 v) {
-    if (COH) {
-        unsigned long long *q = (unsigned long long *)p;
-        __hip_atomic_store(q, ((unsigned long long)v.y << 32) | v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(q + 1, ((unsigned long long)v.w << 32) | v.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        *p = v;
-    }
-}
-template <bool COH> __device__ __forceinline__ void st_u16(uint16_t *p, uint16_t v) {
-    if (COH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *p = v;
-}
-
 // (value, index) max with lowest index on ties
 __device__ __forceinline__ void argmax_merge(float &v, int &i, float v2, int i2) {
     if (v2 > v || (v2 == v && i2 < i)) { v = v2; i = i2; }
@@ -700,7 +675,6 @@ struct GemmArgs {
 
 // rstd[row] = rsqrt(sum_g ssq[row][g] / d + eps) for the 32 rows of a tile, into LDS.  512 threads: 16 per
 // row, each sums the groups g = j, j + 16, .. in order, then a fixed butterfly over the 16 partial sums.
-template <bool COH>
 __device__ __forceinline__ void tile_rstd(const float *ssq, float *rstd, int grow0, int ncg, int d, float eps) {
     const int tidx = opaque_tid();
     const int row = tidx >> 4, j = tidx & 15;
@@ -717,7 +691,7 @@ __device__ __forceinline__ void tile_rstd(const float *ssq, float *rstd, int gro
 // a head, and with it every rotation pair, lies inside one tile.
 // pre (optional): what qkv_prefetch loaded for this thread's item while the tile was still being summed.
 constexpr int QKV_PRE = 19;   // 8 (cos, sin) pairs, the row's cache slot, its sequence, its attention row
-template <bool COH, int WIDTH = CG, int STRIDE = RED_STRIDE, bool PRE = false>
+template <int WIDTH = CG, int STRIDE = RED_STRIDE, bool PRE = false>
 __device__ __forceinline__ void epi_qkv(const GemmArgs &a, const float *tile, const float *rstd, int cg, int t,
                                         const float (&pre)[QKV_PRE]) {
     const int tidx = opaque_tid();
@@ -752,8 +726,8 @@ __device__ __forceinline__ void epi_qkv(const GemmArgs &a, const float *tile, co
             const int qr = PRE ? __float_as_int(pre[18]) : a.rm.qrow[grow];
             if (qr >= 0) {
                 size_t vec = ((size_t)((qr >> 5) * Hq + head) * (hd / 16)) * 64 + frag_vec(qr & 31, i0 >> 3);
-                st16<COH>(a.qhi + vec, hi);
-                st16<COH>(a.qlo + vec, lo);
+                a.qhi[vec] = hi;
+                a.qlo[vec] = lo;
             }
         } else {
             const int slot = PRE ? __float_as_int(pre[16]) : a.rm.slot[grow];
@@ -761,11 +735,11 @@ __device__ __forceinline__ void epi_qkv(const GemmArgs &a, const float *tile, co
                 const int b = PRE ? __float_as_int(pre[17]) : a.rm.seq[grow];
                 size_t base = (size_t)b * a.kv.seq_stride + (size_t)head * a.kv.head_stride;
                 if (kind == 1) {
-                    st16<COH>((uint4 *)(a.kv.k + base + k_cache_off(slot, i0 >> 3, hd)), pack8(v));
+                    *(uint4 *)(a.kv.k + base + k_cache_off(slot, i0 >> 3, hd)) = pack8(v);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        st_u16<COH>(a.kv.vt + base + v_cache_off(slot, i0 + e, hd), (uint16_t)f2bf(v[e]));
+                        a.kv.vt[base + v_cache_off(slot, i0 + e, hd)] = (uint16_t)f2bf(v[e]);
                 }
             }
         }
@@ -800,7 +774,6 @@ __device__ __forceinline__ void qkv_prefetch(const GemmArgs &a, float (&pre)[QKV
 // O-proj / down-proj epilogue: h += y; new fragment planes of h; per-group sum of squares.
 // `hreg` holds the old h values of this thread's elements e = threadIdx.x + 512*i (row e>>7, column e&127),
 // loaded by resid_prefetch() before the tile was ready.  `tile` is overwritten with the new h values.
-template <bool COH>
 __device__ __forceinline__ void resid_prefetch(const GemmArgs &a, float (&hreg)[8], int cg, int t) {
     const int tidx = opaque_tid();
 #pragma unroll
@@ -811,7 +784,6 @@ __device__ __forceinline__ void resid_prefetch(const GemmArgs &a, float (&hreg)[
     }
 }
 
-template <bool COH>
 __device__ __forceinline__ void epi_resid(const GemmArgs &a, float *tile, float *scratch, const float (&hreg)[8], int cg, int t) {
     const int tidx = opaque_tid();
     const int N = a.N;
@@ -821,7 +793,7 @@ __device__ __forceinline__ void epi_resid(const GemmArgs &a, float *tile, float 
         const int row = e >> 7, col = e & 127;
         const float v = hreg[i] + tile[row * RED_STRIDE + col];
         float *hp = a.h + (size_t)(t * 32 + row) * N + cg * CG + col;
-        stf<COH>(hp, v);
+        *hp = v;
         tile[row * RED_STRIDE + col] = v;
     }
     __syncthreads();
@@ -831,8 +803,8 @@ __device__ __forceinline__ void epi_resid(const GemmArgs &a, float *tile, float 
         uint4 hi, lo;
         pack8_split(tp, hi, lo);
         size_t v = (size_t)t * (N / 16) * 64 + frag_vec(row, cg * 16 + oct);
-        st16<COH>(a.xhi_out + v, hi);
-        st16<COH>(a.xlo_out + v, lo);
+        a.xhi_out[v] = hi;
+        a.xlo_out[v] = lo;
         float ss = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) ss += tp[e] * tp[e];
@@ -843,8 +815,7 @@ __device__ __forceinline__ void epi_resid(const GemmArgs &a, float *tile, float 
     if (a.ssq_sub == 4) {   // wave w holds the octets 2w, 2w + 1: waves 2b, 2b + 1 make 32-column block b
         if (tidx < 128) {
             const int row = tidx & 31, blk = tidx >> 5;
-            stf<COH>(a.ssq_out + (size_t)(t * 32 + row) * (N / 32) + cg * 4 + blk,
-                     scratch[(2 * blk) * 32 + row] + scratch[(2 * blk + 1) * 32 + row]);
+            a.ssq_out[(size_t)(t * 32 + row) * (N / 32) + cg * 4 + blk] = scratch[(2 * blk) * 32 + row] + scratch[(2 * blk + 1) * 32 + row];
         }
     } else if (a.ssq_sub == 2) {   // waves 4b .. 4b + 3 make 64-column block b
         if (tidx < 64) {
@@ -852,19 +823,18 @@ __device__ __forceinline__ void epi_resid(const GemmArgs &a, float *tile, float 
             float s2 = 0.f;
 #pragma unroll
             for (int w = 0; w < 4; ++w) s2 += scratch[(4 * blk + w) * 32 + row];
-            stf<COH>(a.ssq_out + (size_t)(t * 32 + row) * (N / 64) + cg * 2 + blk, s2);
+            a.ssq_out[(size_t)(t * 32 + row) * (N / 64) + cg * 2 + blk] = s2;
         }
     } else if (tidx < 32) {
         float s2 = 0.f;
 #pragma unroll
         for (int w = 0; w < 8; ++w) s2 += scratch[w * 32 + tidx];   // fixed order
-        stf<COH>(a.ssq_out + (size_t)(t * 32 + tidx) * (N / CG) + cg, s2);
+        a.ssq_out[(size_t)(t * 32 + tidx) * (N / CG) + cg] = s2;
     }
 }
 
 // gate/up epilogue: group = 64 gate + 64 up channels -> SiLU(g) * u, fragment planes over F.  Four channels per thread, so that
 // all eight waves work and the code, which every launch reads anew, is half as long.
-template <bool COH>
 __device__ __forceinline__ void epi_swiglu(const GemmArgs &a, const float *tile, const float *rstd, int cg, int t) {
     const int tidx = opaque_tid();
     const int row = tidx & 31, c4 = (tidx >> 5) * 4;   // 16 groups of 4 channels
@@ -886,7 +856,6 @@ __device__ __forceinline__ void epi_swiglu(const GemmArgs &a, const float *tile,
 
 // LM-head epilogue: RMSNorm scale, optional logits store, per-(row, group) argmax / sumexp / Gumbel-max.
 // LM rows are the first n_lm GEMM rows of the pass, k of each sequence.
-template <bool COH>
 __device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile, const float *rstd, int cg, int t) {
     const int tidx = opaque_tid();
     if (tidx >= 256) return;
@@ -936,7 +905,7 @@ __device__ __forceinline__ void epi_lmhead(const GemmArgs &a, const float *tile,
     for (int off = 1; off < 8; off <<= 1) se += shx(se, off);
     if (live && sub == 0) {
         RowStat *sp = a.stat + lm * a.ncg_v + cg;
-        stf<COH>(&sp->m, m); sti<COH>(&sp->idx, idx); stf<COH>(&sp->sumexp, se); stf<COH>(&sp->gm, gm); sti<COH>(&sp->gidx, gidx);
+        sp->m = m; sp->idx = idx; sp->sumexp = se; sp->gm = gm; sp->gidx = gidx;
     }
 }
 
@@ -994,23 +963,23 @@ __device__ __forceinline__ void epi_router(const GemmArgs &a, const float *tile,
 }
 
 // RSTD_READY: `rstd` already holds the tile's factors (tile_rstd ran before a barrier the caller has passed).
-template <int EPI, bool COH, bool RSTD_READY = false>
+template <int EPI, bool RSTD_READY = false>
 __device__ __forceinline__ void run_epilogue(const GemmArgs &a, float *tile, float *rstd, float *scratch,
                                              const float (&hreg)[8], int cg, int t) {
     // caller has synchronised after filling `tile`
     if (EPI != EPI_RESID && !RSTD_READY) {
-        tile_rstd<COH>(a.ssq_in, rstd, t * 32, a.ncg_in, a.d_in, a.eps);
+        tile_rstd(a.ssq_in, rstd, t * 32, a.ncg_in, a.d_in, a.eps);
         __syncthreads();
     }
     if (EPI == EPI_QKV) {
         // the wide workgroups load the epilogue's inputs here: requesting them ahead of the tile measured slower
         const float none[QKV_PRE] = {};
-        epi_qkv<COH>(a, tile, rstd, cg, t, none);
+        epi_qkv<>(a, tile, rstd, cg, t, none);
     }
-    else if (EPI == EPI_RESID) epi_resid<COH>(a, tile, scratch, hreg, cg, t);
-    else if (EPI == EPI_SWIGLU) epi_swiglu<COH>(a, tile, rstd, cg, t);
+    else if (EPI == EPI_RESID) epi_resid(a, tile, scratch, hreg, cg, t);
+    else if (EPI == EPI_SWIGLU) epi_swiglu(a, tile, rstd, cg, t);
     else if (EPI == EPI_ROUTER) epi_router(a, tile, rstd, t);
-    else epi_lmhead<COH>(a, tile, rstd, cg, t);
+    else epi_lmhead(a, tile, rstd, cg, t);
 }
 
 // Sum of the 8 waves' accumulators (one 32 x 128 tile each, MFMA register layout) in the fixed order
@@ -1055,7 +1024,7 @@ struct GemmSmem {
 // Sums the S partial tiles of column group cg (row-tile group z) in order s = 0..S-1 and runs the epilogue.
 // RSTD_EARLY: sm.rstd already holds the RMSNorm factors of the group's MT row tiles (gemm_block computed them
 // while its first weights were on their way).
-template <int MT, int EPI, bool COH, bool RSTD_EARLY = false>
+template <int MT, int EPI, bool RSTD_EARLY = false>
 __device__ __forceinline__ void gemm_finish(const GemmArgs &a, GemmSmem &sm, int cg, int z) {
     const int tidx = opaque_tid();
     float *tile = sm.tile;
@@ -1066,7 +1035,7 @@ __device__ __forceinline__ void gemm_finish(const GemmArgs &a, GemmSmem &sm, int
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int ct = z * MT + mt;
-        if (EPI == EPI_RESID) resid_prefetch<COH>(a, hreg[mt], cg, ct);
+        if (EPI == EPI_RESID) resid_prefetch(a, hreg[mt], cg, ct);
         const size_t sstride = (size_t)a.rows_total * N;
         const float *p[2];
 #pragma unroll
@@ -1105,7 +1074,7 @@ __device__ __forceinline__ void gemm_finish(const GemmArgs &a, GemmSmem &sm, int
             tp[0] = v[mt][i].x; tp[1] = v[mt][i].y; tp[2] = v[mt][i].z; tp[3] = v[mt][i].w;
         }
         __syncthreads();
-        run_epilogue<EPI, COH, RSTD_EARLY>(a, tile, sm.rstd + 32 * mt, sm.red, hreg[mt], cg, ct);
+        run_epilogue<EPI, RSTD_EARLY>(a, tile, sm.rstd + 32 * mt, sm.red, hreg[mt], cg, ct);
     }
 }
 
@@ -1118,7 +1087,7 @@ __device__ __forceinline__ void gemm_stamp(const GemmArgs &a, int lin, int i) {
 // With S > 1 the block that arrives last at the group's counter finishes the group.
 // WSTREAM: weights are read once by the whole grid (non-temporal loads); false: several workgroups of an XCD read
 // the same weights at about the same time and should find them in its L2 (plain loads).
-template <int MT, int EPI, bool COH, bool WSTREAM = true>
+template <int MT, int EPI, bool WSTREAM = true>
 __device__ __forceinline__ void gemm_block(const GemmArgs &a, GemmSmem &sm, int cg, int s, int z, int ncg) {
     const int tidx = opaque_tid();
     float *red = sm.red, *tile = sm.tile, *s_rstd = sm.rstd;
@@ -1250,10 +1219,10 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &a, GemmSmem &sm, int 
     for (int mt = 0; mt < MT; ++mt) {
         const int ct = z * MT + mt;
         if (mt > 0) __syncthreads();
-        if (EPI == EPI_RESID && S == 1) resid_prefetch<COH>(a, hreg, cg, ct);
+        if (EPI == EPI_RESID && S == 1) resid_prefetch(a, hreg, cg, ct);
         reduce_waves_to_tile(acc[mt], red, tile, w, lane);
         if (S == 1) {
-            run_epilogue<EPI, COH, RSTD_EARLY>(a, tile, s_rstd + 32 * mt, red, hreg, cg, ct);
+            run_epilogue<EPI, RSTD_EARLY>(a, tile, s_rstd + 32 * mt, red, hreg, cg, ct);
         } else {
             float *out = a.part + ((size_t)s * a.rows_total + (size_t)ct * 32) * N + (size_t)cg * CG;
 #pragma unroll
@@ -1276,14 +1245,14 @@ __device__ __forceinline__ void gemm_block(const GemmArgs &a, GemmSmem &sm, int 
         else prefetch_next(a.nx, sm.red);
         return;
     }
-    gemm_finish<MT, EPI, COH, RSTD_EARLY>(a, sm, cg, z);
+    gemm_finish<MT, EPI, RSTD_EARLY>(a, sm, cg, z);
     gemm_stamp(a, lin, 4);
 }
 
 template <int MT, int EPI>
 __global__ __launch_bounds__(512) void k_gemm(const GemmArgs a) {
     __shared__ GemmSmem sm;
-    gemm_block<MT, EPI, false>(a, sm, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x);
+    gemm_block<MT, EPI>(a, sm, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x);
 }
 
 // The same GEMM over Z > 1 row-tile groups (batched passes, prefill chunks): every group needs the same weights.
@@ -1295,7 +1264,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(const GemmArgs a, int ncg, in
     __shared__ GemmSmem sm;
     const int lin = blockIdx.x, x = lin & 7, q = lin >> 3;
     const int z = q % Z, p = 8 * (q / Z) + x;
-    if (p < ncg * a.S) gemm_block<MT, EPI, false, false>(a, sm, p % ncg, p / ncg, z, ncg);
+    if (p < ncg * a.S) gemm_block<MT, EPI, false>(a, sm, p % ncg, p / ncg, z, ncg);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1357,7 +1326,7 @@ __global__ __launch_bounds__(512) void k_gemm_narrow(const GemmArgs a, int ngrp,
             hreg[i] = a.h[(size_t)(t * 32 + (e >> 5)) * N + p * 32 + (e & 31)];
         }
     } else {   // RMSNorm factors of the input rows, requested behind the first operands
-        tile_rstd<false>(a.ssq_in, sm.rstd, t * 32, a.ncg_in, a.d_in, a.eps);
+        tile_rstd(a.ssq_in, sm.rstd, t * 32, a.ncg_in, a.d_in, a.eps);
     }
     f32x16 acc[NB];
 #pragma unroll
@@ -1407,7 +1376,7 @@ __global__ __launch_bounds__(512) void k_gemm_narrow(const GemmArgs a, int ngrp,
     }
     __syncthreads();
     if (EPI == EPI_QKV) {
-        epi_qkv<false, 32 * NB, TS, true>(a, sm.tile, sm.rstd, p, t, qpre);
+        epi_qkv<32 * NB, TS, true>(a, sm.tile, sm.rstd, p, t, qpre);
     } else {
         // h += y; new fragment planes of h; sums of squares of the block's 32 columns
 #pragma unroll
