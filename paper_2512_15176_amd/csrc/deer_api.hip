@@ -424,6 +424,13 @@ double small_us(double base, int N, int KS, int wgs, int S, int frags) {   // fr
 double stream_small_us(int N, int KS, int MT, int zg, int S) {
     return small_us(MT == 2 ? (S > 1 ? 14.0 : 12.0) : (S > 1 ? 8.2 : 5.6), N, KS, N / CG * S * zg, S, 4 + 2 * MT);
 }
+// The streaming kernel against the blocked one: of few row tiles the lower of its two estimates, since the blocked kernel's own
+// is too low there (four row tiles of gate/up, microseconds streaming / blocked and their estimates: 9728 x 896 18.1 / 19.1,
+// 16.4 or 20.8 / 19.7; 11264 x 1408 23.6 / 29.8, 22.6 or 25.3 / 23.6; 11776 x 2944 32.3 / 46.5, 35.7 or 33.0 / 34.2).
+double stream_or_small_us(int N, int KS, int MT, int zg, int S) {
+    const double us = stream_us(N, KS, MT, zg, S);
+    return MT * zg <= SLIM_TILES ? std::min(us, stream_small_us(N, KS, MT, zg, S)) : us;
+}
 // k_gemm_slim for one GEMM of a pass; C == 0: the wide kernels
 struct SlimPlan { int C = 0, S = 1, ngrp = 0, pairs = 0; double us = 1e30; };
 SlimPlan plan_slim(int epi, int N, int KS, int ntiles, int hd, int ssq_sub, size_t part_floats) {
@@ -521,7 +528,7 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     if constexpr (EPI != EPI_ROUTER) if (c->block_gemm > 0 && ntiles > 1) {
         const BlockPlan bp = c->force_nb ? forced_block(c, a.N, a.KS, ntiles, EPI == EPI_LMHEAD)
                                          : plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);
-        const double old_us = narrow ? narrow_us(a.N, a.KS, ntiles, EPI == EPI_QKV) : slim ? sp.us : stream_us(a.N, a.KS, MT, zg, wide_S);
+        const double old_us = narrow ? narrow_us(a.N, a.KS, ntiles, EPI == EPI_QKV) : slim ? sp.us : stream_or_small_us(a.N, a.KS, MT, zg, wide_S);
         const bool forced = c->force_nb || (c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8);   // tests cover it at small sizes
         if (forced || bp.us < 0.97 * old_us) {
             a.S = bp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;

@@ -210,3 +210,20 @@ print(out)
             assert (S - 1) * 8 * -(-ks // (8 * S)) < ks, (d, ks, tiles, S)
             seen += 1
     assert seen >= 10, got
+
+
+def test_gate_up_of_four_row_tiles_takes_the_faster_kernel(tmp_path):
+    """Microseconds streaming / blocked: 9728 columns of d = 896 18.1 / 19.1, 11264 of 1408 23.6 / 29.8, 24576 of 4096 81 / 73."""
+    got = routes(tmp_path, """
+out = []
+for d, hq, hd, ff in ((896, 14, 64, 4864), (1408, 11, 128, 5632), (4096, 32, 128, 12288)):
+    t = di.ModelShape(1, d, hq, 1 if hq % 2 else 2, hd, ff, 1152, rope_base=1e4)
+    e = engine(t, di.ModelShape(1, 128, 4, 2, 32, 512, 1152, rope_base=1e4), 4, 256)
+    e.set_prefilled([100] * 4, [5] * 4)
+    assert e.draft_block(32) == 0
+    e.stub.stub_reset()
+    assert e.verify_block(32) == 0
+    out.append("block" in [n for n, _ in e.launches() if "k_gemm" in n][2])
+print(out)
+""")
+    assert got == [False, False, True], got
