@@ -253,10 +253,11 @@ int deer_debug_stream_read(deer_ctx *c, const void *buf_dev, size_t bytes, int32
 int deer_debug_gemm_stamps(deer_ctx *c, int model, int launch, uint64_t *stamps_host, int32_t max_blocks, int32_t *blocks);
 
 /* GEMMs of passes of several row tiles run blocked (128 x 128 or 128 x 256 tiles through LDS) where that is estimated
- * to be faster than the weight-streaming kernel (min_tiles = 128, the default; larger values: the same).  0 switches the
- * blocked kernel off, and the streaming kernel's form in small workgroups that passes of few row tiles use; the former also for the gate/up projections of a mixture's experts (their down projections always run blocked);
- * 1 .. 127 make every dense GEMM of a pass with at least 8 row tiles take it.  Results agree within rounding (different
- * summation order over K). */
+ * to be faster than the weight-streaming kernel (min_tiles = 128, the default; larger values: the same).  1 .. 127 make
+ * every dense GEMM of a pass with at least 8 row tiles take it.  0 switches the blocked kernel off, also for the gate/up
+ * projections of a mixture's experts (their down projections always run blocked).  0 switches off, too, the streaming
+ * kernel's form in small workgroups, which passes of few row tiles take.  Results agree within rounding (different summation
+ * order over K). */
 int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles);
 
 /* Test aid: makes every dense GEMM of a pass of at least two row tiles run in one form of the blocked kernel (unless

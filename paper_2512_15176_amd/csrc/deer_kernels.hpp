@@ -1416,10 +1416,12 @@ __global__ __launch_bounds__(512) void k_gemm_narrow(const GemmArgs a, int ngrp,
 // that it needs no LDS tile on its way, and the residual epilogue works on registers.
 // What bounds a launch: about 6 us of start, exchange and epilogue (4.7 without shares), and behind that HBM (6.5 TB/s) or
 // what one compute unit draws, 60 to 75 KB per microsecond of weights and activations together as long as the weights come
-// from HBM.  So: as many workgroups as compute units, each with few bytes; the host picks C and S (plan_slim).
-// Back to back with rotating weights, one row tile, microseconds against k_gemm: O 4096 x 4096 13.2 -> 11.0, 4096 x 2560
-// 12.4 -> 9.4, 4096 x 2048 11.9 -> 8.6; down 9728 x 2560 18.1 -> 14.0, 4864 x 896 11.7 -> 7.4 (12288 x 4096: 22.3 and 21.6);
-// QKV 2048 x 5120 11.9 -> 9.3, gate/up 896 x 9728 10.4 -> 7.9.
+// from HBM (the estimate takes 62).  So: as many workgroups as compute units, each with few bytes; the host picks C and S
+// (plan_slim).  One row tile, microseconds against k_gemm.  Launched alone, back to back with rotating weights: O 4096 x 4096
+// 13.2 -> 11.0, 4096 x 2560 12.4 -> 9.4, 4096 x 2048 11.9 -> 8.6; down 9728 x 2560 18.1 -> 14.0, 4864 x 896 11.7 -> 7.4
+// (12288 x 4096: 22.3 and 21.6); QKV 2048 x 5120 11.9 -> 9.3, gate/up 896 x 9728 10.4 -> 7.9.  In a pass at full depth: 8B O
+// 12.5 -> 11.3, down 24.5 -> 23.5 (QKV 17.4 and 17.7: nothing gained there), 4B O 11.7 -> 9.9, down 19.8 -> 16.1, QKV one
+// microsecond, drafter gate/up 11.5 -> 9.1, down 12.4 -> 9.0.
 // grid: 1-D; with P = s * ngrp + p, the Z row tiles of (column group p, share s) get the ids 8 * ((P / 8) * Z + z) + P % 8
 // (one XCD).  Sums of squares are written per 32 C columns (GemmArgs::ssq_sub == 4 / C).
 // ------------------------------------------------------------------------------------------
