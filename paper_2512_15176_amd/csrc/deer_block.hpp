@@ -373,7 +373,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
 // Workgroup id -> (column block and K share p, row block).  Ids 8 apart share an XCD; every XCD gets one contiguous run
 // of the order (band of up to 8 row blocks, p, row block in the band), so that the workgroups it runs together read few
 // weight columns and few rows.  The order has no gaps: with a last band counted as high as the others (workgroups without a
-// block) the runs would begin at the same column in every band, but gate/up of 105 row tiles took 573 us so and takes 528
+// block) the runs would begin at the same column in every band, but the 4B's gate/up of 104 row tiles took 573 us so and takes 528
 // (9728 x 896 124 and 109; QKV 202 and 203).
 struct BlockItem { int p, rb; };
 __device__ __forceinline__ BlockItem block_at(int i, int P, int nrb, int band) {
