@@ -1,12 +1,14 @@
 """GPU parity of the small-workgroup streaming GEMMs (one or two 32-column blocks per workgroup, K in up to eight shares),
 which passes of one to four row tiles take by an estimate, against the wide streaming kernels: head dims 32, 64 and 128 (the
-blocks of a rotation pair are neighbours or two apart), contractions that leave waves without k-steps, ragged last tiles.
+blocks of a rotation pair are neighbours or two apart), contractions that leave waves without k-steps, ragged last tiles;
+and of passes of one row tile against the oracle.
 test_host_routes.py checks that these shapes take them."""
 import numpy as np
 import pytest
 
 import deer_inputs as di
-from gpu_common import gpu_available
+from oracle import deer_oracle as O
+from gpu_common import StoredWeights, fill_seeded_cache, gpu_available, make_engine, make_pair
 from test_gpu_block_forms import _compare, _engine
 
 pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
@@ -45,4 +47,36 @@ def test_slim_launches_agree_with_the_wide_ones(name):
             out[mode] = ([x.view(torch.bfloat16).clone() for x in eng._kv], res)
         print(name, lens, k, flush=True)
         _compare(out[0], out[128])
+    eng.close()
+
+
+# Relative error of a row's logits.  One layer: activations enter as two bf16 planes (2^-17 = 7.6e-6 each time), four times
+# that; a product without its second plane would be off by 2^-9 / sqrt(3) = 1e-3.  Two layers: one K or V value of a block's own
+# rows that rounds the other way (2^-8 of it, one key of about 100) moves the rows above it by up to 1e-4 or so.
+ORACLE = {1: 3e-5, 2: 3e-4}
+
+
+@pytest.mark.parametrize("name", SHAPES)
+@pytest.mark.parametrize("layers", [1, 2])
+def test_slim_launches_against_the_oracle(name, layers):
+    """One row tile, draft and verify, behind stand-in keys and values."""
+    import torch
+    d, hq, hkv, hd, ff = SHAPES[name]
+    t, k, n = di.ModelShape(layers, d, hq, hkv, hd, ff, 1152, rope_base=1e4), 32, 70
+    wt, wd = StoredWeights(t, di.TARGET_SEED, "bf16"), StoredWeights(t, di.DRAFTER_SEED, "bf16")
+    eng = make_engine(t, t, wt, wd, 1, 192, k)
+    block = [int(v) for v in np.random.default_rng(d).integers(0, t.vocab, k)]
+    pair = make_pair(t, t, wt, wd, 192)
+    pair.x = [0] * (n - 1) + [7]
+    fill_seeded_cache(eng, torch, 0, t, 0, n - 1, pair.tc)
+    fill_seeded_cache(eng, torch, 1, t, 0, n, pair.dc)
+    eng.set_prefilled([n], [7])
+    eng.draft_block(k, 0.0, 0)
+    zd = pair.draft_logits(k)
+    zt = O.deer_iteration(pair, k, 0.0, None, draft_override=block)["target_logits"]
+    eng.verify_block(k, 0.0, torch.tensor([block], dtype=torch.int32, device="cuda"))
+    for got, want in ((eng.debug_get_logits(1, k)[0], zd), (eng.debug_get_logits(0, k)[0], zt)):
+        off = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
+        print(f"[{name}, {layers} layers] rows off by {off.max():.2e}, mean {off.mean():.2e}")
+        assert off.max() < ORACLE[layers], off.max()
     eng.close()
