@@ -446,6 +446,9 @@ SlimPlan plan_slim(int epi, int N, int KS, int ntiles, int hd, int ssq_sub, size
         const double us = small_us((S > 1 ? 6.0 : 4.7) + 0.4 * (C - 1), N, KS, ngrp * S * ntiles, S, C + 2);
         if (us < best.us) best = SlimPlan{C, S, ngrp, epi == EPI_SWIGLU || (epi == EPI_QKV && hd == 128), us};
     }
+    // Where it is the stream that counts, it runs at 6.0 TB/s: the workgroups draw the activations twice as often as wide ones
+    // (18944 x 3584 over one row tile 31.9 wide and 33.3 slim; 12288 x 4096 24.5 and 23.5).
+    best.us = std::max(best.us, (best.S > 1 ? 6.0 : 4.7) + 0.4 * (C - 1) + (double)N * KS * 32.0 / 6.0e6);
     return best;
 }
 // shares that meet through memory (megabytes): cheap while the L2s hold them

@@ -227,3 +227,21 @@ for d, hq, hd, ff in ((896, 14, 64, 4864), (1408, 11, 128, 5632), (4096, 32, 128
 print(out)
 """)
     assert got == [False, False, True], got
+
+
+def test_down_projections_take_the_faster_streaming_kernel(tmp_path):
+    """One row tile, microseconds wide / small workgroups: 12288 x 4096 in a pass 24.5 / 23.5, 9728 x 2560 19.8 / 16.1, 18944 x
+    3584 31.9 / 33.3."""
+    got = routes(tmp_path, """
+out = []
+for d, hq, ff in ((4096, 32, 12288), (2560, 32, 9728), (3584, 28, 18944)):
+    t = di.ModelShape(1, d, hq, 4, 128, ff, 1152, rope_base=1e4)
+    e = engine(t, di.ModelShape(1, 128, 4, 2, 32, 512, 1152, rope_base=1e4), 1, 256)
+    e.set_prefilled([100], [5])
+    assert e.draft_block(32) == 0
+    e.stub.stub_reset()
+    assert e.verify_block(32) == 0
+    out.append("k_gemm_slim" in [n for n, _ in e.launches() if "k_gemm" in n][3])
+print(out)
+""")
+    assert got == [True, True, False], got
