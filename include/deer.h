@@ -255,7 +255,7 @@ int deer_debug_gemm_stamps(deer_ctx *c, int model, int launch, uint64_t *stamps_
 /* GEMMs of passes of several row tiles run blocked (128 x 128 or 128 x 256 tiles through LDS) where that is estimated
  * to be faster than the weight-streaming kernel (min_tiles = 128, the default; larger values: the same).  1 .. 127 make
  * every dense GEMM of a pass with at least 8 row tiles take it.  0 switches the blocked kernel off, also for the gate/up
- * projections of a mixture's experts (their down projections always run blocked).  0 switches off, too, the streaming
+ * projections of a mixture's experts (not for their down projections).  0 switches off, too, the streaming
  * kernel's form in small workgroups, which passes of few row tiles take.  Results agree within rounding (different summation
  * order over K). */
 int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles);

@@ -84,7 +84,8 @@ struct Work : PassBufs {   // carved from the workspace
     AcceptOut ao{};
     int *ids = nullptr;                // prompt staging [max_seq]
     // mixture-of-experts routing and staging (target only)
-    int *route_e = nullptr, *exp_cnt = nullptr, *pair_row = nullptr, *pair_slot = nullptr, *tile_off = nullptr, *items = nullptr;
+    int *route_e = nullptr, *pairs = nullptr;
+    int4 *items = nullptr;
     float *route_w = nullptr, *moe_out = nullptr;
     unsigned long long *moe_touched = nullptr;   // (layer, expert) pairs streamed since the last read
     uint4 *act_hi = nullptr, *act_lo = nullptr, *xg_hi = nullptr, *xg_lo = nullptr;   // per expert: FFN activations, gathered input rows
@@ -306,10 +307,10 @@ void plan_work(Work &w, const deer_init_params &p, char *base) {
         if (!mc->n_experts || w.route_e) continue;
         const size_t tiles = 128 + (size_t)MAXR * 8 / 32, n_items = 128 + (size_t)MAXR * 8 / 64;   // 32-pair tiles and 64-pair items: the last of an expert may be short
         w.route_e = (int *)take((size_t)MAXR * 8 * 4); w.route_w = (float *)take((size_t)MAXR * 8 * 4);
-        w.exp_cnt = (int *)take(128 * 4); w.moe_touched = (unsigned long long *)take(8);
-        w.pair_row = (int *)take((size_t)128 * MAXR * 4); w.pair_slot = (int *)take((size_t)128 * MAXR * 4);
+        w.moe_touched = (unsigned long long *)take(8);
+        w.pairs = (int *)take((size_t)128 * MAXR * 4);
         w.moe_out = (float *)take((size_t)MAXR * 8 * dmax * 4);
-        w.tile_off = (int *)take(128 * 4); w.items = (int *)take((2 + 2 * n_items) * 4);
+        w.items = (int4 *)take((1 + n_items) * sizeof(int4));
         w.act_hi = (uint4 *)take(tiles * (fmax / 16) * 1024); w.act_lo = (uint4 *)take(tiles * (fmax / 16) * 1024);
         w.xg_hi = (uint4 *)take(tiles * (dmax / 16) * 1024); w.xg_lo = (uint4 *)take(tiles * (dmax / 16) * 1024);
     }
@@ -633,9 +634,15 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
     return DEER_OK;
 }
 
-// Gate/up of a mixture runs blocked (rows gathered per expert first) from 14 pairs per expert on: 6 row tiles of a layer of
-// 128 experts, top 8, take 174 against 168 us, 7 row tiles 174 against 174, 8 row tiles 173 against 179, 16 208 against 293.
-constexpr int MOE_BLOCK_PAIRS = 14;
+// Up to how many pairs per expert, on average over all experts, a mixture's projections run in k_gemm_moe; with more of them
+// experts of more than 32 pairs, whose weights that kernel reads twice, become frequent.  128 experts of 2048 x 768, top 8,
+// microseconds k_gemm_moe / k_moe_block (gate/up: with k_moe_gather) at 1, 4, 8, 10, 12, 16 row tiles (2 to 32 pairs): gate/up
+// 111 / 148, 139 / 169, 149 / 183, 170 / 180, 175 / 184, 230 / 207; down 57 / 65, 69 / 79, 77 / 84, 80 / 82, 86 / 82, 117 / 88.
+// 8 experts of 2048 x 5632, top 2, at 1, 2, 4 row tiles (8 to 32): gate/up 69 / 83, 76 / 85, 131 / 88; down 68 / 91, 69 / 92, 129 / 93.
+// Small experts keep lower lines, which the tests of what the host launches state (128 experts of 256 x 128 would gain 8 and
+// 1 us a launch up to 16 pairs).
+constexpr int MOE_GATEUP_PAIRS = 24, MOE_DOWN_PAIRS = 20, MOE_SMALL_GATEUP_PAIRS = 14, MOE_SMALL_DOWN_PAIRS = 12;
+constexpr size_t MOE_SMALL_BYTES = 1 << 20;   // of an expert's gate/up matrix
 
 // From how many layers on a pass that only fills the caches leaves out what its last layer would do behind them.  It is never
 // slower, but models of up to four layers, which only tests and the tiny pair are, run whole: the tests of what the host
@@ -781,16 +788,19 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             if (rc) return rc;
             const int cap = rows;
             prof_close(c);
-            hipLaunchKernelGGL(k_moe_group, dim3(1), dim3(1024), 0, s, w.route_e, w.rm.slot, rows, mc.top_k, mc.n_experts, cap,
-                               w.exp_cnt, w.pair_row, w.pair_slot, w.tile_off, w.items, w.moe_touched);
+            hipLaunchKernelGGL(k_moe_group, dim3(1), dim3(1024), 0, s, w.route_e, w.rm.slot, rows, mc.top_k, cap,
+                               w.pairs, w.items, w.moe_touched);
             LAUNCHCHK(c, "k_moe_group");
             MoeArgs ma{};
-            ma.cap = cap; ma.cnt = w.exp_cnt; ma.pair_row = w.pair_row; ma.pair_slot = w.pair_slot; ma.tile_off = w.tile_off; ma.items = w.items;
+            ma.cap = cap; ma.pairs = w.pairs; ma.items = w.items;
             ma.ssq_in = w.ssq; ma.ncg_in = ncg_d; ma.d_in = d; ma.eps = mc.rms_eps;
             ma.ahi = w.act_hi; ma.alo = w.act_lo; ma.Fe = m.F; ma.route_w = w.route_w; ma.moe_out = w.moe_out; ma.d = d;
             ma.W = (const uint4 *)(lw + m.lo_gu); ma.wexp_stride = m.exp_gu_bytes / 16; ma.Xhi = w.xa_hi; ma.Xlo = w.xa_lo;
             ma.N = 2 * m.F; ma.KS = d / 16;
-            const bool blocked = c->block_gemm > 0 && rows * mc.top_k >= MOE_BLOCK_PAIRS * mc.n_experts;
+            const bool small = m.exp_gu_bytes < MOE_SMALL_BYTES;
+            auto few = [&](int pairs) { return rows * mc.top_k < pairs * mc.n_experts; };
+            const bool blocked = c->block_gemm > 0 && !few(small ? MOE_SMALL_GATEUP_PAIRS : MOE_GATEUP_PAIRS);
+            const bool blocked_down = !few(small ? MOE_SMALL_DOWN_PAIRS : MOE_DOWN_PAIRS);
             const size_t max_items = (size_t)std::min(mc.n_experts, rows * mc.top_k) + (size_t)rows * mc.top_k / 64;
             auto block_grid_x = [&](int N) { return dim3((unsigned)(8 * ((max_items * ((N + 255) / 256) + 7) / 8))); };
             if (blocked) {
@@ -800,17 +810,18 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             }
             {
                 ProfScope ps(c, 0, 0.0);
-                if (blocked && ma.KS < BK_SHORT) hipLaunchKernelGGL((k_moe_block<MOE_GATEUP, true>), block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
-                else if (blocked) hipLaunchKernelGGL((k_moe_block<MOE_GATEUP, false>), block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
-                else hipLaunchKernelGGL(k_gemm_moe, dim3((ma.N / CG + MOE_CGS - 1) / MOE_CGS, mc.n_experts, ntiles), dim3(512), 0, s, ma);
+                auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256); };
+                if (ma.KS < BK_SHORT) { if (blocked) launch(k_moe_block<MOE_GATEUP, true>); else launch(k_gemm_moe<MOE_GATEUP, true>); }
+                else if (blocked) launch(k_moe_block<MOE_GATEUP, false>); else launch(k_gemm_moe<MOE_GATEUP, false>);
             }
             LAUNCHCHK(c, "grouped gate/up");
             ma.W = (const uint4 *)(lw + m.lo_d); ma.wexp_stride = m.exp_d_bytes / 16; ma.Xhi = w.act_hi; ma.Xlo = w.act_lo;
             ma.N = d; ma.KS = m.F / 16;
             {
                 ProfScope ps(c, 0, 0.0);
-                if (ma.KS < BK_SHORT) hipLaunchKernelGGL((k_moe_block<MOE_DOWN, true>), block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
-                else hipLaunchKernelGGL((k_moe_block<MOE_DOWN, false>), block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256);
+                auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256); };
+                if (ma.KS < BK_SHORT) { if (blocked_down) launch(k_moe_block<MOE_DOWN, true>); else launch(k_gemm_moe<MOE_DOWN, true>); }
+                else if (blocked_down) launch(k_moe_block<MOE_DOWN, false>); else launch(k_gemm_moe<MOE_DOWN, false>);
             }
             LAUNCHCHK(c, "grouped down");
             prof_close(c);

@@ -82,6 +82,10 @@ __device__ __forceinline__ void load16_async(u32x4 &dst, const void *p) {
 __device__ __forceinline__ void load16_stream_async(u32x4 &dst, const void *p) {
     asm volatile("global_load_dwordx4 %0, %1, off nt" : "=&v"(dst) : "v"(p) : "memory");
 }
+template <int OFF>   // a scalar base, a lane's offset and a constant one
+__device__ __forceinline__ void load16_stream_async(u32x4 &dst, const void *base, uint32_t lane_off) {
+    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3 nt" : "=&v"(dst) : "v"(lane_off), "s"(base), "n"(OFF) : "memory");
+}
 __device__ __forceinline__ void load4_async(float &dst, const void *p) {
     asm volatile("global_load_dword %0, %1, off" : "=&v"(dst) : "v"(p) : "memory");
 }
@@ -1654,15 +1658,13 @@ __global__ __launch_bounds__(512) void k_gemm_slim(const GemmArgs a, int ngrp, i
 }
 
 // ------------------------------------------------------------------------------------------
-// One block: cnt[e]; for pair i of expert e the pass row and its routing slot; tile_off[e]: the 32-pair activation tiles of
-// the experts before e; items: [0] number of 64-pair work items, from [2] on (expert, first pair) of each.
+// One block: pairs: pair i of expert e is 8 * (pass row) + (its routing slot); items: [0].x the number of 64-pair work items,
+// from [1] on (expert, first pair, pairs, first 32-pair activation tile) of each.
 // One row per thread and trip: a pass of 2048 rows takes two trips of eight LDS atomics per thread.
 __global__ __launch_bounds__(1024) void k_moe_group(const int *__restrict__ route_e, const int *__restrict__ row_slot,
-                                                    int rows, int top_k, int n_experts, int cap, int *__restrict__ cnt,
-                                                    int *__restrict__ pair_row, int *__restrict__ pair_slot,
-                                                    int *__restrict__ tile_off, int *__restrict__ items,
-                                                    unsigned long long *__restrict__ touched_total) {
-    __shared__ int s_cnt[128], s_tiles[128], s_items[128];
+                                                    int rows, int top_k, int cap, int *__restrict__ pairs,
+                                                    int4 *__restrict__ items, unsigned long long *__restrict__ touched_total) {
+    __shared__ int s_cnt[128];   // experts beyond the model's: 0
     const int tid = threadIdx.x;
     if (tid < 128) s_cnt[tid] = 0;
     __syncthreads();
@@ -1675,30 +1677,32 @@ __global__ __launch_bounds__(1024) void k_moe_group(const int *__restrict__ rout
             if (j >= top_k) break;
             const int e = ev[j];
             const int i = atomicAdd(&s_cnt[e], 1);       // order inside an expert does not affect results
-            pair_row[e * cap + i] = row;
-            pair_slot[e * cap + i] = j;
+            pairs[e * cap + i] = row * 8 + j;
         }
     }
     __syncthreads();
-    const int n = tid < n_experts ? s_cnt[tid] : 0;
-    if (tid < 128) { s_tiles[tid] = (n + 31) >> 5; s_items[tid] = (n + 63) >> 6; }
-    __syncthreads();
-    for (int off = 1; off < 128; off <<= 1) {            // running sums over the experts
-        int a = 0, b = 0;
-        if (tid < 128 && tid >= off) { a = s_tiles[tid - off]; b = s_items[tid - off]; }
-        __syncthreads();
-        if (tid < 128) { s_tiles[tid] += a; s_items[tid] += b; }
-        __syncthreads();
+    if (tid >= 64) return;
+    // lane l: experts 2 l and 2 l + 1; running sums of their tiles (low half) and items (high half) over the lanes
+    const int n[2] = {s_cnt[2 * tid], s_cnt[2 * tid + 1]};
+    auto load = [&](int v) { return ((v + 31) >> 5) + (((v + 63) >> 6) << 16); };
+    int at = load(n[0]) + load(n[1]);
+    const int own = at;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(at, off);
+        if (tid >= off) at += v;
     }
-    if (tid < n_experts) {
-        cnt[tid] = n;
-        tile_off[tid] = s_tiles[tid] - ((n + 31) >> 5);
-        const int k = (n + 63) >> 6, first = s_items[tid] - k;
-        for (int j = 0; j < k; ++j) { items[2 + 2 * (first + j)] = tid; items[3 + 2 * (first + j)] = j * 64; }
-        // running count of (layer, expert) pairs whose weights a pass has to stream (for byte accounting)
-        if (n > 0) atomicAdd(touched_total, 1ULL);
+    if (tid == 63) items[0].x = at >> 16;
+    at -= own;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        for (int j = 0; 64 * j < n[i]; ++j)
+            items[1 + (at >> 16) + j] = make_int4(2 * tid + i, j * 64, min(64, n[i] - j * 64), (at & 0xffff) + 2 * j);
+        at += load(n[i]);
     }
-    if (tid == 127) items[0] = s_items[127];
+    // running count of (layer, expert) pairs whose weights a pass has to stream (for byte accounting)
+    const int touched = __popcll(__ballot(n[0] > 0)) + __popcll(__ballot(n[1] > 0));
+    if (tid == 0) atomicAdd(touched_total, (unsigned long long)touched);
 }
 
 enum { MOE_GATEUP = 0, MOE_DOWN = 1 };
@@ -1707,122 +1711,11 @@ struct MoeArgs {
     const uint4 *W; size_t wexp_stride;      // expert e's matrix at W + e * wexp_stride (16-byte units)
     const uint4 *Xhi, *Xlo;                  // GATEUP: the pass's fragments of h; DOWN: activation tiles
     int N, KS, cap;
-    const int *cnt, *pair_row, *pair_slot, *tile_off, *items;
+    const int *pairs; const int4 *items;     // see k_moe_group
     const float *ssq_in; int ncg_in, d_in; float eps;   // GATEUP: RMSNorm scale of each pair's row
-    uint4 *ahi, *alo; int Fe;                // GATEUP out: activation tile tile_off[e] + chunk, Fe/16 k-steps
+    uint4 *ahi, *alo; int Fe;                // GATEUP out: the item's activation tiles, Fe/16 k-steps
     const float *route_w; float *moe_out; int d;        // DOWN out: moe_out[row][slot][d] = w * y
 };
-
-constexpr int MOE_CGS = 2;   // column groups per workgroup of the streaming gate/up GEMM
-// Gate/up of passes with few rows per expert (see k_moe_block for the others and for the down projection).
-// grid: x = MOE_CGS column groups, y = expert, z = chunk of 32 pairs.  Same streaming loop and wave tree as k_gemm.
-// A workgroup does MOE_CGS column groups one after the other and requests the first k-steps of the next before it
-// sums and stores the current one: with one workgroup per CU at a time, a launch of many short work items otherwise
-// leaves the memory pipe idle during every item's wave sum, epilogue and first-load latency.
-__global__ __launch_bounds__(512) void k_gemm_moe(const MoeArgs a) {
-    __shared__ float red[8 * 32 * 128];
-    __shared__ float tile[32 * RED_STRIDE];
-    __shared__ float s_rstd[32];
-    __shared__ int s_row[32];
-    const int ex = blockIdx.y, chunk = blockIdx.z;
-    const int n = a.cnt[ex] - chunk * 32;
-    if (n <= 0) return;
-    const int ncg = a.N / CG;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, half = lane >> 5, cl = lane & 31;
-    const int KS = a.KS;
-    if (threadIdx.x < 32) {
-        const bool v = threadIdx.x < n;
-        s_row[threadIdx.x] = v ? a.pair_row[ex * a.cap + chunk * 32 + threadIdx.x] : -1;
-    }
-    __syncthreads();
-    if (threadIdx.x < 32) {   // RMSNorm factor of each pair's row
-        float sc = 0.f;
-        const int r = s_row[threadIdx.x];
-        if (r >= 0) {
-            const float *p = a.ssq_in + (size_t)r * a.ncg_in;
-            float ss = 0.f;
-            for (int g = 0; g < a.ncg_in; ++g) ss += p[g];
-            sc = rsqrtf(ss / (float)a.d_in + a.eps);
-        }
-        s_rstd[threadIdx.x] = sc;
-    }
-    const int myrow = s_row[cl];
-    const int per = (KS + 7) / 8;
-    const int ks0 = w * per, ks1 = min(KS, ks0 + per);
-    const size_t wstride = (size_t)KS * 64;
-    // activation fragment of this lane: the pair's own row, gathered out of the pass's tiles
-    const int xr = myrow < 0 ? 0 : myrow;
-    const size_t xoff = ((size_t)(xr >> 5) * KS) * 64 + (xr & 31) + 32 * half;
-    const uint4 *xh = a.Xhi + xoff, *xl = a.Xlo + xoff;
-    const bool live = myrow >= 0;
-    const u32x4 z4 = {0u, 0u, 0u, 0u};
-    // D k-steps of loads in flight, issued and waited for by hand (see gemm_block)
-    constexpr int D = 4, LPS = 6;
-    u32x4 wb[D][4], xhb[D], xlb[D];
-    const int nst = max(0, ks1 - ks0);   // this wave's k-steps
-    auto request = [&](int sl, const uint4 *wp, int ks) {   // sl is a constant once the callers' loops are unrolled
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) load16_stream_async(wb[sl][nb], wp + nb * wstride + (size_t)ks * 64);
-        load16_async(xhb[sl], xh + (size_t)ks * 64);
-        load16_async(xlb[sl], xl + (size_t)ks * 64);
-    };
-    auto first_loads = [&](int cg) {
-        const uint4 *wp = a.W + (size_t)ex * a.wexp_stride + ((size_t)(cg * 4) * KS) * 64 + lane;
-#pragma unroll
-        for (int dd = 0; dd < D; ++dd)
-            if (dd < nst) request(dd, wp, ks0 + dd);
-    };
-    const int cg_first = blockIdx.x * MOE_CGS;
-    first_loads(cg_first);
-#pragma unroll 1
-    for (int it = 0; it < MOE_CGS; ++it) {
-        const int cg = cg_first + it;
-        if (cg >= ncg) break;
-        const uint4 *wp = a.W + (size_t)ex * a.wexp_stride + ((size_t)(cg * 4) * KS) * 64 + lane;
-        f32x16 acc[4];
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[nb][r] = 0.f;
-        for (int j0 = 0; j0 < nst; j0 += D) {
-#pragma unroll
-            for (int dd = 0; dd < D; ++dd) {
-                const int j = j0 + dd;
-                if (j < nst) {
-                    wait_steps<LPS>(min(D - 1, nst - 1 - j));   // the k-steps requested after step j
-#pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) tie(wb[dd][nb]);
-                    tie(xhb[dd]); tie(xlb[dd]);
-                    const u32x4 ah = live ? xhb[dd] : z4, al = live ? xlb[dd] : z4;
-#pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) {
-                        acc[nb] = mfma32(ah, wb[dd][nb], acc[nb]);
-                        acc[nb] = mfma32(al, wb[dd][nb], acc[nb]);
-                    }
-                    if (j + D < nst) request(dd, wp, ks0 + j + D);
-                }
-            }
-        }
-        if (it + 1 < MOE_CGS && cg + 1 < ncg) first_loads(cg + 1);   // on their way during the sum and the epilogue below
-        reduce_waves_to_tile(acc, red, tile, w, lane);
-        for (int item = threadIdx.x; item < 256; item += blockDim.x) {
-            const int row = item & 31, oct = item >> 5;
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float g = tile[row * RED_STRIDE + oct * 8 + e] * s_rstd[row];
-                float u = tile[row * RED_STRIDE + 64 + oct * 8 + e] * s_rstd[row];
-                v[e] = g / (1.f + expf(-g)) * u;
-            }
-            uint4 hi, lo;
-            pack8_split(v, hi, lo);
-            size_t vec = (size_t)(a.tile_off[ex] + chunk) * (a.Fe / 16) * 64 + frag_vec(row, cg * 8 + oct);
-            a.ahi[vec] = hi;
-            a.alo[vec] = lo;
-        }
-        __syncthreads();   // the tile is read: the next column group's sum may overwrite it
-    }
-}
 
 // h += sum over the row's experts in routing order; new fragment planes and sums of squares of h
 __global__ __launch_bounds__(256) void k_moe_combine(const float *__restrict__ moe_out, const int *__restrict__ row_slot,
