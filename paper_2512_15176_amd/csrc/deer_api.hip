@@ -2,6 +2,7 @@
 // The C ABI is declared in include/deer.h.  Nothing here allocates device memory.
 #include "deer_kernels.hpp"
 #include "deer_block.hpp"
+#include "deer_stream.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -39,6 +40,7 @@ constexpr int PREFILL_TILES = 128;   // row tiles that a prefill pass may have a
 constexpr int PART_TILES_MIN = 16;   // split-K partials exist for passes of up to max(2 * batch, 16) row tiles
 constexpr int MAX_NS = 32;          // key-range splits of block attention
 constexpr size_t H_UP_MAX = 1 << 20;  // most page-locked host memory of a context for uploads
+constexpr int LM_TILES = 2;          // LM heads of up to so many row tiles run in k_lm_head
 constexpr int SLIM_MAX_D = 4096, SLIM_TILES = 4;   // passes of up to 4 row tiles of a model up to this width may use k_gemm_slim (64 sums of squares per row)
 constexpr int NARROW_MAX_D = 1024;  // residual width up to which a dense model's O projection runs in 32-column workgroups
 constexpr int NEXT_SPAN_BYTES = 16 << 10;      // fetched ahead per 32-column block of a next-launch workgroup (4 blocks: 8 loads per thread)
@@ -530,6 +532,16 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     SlimPlan sp;
     if (!narrow && force_S <= 0 && a.slim) sp = plan_slim(EPI, a.N, a.KS, ntiles, a.hd, a.ssq_sub, c->wk.part_floats);
     const bool slim = sp.C > 0 && sp.us < 0.98 * stream_small_us(a.N, a.KS, MT, zg, wide_S);
+    if constexpr (EPI == EPI_LMHEAD) if (c->slim && ntiles <= LM_TILES && !c->force_nb) {
+        ProfScope ps(c, 0, (double)a.N * K * 2.0);
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((a.N + 255) / 256), dim3(256), 0, c->stream, a, ntiles); };
+        const bool sh = a.KS < BK_SHORT;
+        if (ntiles == 1) { if (sh) launch(k_lm_head<4, 1, 2, true, 3>); else launch(k_lm_head<4, 1, 2, false, 3>); }
+        else if (sh) launch(k_lm_head<4, 2, 2, true, 2>);
+        else launch(k_lm_head<4, 2, 2, false, 2>);
+        LAUNCHCHK(c, "k_lm_head");
+        return DEER_OK;
+    }
     if constexpr (EPI != EPI_ROUTER) if (c->block_gemm > 0 && ntiles > 1) {
         const BlockPlan bp = c->force_nb ? forced_block(c, a.N, a.KS, ntiles, EPI == EPI_LMHEAD)
                                          : plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);

@@ -323,7 +323,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
             }
         }
     } else if (EPI == EPI_LMHEAD) {
-        const int V = a.N, sub = lane & 7;   // 8 lanes per row, 16 columns each; 8 rows at a time
+        const int V = a.N, sub = lane & 7;   // 8 lanes per row, 16 columns each (4 of every 32: a store fills whole lines); 8 rows at a time
         const float T = a.T, invT = T > 0.f ? 1.f / T : 1.f;
 #pragma unroll 1
         for (int r0 = 0; r0 < 32; r0 += 8) {
@@ -333,22 +333,26 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
             const bool live = (int)lm < a.n_lm && (int)lm % opaque_s(a.k) >= a.k_lo;
             float m = -INFINITY, gm = -INFINITY, se = 0.f;
             int idx = 0x7fffffff, gidx = 0x7fffffff;
-            const float4 *tp = (const float4 *)(tile + lr * BT_STRIDE + sub * 16);   // (short loops over the tile: see epi_lmhead)
+            const float4 *tp = (const float4 *)(tile + lr * BT_STRIDE) + sub;   // (short loops over the tile: see epi_lmhead)
             if (live) {
-                float4 *q = a.logits ? (float4 *)(a.logits + lm * V + (size_t)cg * CG + sub * 16) : nullptr;
+                float4 *q = a.logits ? (float4 *)(a.logits + lm * V + (size_t)cg * CG) + sub : nullptr;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float4 z = make_float4(tp[e].x * sc, tp[e].y * sc, tp[e].z * sc, tp[e].w * sc);
-                    if (q) q[e] = z;
-                    const int v = cg * CG + sub * 16 + 4 * e;
+                    const float4 z = make_float4(tp[8 * e].x * sc, tp[8 * e].y * sc, tp[8 * e].z * sc, tp[8 * e].w * sc);
+                    if (q) q[8 * e] = z;
+                    const int v = cg * CG + 4 * (8 * e + sub);
                     argmax_merge(m, idx, z.x, v); argmax_merge(m, idx, z.y, v + 1); argmax_merge(m, idx, z.z, v + 2); argmax_merge(m, idx, z.w, v + 3);
                 }
                 if (T > 0.f && a.draw) {
                     const uint64_t key = row_key(a.seed, TAG_DRAFT, (uint64_t)a.rm.seq[lm], (uint64_t)a.rm.pos[lm]);
-#pragma unroll 2
-                    for (int e = 0; e < 16; ++e) {
-                        const int v = cg * CG + sub * 16 + e;
-                        argmax_merge(gm, gidx, ((const float *)tp)[e] * sc * invT + gumbel(key, (uint64_t)v), v);
+                    int v = cg * CG + 4 * sub;
+#pragma unroll 1
+                    for (int e = 0; e < 4; ++e, v += 32) {
+                        const float4 z = make_float4(tp[8 * e].x * sc, tp[8 * e].y * sc, tp[8 * e].z * sc, tp[8 * e].w * sc);
+                        argmax_merge(gm, gidx, z.x * invT + gumbel(key, (uint64_t)v), v);
+                        argmax_merge(gm, gidx, z.y * invT + gumbel(key, (uint64_t)(v + 1)), v + 1);
+                        argmax_merge(gm, gidx, z.z * invT + gumbel(key, (uint64_t)(v + 2)), v + 2);
+                        argmax_merge(gm, gidx, z.w * invT + gumbel(key, (uint64_t)(v + 3)), v + 3);
                     }
                 }
             }
@@ -360,8 +364,11 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs &a, float *tile, in
                 argmax_merge(gm, gidx, g2, gi2);
             }
             if (live && T > 0.f) {
-#pragma unroll 4
-                for (int e = 0; e < 16; ++e) se += expf((((const float *)tp)[e] * sc - m) * invT);
+#pragma unroll 1
+                for (int e = 0; e < 4; ++e) {
+                    const float4 z = tp[8 * e];
+                    se += expf((z.x * sc - m) * invT); se += expf((z.y * sc - m) * invT); se += expf((z.z * sc - m) * invT); se += expf((z.w * sc - m) * invT);
+                }
             }
 #pragma unroll
             for (int off = 1; off < 8; off <<= 1) se += shx(se, off);
@@ -675,167 +682,6 @@ __global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) 
             const float4 y = *(const float4 *)(tile + r * BT_STRIDE + c4);
             *(float4 *)(a.moe_out + (size_t)p * a.d + (size_t)cg * CG + c4) = make_float4(y.x * g, y.y * g, y.z * g, y.w * g);
         }
-    }
-}
-
-// Grouped expert GEMMs of passes with few rows per expert, where the expert weights' stream is all there is.  A workgroup owns
-// 256 columns of one item of k_moe_group and multiplies up to 32 of its pairs at a time; wave w has 64 of the columns: two
-// neighbouring 32-column blocks, of gate/up the gate and the up block of 32 channels.  Its weights, which no other wave needs,
-// go straight to registers, eight k-steps ahead; the activations, which all four waves need, go through the LDS four k-steps
-// at a time, with one barrier for those.  Gate/up gathers its rows out of the pass's fragments (lanes past the last pair
-// repeat it).  The products are taken as W^T X^T: a lane then holds 16 columns of one row, and both epilogues run from
-// registers.  The sums are folded as in block_loop.
-// Bound: HBM.  Layer of 128 experts, top 8, d = 2048, expert width 768, microseconds before -> now: gate/up (a workgroup of
-// eight waves with an eighth of K each and their sums through the LDS) at 1 row tile, 111 experts or 698 MB, 125 -> 116 (6.0 TB/s),
-// at 4 row tiles, 805 MB, 160 -> 139; down (k_moe_block: two row tiles of products and LDS for one to eight pairs, 36 KB of
-// weights on their way per compute unit against 96 to 192 here) 72 -> 60 and 80 -> 70.  Three workgroups per compute unit; with
-// two 2 % slower.
-constexpr int MF_KS = 4;   // k-steps per stage: every contraction here is a multiple (d_model of 128, expert widths of 64)
-struct GemmMoeSmem { uint4 x[3][MF_KS][2][64]; };   // [stage][k-step][hi, lo][lane]
-
-template <int MODE, bool SHORT>
-__global__ __launch_bounds__(256, 3) void k_gemm_moe(const MoeArgs a, int ncb) {
-    __shared__ __attribute__((aligned(16))) GemmMoeSmem sm;
-    const int total = a.items[0].x * ncb, per8 = (total + 7) >> 3;
-    const int lin = blockIdx.x, i = (lin & 7) * per8 + (lin >> 3);
-    if ((lin >> 3) >= per8 || i >= total) return;
-    const int item = __builtin_amdgcn_readfirstlane(i / opaque_s(ncb)), cb = i - item * ncb;
-    const int4 it = a.items[1 + item];
-    const int ex = it.x, n_all = it.z;
-    const int w = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
-    const int KS = a.KS, nq = KS / MF_KS, fold = block_fold(KS) / MF_KS;
-    const int unit = cb * 4 + w, units = a.N / 64;   // this wave's 64 columns; past the matrix: the last ones again, not stored
-    const int uu = min(unit, units - 1);
-    const int b0 = MODE == MOE_GATEUP ? (uu >> 1) * 4 + (uu & 1) : 2 * uu, b1 = MODE == MOE_GATEUP ? b0 + 2 : b0 + 1;
-    const uint4 *we = a.W + (size_t)ex * a.wexp_stride;
-#pragma unroll 1
-    for (int first = 0; first < n_all; first += 32) {   // row tiles of the item (the second one finds the weights in the L2)
-        const int n = min(32, n_all - first), at = it.w + (first >> 5);
-        const int *pairs = a.pairs + (size_t)ex * a.cap + it.y + first;
-        const uint32_t lo = (opaque_tid() & 63) * 16;
-        float pr_f;
-        if (MODE == MOE_GATEUP) load4_async(pr_f, pairs + min((int)(lo >> 4) & 31, n - 1));
-        u32x4 wb[2][MF_KS][2];
-        const uint4 *w0 = we + (size_t)b0 * KS * 64, *w1 = we + (size_t)b1 * KS * 64;   // the stage requested next
-        auto request_w = [&](auto set_c, auto j_c) {
-            constexpr int set = decltype(set_c)::value, j = decltype(j_c)::value;
-            load16_stream_async<j * 1024>(wb[set][j][0], w0, lo);
-            load16_stream_async<j * 1024>(wb[set][j][1], w1, lo);
-            if (j == MF_KS - 1) { w0 += MF_KS * 64; w1 += MF_KS * 64; }
-        };
-        auto request_w4 = [&](auto set_c) {
-            request_w(set_c, std::integral_constant<int, 0>{}); request_w(set_c, std::integral_constant<int, 1>{});
-            request_w(set_c, std::integral_constant<int, 2>{}); request_w(set_c, std::integral_constant<int, 3>{});
-        };
-        request_w4(std::integral_constant<int, 0>{});
-        uint32_t vo = lo;
-        size_t tile = (size_t)at * KS * 1024;
-        if (MODE == MOE_GATEUP) {
-            wait_loads<2 * MF_KS>();
-            tie(pr_f);
-            const int pr = __float_as_int(pr_f) >> 3;   // this lane's row
-            vo = (uint32_t)(pr >> 5) * (uint32_t)KS * 1024u + (pr & 31) * 16 + (lo & 512);
-            tile = 0;
-        }
-        const char *xh = (const char *)a.Xhi + tile, *xl = (const char *)a.Xlo + tile;
-        auto request_x = [&](int slot, int q) {   // this wave's k-step of stage q
-            const char *ph = xh + (size_t)(q * MF_KS + w) * 1024, *pl = xl + (size_t)(q * MF_KS + w) * 1024;
-            asm volatile("" : "+s"(ph), "+s"(pl));   // scalar addresses
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(ph + vo),
-                                             (void __attribute__((address_space(3))) *)sm.x[slot][w][0], 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1))) *)(pl + vo),
-                                             (void __attribute__((address_space(3))) *)sm.x[slot][w][1], 16, 0, 0);
-        };
-        request_x(0, 0);
-        if (nq > 1) {
-            request_x(1, 1);
-            request_w4(std::integral_constant<int, 1>{});
-        }
-        f32x16 acc[2], sum[2];
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) { acc[b][r] = 0.f; sum[b][r] = 0.f; }
-        int slot = 0;
-        constexpr int LPS = 2 + 2 * MF_KS;   // loads of a stage
-        auto stage = [&](auto set_c, int q) {
-            constexpr int set = decltype(set_c)::value;
-            if (q > 0 && q % fold == 0) {   // see BK_SHORT
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float s = sum[b][r], c = acc[b][r], t = s + c;
-                        sum[b][r] = t;
-                        acc[b][r] = SHORT ? __builtin_amdgcn_fmed3f(c - (t - s), -3.4028234e38f, 3.4028234e38f) : 0.f;
-                        if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (registers)
-                    }
-            }
-            if (q + 1 < nq) wait_loads<LPS>(); else wait_loads<0>();   // stage q has landed
-#pragma unroll
-            for (int j = 0; j < MF_KS; ++j) { tie(wb[set][j][0]); tie(wb[set][j][1]); }
-            barrier_keep_loads();   // everybody's share of it has, and everybody has read stage q - 1
-            const bool more = q + 2 < nq;
-            if (more) request_x(slot == 0 ? 2 : slot - 1, q + 2);
-            const uint32_t xa = lds_addr32(&sm) + slot * (MF_KS * 2048) + lo;
-            u32x4 x[2][2];
-            lds_frag<0>(x[0][0], xa); lds_frag<1024>(x[0][1], xa);
-            auto step = [&](auto j_c) {
-                constexpr int j = decltype(j_c)::value;
-                if constexpr (j + 1 < MF_KS) { lds_frag<(j + 1) * 2048>(x[(j + 1) & 1][0], xa); lds_frag<(j + 1) * 2048 + 1024>(x[(j + 1) & 1][1], xa); }
-                wait_lds<j + 1 < MF_KS ? 2 : 0>();
-                tie(x[j & 1][0]); tie(x[j & 1][1]);
-                acc[0] = mfma32(wb[set][j][0], x[j & 1][0], acc[0]);
-                acc[1] = mfma32(wb[set][j][1], x[j & 1][0], acc[1]);
-                acc[0] = mfma32(wb[set][j][0], x[j & 1][1], acc[0]);
-                acc[1] = mfma32(wb[set][j][1], x[j & 1][1], acc[1]);
-                if (more) request_w(set_c, j_c);
-            };
-            step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
-            step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
-            slot = slot == 2 ? 0 : slot + 1;
-        };
-        for (int q = 0; q < nq; q += 2) {
-            stage(std::integral_constant<int, 0>{}, q);
-            if (q + 1 < nq) stage(std::integral_constant<int, 1>{}, q + 1);
-        }
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[b][r] += sum[b][r];
-        const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
-        // lane (row, half) holds columns 8 q + 4 half .. + 3 of each block, q = 0 .. 3, in registers 4 q ..
-        if (MODE == MOE_GATEUP) {
-            const float rs = wave_rstd(a.ssq_in, pairs[min(row, n - 1)] >> 3, half, a.ncg_in, a.d_in, a.eps);
-            if (unit < units) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float ge = acc[0][4 * q + e] * rs;
-                        v[e] = ge / (1.f + expf(-ge)) * (acc[1][4 * q + e] * rs);
-                    }
-                    const uint32_t h0 = f2bf2(v[0], v[1]), h1 = f2bf2(v[2], v[3]);
-                    const uint32_t l0 = f2bf2(v[0] - __uint_as_float(h0 << 16), v[1] - __uint_as_float(h0 & 0xffff0000u));
-                    const uint32_t l1 = f2bf2(v[2] - __uint_as_float(h1 << 16), v[3] - __uint_as_float(h1 & 0xffff0000u));
-                    const size_t vec = (size_t)at * (a.Fe / 16) * 64 + frag_vec(row, unit * 4 + q);
-                    ((uint2 *)(a.ahi + vec))[half] = make_uint2(h0, h1);
-                    ((uint2 *)(a.alo + vec))[half] = make_uint2(l0, l1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        } else if (row < n && unit < units) {
-            const int pr = pairs[row];
-            const float g = a.route_w[pr];
-            float *o = a.moe_out + (size_t)pr * a.d + (size_t)unit * 64 + 4 * half;
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *(float4 *)(o + 32 * b + 8 * q) = make_float4(acc[b][4 * q] * g, acc[b][4 * q + 1] * g, acc[b][4 * q + 2] * g, acc[b][4 * q + 3] * g);
-        }
-        if (first + 32 < n_all) barrier_keep_loads();   // everybody has read the last stages before the next row tile's arrive
     }
 }
 
