@@ -24,6 +24,8 @@ __device__ __forceinline__ void stream_loop(f32x16 (&acc)[MT][C], const uint4 *(
                                             int nq, int fold, int w, uint32_t lo, F lane_offset) {
     constexpr int P = 2 * MT, XP = SK * P / NW, LPS = XP + SK * C;   // planes; fragments of X, loads per wave and stage
     static_assert(SK * P % NW == 0 && 2 * LPS <= 63, "the counter of loads in flight has six bits");
+    // (a path around the loop would leave the first requests unused, their registers in other hands while the data is on its way)
+    __builtin_assume(nq >= 1);
     u32x4 wb[2][SK][C];
     auto request_w = [&](auto set_c, auto j_c) {
         constexpr int set = decltype(set_c)::value, j = decltype(j_c)::value;
