@@ -57,10 +57,9 @@ __device__ __forceinline__ void block_wait(BlockFrags<NB> &f) {
                      : "+v"(f.w[0]), "+v"(f.w[1]), "+v"(f.xh[0]), "+v"(f.xh[1]), "+v"(f.xl[0]), "+v"(f.xl[1]) :: "memory");
 }
 
-// WC: waves side by side.  The workgroup's row tiles are 2 * 4 / WC, its column tiles NB * WC.
-template <int NB, int NST, int WC = 2>
+template <int NB, int NST>
 struct BlockSmem {
-    static constexpr int RT = 8 / WC, CT = NB * WC, FRAGS = CT + 2 * RT;   // per stage: weight column tiles, row tiles hi, row tiles lo
+    static constexpr int RT = BK_RT, CT = 2 * NB, FRAGS = CT + 2 * RT;   // per stage: weight column tiles, row tiles hi, row tiles lo
     union {
         uint4 st[NST][FRAGS * 64];
         float tile[4][32 * BT_STRIDE];                 // epilogue: one 32 x 128 tile per wave
@@ -76,14 +75,14 @@ struct BlockSmem {
 // What is not a product has to be short or stand between products: a matrix instruction occupies its pipe for 32 cycles
 // and the wave's other instructions issue meanwhile.  The steady state therefore runs without any condition (NST k-steps
 // per trip, buffers at constant offsets); the last up to 2 NST - 1 k-steps take the general form.
-template <int NB, int NST, int WC, int LPW, bool SHORT>
+template <int NB, int NST, int LPW, bool SHORT>
 __device__ __forceinline__ void block_loop(f32x16 (&acc)[2][NB], const char *(&base)[LPW], const uint32_t (&vo)[LPW],
-                                           BlockSmem<NB, NST, WC> &sm, int n, int fold, int w, int lane) {
-    using SM = BlockSmem<NB, NST, WC>;
+                                           BlockSmem<NB, NST> &sm, int n, int fold, int w, int lane) {
+    using SM = BlockSmem<NB, NST>;
     constexpr int SB = SM::FRAGS * 1024;
     static_assert((NST == 4 || NST == 8) && (NST - 1) * LPW <= 63, "the loops below are written for these; the counter of loads in flight has six bits");
     const uint32_t s0 = lds_addr32(sm.st[0]) + lane * 16;
-    const uint32_t ow = s0 + (w % WC) * NB * 1024, ox = s0 + (SM::CT + (w / WC) * 2) * 1024;
+    const uint32_t ow = s0 + (w & 1) * NB * 1024, ox = s0 + (SM::CT + (w >> 1) * 2) * 1024;
     // this wave's i-th fragment of the next k-step to be requested
     auto request1 = [&](int buf, int i) {
         asm volatile("" : "+s"(base[i]));   // stays a scalar address
@@ -524,7 +523,7 @@ __global__ __launch_bounds__(256, sizeof(BlockSmem<NB, NST>) <= 80 * 1024 ? 2 : 
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
-        block_loop<NB, NST, 2, LPW, SHORT>(acc, base, vo, sm, n, block_fold(KS), w, ln);
+        block_loop<NB, NST, LPW, SHORT>(acc, base, vo, sm, n, block_fold(KS), w, ln);
 
         const int lane = opaque_tid() & 63;
         if (nsh > 1) {
@@ -594,94 +593,6 @@ __global__ __launch_bounds__(256) void k_moe_gather(const float *__restrict__ h,
         const size_t vec = (size_t)(at + tile) * (a.d_in / 16) * 64 + frag_vec(row, cg * 16 + oct);
         xhi[vec] = hi;
         xlo[vec] = lo;
-    }
-}
-
-// Grouped expert GEMMs of passes with several rows per expert (k_gemm_moe does the others).  A workgroup
-// owns up to 64 (row, expert) pairs of one expert and 256 columns (four waves side by side, 64 columns each); work items
-// (k_moe_group) are blocks of 64 pairs.  64 rows rather than 128: the pairs of an expert are few and uneven, and rows past
-// them are multiplied for nothing.  Consecutive workgroups of an XCD take the column blocks of one item, then the expert's
-// next item, whose weights are then in that L2.
-// Bound: the matrix cores and the L2 -> LDS path.  Layer of 128 experts, top 8, d = 2048, expert width 768, microseconds at
-// 16 / 64 / 128 row tiles against a streaming kernel with 32-pair chunks: down 86 / 162 / 283 for 137 / 429 / 826, gate/up with
-// the gather before it 208 / 325 / 549 for 293 / 1057 / 2370.
-template <int MODE, bool SHORT>
-__global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) {
-    constexpr int NB = 2, NST = 4, WC = 4;
-    using SM = BlockSmem<NB, NST, WC>;
-    constexpr int LPW = SM::FRAGS / 4;
-    __shared__ __attribute__((aligned(16))) SM sm;
-    const int total = a.items[0].x * ncb, per8 = (total + 7) >> 3;
-    const int lin = blockIdx.x, i = (lin & 7) * per8 + (lin >> 3);
-    if ((lin >> 3) >= per8 || i >= total) return;
-    const int item = i / opaque_s(ncb), cb = i - item * ncb;
-    const int4 it = a.items[1 + item];
-    const int ex = it.x, n = it.z, at = it.w;          // its expert, pairs, first activation tile
-    const int tidx = opaque_tid();
-    const int w = __builtin_amdgcn_readfirstlane(tidx >> 6), lane = tidx & 63, half = lane >> 5;
-    const int KS = a.KS;
-    const int *pairs = a.pairs + (size_t)ex * a.cap + it.y;
-    const char *base[LPW];
-    uint32_t vo[LPW];
-#pragma unroll
-    for (int j = 0; j < LPW; ++j) {
-        const int f = w * LPW + j;
-        vo[j] = lane * 16;
-        if (f < SM::CT) base[j] = (const char *)(a.W + (size_t)ex * a.wexp_stride + (size_t)min(cb * SM::CT + f, a.N / 32 - 1) * KS * 64);
-        else {
-            const int x = f - SM::CT, rt = min(x & (SM::RT - 1), (n - 1) >> 5);   // a row tile without pairs repeats the first one
-            base[j] = (const char *)((x < SM::RT ? a.Xhi : a.Xlo) + (size_t)(at + rt) * KS * 64);
-        }
-    }
-    f32x16 acc[2][NB];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[mt][nb][r] = 0.f;
-    block_loop<NB, NST, WC, LPW, SHORT>(acc, base, vo, sm, KS, block_fold(KS), w, lane);
-    __syncthreads();   // every wave has read the ring: the epilogue tiles reuse it
-    // two waves make a column group: tile (group w >> 1, row tile mt); wave w finishes row tile w & 1 of its group
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) wave_park<NB>(acc[mt], sm.tile[(w >> 1) * 2 + mt], (w & 1) * 64, lane);
-    __syncthreads();
-    const int mt = w & 1, cg = cb * 2 + (w >> 1), row = lane & 31;
-    if (mt * 32 >= n || cg * CG >= a.N) return;
-    const float *tile = sm.tile[w];
-    if (MODE == MOE_GATEUP) {
-        const float rs = wave_rstd(a.ssq_in, pairs[min(mt * 32 + row, n - 1)] >> 3, half, a.ncg_in, a.d_in, a.eps);
-#pragma unroll 1
-        for (int j = 0; j < 4; ++j) {
-            const int oct = 2 * j + half;
-            const float *g = tile + row * BT_STRIDE + oct * 8, *u = g + 64;
-            float v[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float ge = g[e] * rs;
-                v[e] = ge / (1.f + expf(-ge)) * (u[e] * rs);
-            }
-            uint4 hi, lo;
-            pack8_split(v, hi, lo);
-            const size_t vec = (size_t)(at + mt) * (a.Fe / 16) * 64 + frag_vec(row, cg * 8 + oct);
-            a.ahi[vec] = hi;
-            a.alo[vec] = lo;
-        }
-    } else {
-        // lane l knows pair l & 31 of the tile; rows 2 j + half, 512 bytes each
-        const int q = mt * 32 + row;
-        const int pr = q < n ? pairs[q] : -1;
-        const float wgt = q < n ? a.route_w[pr] : 0.f;
-        const int c4 = row * 4;
-#pragma unroll 4
-        for (int j = 0; j < 16; ++j) {
-            const int r = 2 * j + half;
-            const int p = __builtin_amdgcn_ds_bpermute(r << 2, pr);
-            const float g = __int_as_float(__builtin_amdgcn_ds_bpermute(r << 2, __float_as_int(wgt)));
-            if (p < 0) continue;
-            const float4 y = *(const float4 *)(tile + r * BT_STRIDE + c4);
-            *(float4 *)(a.moe_out + (size_t)p * a.d + (size_t)cg * CG + c4) = make_float4(y.x * g, y.y * g, y.z * g, y.w * g);
-        }
     }
 }
 

@@ -82,9 +82,11 @@ __device__ __forceinline__ void load16_async(u32x4 &dst, const void *p) {
 __device__ __forceinline__ void load16_stream_async(u32x4 &dst, const void *p) {
     asm volatile("global_load_dwordx4 %0, %1, off nt" : "=&v"(dst) : "v"(p) : "memory");
 }
-template <int OFF>   // a scalar base, a lane's offset and a constant one
-__device__ __forceinline__ void load16_stream_async(u32x4 &dst, const void *base, uint32_t lane_off) {
-    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3 nt" : "=&v"(dst) : "v"(lane_off), "s"(base), "n"(OFF) : "memory");
+// a scalar base, a lane's offset and a constant one; NT: non-temporal
+template <int OFF, bool NT>
+__device__ __forceinline__ void load16_async(u32x4 &dst, const void *base, uint32_t lane_off) {
+    if constexpr (NT) asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3 nt" : "=&v"(dst) : "v"(lane_off), "s"(base), "n"(OFF) : "memory");
+    else asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=&v"(dst) : "v"(lane_off), "s"(base), "n"(OFF) : "memory");
 }
 __device__ __forceinline__ void load4_async(float &dst, const void *p) {
     asm volatile("global_load_dword %0, %1, off" : "=&v"(dst) : "v"(p) : "memory");

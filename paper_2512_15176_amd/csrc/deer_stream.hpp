@@ -1,5 +1,5 @@
-// GEMMs that stream a matrix once for few rows: the expert projections of decoding passes and the LM heads of up to four row
-// tiles.  They leave a wave so many columns that K need not be shared among waves.
+// GEMMs with columns enough that K need not be shared among waves: the expert projections of a mixture and the LM heads of up
+// to two row tiles.
 //
 // A wave owns C 32-column blocks over the whole of K.  Its weights, which no other wave needs, go straight to registers, eight
 // k-steps ahead; the activations, which all waves of a workgroup need, go through the LDS in stages of four k-steps, with one
@@ -19,7 +19,7 @@ template <int MT> struct StreamRing { uint4 x[3][SK][2 * MT][64]; };   // [stage
 // wp[c]: the blocks; xb[i] + lane offset: this wave's fragments of stage 0 (fragment f = w * XP + i: k-step f / (2 MT), plane f
 // % (2 MT)); lane_offset: called behind the first weights' requests, with 4 C + `extra` loads in flight at most.
 // The sums are folded as in block_loop (see BK_SHORT).  Ends with every LDS read of this wave done and no loads in flight.
-template <int NW, int MT, int C, bool SHORT, typename F>
+template <int NW, int MT, int C, bool SHORT, bool ONCE, typename F>
 __device__ __forceinline__ void stream_loop(f32x16 (&acc)[MT][C], const uint4 *(&wp)[C], const char *(&xb)[SK * 2 * MT / NW], StreamRing<MT> &ring,
                                             int nq, int fold, int w, uint32_t lo, F lane_offset) {
     constexpr int P = 2 * MT, XP = SK * P / NW, LPS = XP + SK * C;   // planes; fragments of X, loads per wave and stage
@@ -31,7 +31,7 @@ __device__ __forceinline__ void stream_loop(f32x16 (&acc)[MT][C], const uint4 *(
         constexpr int set = decltype(set_c)::value, j = decltype(j_c)::value;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            load16_stream_async<j * 1024>(wb[set][j][c], wp[c], lo);
+            load16_async<j * 1024, ONCE>(wb[set][j][c], wp[c], lo);
             if (j == SK - 1) wp[c] += SK * 64;
         }
     };
@@ -117,6 +117,27 @@ __device__ __forceinline__ void stream_loop(f32x16 (&acc)[MT][C], const uint4 *(
             for (int r = 0; r < 16; ++r) acc[mt][c][r] += sum[mt][c][r];
 }
 
+// SiLU(gate) * up of 32 channels of one row tile, from the accumulators of their two blocks (lane (row, half) holds columns 8 q + 4 half
+// .. + 3 of a block in registers 4 q ..), into activation tile `tile`: channels 32 unit ..
+__device__ __forceinline__ void moe_swiglu(const MoeArgs &a, const f32x16 &gate, const f32x16 &up, float rs, int tile, int unit, int row, int half) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float ge = gate[4 * q + e] * rs;
+            v[e] = ge / (1.f + expf(-ge)) * (up[4 * q + e] * rs);
+        }
+        const uint32_t h0 = f2bf2(v[0], v[1]), h1 = f2bf2(v[2], v[3]);
+        const uint32_t l0 = f2bf2(v[0] - __uint_as_float(h0 << 16), v[1] - __uint_as_float(h0 & 0xffff0000u));
+        const uint32_t l1 = f2bf2(v[2] - __uint_as_float(h1 << 16), v[3] - __uint_as_float(h1 & 0xffff0000u));
+        const size_t vec = (size_t)tile * (a.Fe / 16) * 64 + frag_vec(row, unit * 4 + q);
+        ((uint2 *)(a.ahi + vec))[half] = make_uint2(h0, h1);
+        ((uint2 *)(a.alo + vec))[half] = make_uint2(l0, l1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // Grouped expert GEMMs of passes with few rows per expert, where the expert weights' stream is all there is.  A workgroup owns
 // 256 columns of one item of k_moe_group and multiplies up to 32 of its pairs at a time; a wave has 64 of the columns, of
 // gate/up the gate and the up block of 32 channels.  Gate/up gathers its rows out of the pass's fragments (lanes past the last
@@ -152,7 +173,7 @@ __global__ __launch_bounds__(256, 3) void k_gemm_moe(const MoeArgs a, int ncb) {
         const size_t xo = ((MODE == MOE_GATEUP ? 0 : (size_t)at * KS) + w) * 1024;
         const char *xb[2] = {(const char *)a.Xhi + xo, (const char *)a.Xlo + xo};
         f32x16 acc[1][2];
-        stream_loop<4, 1, 2, SHORT>(acc, wp, xb, ring, KS / SK, block_fold(KS) / SK, w, lo, [&]() -> uint32_t {
+        stream_loop<4, 1, 2, SHORT, true>(acc, wp, xb, ring, KS / SK, block_fold(KS) / SK, w, lo, [&]() -> uint32_t {
             if (MODE == MOE_DOWN) return lo;
             wait_loads<2 * SK>();
             tie(pr_f);
@@ -160,27 +181,9 @@ __global__ __launch_bounds__(256, 3) void k_gemm_moe(const MoeArgs a, int ncb) {
             return (uint32_t)(pr >> 5) * (uint32_t)KS * 1024u + (pr & 31) * 16 + (lo & 512);
         });
         const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
-        // lane (row, half) holds columns 8 q + 4 half .. + 3 of each block, q = 0 .. 3, in registers 4 q ..
         if (MODE == MOE_GATEUP) {
             const float rs = wave_rstd(a.ssq_in, pairs[min(row, n - 1)] >> 3, half, a.ncg_in, a.d_in, a.eps);
-            if (unit < units) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float ge = acc[0][0][4 * q + e] * rs;
-                        v[e] = ge / (1.f + expf(-ge)) * (acc[0][1][4 * q + e] * rs);
-                    }
-                    const uint32_t h0 = f2bf2(v[0], v[1]), h1 = f2bf2(v[2], v[3]);
-                    const uint32_t l0 = f2bf2(v[0] - __uint_as_float(h0 << 16), v[1] - __uint_as_float(h0 & 0xffff0000u));
-                    const uint32_t l1 = f2bf2(v[2] - __uint_as_float(h1 << 16), v[3] - __uint_as_float(h1 & 0xffff0000u));
-                    const size_t vec = (size_t)at * (a.Fe / 16) * 64 + frag_vec(row, unit * 4 + q);
-                    ((uint2 *)(a.ahi + vec))[half] = make_uint2(h0, h1);
-                    ((uint2 *)(a.alo + vec))[half] = make_uint2(l0, l1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
+            if (unit < units) moe_swiglu(a, acc[0][0], acc[0][1], rs, at, unit, row, half);
         } else if (row < n && unit < units) {
             const int pr = pairs[row];
             const float g = a.route_w[pr];
@@ -192,6 +195,73 @@ __global__ __launch_bounds__(256, 3) void k_gemm_moe(const MoeArgs a, int ncb) {
                     *(float4 *)(o + 32 * b + 8 * q) = make_float4(acc[0][b][4 * q] * g, acc[0][b][4 * q + 1] * g, acc[0][b][4 * q + 2] * g, acc[0][b][4 * q + 3] * g);
         }
         if (first + 32 < n_all) barrier_keep_loads();   // everybody has read the last stages before the next row tile's arrive
+    }
+}
+
+// Grouped expert GEMMs of passes with several rows per expert: a workgroup owns up to 64 (row, expert) pairs of one expert, whose
+// input rows lie gathered in its activation tiles, and 256 columns.  64 rows rather than 128: the pairs of an expert are few and
+// uneven, and rows past them are multiplied for nothing.  Consecutive workgroups of an XCD take the column blocks of one item,
+// then the expert's next item, whose weights are then in that L2.
+// Bound: the path from the L2 (12 KB per k-step; a compute unit's loads come back in order, so that weights from HBM hold up
+// activations from the L2).  Layer of 128 experts, top 8, d = 2048, expert width 768, microseconds with both operands through the
+// LDS and a barrier per k-step -> here, at 16, 32, 64 row tiles: gate/up 202 -> 188, 233 -> 226, 292 -> 281; down 88 -> 89, 111 -> 108,
+// 159 -> 151.
+template <int MODE>
+union MoeBlockSmem {
+    StreamRing<2> ring;
+    float4 y[4][8 * 66];   // MOE_DOWN: a wave's results of one row tile, 64 columns per row (see k_lm_head)
+};
+
+template <int MODE, bool SHORT>
+__global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) {
+    __shared__ __attribute__((aligned(16))) MoeBlockSmem<MODE> sm;
+    const int total = a.items[0].x * ncb, per8 = (total + 7) >> 3;
+    const int lin = blockIdx.x, i = (lin & 7) * per8 + (lin >> 3);
+    if ((lin >> 3) >= per8 || i >= total) return;
+    const int item = __builtin_amdgcn_readfirstlane(i / opaque_s(ncb)), cb = i - item * ncb;
+    const int4 it = a.items[1 + item];
+    const int ex = it.x, n = it.z, at = it.w;
+    const int w = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
+    const int KS = a.KS;
+    const int unit = cb * 4 + w, units = a.N / 64, uu = min(unit, units - 1);   // as in k_gemm_moe
+    const int b0 = MODE == MOE_GATEUP ? (uu >> 1) * 4 + (uu & 1) : 2 * uu, b1 = MODE == MOE_GATEUP ? b0 + 2 : b0 + 1;
+    const uint4 *we = a.W + (size_t)ex * a.wexp_stride;
+    const uint4 *wp[2] = {we + (size_t)b0 * KS * 64, we + (size_t)b1 * KS * 64};
+    const char *xb[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p)   // (a row tile without pairs repeats the first one)
+        xb[p] = (const char *)(p < 2 ? a.Xhi : a.Xlo) + ((size_t)(at + min(p & 1, (n - 1) >> 5)) * KS + w) * 1024;
+    const uint32_t lo = (opaque_tid() & 63) * 16;
+    f32x16 acc[2][2];
+    stream_loop<4, 2, 2, SHORT, false>(acc, wp, xb, sm.ring, KS / SK, block_fold(KS) / SK, w, lo, [&]() { return lo; });
+    const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
+    const int *pairs = a.pairs + (size_t)ex * a.cap + it.y;
+    if (MODE == MOE_DOWN) barrier_keep_loads();   // everybody has read the last stage: the results take the ring's place
+    if (unit >= units) return;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) {
+        if (mt * 32 >= n) break;
+        const int pr = pairs[min(mt * 32 + row, n - 1)];
+        if (MODE == MOE_GATEUP) moe_swiglu(a, acc[mt][0], acc[mt][1], wave_rstd(a.ssq_in, pr >> 3, half, a.ncg_in, a.d_in, a.eps), at + mt, unit, row, half);
+        else {
+            // float4 g = 8 b + 2 q + half of a row's 64 columns, stored as whole rows: 16 lanes per row, 4 rows at a time
+            auto yi = [](int g, int r) { return (g >> 1) * 66 + (g & 1) * 33 + r; };
+            const float g = a.route_w[pr];
+            float4 *y = sm.y[w];
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    y[yi(8 * b + 2 * q + half, row)] = make_float4(acc[mt][b][4 * q] * g, acc[mt][b][4 * q + 1] * g, acc[mt][b][4 * q + 2] * g, acc[mt][b][4 * q + 3] * g);
+            wave_lds_sync();
+#pragma unroll 4
+            for (int j = 0; j < 8; ++j) {
+                const int r = 4 * j + (lane >> 4), p = __builtin_amdgcn_ds_bpermute(r << 2, pr);
+                const float4 v = y[yi(lane & 15, r)];
+                if (mt * 32 + r < n) *(float4 *)(a.moe_out + (size_t)p * a.d + (size_t)unit * 64 + 4 * (lane & 15)) = v;
+            }
+            wave_lds_sync();
+        }
     }
 }
 
@@ -232,7 +302,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_lm_head(const GemmArgs a, int 
         xb[i] = (const char *)(p < MT ? a.Xhi : a.Xlo) + ((size_t)t * KS + ks) * 1024;
     }
     f32x16 acc[MT][C];
-    stream_loop<NW, MT, C, SHORT>(acc, wp, xb, sm.ring, KS / SK, block_fold(KS) / SK, w, lo, [&]() -> uint32_t {
+    stream_loop<NW, MT, C, SHORT, true>(acc, wp, xb, sm.ring, KS / SK, block_fold(KS) / SK, w, lo, [&]() -> uint32_t {
         // RMSNorm factors of the rows, behind the requests of the first weights
         constexpr int TPR = 2 * NW / MT;   // threads per row
         const int tid = opaque_tid(), row = tid / TPR, j = tid % TPR;

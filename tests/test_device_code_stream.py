@@ -16,8 +16,8 @@ from paper_2512_15176_amd import build
 SOURCE = """
 #include "deer_stream.hpp"
 namespace deer {
-#define MOE(S) template __global__ void k_gemm_moe<MOE_GATEUP, S>(const MoeArgs, int); template __global__ void k_gemm_moe<MOE_DOWN, S>(const MoeArgs, int);
-MOE(true) MOE(false)
+#define MOE(M, S) template __global__ void k_gemm_moe<M, S>(const MoeArgs, int); template __global__ void k_moe_block<M, S>(const MoeArgs, int);
+MOE(MOE_GATEUP, true) MOE(MOE_GATEUP, false) MOE(MOE_DOWN, true) MOE(MOE_DOWN, false)
 #define LM(MT, S, WPE) template __global__ void k_lm_head<4, MT, 2, S, WPE>(const GemmArgs, int);
 LM(1, true, 3) LM(1, false, 3) LM(2, true, 2) LM(2, false, 2)
 }
@@ -41,10 +41,16 @@ def test_registers_of_streamed_loads_are_left_alone(tmp_path):
     api = open(build.SOURCES[0]).read()   # the forms above are those that the host launches
     assert set(re.findall(r"k_lm_head<4, (\d), 2, (\w+), (\d)>", api)) == set(re.findall(r"LM\((\d), (\w+), (\d)\)", SOURCE))
     kernels = 0
-    for name, body in re.findall(r"^(_ZN4deer\w*(?:k_gemm_moe|k_lm_head)\w*):(.*?)^\.Lfunc_end", text, re.S | re.M):
-        lines = [l.split(";")[0].strip() for l in body.split("\n")]
-        ops = [re.split(r"[ ,]+", l) for l in lines if l and not l.startswith(".")]
-        loads = [i for i, o in enumerate(ops) if o[0] == "global_load_dwordx4" and "nt" in o]
+    for name, body in re.findall(r"^(_ZN4deer\w*(?:k_gemm_moe|k_moe_block|k_lm_head)\w*):(.*?)^\.Lfunc_end", text, re.S | re.M):
+        ops, asm, inside = [], [], False   # asm: ops from asm statements
+        for line in body.split("\n"):
+            inside = "#ASMSTART" in line or inside and "#ASMEND" not in line
+            code = line.split(";")[0].strip()
+            if code and not code.startswith("."):
+                if inside:
+                    asm.append(len(ops))
+                ops.append(re.split(r"[ ,]+", code))
+        loads = [i for i in asm if ops[i][0] == "global_load_dwordx4"]
         products = [i for i, o in enumerate(ops) if o[0].startswith("v_mfma")]
         held = set().union(*(registers(ops[i][1]) for i in loads))
         assert len(loads) >= 16 and len(held) >= 64, name
@@ -53,4 +59,4 @@ def test_registers_of_streamed_loads_are_left_alone(tmp_path):
             assert not touched or i in loads or (i in products and not registers(ops[i][1]) & held), (name, ops[i])
         assert not any(o[0].startswith(("scratch_", "v_accvgpr")) for o in ops), name
         kernels += 1
-    assert kernels == 8
+    assert kernels == 12
