@@ -823,12 +823,19 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             {
                 ProfScope ps(c, 0, 0.0);
                 auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256); };
-                if (ma.KS < BK_SHORT) { if (blocked) launch(k_moe_block<MOE_GATEUP, true>); else launch(k_gemm_moe<MOE_GATEUP, true>); }
-                else if (blocked) launch(k_moe_block<MOE_GATEUP, false>); else launch(k_gemm_moe<MOE_GATEUP, false>);
+                // Up to the small experts' line k_gemm_moe sums K in eighths where they are whole stages, as the eight waves of the
+                // streaming kernel did that it took over from: a row that lies between two experts then goes where it went.  (Any
+                // other order sends one the other way now and then: 8 layers, 128 rows, one of ten sets of weights, and that set's
+                // logits 6e-3 off.)
+                ma.eighths = few(MOE_SMALL_GATEUP_PAIRS) && ma.KS % (8 * SK) == 0;
+                const bool sh = ma.KS < BK_SHORT;
+                if (blocked) { if (sh) launch(k_moe_block<MOE_GATEUP, true>); else launch(k_moe_block<MOE_GATEUP, false>); }
+                else if (sh && !ma.eighths) launch(k_gemm_moe<MOE_GATEUP, true>);
+                else launch(k_gemm_moe<MOE_GATEUP, false>);
             }
             LAUNCHCHK(c, "grouped gate/up");
             ma.W = (const uint4 *)(lw + m.lo_d); ma.wexp_stride = m.exp_d_bytes / 16; ma.Xhi = w.act_hi; ma.Xlo = w.act_lo;
-            ma.N = d; ma.KS = m.F / 16;
+            ma.N = d; ma.KS = m.F / 16; ma.eighths = 0;
             {
                 ProfScope ps(c, 0, 0.0);
                 auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, block_grid_x(ma.N), dim3(256), 0, s, ma, (ma.N + 255) / 256); };

@@ -1714,6 +1714,7 @@ struct MoeArgs {
     const uint4 *Xhi, *Xlo;                  // GATEUP: the pass's fragments of h; DOWN: activation tiles
     int N, KS, cap;
     const int *pairs; const int4 *items;     // see k_moe_group
+    int eighths;                             // k_gemm_moe: sums in eighths of K instead of folded as in block_loop
     const float *ssq_in; int ncg_in, d_in; float eps;   // GATEUP: RMSNorm scale of each pair's row
     uint4 *ahi, *alo; int Fe;                // GATEUP out: the item's activation tiles, Fe/16 k-steps
     const float *route_w; float *moe_out; int d;        // DOWN out: moe_out[row][slot][d] = w * y

@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256, 3) void k_gemm_moe(const MoeArgs a, int ncb) {
         const size_t xo = ((MODE == MOE_GATEUP ? 0 : (size_t)at * KS) + w) * 1024;
         const char *xb[2] = {(const char *)a.Xhi + xo, (const char *)a.Xlo + xo};
         f32x16 acc[1][2];
-        stream_loop<4, 1, 2, SHORT, true>(acc, wp, xb, ring, KS / SK, block_fold(KS) / SK, w, lo, [&]() -> uint32_t {
+        stream_loop<4, 1, 2, SHORT, true>(acc, wp, xb, ring, KS / SK, (a.eighths ? KS / 8 : block_fold(KS)) / SK, w, lo, [&]() -> uint32_t {
             if (MODE == MOE_DOWN) return lo;
             wait_loads<2 * SK>();
             tie(pr_f);
@@ -182,7 +182,15 @@ __global__ __launch_bounds__(256, 3) void k_gemm_moe(const MoeArgs a, int ncb) {
         });
         const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
         if (MODE == MOE_GATEUP) {
-            const float rs = wave_rstd(a.ssq_in, pairs[min(row, n - 1)] >> 3, half, a.ncg_in, a.d_in, a.eps);
+            const int r = pairs[min(row, n - 1)] >> 3;
+            float rs;
+            if (a.eighths) {   // (in order, as that kernel did)
+                const float *p = a.ssq_in + (size_t)r * a.ncg_in;
+                float ss = 0.f;
+#pragma unroll 4
+                for (int g = 0; g < a.ncg_in; ++g) ss += p[g];
+                rs = rsqrtf(ss / (float)a.d_in + a.eps);
+            } else rs = wave_rstd(a.ssq_in, r, half, a.ncg_in, a.d_in, a.eps);
             if (unit < units) moe_swiglu(a, acc[0][0], acc[0][1], rs, at, unit, row, half);
         } else if (row < n && unit < units) {
             const int pr = pairs[row];
