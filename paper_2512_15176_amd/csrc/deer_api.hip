@@ -370,6 +370,13 @@ const char *check_params(const deer_init_params *p) {
 // wave of workgroups costs more than idle CUs).  Measured on MI355X with the 8B- and 4B-shaped matrices: the split-K
 // tail (partial store, arrival, the last workgroup's sum) makes ~224 workgroups the best target for matrices with up
 // to 256 k-steps, 256 for longer contractions; at most 8 splits; none for contractions of up to 64 k-steps.
+// Rounds of streaming workgroups.  With several row-tile groups those of one (column group, K split) pair share an XCD (see
+// k_gemm_rows), so it is an XCD's 32 compute units that must hold them: 20 column groups in 12 row-tile groups are 240
+// workgroups, but three column groups on some XCDs, 36 workgroups each (4B down, 24 row tiles: 155 us, at 20 row tiles 86).
+int stream_rounds(int N, int S, int zg) {
+    const int pairs = N / CG * S;
+    return zg > 1 ? ((pairs + 7) / 8 * zg + 31) / 32 : (pairs + 255) / 256;
+}
 int choose_split(int N, int KS, int zgroups) {
     const int blocks = (N / CG) * zgroups;
     const int target = KS > 256 ? 256 : 224;
@@ -383,7 +390,10 @@ int choose_split(int N, int KS, int zgroups) {
     if (KS <= 64) S = 1;
     S = std::min(S, std::max(1, KS / 16));           // at least 16 k-steps per workgroup
     S = std::min<int>(S, (int)(PART_COLS / (size_t)N));
-    return std::max(S, 1);
+    S = std::max(S, 1);
+    // no second round for the sake of one more share (drafter down, 7 row tiles: 35 pairs are five on some XCDs, 20 us; in 4 shares 16)
+    while (S > 1 && stream_rounds(N, S, zgroups) > 1) --S;
+    return S;
 }
 
 // deer_debug_gemm_stamps: the chosen launch and the one after it record their workgroups' stamps, each in its half of
@@ -402,10 +412,10 @@ unsigned long long *stamp_buffer(deer_ctx *c, size_t workgroups) {
 // launches of the 4B, 8B and drafter matrices (K = 896 .. 12288, N = 896 .. 24576) over 2 .. 128 row tiles and are good to
 // about 15 %; the choice between kernels needs no more, since near a boundary both take the same time.
 // Streaming kernel with MT row tiles per workgroup (8B gate/up at 16 tiles: 6 rounds, 227 us; down: 1 round, 105 us):
-// (an odd number of many tiles leaves one per workgroup, whose weights come from L2 once per tile: 0.1 us per k-step)
+// (an odd number of many tiles leaves one per workgroup, whose weights come from L2 once per tile: 0.1 us per k-step; of few
+// tiles 0.075: 8B down at 5 row tiles 73 us, gate/up 107, O 28, 4B gate/up 55; 2048 columns over 8 row tiles 21)
 double stream_us(int N, int KS, int MT, int zg, int S) {
-    const double rounds = std::ceil((double)(N / CG) * S * zg / 256.0);
-    return 5.0 + rounds * (MT == 2 ? 5.0 + 0.125 * KS / S : 4.0 + (zg > 16 ? 0.1 : 0.07) * KS / S) + (S > 1 ? 6.0 : 0.0);
+    return 5.0 + stream_rounds(N, S, zg) * (MT == 2 ? 5.0 + 0.125 * KS / S : 4.0 + (zg > 16 ? 0.1 : 0.075) * KS / S) + (S > 1 ? 6.0 : 0.0);
 }
 // Narrow workgroups of a small model: rounds of them (ids are padded to 8 column groups, see k_gemm_narrow) on 256 compute
 // units.  Fitted to O projections of N = 256 .. 1024, K = 256 .. 1024 and QKV of N = 512 .. 3072 over 1 .. 105 row tiles;
@@ -459,6 +469,9 @@ double meet_us(double mb) { return mb <= 20.0 ? 0.2 * mb : 4.0 + 0.55 * (mb - 20
 // Blocked kernel: NB = 4 (128 x 256 per workgroup: 0.3 to 0.4 us per k-step, the more the busier the chip) or NB = 2
 // (128 x 128: 0.16 us with 64 workgroups, 0.24 with one per compute unit, 0.225 to 0.235 with more).
 struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; int full = 0, G = 0, piece = 0; };   // full: blocks run whole, 0: all (see BlockDeal)
+// The ring of 8 pays from 144 k-steps on (one workgroup per compute unit, ring of 4 / 8: 5120 x 2048, 128 k-steps, at 16 and 24
+// row tiles 38.4 / 41.0 and 41.6 / 44.2 us; 6144 x 2560, 160 k-steps, at 12 48.4 / 44.8).
+constexpr int BK_DEEP = 144;
 BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size_t part_floats) {
     BlockPlan best;
     const int nrb = (ntiles + BK_RT - 1) / BK_RT;
@@ -481,7 +494,7 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
             // fewer workgroups get more of the L2s each
             const double step = NB == 4 ? (q <= 1.0 ? 0.30 + 0.09 * q : q <= 2.0 ? 0.36 : 0.40) : (q <= 1.0 ? 0.15 + 0.09 * q : q <= 2.0 ? 0.225 : 0.235);
             const double us = 10.0 + units * per * step + (S > 1 ? S + meet_us(tile_bytes * 1e-6) : 0.0);
-            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0 && KS >= BK_SHORT, us};   // (short contractions: the ring of 8 takes 2 us more)
+            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0 && KS >= BK_DEEP, us};
         }
         // More blocks than compute units: an equal number of whole blocks for each, the rest in pieces of at least an eighth
         // of a block.  A compute unit's rate hardly depends on how many workgroups share it, so that a launch takes the k-steps
