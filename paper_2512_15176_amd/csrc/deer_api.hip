@@ -545,8 +545,24 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     SlimPlan sp;
     if (!narrow && force_S <= 0 && a.slim) sp = plan_slim(EPI, a.N, a.KS, ntiles, a.hd, a.ssq_sub, c->wk.part_floats);
     const bool slim = sp.C > 0 && sp.us < 0.98 * stream_small_us(a.N, a.KS, MT, zg, wide_S);
+    if constexpr (EPI == EPI_SWIGLU) if (c->slim && pairs && ntiles == 2 && a.KS >= BK_SHORT && !c->force_nb) {
+        // Two row tiles of a matrix too large for a tile per workgroup.  Shares of K for one workgroup on every compute unit, for
+        // two where one would have the whole of K (microseconds, k_gemm / here: 19456 x 2560 in 3 shares 32.2 / 29.3, 24576 x
+        // 4096 in 2 51.5 / 49.1, 37888 x 3584 in 1 78 / 67 to 75, in 3 62)
+        const int ncb = (a.N + 255) / 256, nq = a.KS / SK;
+        int S = std::max(1, ncb <= 128 ? 256 / ncb : 512 / ncb);
+        S = std::min({S, 8, nq / 4});
+        while (S > 1 && ((S - 1) * ((nq + S - 1) / S) >= nq || (size_t)S * ncb * GU_PART > c->wk.part_floats)) --S;
+        a.S = S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
+        c->gemm_launch_idx++;
+        ProfScope ps(c, 0, (double)a.N * K * 2.0);
+        hipLaunchKernelGGL(k_gemm_gateup, dim3((unsigned)(ncb * S)), dim3(256), 0, c->stream, a, ncb, (nq + S - 1) / S);
+        LAUNCHCHK(c, "k_gemm_gateup");
+        return DEER_OK;
+    }
     if constexpr (EPI == EPI_LMHEAD) if (c->slim && ntiles <= LM_TILES && !c->force_nb) {
         ProfScope ps(c, 0, (double)a.N * K * 2.0);
+        c->gemm_launch_idx++;
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((a.N + 255) / 256), dim3(256), 0, c->stream, a, ntiles); };
         const bool sh = a.KS < BK_SHORT;
         if (ntiles == 1) { if (sh) launch(k_lm_head<4, 1, 2, true, 3>); else launch(k_lm_head<4, 1, 2, false, 3>); }

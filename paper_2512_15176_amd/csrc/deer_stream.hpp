@@ -118,8 +118,8 @@ __device__ __forceinline__ void stream_loop(f32x16 (&acc)[MT][C], const uint4 *(
 }
 
 // SiLU(gate) * up of 32 channels of one row tile, from the accumulators of their two blocks (lane (row, half) holds columns 8 q + 4 half
-// .. + 3 of a block in registers 4 q ..), into activation tile `tile`: channels 32 unit ..
-__device__ __forceinline__ void moe_swiglu(const MoeArgs &a, const f32x16 &gate, const f32x16 &up, float rs, int tile, int unit, int row, int half) {
+// .. + 3 of a block in registers 4 q ..), into activation tile `tile` of F channels: channels 32 unit ..
+__device__ __forceinline__ void stream_swiglu(uint4 *ahi, uint4 *alo, int F, const f32x16 &gate, const f32x16 &up, float rs, int tile, int unit, int row, int half) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         float v[4];
@@ -131,9 +131,9 @@ __device__ __forceinline__ void moe_swiglu(const MoeArgs &a, const f32x16 &gate,
         const uint32_t h0 = f2bf2(v[0], v[1]), h1 = f2bf2(v[2], v[3]);
         const uint32_t l0 = f2bf2(v[0] - __uint_as_float(h0 << 16), v[1] - __uint_as_float(h0 & 0xffff0000u));
         const uint32_t l1 = f2bf2(v[2] - __uint_as_float(h1 << 16), v[3] - __uint_as_float(h1 & 0xffff0000u));
-        const size_t vec = (size_t)tile * (a.Fe / 16) * 64 + frag_vec(row, unit * 4 + q);
-        ((uint2 *)(a.ahi + vec))[half] = make_uint2(h0, h1);
-        ((uint2 *)(a.alo + vec))[half] = make_uint2(l0, l1);
+        const size_t vec = (size_t)tile * (F / 16) * 64 + frag_vec(row, unit * 4 + q);
+        ((uint2 *)(ahi + vec))[half] = make_uint2(h0, h1);
+        ((uint2 *)(alo + vec))[half] = make_uint2(l0, l1);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256, 3) void k_gemm_moe(const MoeArgs a, int ncb) {
                 for (int g = 0; g < a.ncg_in; ++g) ss += p[g];
                 rs = rsqrtf(ss / (float)a.d_in + a.eps);
             } else rs = wave_rstd(a.ssq_in, r, half, a.ncg_in, a.d_in, a.eps);
-            if (unit < units) moe_swiglu(a, acc[0][0], acc[0][1], rs, at, unit, row, half);
+            if (unit < units) stream_swiglu(a.ahi, a.alo, a.Fe, acc[0][0], acc[0][1], rs, at, unit, row, half);
         } else if (row < n && unit < units) {
             const int pr = pairs[row];
             const float g = a.route_w[pr];
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) 
     for (int mt = 0; mt < 2; ++mt) {
         if (mt * 32 >= n) break;
         const int pr = pairs[min(mt * 32 + row, n - 1)];
-        if (MODE == MOE_GATEUP) moe_swiglu(a, acc[mt][0], acc[mt][1], wave_rstd(a.ssq_in, pr >> 3, half, a.ncg_in, a.d_in, a.eps), at + mt, unit, row, half);
+        if (MODE == MOE_GATEUP) stream_swiglu(a.ahi, a.alo, a.Fe, acc[mt][0], acc[mt][1], wave_rstd(a.ssq_in, pr >> 3, half, a.ncg_in, a.d_in, a.eps), at + mt, unit, row, half);
         else {
             // float4 g = 8 b + 2 q + half of a row's 64 columns, stored as whole rows: 16 lanes per row, 4 rows at a time
             auto yi = [](int g, int r) { return (g >> 1) * 66 + (g & 1) * 33 + r; };
@@ -271,6 +271,77 @@ __global__ __launch_bounds__(256, 2) void k_moe_block(const MoeArgs a, int ncb) 
             wave_lds_sync();
         }
     }
+}
+
+// RMSNorm factors of the rows of nrt <= MT row tiles, by the whole workgroup
+template <int NW, int MT>
+__device__ __forceinline__ void stream_rstd(const GemmArgs &a, int nrt, float *rstd) {
+    constexpr int TPR = 2 * NW / MT;   // threads per row
+    const int tid = opaque_tid(), row = tid / TPR, j = tid % TPR;
+    const float *p = a.ssq_in + (size_t)min(row, nrt * 32 - 1) * a.ncg_in;
+    float s = 0.f;
+    for (int g = j; g < a.ncg_in; g += TPR) s += p[g];
+#pragma unroll
+    for (int off = 1; off < TPR; off <<= 1) s += shx(s, off);
+    if (j == 0) rstd[row] = rsqrtf(s / (float)a.d_in + a.eps);
+}
+
+// Gate/up of a dense pass of two row tiles: a workgroup has 256 columns (128 channels) and one of S shares of K.
+// Bound: HBM and what a compute unit draws (12 KB per k-step); against k_gemm<2>, which draws 8 KB per k-step for half the
+// columns and sums eight waves twice: 24576 x 4096 51.5 -> 49.1 us, 19456 x 2560 32.2 -> 29.3.
+constexpr size_t GU_PART = 4 * 16 * 256;   // floats of a workgroup's sums: [wave][(row tile, block, quad)][lane][4]
+struct GateupSmem {
+    StreamRing<2> ring;
+    float rstd[64];
+    int last;
+};
+__global__ __launch_bounds__(256, 2) void k_gemm_gateup(const GemmArgs a, int ncb, int per) {   // per: stages of a share
+    __shared__ __attribute__((aligned(16))) GateupSmem sm;
+    const int S = a.S, s = blockIdx.x / opaque_s(ncb), cb = blockIdx.x - s * ncb;
+    const int w = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
+    const int KS = a.KS, q0 = s * per, n = min(per, KS / SK - q0);   // the host keeps every share non-empty
+    const int unit = cb * 4 + w, units = a.N / 64, uu = min(unit, units - 1);   // as in k_gemm_moe
+    const int b0 = (uu >> 1) * 4 + (uu & 1);
+    const uint4 *wp[2] = {a.W + ((size_t)b0 * KS + q0 * SK) * 64, a.W + ((size_t)(b0 + 2) * KS + q0 * SK) * 64};
+    const char *xb[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) xb[p] = (const char *)(p < 2 ? a.Xhi : a.Xlo) + ((size_t)(p & 1) * KS + q0 * SK + w) * 1024;
+    const uint32_t lo = (opaque_tid() & 63) * 16;
+    f32x16 acc[2][2];
+    stream_loop<4, 2, 2, false, true>(acc, wp, xb, sm.ring, n, block_fold(KS) / SK, w, lo, [&]() -> uint32_t { stream_rstd<4, 2>(a, 2, sm.rstd); return lo; });
+    const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
+    if (S > 1) {
+        float *p0 = a.part + (size_t)w * (16 * 256) + lane * 4, *pw = p0 + ((size_t)s * ncb + cb) * GU_PART;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const f32x16 &v = acc[i >> 3][(i >> 2) & 1];
+            store16_agent(pw + i * 256, v[4 * (i & 3)], v[4 * (i & 3) + 1], v[4 * (i & 3) + 2], v[4 * (i & 3) + 3]);
+        }
+        if (!arrive_last(a.counters + cb, S, &sm.last)) return;
+        f32x16 sum[2][2] = {};   // the shares in their order, whoever sums them
+        for (int u = 0; u < S; ++u) {
+            u32x4 v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) load16_agent_async(v[i], p0 + ((size_t)u * ncb + cb) * GU_PART + i * 256);
+            wait_loads<0>();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                tie(v[i]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float x = __uint_as_float(v[i][e]);
+                    sum[i >> 3][(i >> 2) & 1][4 * (i & 3) + e] = u == 0 ? x : sum[i >> 3][(i >> 2) & 1][4 * (i & 3) + e] + x;
+                }
+            }
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[mt][c] = sum[mt][c];
+    } else barrier_keep_loads();   // the RMSNorm factors are there (with shares: behind arrive_last)
+    if (unit >= units) return;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt) stream_swiglu(a.ahi, a.alo, a.F, acc[mt][0], acc[mt][1], sm.rstd[mt * 32 + row], mt, unit, row, half);
 }
 
 // LM head of a pass of nrt <= MT row tiles with logits: a workgroup has 256 columns, i.e. two of the column groups whose
@@ -311,15 +382,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_lm_head(const GemmArgs a, int 
     }
     f32x16 acc[MT][C];
     stream_loop<NW, MT, C, SHORT, true>(acc, wp, xb, sm.ring, KS / SK, block_fold(KS) / SK, w, lo, [&]() -> uint32_t {
-        // RMSNorm factors of the rows, behind the requests of the first weights
-        constexpr int TPR = 2 * NW / MT;   // threads per row
-        const int tid = opaque_tid(), row = tid / TPR, j = tid % TPR;
-        const float *p = a.ssq_in + (size_t)min(row, nrt * 32 - 1) * a.ncg_in;
-        float s = 0.f;
-        for (int g = j; g < a.ncg_in; g += TPR) s += p[g];
-#pragma unroll
-        for (int off = 1; off < TPR; off <<= 1) s += shx(s, off);
-        if (j == 0) sm.rstd[row] = rsqrtf(s / (float)a.d_in + a.eps);
+        stream_rstd<NW, MT>(a, nrt, sm.rstd);   // behind the requests of the first weights
         return lo;
     });
     barrier_keep_loads();   // everybody has read the last stage: the logits take the ring's place

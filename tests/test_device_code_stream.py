@@ -41,7 +41,7 @@ def test_registers_of_streamed_loads_are_left_alone(tmp_path):
     api = open(build.SOURCES[0]).read()   # the forms above are those that the host launches
     assert set(re.findall(r"k_lm_head<4, (\d), 2, (\w+), (\d)>", api)) == set(re.findall(r"LM\((\d), (\w+), (\d)\)", SOURCE))
     kernels = 0
-    for name, body in re.findall(r"^(_ZN4deer\w*(?:k_gemm_moe|k_moe_block|k_lm_head)\w*):(.*?)^\.Lfunc_end", text, re.S | re.M):
+    for name, body in re.findall(r"^(_ZN4deer\w*(?:k_gemm_moe|k_moe_block|k_lm_head|k_gemm_gateup)\w*):(.*?)^\.Lfunc_end", text, re.S | re.M):
         ops, asm, inside = [], [], False   # asm: ops from asm statements
         for line in body.split("\n"):
             inside = "#ASMSTART" in line or inside and "#ASMEND" not in line
@@ -52,6 +52,7 @@ def test_registers_of_streamed_loads_are_left_alone(tmp_path):
                 ops.append(re.split(r"[ ,]+", code))
         loads = [i for i in asm if ops[i][0] == "global_load_dwordx4"]
         products = [i for i, o in enumerate(ops) if o[0].startswith("v_mfma")]
+        loads = [i for i in loads if "sc1" not in ops[i]]   # (partial sums: waited for where they are requested)
         held = set().union(*(registers(ops[i][1]) for i in loads))
         assert len(loads) >= 16 and len(held) >= 64, name
         for i in range(loads[0], products[-1] + 1):
@@ -59,4 +60,4 @@ def test_registers_of_streamed_loads_are_left_alone(tmp_path):
             assert not touched or i in loads or (i in products and not registers(ops[i][1]) & held), (name, ops[i])
         assert not any(o[0].startswith(("scratch_", "v_accvgpr")) for o in ops), name
         kernels += 1
-    assert kernels == 12
+    assert kernels == 13
