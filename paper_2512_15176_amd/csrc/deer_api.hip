@@ -644,7 +644,7 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
 
 // draw: the pass samples its rows' tokens (Gumbel-max over the perturbed logits): the drafter's pass at T > 0; the target's
 // rows only need the maximum and the sum of exponentials
-struct LmPlan { bool on; int n_lm, k; float T; uint64_t seed; int k_lo = 0; bool draw = false; };   // n_lm rows with logits, k per sequence
+struct LmPlan { bool on; int n_lm, k; float T; uint64_t seed; int k_lo = 0; bool draw = false; int *draft = nullptr; };   // n_lm rows with logits, k per sequence
 
 template <int HD>
 int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_head, float scale_log2e, double kv_bytes,
@@ -887,7 +887,7 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
         int rc = launch_gemm<EPI_LMHEAD>(c, a, d, (lm.n_lm + 31) / 32, 1);
         if (rc) return rc;
         prof_close(c);
-        hipLaunchKernelGGL(k_rowstat_final, dim3(lm.n_lm), dim3(256), 0, s, w.stat, V / CG, lm.T, w.res[model], lm.k, lm.k_lo);
+        hipLaunchKernelGGL(k_rowstat_final, dim3(lm.n_lm), dim3(256), 0, s, w.stat, V / CG, lm.T, w.res[model], lm.k, lm.k_lo, w.st, lm.draft);
         LAUNCHCHK(c, "k_rowstat_final");
     }
     prof_close(c);
@@ -1208,12 +1208,10 @@ int deer_draft_block_multipass(deer_ctx *c, int32_t k, float T, uint64_t seed, i
         PassRows pr{};
         pr.kind = ROWS_DRAFT; pr.st = w.st; pr.tokens = draft_dev; pr.k = k; pr.nrows = 0; pr.vocab = c->p.drafter.vocab;
         pr.mask_id = c->p.mask_token_id; pr.n_fixed = lo; pr.B = B; pr.n_ingest = n_ing; pr.share = k + max_ing <= 32;
-        LmPlan lm{true, B * k, k, T, seed, lo, T > 0.f};
+        LmPlan lm{true, B * k, k, T, seed, lo, T > 0.f, draft_dev};
         int rc = run_pass(c, DEER_DRAFTER, (B * k + n_ing + 31) / 32, n_ing > 0 && !pr.share ? 2 * B : B, maxlim, lm, keys, pr);
         if (rc) return rc;
-        hipLaunchKernelGGL(k_draft_finish, dim3(B), dim3(32), 0, c->stream, w.st, w.res[DEER_DRAFTER], draft_dev, k, lo);
-        LAUNCHCHK(c, "k_draft_finish");
-        n_ing = max_ing = 0;   // the device-side counts were cleared by k_draft_finish
+        n_ing = max_ing = 0;   // the device-side counts were cleared by k_rowstat_final
     }
     std::fill(c->h_ing_n.begin(), c->h_ing_n.end(), 0);
     c->cur_k = k;

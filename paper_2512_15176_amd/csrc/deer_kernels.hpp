@@ -1774,55 +1774,65 @@ struct RowResult {   // per LM row
 };
 
 // one block per LM row: merge the per-group partials
+// draft != null (the drafter's pass): the row's token goes there, and the last row of a sequence counts the tokens that the pass
+// took in.
+// Latency: one workgroup per row, one round trip for its column groups' results (up to RS_HELD of them per thread stay in
+// registers for the sum of exponentials), waves merged by shuffles.
+constexpr int RS_HELD = 8;
 __global__ __launch_bounds__(256) void k_rowstat_final(const RowStat *__restrict__ stat, int ncg_v, float T,
-                                                       RowResult *__restrict__ res, int k, int k_lo) {
-    __shared__ float sm[256]; __shared__ int si[256]; __shared__ float sg[256]; __shared__ int sgi[256];
-    __shared__ float ss[256];
-    const int row = blockIdx.x;
+                                                       RowResult *__restrict__ res, int k, int k_lo, SeqState st, int *__restrict__ draft) {
+    __shared__ float sm[4], sg[4], ss[4]; __shared__ int si[4], sgi[4];
+    const int row = blockIdx.x, tid = threadIdx.x, w = tid >> 6;
+    if (draft && tid == 64 && row % k == k - 1) { const int b = row / k; st.dr_len[b] += st.ing_n[b]; st.ing_n[b] = 0; }
     if (row % k < k_lo) return;   // kept from an earlier pass
     const RowStat *p = stat + (size_t)row * ncg_v;
     float m = -INFINITY, gm = -INFINITY; int idx = 0x7fffffff, gidx = 0x7fffffff;
-    for (int g = threadIdx.x; g < ncg_v; g += 256) {
+    RowStat v[RS_HELD];
+#pragma unroll
+    for (int i = 0; i < RS_HELD; ++i) {
+        const int g = tid + 256 * i;
+        if (g < ncg_v) v[i] = p[g];
+        else v[i] = RowStat{-INFINITY, 0x7fffffff, 0.f, -INFINITY, 0x7fffffff};
+    }
+#pragma unroll
+    for (int i = 0; i < RS_HELD; ++i) { argmax_merge(m, idx, v[i].m, v[i].idx); argmax_merge(gm, gidx, v[i].gm, v[i].gidx); }
+    for (int g = tid + 256 * RS_HELD; g < ncg_v; g += 256) {
         argmax_merge(m, idx, p[g].m, p[g].idx);
         argmax_merge(gm, gidx, p[g].gm, p[g].gidx);
     }
-    sm[threadIdx.x] = m; si[threadIdx.x] = idx; sg[threadIdx.x] = gm; sgi[threadIdx.x] = gidx;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) {
-            argmax_merge(sm[threadIdx.x], si[threadIdx.x], sm[threadIdx.x + off], si[threadIdx.x + off]);
-            argmax_merge(sg[threadIdx.x], sgi[threadIdx.x], sg[threadIdx.x + off], sgi[threadIdx.x + off]);
-        }
-        __syncthreads();
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const float m2 = shx(m, off), g2 = shx(gm, off); const int i2 = shx(idx, off), gi2 = shx(gidx, off);
+        argmax_merge(m, idx, m2, i2);
+        argmax_merge(gm, gidx, g2, gi2);
     }
-    const float M = sm[0];
+    if ((tid & 63) == 0) { sm[w] = m; si[w] = idx; sg[w] = gm; sgi[w] = gidx; }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { argmax_merge(m, idx, sm[j], si[j]); argmax_merge(gm, gidx, sg[j], sgi[j]); }
     float se = 0.f;
     if (T > 0.f) {
         const float invT = 1.f / T;
-        for (int g = threadIdx.x; g < ncg_v; g += 256) se += p[g].sumexp * expf((p[g].m - M) * invT);
-    }
-    ss[threadIdx.x] = se;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) ss[threadIdx.x] += ss[threadIdx.x + off];
+#pragma unroll
+        for (int i = 0; i < RS_HELD; ++i)
+            if (tid + 256 * i < ncg_v) se += v[i].sumexp * expf((v[i].m - m) * invT);
+        for (int g = tid + 256 * RS_HELD; g < ncg_v; g += 256) se += p[g].sumexp * expf((p[g].m - m) * invT);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) se += shx(se, off);
+        if ((tid & 63) == 0) ss[w] = se;
         __syncthreads();
+        se = (ss[0] + ss[1]) + (ss[2] + ss[3]);
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         RowResult r;
         const int V = ncg_v * CG;
-        r.argmax = (si[0] >= 0 && si[0] < V) ? si[0] : 0;   // a row of NaNs never updates the index
-        r.zmax = M;
-        if (T > 0.f) { r.sample = (sgi[0] >= 0 && sgi[0] < V) ? sgi[0] : 0; r.lse = M / T + logf(ss[0]); }
+        r.argmax = (idx >= 0 && idx < V) ? idx : 0;   // a row of NaNs never updates the index
+        r.zmax = m;
+        if (T > 0.f) { r.sample = (gidx >= 0 && gidx < V) ? gidx : 0; r.lse = m / T + logf(se); }
         else { r.sample = r.argmax; r.lse = 0.f; }
         res[row] = r;
+        if (draft) draft[row] = r.sample;
     }
-}
-
-// draft pass tail: draft tokens out, drafter cache length advances over the ingested rows
-__global__ void k_draft_finish(SeqState st, const RowResult *__restrict__ res, int *__restrict__ draft, int k, int k_lo) {
-    int b = blockIdx.x, i = threadIdx.x;
-    if (i < k && i >= k_lo) draft[b * k + i] = res[b * k + i].sample;   // positions below k_lo were fixed by earlier passes
-    if (i == 0) { st.dr_len[b] += st.ing_n[b]; st.ing_n[b] = 0; }
 }
 
 // ------------------------------------------------------------------------------------------
