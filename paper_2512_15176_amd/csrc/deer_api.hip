@@ -411,11 +411,13 @@ unsigned long long *stamp_buffer(deer_ctx *c, size_t workgroups) {
 // and the epilogue, a part per k-step of a workgroup, and what the shares of a split K cost.  The constants are fitted to
 // launches of the 4B, 8B and drafter matrices (K = 896 .. 12288, N = 896 .. 24576) over 2 .. 128 row tiles and are good to
 // about 15 %; the choice between kernels needs no more, since near a boundary both take the same time.
-// Streaming kernel with MT row tiles per workgroup (8B gate/up at 16 tiles: 6 rounds, 227 us; down: 1 round, 105 us):
-// (an odd number of many tiles leaves one per workgroup, whose weights come from L2 once per tile: 0.1 us per k-step; of few
-// tiles 0.075: 8B down at 5 row tiles 73 us, gate/up 107, O 28, 4B gate/up 55; 2048 columns over 8 row tiles 21)
+// Streaming kernel with MT row tiles per workgroup, microseconds per k-step: pairs in one round 0.134 (8B down and O at 16 row
+// tiles 113 and 45 us), in more 0.125 (8B gate/up at 16: 6 rounds, 227); one tile 0.075 (8B down at 5 row tiles 73, gate/up 107, O
+// 28, 4B gate/up 55; 2048 columns over 8 row tiles 21), of an odd number of many tiles, whose weights come from L2 once per
+// tile, 0.1.
 double stream_us(int N, int KS, int MT, int zg, int S) {
-    return 5.0 + stream_rounds(N, S, zg) * (MT == 2 ? 5.0 + 0.125 * KS / S : 4.0 + (zg > 16 ? 0.1 : 0.075) * KS / S) + (S > 1 ? 6.0 : 0.0);
+    const int rounds = stream_rounds(N, S, zg);
+    return 5.0 + rounds * (MT == 2 ? 5.0 + (rounds == 1 ? 0.134 : 0.125) * KS / S : 4.0 + (zg > 16 ? 0.1 : 0.075) * KS / S) + (S > 1 ? 6.0 : 0.0);
 }
 // Narrow workgroups of a small model: rounds of them (ids are padded to 8 column groups, see k_gemm_narrow) on 256 compute
 // units.  Fitted to O projections of N = 256 .. 1024, K = 256 .. 1024 and QKV of N = 512 .. 3072 over 1 .. 105 row tiles;
