@@ -471,9 +471,6 @@ double meet_us(double mb) { return mb <= 20.0 ? 0.2 * mb : 4.0 + 0.55 * (mb - 20
 // Blocked kernel: NB = 4 (128 x 256 per workgroup: 0.3 to 0.4 us per k-step, the more the busier the chip) or NB = 2
 // (128 x 128: 0.16 us with 64 workgroups, 0.24 with one per compute unit, 0.225 to 0.235 with more).
 struct BlockPlan { int NB = 2, S = 1; bool deep = false; double us = 1e30; int full = 0, G = 0, piece = 0; };   // full: blocks run whole, 0: all (see BlockDeal)
-// The ring of 8 pays from 144 k-steps on (one workgroup per compute unit, ring of 4 / 8: 5120 x 2048, 128 k-steps, at 16 and 24
-// row tiles 38.4 / 41.0 and 41.6 / 44.2 us; 6144 x 2560, 160 k-steps, at 12 48.4 / 44.8).
-constexpr int BK_DEEP = 144;
 BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size_t part_floats) {
     BlockPlan best;
     const int nrb = (ntiles + BK_RT - 1) / BK_RT;
@@ -496,7 +493,9 @@ BlockPlan plan_block(int N, int KS, int ntiles, bool lm_head, bool mixture, size
             // fewer workgroups get more of the L2s each
             const double step = NB == 4 ? (q <= 1.0 ? 0.30 + 0.09 * q : q <= 2.0 ? 0.36 : 0.40) : (q <= 1.0 ? 0.15 + 0.09 * q : q <= 2.0 ? 0.225 : 0.235);
             const double us = 10.0 + units * per * step + (S > 1 ? S + meet_us(tile_bytes * 1e-6) : 0.0);
-            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0 && KS >= BK_DEEP, us};
+            // (short contractions: the ring of 8 takes 2 us more; of 128 k-steps, rings of 4 / 8: 12288 columns over 3, 6 and 8 row tiles
+            // 28.6 / 26.4, 40.1 / 38.6, 40.8 / 39.0, 4096 over 18, 20 and 28 42.0 / 40.8, 42.2 / 41.1, 45.4 / 43.5, 5120 over 7 and 18 27.5 / 29.0, 44.6 / 42.7)
+            if (us < best.us) best = BlockPlan{NB, S, NB == 2 && q <= 1.0 && KS >= BK_SHORT, us};
         }
         // More blocks than compute units: an equal number of whole blocks for each, the rest in pieces of at least an eighth
         // of a block.  A compute unit's rate hardly depends on how many workgroups share it, so that a launch takes the k-steps

@@ -6,7 +6,8 @@
 
 typedef struct { uint32_t x, y, z; } dim3_t;
 typedef struct { char name[256]; const void *fn; } fn_t;
-typedef struct { char name[256]; uint32_t grid[3], block[3]; } launch_t;
+enum { ARG_BYTES = 120 };   /* of a GEMM's arguments: up to the K shares and the row count (see host_engine.GemmArgs) */
+typedef struct { char name[256]; uint32_t grid[3], block[3]; char arg[ARG_BYTES]; } launch_t;
 enum { OP_LAUNCH, OP_COPY, OP_SYNC, OP_RECORD, OP_WAIT, OP_STREAM_CREATE, OP_EVENT_CREATE, OP_KINDS };
 typedef struct { int kind; void *stream, *what; } op_t;   /* what: the event, or a pass's residual rows (see hipLaunchKernel) */
 
@@ -22,6 +23,7 @@ static char symbol[1 << 20];
 
 int stub_launches(void) { return n_launches; }
 const char *stub_launch(int i, uint32_t *grid) { memcpy(grid, launches[i].grid, 12); return launches[i].name; }
+const char *stub_launch_arg(int i) { return launches[i].arg; }
 int stub_syncs(void) { return n_syncs; }
 int stub_copies(void) { return n_copies; }
 void stub_reset(void) {
@@ -61,6 +63,7 @@ int hipLaunchKernel(const void *fn, dim3_t grid, dim3_t block, void **args, size
     l->name[0] = 0;
     for (int i = 0; i < n_fns; ++i) if (fns[i].fn == fn) strcpy(l->name, fns[i].name);
     memcpy(l->grid, &grid, 12); memcpy(l->block, &block, 12);
+    if (strstr(l->name, "8GemmArgs")) memcpy(l->arg, args[0], ARG_BYTES); else memset(l->arg, 0, ARG_BYTES);
     op(OP_LAUNCH, stream, strstr(l->name, "k_pass_begin") ? *(void **)args[3] : 0);   /* its fourth argument: the pass's residual rows */
     return 0;
 }

@@ -11,6 +11,15 @@ ROOT = os.path.dirname(os.path.dirname(HERE))
 OPS = ("launch", "copy", "sync", "record", "wait", "stream_create", "event_create")
 
 
+class GemmArgs(C.Structure):
+    """The beginning of a GEMM launch's argument: what it fetches ahead (the next launch's matrix, its workgroups and column
+    groups), its operands and sizes; S shares of K."""
+    _fields_ = [("nx_base", C.c_void_p), ("nx_nwg", C.c_int), ("nx_ncg", C.c_int), ("nx_span", C.c_int), ("nx_block_bytes", C.c_longlong),
+                ("nx_split_bytes", C.c_longlong), ("nx_narrow_nb", C.c_int), ("nx_Z", C.c_int), ("nx_nblk", C.c_int), ("nx_pairs", C.c_int),
+                ("kv_fetch_bytes", C.c_int), ("W", C.c_void_p), ("Xhi", C.c_void_p), ("Xlo", C.c_void_p), ("part", C.c_void_p),
+                ("counters", C.c_void_p), ("N", C.c_int), ("KS", C.c_int), ("S", C.c_int), ("rows_total", C.c_int)]
+
+
 def run_script(tmp_path, text):
     """Runs the script in a process without torch; returns what it prints."""
     lib = os.path.join(str(tmp_path), "libhipstub.so")
@@ -29,6 +38,7 @@ class HostEngine:
     def open(cls, stub_path):
         cls.stub = C.CDLL(stub_path, mode=C.RTLD_GLOBAL)
         cls.stub.stub_launch.restype = C.c_char_p
+        cls.stub.stub_launch_arg.restype = C.POINTER(GemmArgs)
         from paper_2512_15176_amd import binding
         cls.binding, cls.lib = binding, binding.load_library()
 
@@ -67,6 +77,10 @@ class HostEngine:
             g = (C.c_uint32 * 3)()
             out.append((self.stub.stub_launch(i, g).decode(), tuple(g)))
         return out
+
+    def gemms(self):
+        """(kernel name, grid, arguments) of the GEMM launches among them."""
+        return [(n, g, self.stub.stub_launch_arg(i).contents) for i, (n, g) in enumerate(self.launches()) if "8GemmArgs" in n]
 
     def ops(self):
         """(kind, stream, what) in the order of the calls since the last stub_reset: kernels (with the residual rows of the
