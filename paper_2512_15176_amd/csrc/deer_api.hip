@@ -411,13 +411,17 @@ unsigned long long *stamp_buffer(deer_ctx *c, size_t workgroups) {
 // and the epilogue, a part per k-step of a workgroup, and what the shares of a split K cost.  The constants are fitted to
 // launches of the 4B, 8B and drafter matrices (K = 896 .. 12288, N = 896 .. 24576) over 2 .. 128 row tiles and are good to
 // about 15 %; the choice between kernels needs no more, since near a boundary both take the same time.
-// Streaming kernel with MT row tiles per workgroup, microseconds per k-step: pairs in one round 0.134 (8B down and O at 16 row
-// tiles 113 and 45 us), in more 0.125 (8B gate/up at 16: 6 rounds, 227); one tile 0.075 (8B down at 5 row tiles 73, gate/up 107, O
-// 28, 4B gate/up 55; 2048 columns over 8 row tiles 21), of an odd number of many tiles, whose weights come from L2 once per
-// tile, 0.1.
+// Streaming kernel with MT row tiles per workgroup, microseconds per k-step of a workgroup: pairs 0.125 (8B gate/up at 16 row
+// tiles: 6 rounds, 227 us; O at 10 and 12 42, measured 41), in one round of 300 or more 0.134 (8B down at 14 and 16 108 and 113;
+// 4B down at 10 and 12, two shares, 52 and 53); one tile 0.075 (8B down at 5 row tiles 72, 4B down at 9 57, mixture's QKV at 12
+// 36), of short contractions 0.07 (6144 x 1024 over 6 to 8 17, 2560 x 1536 over 11 23), of an odd number of many tiles, whose
+// weights come from L2 once per tile, 0.1.  Where more rounds on some XCDs than over the whole chip are needed, each of these costs its k-steps,
+// but not the fixed part; with shares it begins while others meet (4B down at 24 row tiles 152 us, O at 11 45, drafter down at
+// 7, 9, 11 and, in pairs, 18 and 24: 18.5, 20.4, 24.0, 32.8 and 40.6).
 double stream_us(int N, int KS, int MT, int zg, int S) {
-    const int rounds = stream_rounds(N, S, zg);
-    return 5.0 + rounds * (MT == 2 ? 5.0 + (rounds == 1 ? 0.134 : 0.125) * KS / S : 4.0 + (zg > 16 ? 0.1 : 0.075) * KS / S) + (S > 1 ? 6.0 : 0.0);
+    const int rounds = stream_rounds(N, S, zg), even = (N / CG * S * zg + 255) / 256;   // even: if the XCDs shared the workgroups evenly
+    const double per = (double)KS / S, loop = per * (MT == 2 ? (rounds == 1 && per >= 300 ? 0.134 : 0.125) : zg > 16 ? 0.1 : KS >= BK_SHORT ? 0.075 : 0.07);
+    return 5.0 + even * (MT == 2 ? 5.0 : 4.0) + rounds * loop + (S > 1 ? 6.0 - (rounds - even) * (MT == 2 ? 2.0 : 4.0) : 0.0);
 }
 // Narrow workgroups of a small model: rounds of them (ids are padded to 8 column groups, see k_gemm_narrow) on 256 compute
 // units.  Fitted to O projections of N = 256 .. 1024, K = 256 .. 1024 and QKV of N = 512 .. 3072 over 1 .. 105 row tiles;
@@ -577,7 +581,11 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
                                          : plan_block(a.N, a.KS, ntiles, EPI == EPI_LMHEAD, c->p.target.n_experts || c->p.drafter.n_experts, c->wk.part_floats);
         const double old_us = narrow ? narrow_us(a.N, a.KS, ntiles, EPI == EPI_QKV) : slim ? sp.us : stream_or_small_us(a.N, a.KS, MT, zg, wide_S);
         const bool forced = c->force_nb || (c->block_gemm > 0 && c->block_gemm < 128 && ntiles >= 8);   // tests cover it at small sizes
-        if (forced || bp.us < 0.97 * old_us) {
+        // Not where the streaming kernel has three or more shares of up to 104 k-steps: its waves' chains of sums, of up to 13, are
+        // then shorter than the blocked kernel's (error against 64 bits, 896 x 4864 at 18 and 24 row tiles 0.99 and 1.04e-7, blocked
+        // 1.10 and 1.07e-7; chains of 23, 1536 x 8960 at 14, 1.26 and 1.13e-7).  It costs 4 and 9 us there.
+        const bool short_chains = !narrow && !slim && wide_S >= 3 && a.KS <= wide_S * BK_SHORT;
+        if (forced || (!short_chains && bp.us < 0.97 * old_us)) {
             a.S = bp.S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
             const int nrb = (ntiles + BK_RT - 1) / BK_RT, ncb = (a.N + 64 * bp.NB - 1) / (64 * bp.NB), band = block_band(nrb);
             const int blocks = nrb * ncb * a.S;

@@ -38,8 +38,24 @@ print(out)
 
 # microseconds streaming / blocked
 FASTER = [
+    ("d1024", (6, 7, 8), "gate/up", "streaming"),        # 16.8 / 20.1, 16.7 / 20.2, 17.0 / 20.8
+    ("d1024", (28,), "down", "streaming"),               # 26.1 / 27.1
+    ("d1536", (11, 12), "QKV", "streaming"),             # 22.8 / 25.4, 23.6 / 25.5: 36 workgroups on some XCDs
+    ("d1536", (24,), "QKV", "block, ring of 4"),         # 37.8 / 29.9
+    ("d1536", (18, 20), "down", "streaming"),            # 49.0 / 49.2, 49.4 / 50.9
+    ("d1536", (14,), "down", "block, ring of 8"),        # 56.6 / 43.8
+    ("d2048", (14, 16), "down", "streaming"),            # 37.6 / 39.0, 38.3 / 40.6
+    ("d2048", (18, 20), "O", "streaming"),               # 24.1 / 26.3, 24.4 / 27.0
+    ("d2048", (24, 28), "down", "block, ring of 8"),     # 56.7 / 53.7, 59.1 / 55.6
     ("d2048", (3, 4, 6, 8), "gate/up", "block, ring of 8"),  # (rings of 4 / 8) 28.6 / 26.4, 29.8 / 28.4, 40.1 / 38.6, 40.8 / 39.0
     ("d2048", (18, 20, 28), "QKV", "block, ring of 8"),      # 42.0 / 40.8, 42.2 / 41.1, 45.4 / 43.5
+    ("d2560", (11, 12), "O", "block, ring of 8"),        # 45.0 / 30.8, 45.1 / 30.8
+    ("d2560", (24,), "O", "block, ring of 8"),           # 71.6 / 46.8
+    ("d2560", (9, 10, 11, 24), "down", "block, ring of 8"),  # 56.9 / 48.9, 52.4 / 49.6, 94.9 / 50.1, 152 / 91
+    ("d2560", (18, 20), "O", "streaming"),               # 41.8 / 42.2, 42.5 / 44.4
+    ("d4096", (6, 8), "QKV", "streaming"),               # 42.9 / 44.0, 43.9 / 47.8
+    ("d4096", (10, 12), "O", "streaming"),               # 40.8 / 40.8, 41.3 / 43.8
+    ("d4096", (5, 7, 16), "down", "block, ring of 8"),   # 72.0 / 60.1, 72.8 / 64.2, 112.6 / 110.4
 ]
 
 
