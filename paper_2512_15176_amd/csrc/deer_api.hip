@@ -366,10 +366,6 @@ const char *check_params(const deer_init_params *p) {
 // ---------------------------------------------------------------------------------------------
 // launches
 // ---------------------------------------------------------------------------------------------
-// K splits per column group: as many as keep the launch within one wave of workgroups (rounded down: a second
-// wave of workgroups costs more than idle CUs).  Measured on MI355X with the 8B- and 4B-shaped matrices: the split-K
-// tail (partial store, arrival, the last workgroup's sum) makes ~224 workgroups the best target for matrices with up
-// to 256 k-steps, 256 for longer contractions; at most 8 splits; none for contractions of up to 64 k-steps.
 // Rounds of streaming workgroups.  With several row-tile groups those of one (column group, K split) pair share an XCD (see
 // k_gemm_rows), so it is an XCD's 32 compute units that must hold them: 20 column groups in 12 row-tile groups are 240
 // workgroups, but three column groups on some XCDs, 36 workgroups each (4B down, 24 row tiles: 155 us, at 20 row tiles 86).
@@ -377,6 +373,10 @@ int stream_rounds(int N, int S, int zg) {
     const int pairs = N / CG * S;
     return zg > 1 ? ((pairs + 7) / 8 * zg + 31) / 32 : (pairs + 255) / 256;
 }
+// K splits per column group: as many as keep the launch within one wave of workgroups (rounded down: a second
+// wave of workgroups costs more than idle CUs).  Measured on MI355X with the 8B- and 4B-shaped matrices: the split-K
+// tail (partial store, arrival, the last workgroup's sum) makes ~224 workgroups the best target for matrices with up
+// to 256 k-steps, 256 for longer contractions; at most 8 splits; none for contractions of up to 64 k-steps.
 int choose_split(int N, int KS, int zgroups) {
     const int blocks = (N / CG) * zgroups;
     const int target = KS > 256 ? 256 : 224;
@@ -391,8 +391,13 @@ int choose_split(int N, int KS, int zgroups) {
     S = std::min(S, std::max(1, KS / 16));           // at least 16 k-steps per workgroup
     S = std::min<int>(S, (int)(PART_COLS / (size_t)N));
     S = std::max(S, 1);
-    // no second round for the sake of one more share (drafter down, 7 row tiles: 35 pairs are five on some XCDs, 20 us; in 4 shares 16)
-    while (S > 1 && stream_rounds(N, S, zgroups) > 1) --S;
+    // Fewer where that saves a round on some XCDs, down to five (drafter down, 5 and 6 row tiles, 7 and 6 shares: 16.7 and 17.4 us,
+    // in 6 and 5 shares 12.8 and 13.4).  Not fewer: the waves' chains of sums grow (error against 64 bits at 7, 9 and 11 row tiles,
+    // 5, 4 and 3 shares: 0.97, 1.00 and 1.03e-7; one share fewer 0.99, 1.04 and 1.15e-7).  And not where it saves none: the
+    // router, one column group, has at most eight pairs, one to an XCD, however many shares, and its shares are what spreads
+    // it over the XCDs (128 x 2048 over 33, 66 and 128 row tiles in 6, 6 and 3 shares: 19, 35 and 51 us, in one 33, 53 and 60).
+    for (int s = S - 1; s >= 5; --s)
+        if (stream_rounds(N, s, zgroups) < stream_rounds(N, S, zgroups)) S = s;
     return S;
 }
 
