@@ -40,7 +40,7 @@ constexpr int PREFILL_TILES = 128;   // row tiles that a prefill pass may have a
 constexpr int PART_TILES_MIN = 16;   // split-K partials exist for passes of up to max(2 * batch, 16) row tiles
 constexpr int MAX_NS = 32;          // key-range splits of block attention
 constexpr size_t H_UP_MAX = 1 << 20;  // most page-locked host memory of a context for uploads
-constexpr int LM_TILES = 2;          // LM heads of up to so many row tiles run in k_lm_head
+constexpr int LM_TILES = 2, LM_COLS = 256 * 128;   // LM heads of up to so many row tiles and more columns run in k_lm_head
 constexpr int SLIM_MAX_D = 4096, SLIM_TILES = 4;   // passes of up to 4 row tiles of a model up to this width may use k_gemm_slim (64 sums of squares per row)
 constexpr int NARROW_MAX_D = 1024;  // residual width up to which a dense model's O projection runs in 32-column workgroups
 constexpr int NEXT_SPAN_BYTES = 16 << 10;      // fetched ahead per 32-column block of a next-launch workgroup (4 blocks: 8 loads per thread)
@@ -570,7 +570,10 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
         LAUNCHCHK(c, "k_gemm_gateup");
         return DEER_OK;
     }
-    if constexpr (EPI == EPI_LMHEAD) if (c->slim && ntiles <= LM_TILES && !c->force_nb) {
+    // Up to 32768 columns the streaming kernel's workgroups of 128 columns go in one round, K shared among their waves, and half
+    // as many of 256 with the whole of K in each wave take longer (microseconds streaming / k_lm_head, one row tile: 1024 columns of d = 896 11
+    // / 16, of 4096 31 / 47; 32000 of 896 15 / 22, of 4096 46 / 59; two row tiles of 4096 56 / 71; 50304 of 896 26 / 23, of 4096 85 / 66).
+    if constexpr (EPI == EPI_LMHEAD) if (c->slim && ntiles <= LM_TILES && a.N > LM_COLS && !c->force_nb) {
         ProfScope ps(c, 0, (double)a.N * K * 2.0);
         c->gemm_launch_idx++;
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((a.N + 255) / 256), dim3(256), 0, c->stream, a, ntiles); };

@@ -1,4 +1,4 @@
-"""The LM head of passes of one and two row tiles (columns streamed by one wave each): logits against 64 bits, no further off
+"""The LM head of passes of one and two row tiles over more than 32768 columns (columns streamed by one wave each): logits against 64 bits, no further off
 than the weight-streaming kernel's, and the tokens drawn from them the same; vocabularies that leave half a workgroup without
 columns, ragged numbers of rows, both ways to fold.  Its input is exact: a model whose layer adds nothing (zero output and down
 projections) hands it the embedding rows themselves.  And (on the CPU) which passes take it."""
@@ -20,7 +20,7 @@ BOUND = 1.05
 
 @pytest.mark.gpu
 @pytest.mark.skipif(not gpu_available(), reason="needs a GPU")
-@pytest.mark.parametrize("d,vocab", [(256, 2048), (896, 1152), (896, 16384), (1536, 2048), (1664, 1152), (4096, 16384)])
+@pytest.mark.parametrize("d,vocab", [(256, 33024), (896, 32896), (896, 49152), (1536, 33024), (1664, 32896), (4096, 49152)])
 def test_logits_and_draws(d, vocab):
     import torch
     from paper_2512_15176_amd import DeerEngine, binding
@@ -63,8 +63,9 @@ def test_logits_and_draws(d, vocab):
 def test_which_passes_take_it(tmp_path):
     out = run_script(tmp_path, """
 import deer_inputs as di
-t = di.ModelShape(1, 1664, 4, 2, 64, 256, 1152, rope_base=1e4)
-e = HostEngine(t, di.ModelShape(1, 256, 4, 2, 64, 256, 1152, rope_base=1e4), 3, 128)
+def engine(vocab):
+    return HostEngine(di.ModelShape(1, 1664, 4, 2, 64, 256, vocab, rope_base=1e4), di.ModelShape(1, 256, 4, 2, 64, 256, vocab, rope_base=1e4), 3, 128)
+e = engine(32896)
 def heads(call):
     e.stub.stub_reset()
     assert call() == 0
@@ -75,6 +76,9 @@ for B, k, on in ((1, 1, 1), (1, 32, 1), (2, 16, 1), (2, 17, 2), (2, 32, 2), (3, 
     assert d == ["ILi4ELi%dELi2ELb1E" % on] * (on > 0) and v == ["ILi4ELi%dELi2ELb0E" % on] * (on > 0), (B, k, d, v)
 e.lib.deer_debug_gemm_tiled(e.ctx, 0)
 assert e.set_prefilled([40], [3]) == 0 and heads(lambda: e.draft_block(8)) == []
+for vocab in (1152, 32000, 32768):   # one round of the streaming kernel's workgroups
+    e = engine(vocab)
+    assert e.set_prefilled([40], [3]) == 0 and heads(lambda: e.draft_block(32)) == heads(lambda: e.verify_block(32)) == []
 print("checked")
 """)
     assert out == "checked\n"
