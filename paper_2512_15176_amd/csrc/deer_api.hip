@@ -555,10 +555,13 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     SlimPlan sp;
     if (!narrow && force_S <= 0 && a.slim) sp = plan_slim(EPI, a.N, a.KS, ntiles, a.hd, a.ssq_sub, c->wk.part_floats);
     const bool slim = sp.C > 0 && sp.us < 0.98 * stream_small_us(a.N, a.KS, MT, zg, wide_S);
-    if constexpr (EPI == EPI_SWIGLU) if (c->slim && pairs && ntiles == 2 && a.KS >= BK_SHORT && !c->force_nb) {
-        // Two row tiles of a matrix too large for a tile per workgroup.  Shares of K for one workgroup on every compute unit, for
-        // two where one would have the whole of K (microseconds, k_gemm / here: 19456 x 2560 in 3 shares 32.2 / 29.3, 24576 x
-        // 4096 in 2 51.5 / 49.1, 37888 x 3584 in 1 78 / 67 to 75, in 3 62)
+    if constexpr (EPI == EPI_SWIGLU) if (c->slim && pairs && ntiles == 2 && a.KS >= BK_SHORT && wide_S <= 2 && !c->force_nb) {
+        // Two row tiles of a matrix too large for a tile per workgroup, of which the streaming kernel has no more than two shares
+        // (more fill the chip: three of 8320 and 9216 x 4096 27.4 and 28.6 us, here 27.8 and 29.4; four of 8192 x 5120 27.6 / 29.6,
+        // small workgroups of 8192 x 4096 25.8 / 28.0).  Shares of K for one workgroup on every compute unit, for two where one
+        // would have the whole of K (microseconds, k_gemm / here: 10240 and 12288 x 4096 34.0 / 29.7 and 35.4 / 31.3, 10240 x
+        // 2560 26.0 / 23.4, 12800 x 5120 41.0 / 35.5, 19456 x 2560 in 3 shares 32.2 / 29.3, 24576 x 4096 in 2 51.5 / 49.1, 37888
+        // x 3584 in 1 78 / 67 to 75, in 3 62)
         const int ncb = (a.N + 255) / 256, nq = a.KS / SK;
         int S = std::max(1, ncb <= 128 ? 256 / ncb : 512 / ncb);
         S = std::min({S, 8, nq / 4});

@@ -16,6 +16,8 @@ from host_engine import run_script   # noqa: E402
 # (d_model, d_ff, shares): 104, 112 and 160 k-steps; column blocks 64, 65 (the last with two waves of columns), 120 and 161
 SHAPES = [(1664, 8192, 4), (1792, 8256, 3), (2560, 15360, 2), (1664, 20544, 3)]
 LENS, K = [34, 31], 32
+# not taken: below 51 MB, below 104 k-steps, columns so few that the streaming kernel has three shares of K or more, or small workgroups
+NONE = [(1664, 4608), (1536, 9216), (4096, 4608), (5120, 4096), (4096, 4096), (8192, 2048)]
 
 
 def shape(d, ff):
@@ -48,7 +50,7 @@ def grids(e, call):
     assert call() == 0
     return [g[0] for n, g in e.launches() if "k_gemm_gateup" in n]
 out = []
-for d, ff in {[s[:2] for s in SHAPES] + [(1664, 4608), (1536, 9216)]!r}:   # the last two: below 51 MB, below 104 k-steps
+for d, ff in {[s[:2] for s in SHAPES] + [(4096, 5120)] + NONE!r}:
     t = di.ModelShape(2, d, 8, 2, 64, ff, 1152, rope_base=1e4)
     e = HostEngine(t, di.ModelShape(1, 384, 6, 3, 64, 640, 1152, rope_base=1e4), 3, 128)
     one = grids(e, lambda: e.prefill([[3] * 33]))
@@ -63,4 +65,4 @@ for d, ff in {[s[:2] for s in SHAPES] + [(1664, 4608), (1536, 9216)]!r}:   # the
     out.append(two)
 print(out)
 """)
-    assert eval(out) == [[-(-ff * 2 // 256) * s] * 2 for _, ff, s in SHAPES] + [[], []], out
+    assert eval(out) == [[-(-ff * 2 // 256) * s] * 2 for _, ff, s in SHAPES] + [[40 * 6] * 2] + [[]] * len(NONE), out
