@@ -848,8 +848,15 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             rc = launch_gemm<EPI_ROUTER>(c, a, d, ntiles, 0);
             if (rc) return rc;
             const int cap = rows;
+            const bool small = m.exp_gu_bytes < MOE_SMALL_BYTES;
+            auto few = [&](int pairs) { return rows * mc.top_k < pairs * mc.n_experts; };
+            const bool blocked = c->block_gemm > 0 && !few(small ? MOE_SMALL_GATEUP_PAIRS : MOE_GATEUP_PAIRS);
+            const bool blocked_down = !few(small ? MOE_SMALL_DOWN_PAIRS : MOE_DOWN_PAIRS);
+            // Items of 32 pairs where k_gemm_moe, which multiplies 32 at a time, takes both projections: the row tiles of an expert
+            // with more then run beside each other
+            const int item_pairs = blocked || blocked_down ? 64 : 32;
             prof_close(c);
-            hipLaunchKernelGGL(k_moe_group, dim3(1), dim3(1024), 0, s, w.route_e, w.rm.slot, rows, mc.top_k, cap,
+            hipLaunchKernelGGL(k_moe_group, dim3(1), dim3(1024), 0, s, w.route_e, w.rm.slot, rows, mc.top_k, cap, item_pairs,
                                w.pairs, w.items, w.moe_touched);
             LAUNCHCHK(c, "k_moe_group");
             MoeArgs ma{};
@@ -858,11 +865,7 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             ma.ahi = w.act_hi; ma.alo = w.act_lo; ma.Fe = m.F; ma.route_w = w.route_w; ma.moe_out = w.moe_out; ma.d = d;
             ma.W = (const uint4 *)(lw + m.lo_gu); ma.wexp_stride = m.exp_gu_bytes / 16; ma.Xhi = w.xa_hi; ma.Xlo = w.xa_lo;
             ma.N = 2 * m.F; ma.KS = d / 16;
-            const bool small = m.exp_gu_bytes < MOE_SMALL_BYTES;
-            auto few = [&](int pairs) { return rows * mc.top_k < pairs * mc.n_experts; };
-            const bool blocked = c->block_gemm > 0 && !few(small ? MOE_SMALL_GATEUP_PAIRS : MOE_GATEUP_PAIRS);
-            const bool blocked_down = !few(small ? MOE_SMALL_DOWN_PAIRS : MOE_DOWN_PAIRS);
-            const size_t max_items = (size_t)std::min(mc.n_experts, rows * mc.top_k) + (size_t)rows * mc.top_k / 64;
+            const size_t max_items = (size_t)std::min(mc.n_experts, rows * mc.top_k) + (size_t)rows * mc.top_k / item_pairs;
             auto block_grid_x = [&](int N) { return dim3((unsigned)(8 * ((max_items * ((N + 255) / 256) + 7) / 8))); };
             if (blocked) {
                 hipLaunchKernelGGL(k_moe_gather, dim3(ncg_d, (unsigned)max_items), dim3(256), 0, s, w.h, ma, w.xg_hi, w.xg_lo);

@@ -1660,11 +1660,11 @@ __global__ __launch_bounds__(512) void k_gemm_slim(const GemmArgs a, int ngrp, i
 }
 
 // ------------------------------------------------------------------------------------------
-// One block: pairs: pair i of expert e is 8 * (pass row) + (its routing slot); items: [0].x the number of 64-pair work items,
-// from [1] on (expert, first pair, pairs, first 32-pair activation tile) of each.
+// One block: pairs: pair i of expert e is 8 * (pass row) + (its routing slot); items: [0].x the number of work items of up to
+// item_pairs (32 or 64) pairs, from [1] on (expert, first pair, pairs, first 32-pair activation tile) of each.
 // One row per thread and trip: a pass of 2048 rows takes two trips of eight LDS atomics per thread.
 __global__ __launch_bounds__(1024) void k_moe_group(const int *__restrict__ route_e, const int *__restrict__ row_slot,
-                                                    int rows, int top_k, int cap, int *__restrict__ pairs,
+                                                    int rows, int top_k, int cap, int item_pairs, int *__restrict__ pairs,
                                                     int4 *__restrict__ items, unsigned long long *__restrict__ touched_total) {
     __shared__ int s_cnt[128];   // experts beyond the model's: 0
     const int tid = threadIdx.x;
@@ -1686,7 +1686,8 @@ __global__ __launch_bounds__(1024) void k_moe_group(const int *__restrict__ rout
     if (tid >= 64) return;
     // lane l: experts 2 l and 2 l + 1; running sums of their tiles (low half) and items (high half) over the lanes
     const int n[2] = {s_cnt[2 * tid], s_cnt[2 * tid + 1]};
-    auto load = [&](int v) { return ((v + 31) >> 5) + (((v + 63) >> 6) << 16); };
+    const int sh = item_pairs == 32 ? 5 : 6;
+    auto load = [&](int v) { return ((v + 31) >> 5) + (((v + item_pairs - 1) >> sh) << 16); };
     int at = load(n[0]) + load(n[1]);
     const int own = at;
 #pragma unroll
@@ -1698,8 +1699,8 @@ __global__ __launch_bounds__(1024) void k_moe_group(const int *__restrict__ rout
     at -= own;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        for (int j = 0; 64 * j < n[i]; ++j)
-            items[1 + (at >> 16) + j] = make_int4(2 * tid + i, j * 64, min(64, n[i] - j * 64), (at & 0xffff) + 2 * j);
+        for (int j = 0; j << sh < n[i]; ++j)
+            items[1 + (at >> 16) + j] = make_int4(2 * tid + i, j << sh, min(item_pairs, n[i] - (j << sh)), (at & 0xffff) + (j << sh >> 5));
         at += load(n[i]);
     }
     // running count of (layer, expert) pairs whose weights a pass has to stream (for byte accounting)

@@ -139,7 +139,9 @@ __device__ __forceinline__ void stream_swiglu(uint4 *ahi, uint4 *alo, int F, con
 }
 
 // Grouped expert GEMMs of passes with few rows per expert, where the expert weights' stream is all there is.  A workgroup owns
-// 256 columns of one item of k_moe_group and multiplies up to 32 of its pairs at a time; a wave has 64 of the columns, of
+// 256 columns of one item of k_moe_group and multiplies up to 32 of its pairs at a time (items have 32 unless the blocked kernel
+// takes the down projection: all rows to the same 8 of 128 experts, layer of 2048 x 768, gate/up and down of 2, 4, 6, 8 row tiles in items of 64
+// 61 + 26, 66 + 45, 93 + 49, 125 + 52 us, of 32 36 + 17, 63 + 28, 71 + 38, 77 + 42); a wave has 64 of the columns, of
 // gate/up the gate and the up block of 32 channels.  Gate/up gathers its rows out of the pass's fragments (lanes past the last
 // pair repeat it).
 // Bound: HBM.  Layer of 128 experts, top 8, d = 2048, expert width 768, microseconds before -> now: gate/up (the streaming
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(256, 3) void k_gemm_moe(const MoeArgs a, int ncb) {
     const int b0 = MODE == MOE_GATEUP ? (uu >> 1) * 4 + (uu & 1) : 2 * uu, b1 = MODE == MOE_GATEUP ? b0 + 2 : b0 + 1;
     const uint4 *we = a.W + (size_t)ex * a.wexp_stride;
 #pragma unroll 1
-    for (int first = 0; first < n_all; first += 32) {   // row tiles of the item (the second one finds the weights in the L2)
+    for (int first = 0; first < n_all; first += 32) {   // row tiles of an item of 64 (the second one finds the weights in the L2)
         const int n = min(32, n_all - first), at = it.w + (first >> 5);
         const int *pairs = a.pairs + (size_t)ex * a.cap + it.y + first;
         const uint32_t lo = (opaque_tid() & 63) * 16;
