@@ -801,23 +801,23 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
     // attention, no O, gate/up and down.
     const int n_kv = 2 * mc.n_kv_heads * hd;
     const bool caches_only = !lm.on && mc.n_layers >= CACHES_ONLY_LAYERS && n_kv % CG == 0;
+    auto kv_only = [&](int l) { return caches_only && l + 1 == mc.n_layers; };
+    // what the QKV launch of layer l multiplies: all of the matrix, or its columns behind Q's
+    auto qkv_matrix = [&](int l) { return m.w + m.off_layers + (size_t)l * m.layer_bytes + m.lo_qkv + (kv_only(l) ? (size_t)(m.kattn / 32) * (d / 16) * 1024 : 0); };
+    auto qkv_cols = [&](int l) { return kv_only(l) ? n_kv : m.n_qkv; };
     for (int l = 0; l < mc.n_layers; ++l) {
         const char *lw = m.w + m.off_layers + (size_t)l * m.layer_bytes;
         GemmArgs a = base;
-        const bool kv_only = caches_only && l + 1 == mc.n_layers;
-        a.W = (const uint4 *)(lw + m.lo_qkv); a.Xhi = w.xa_hi; a.Xlo = w.xa_lo; a.N = m.n_qkv;
+        a.W = (const uint4 *)qkv_matrix(l); a.Xhi = w.xa_hi; a.Xlo = w.xa_lo; a.N = qkv_cols(l);
         a.kv = KvView{m.kv + m.kv_k_base + (size_t)l * m.kv_layer_stride, m.kv + m.kv_v_base + (size_t)l * m.kv_layer_stride,
                       m.kv_seq_stride, m.kv_head_stride, c->p.max_seq};
         // whole key tiles that no row of this pass writes (a pass of one tile appends at most 32 rows)
         if (fetch_ahead && NS_head > 0 && c->batch == 1 && 8 % mc.n_kv_heads == 0)
             a.kv_fetch_bytes = std::min(KV_FETCH_MAX_BYTES, std::max(0, (max_limit - 32) / 32) * 32 * hd * 2);
-        if (kv_only) {   // the columns behind Q's
-            a.W += (size_t)(m.kattn / 32) * (d / 16) * 64;
-            a.N = n_kv; a.Hq = 0; a.kv_fetch_bytes = 0;
-        }
+        if (kv_only(l)) { a.Hq = 0; a.kv_fetch_bytes = 0; }
         int rc = launch_gemm<EPI_QKV>(c, a, d, ntiles, 0);
         if (rc) return rc;
-        if (kv_only) break;
+        if (kv_only(l)) break;
         const NextWeights nx_o = fetch_ahead_narrow ? next_plan_narrow(lw + m.lo_o, d, m.kattn, 1) : next_plan(lw + m.lo_o, d, m.kattn, EPI_RESID);
         if (hd == 128) rc = launch_attn<128>(c, m, l, n_attn, NS, NS_head, scale_log2e, kv_bytes, nx_o);
         else if (hd == 64) rc = launch_attn<64>(c, m, l, n_attn, NS, NS_head, scale_log2e, kv_bytes, nx_o);
@@ -835,8 +835,8 @@ int run_pass(deer_ctx *c, int model, int ntiles, int n_attn, int max_limit, cons
             a = base;
             a.W = (const uint4 *)(lw + m.lo_d); a.Xhi = w.xb_hi; a.Xlo = w.xb_lo; a.N = d;
             if (l + 1 < mc.n_layers)
-                a.nx = fetch_ahead_narrow ? next_plan_narrow(lw + m.layer_bytes + m.lo_qkv, m.n_qkv, d, 2)
-                                          : next_plan(lw + m.layer_bytes + m.lo_qkv, m.n_qkv, d, EPI_QKV);
+                a.nx = fetch_ahead_narrow ? next_plan_narrow(qkv_matrix(l + 1), qkv_cols(l + 1), d, 2)
+                                          : next_plan(qkv_matrix(l + 1), qkv_cols(l + 1), d, EPI_QKV);
             rc = launch_gemm<EPI_RESID>(c, a, m.F, ntiles, 0);
             if (rc) return rc;
         } else {
