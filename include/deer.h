@@ -248,22 +248,24 @@ int deer_debug_stream_read(deer_ctx *c, const void *buf_dev, size_t bytes, int32
  * per row: 0 workgroup started, 1 its first wave has multiplied its K slice, 2 its tile is stored (after the
  * epilogue if the matrix is not split), 3 it has arrived at the column group's counter, 4 it was the last to arrive
  * and has finished the group; 0 = not reached or no such workgroup) into stamps_host (at most max_blocks rows; *blocks = rows available, 0 if nothing was recorded), then
- * selects the launch that records from now on: the `launch`-th streaming GEMM (counted from 0) of every following
- * pass of `model`; launch < 0 switches recording off.  Waits for the stream. */
+ * selects the launch that records from now on: the `launch`-th streaming GEMM (counted from 0; every GEMM that does not run
+ * blocked, but not a mixture's expert projections) of every following pass of `model`; launch < 0 switches recording off.  A
+ * launch of more than 2048 workgroups records nothing.  Waits for the stream. */
 int deer_debug_gemm_stamps(deer_ctx *c, int model, int launch, uint64_t *stamps_host, int32_t max_blocks, int32_t *blocks);
 
 /* GEMMs of passes of several row tiles run blocked (128 x 128 or 128 x 256 tiles through LDS) where that is estimated
  * to be faster than the weight-streaming kernel (min_tiles = 128, the default; larger values: the same).  1 .. 127 make
  * every dense GEMM of a pass with at least 8 row tiles take it.  0 switches the blocked kernel off, also for the gate/up
- * projections of a mixture's experts (not for their down projections).  0 switches off, too, the streaming
- * kernel's form in small workgroups, which passes of few row tiles take.  Results agree within rounding (different summation
- * order over K). */
+ * projections of a mixture's experts (not for their down projections), and with it the streaming kernel's other forms for passes
+ * of few row tiles: small workgroups, and columns streamed by one wave each (LM heads of up to two row tiles, gate/up of two).
+ * Results agree within rounding (different summation order over K). */
 int deer_debug_gemm_tiled(deer_ctx *c, int min_tiles);
 
 /* Test aid: makes every dense GEMM of a pass of at least two row tiles run in one form of the blocked kernel (unless
  * deer_debug_gemm_tiled has switched it off): workgroups of 64 * nb columns (nb = 2 or 4) with `ring` k-steps on their way
  * (4; with nb = 2 also 8, which contractions of less than 104 k-steps take as 4) and K in `splits` shares (1 .. 8; fewer where a share would be empty or the partial sums would not
- * fit; LM heads: 1).  nb = 0: back to the estimate.  DEER_EINVAL for a form that does not exist. */
+ * fit; LM heads: 1).  Gate/up of two row tiles and LM heads of one and two leave their own kernel meanwhile (one row tile: for the streaming one).
+ * nb = 0: back to the estimate.  DEER_EINVAL for a form that does not exist. */
 int deer_debug_gemm_block(deer_ctx *c, int nb, int ring, int splits);
 
 /* Current committed length j per sequence (host mirror). */

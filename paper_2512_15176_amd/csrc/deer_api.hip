@@ -567,6 +567,7 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
         S = std::min({S, 8, nq / 4});
         while (S > 1 && ((S - 1) * ((nq + S - 1) / S) >= nq || (size_t)S * ncb * GU_PART > c->wk.part_floats)) --S;
         a.S = S; a.part = c->wk.part; a.counters = c->wk.gemm_cnt;
+        a.stamps = stamp_buffer(c, (size_t)ncb * S);
         c->gemm_launch_idx++;
         ProfScope ps(c, 0, (double)a.N * K * 2.0);
         hipLaunchKernelGGL(k_gemm_gateup, dim3((unsigned)(ncb * S)), dim3(256), 0, c->stream, a, ncb, (nq + S - 1) / S);
@@ -577,8 +578,9 @@ int launch_gemm(deer_ctx *c, GemmArgs &a, int K, int ntiles, int force_S) {
     // as many of 256 with the whole of K in each wave take longer (microseconds streaming / k_lm_head, one row tile: 1024 columns of d = 896 11
     // / 16, of 4096 31 / 47; 32000 of 896 15 / 22, of 4096 46 / 59; two row tiles of 4096 56 / 71; 50304 of 896 26 / 23, of 4096 85 / 66).
     if constexpr (EPI == EPI_LMHEAD) if (c->slim && ntiles <= LM_TILES && a.N > LM_COLS && !c->force_nb) {
-        ProfScope ps(c, 0, (double)a.N * K * 2.0);
+        a.stamps = stamp_buffer(c, (size_t)(a.N + 255) / 256);
         c->gemm_launch_idx++;
+        ProfScope ps(c, 0, (double)a.N * K * 2.0);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((a.N + 255) / 256), dim3(256), 0, c->stream, a, ntiles); };
         const bool sh = a.KS < BK_SHORT;
         if (ntiles == 1) { if (sh) launch(k_lm_head<4, 1, 2, true, 3>); else launch(k_lm_head<4, 1, 2, false, 3>); }

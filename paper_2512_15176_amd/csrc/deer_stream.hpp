@@ -300,6 +300,7 @@ struct GateupSmem {
 __global__ __launch_bounds__(256, 2) void k_gemm_gateup(const GemmArgs a, int ncb, int per) {   // per: stages of a share
     __shared__ __attribute__((aligned(16))) GateupSmem sm;
     const int S = a.S, s = blockIdx.x / opaque_s(ncb), cb = blockIdx.x - s * ncb;
+    gemm_stamp(a, blockIdx.x, 0);
     const int w = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
     const int KS = a.KS, q0 = s * per, n = min(per, KS / SK - q0);   // the host keeps every share non-empty
     const int unit = cb * 4 + w, units = a.N / 64, uu = min(unit, units - 1);   // as in k_gemm_moe
@@ -311,6 +312,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_gateup(const GemmArgs a, int nc
     const uint32_t lo = (opaque_tid() & 63) * 16;
     f32x16 acc[2][2];
     stream_loop<4, 2, 2, false, true>(acc, wp, xb, sm.ring, n, block_fold(KS) / SK, w, lo, [&]() -> uint32_t { stream_rstd<4, 2>(a, 2, sm.rstd); return lo; });
+    gemm_stamp(a, blockIdx.x, 1);
     const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
     if (S > 1) {
         float *p0 = a.part + (size_t)w * (16 * 256) + lane * 4, *pw = p0 + ((size_t)s * ncb + cb) * GU_PART;
@@ -319,7 +321,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_gateup(const GemmArgs a, int nc
             const f32x16 &v = acc[i >> 3][(i >> 2) & 1];
             store16_agent(pw + i * 256, v[4 * (i & 3)], v[4 * (i & 3) + 1], v[4 * (i & 3) + 2], v[4 * (i & 3) + 3]);
         }
-        if (!arrive_last(a.counters + cb, S, &sm.last)) return;
+        gemm_stamp(a, blockIdx.x, 2);
+        const bool last = arrive_last(a.counters + cb, S, &sm.last);
+        gemm_stamp(a, blockIdx.x, 3);
+        if (!last) return;
         f32x16 sum[2][2] = {};   // the shares in their order, whoever sums them
         for (int u = 0; u < S; ++u) {
             u32x4 v[16];
@@ -344,6 +349,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_gateup(const GemmArgs a, int nc
     if (unit >= units) return;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) stream_swiglu(a.ahi, a.alo, a.F, acc[mt][0], acc[mt][1], sm.rstd[mt * 32 + row], mt, unit, row, half);
+    gemm_stamp(a, blockIdx.x, S > 1 ? 4 : 2);
 }
 
 // LM head of a pass of nrt <= MT row tiles with logits: a workgroup has 256 columns, i.e. two of the column groups whose
@@ -371,6 +377,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_lm_head(const GemmArgs a, int 
     constexpr int XP = SK * 2 * MT / NW, G = 4 / C;   // G: waves of a column group
     const int w = __builtin_amdgcn_readfirstlane(opaque_tid() >> 6);
     const int KS = a.KS, V = a.N;
+    gemm_stamp(a, blockIdx.x, 0);
     const int unit = blockIdx.x * NW + w, units = V / (32 * C);   // this wave's columns; past the matrix: the last ones again, not stored
     const uint32_t lo = (opaque_tid() & 63) * 16;
     const uint4 *wp[C];
@@ -387,6 +394,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_lm_head(const GemmArgs a, int 
         stream_rstd<NW, MT>(a, nrt, sm.rstd);   // behind the requests of the first weights
         return lo;
     });
+    gemm_stamp(a, blockIdx.x, 1);
     barrier_keep_loads();   // everybody has read the last stage: the logits take the ring's place
     const int lane = opaque_tid() & 63, half = lane >> 5, row = lane & 31;
     const float T = a.T, invT = T > 0.f ? 1.f / T : 1.f;
@@ -467,6 +475,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_lm_head(const GemmArgs a, int 
         }
         if (live && half == 0 && w % G == 0) a.stat[(size_t)lm * a.ncg_v + unit / G] = RowStat{m, idx, se, gm, gidx};
     }
+    gemm_stamp(a, blockIdx.x, 2);
 }
 
 }  // namespace deer
