@@ -12,19 +12,21 @@ SOURCES = [os.path.join(PKG_DIR, "csrc", "deer_api.hip")]
 HEADERS = [os.path.join(PKG_DIR, "csrc", "deer_kernels.hpp"), os.path.join(PKG_DIR, "csrc", "deer_block.hpp"), os.path.join(PKG_DIR, "csrc", "deer_stream.hpp"), os.path.join(ROOT, "include", "deer.h")]
 
 
+FLAGS = [
+    "--offload-arch=gfx950", "-O3", "-std=c++17",
+    # packed fp32 instructions are kept off for all device code
+    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG_DIR, "csrc"),
+]
+
+
 def hipcc_path() -> str:
     return shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
 
 def build_library(verbose: bool = False) -> str:
     """Compiles every HIP source for gfx950 and links the shared library.  Always rebuilds."""
-    cmd = [
-        hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-        # packed fp32 instructions are kept off for all device code
-        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG_DIR, "csrc"),
-        "-o", LIB_PATH, *SOURCES,
-    ]
+    cmd = [hipcc_path(), *FLAGS, "-fPIC", "-shared", "-o", LIB_PATH, *SOURCES]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -39,12 +41,7 @@ def build_library(verbose: bool = False) -> str:
 
 def device_assembly(out_path: str) -> str:
     """The gfx950 assembly of the device code, as text (same flags as the library): for checks on the generated code."""
-    cmd = [
-        hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17",
-        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG_DIR, "csrc"),
-        "--cuda-device-only", "-S", "-o", out_path, *SOURCES,
-    ]
+    cmd = [hipcc_path(), *FLAGS, "--cuda-device-only", "-S", "-o", out_path, *SOURCES]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stderr)
