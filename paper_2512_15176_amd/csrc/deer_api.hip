@@ -699,7 +699,8 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
 
 // Up to how many pairs per expert, on average over all experts, a mixture's projections run in k_gemm_moe; with more of them
 // experts of more than 32 pairs, whose weights that kernel reads twice, become frequent.  128 experts of 2048 x 768, top 8,
-// microseconds k_gemm_moe / k_moe_block (gate/up: with k_moe_gather) at 1, 4, 8, 10, 12, 16 row tiles (2 to 32 pairs): gate/up
+// microseconds k_gemm_moe / k_moe_block (gate/up: with k_moe_gather; medians of one sweep over three layers, rows spread evenly) at
+// 1, 4, 8, 10, 12, 16 row tiles (2 to 32 pairs): gate/up
 // 111 / 148, 139 / 169, 149 / 183, 170 / 180, 175 / 184, 230 / 207; down 57 / 65, 69 / 79, 77 / 84, 80 / 82, 86 / 82, 117 / 88.
 // 8 experts of 2048 x 5632, top 2, at 1, 2, 4 row tiles (8 to 32): gate/up 69 / 83, 76 / 85, 131 / 88; down 68 / 91, 69 / 92, 129 / 93.
 // Small experts keep lower lines, which the tests of what the host launches state (128 experts of 256 x 128 would gain 8 and
@@ -707,10 +708,11 @@ int launch_attn(deer_ctx *c, ModelRT &m, int layer, int ntiles, int NS, int NS_h
 constexpr int MOE_GATEUP_PAIRS = 24, MOE_DOWN_PAIRS = 20, MOE_SMALL_GATEUP_PAIRS = 14, MOE_SMALL_DOWN_PAIRS = 12;
 constexpr size_t MOE_SMALL_BYTES = 1 << 20;   // of an expert's gate/up matrix
 
-// From how many layers on a pass that only fills the caches leaves out what its last layer would do behind them.  It is never
-// slower, but models of up to four layers, which only tests and the tiny pair are, run whole: the tests of what the host
-// launches count five launches for each of their layers.  (8 layers of the mixture over 2048 ids 7384 -> 6617 us, 12 of the 4B over
-// 8 prompts 16761 -> 15387, 36 of the 8B over 4096 ids 108.3 -> 105.4 ms, 36 of the 4B over 201 ids 7019 -> 6851 us.)
+// From how many layers on a pass that only fills the caches leaves out what its last layer would do behind them.  Leaving it out is
+// never slower (8 layers of the mixture over 2048 ids 7384 -> 6617 us, 12 of the 4B over 8 prompts 16761 -> 15387, 36 of the 8B over
+// 4096 ids 108.3 -> 105.4 ms, 36 of the 4B over 201 ids 7019 -> 6851 us), so the line is no measured one: shorter models run
+// whole because most parity tests reach the GEMMs of many row tiles through the prompts of models of one or two layers, and
+// would no longer run O, gate/up and down there.  It costs a short drafter, and the tiny pair's request 8 of 40 launches.
 constexpr int CACHES_ONLY_LAYERS = 5;
 
 // One forward pass of `model` over the rows described by the row metadata: ntiles tiles of GEMM rows, n_attn attention tiles.

@@ -144,7 +144,8 @@ __device__ __forceinline__ void stream_swiglu(uint4 *ahi, uint4 *alo, int F, con
 // 61 + 26, 66 + 45, 93 + 49, 125 + 52 us, of 32 36 + 17, 63 + 28, 71 + 38, 77 + 42); a wave has 64 of the columns, of
 // gate/up the gate and the up block of 32 channels.  Gate/up gathers its rows out of the pass's fragments (lanes past the last
 // pair repeat it).
-// Bound: HBM.  Layer of 128 experts, top 8, d = 2048, expert width 768, microseconds before -> now: gate/up (the streaming
+// Bound: HBM.  Layer of 128 experts, top 8, d = 2048, expert width 768, means in a trace of whole decoding passes (in a sweep of three
+// layers, see MOE_GATEUP_PAIRS, 3 to 5 % less), microseconds before -> now: gate/up (the streaming
 // kernel, two column groups per workgroup) at 1 row tile, 111 experts or 698 MB, 125 -> 116 (6.0 TB/s), at 4 row tiles, 805 MB,
 // 160 -> 139; down (k_moe_block: two row tiles of products and LDS for one to eight pairs, 36 KB of
 // weights on their way per compute unit against 96 to 192 here) 72 -> 60 and 80 -> 70.  Three workgroups per compute unit; with
@@ -358,7 +359,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_gateup(const GemmArgs a, int nc
 // workgroup of eight waves at a time on a compute unit) -> here, one row tile: d = 896 66 -> 56 (greedy), 85 -> 65 (drawing), 2048
 // 129 -> 121, 2560 155 -> 146, 4096 237 -> 229; two row tiles: 92 -> 70, 127 -> 97, 158 -> 132, 192 -> 158, 283 -> 237.  Four row tiles
 // in workgroups of eight waves with 32 columns each: 118 (drawing 180), 200, 240, 371 against 113 (160), 197, 240, 363 in k_gemm_block,
-// which therefore keeps passes of more than two.
+// which therefore keeps passes of more than two.  (Up to 32768 columns the streaming kernel is faster: see launch_gemm.)
 template <int NW, int MT, int C>
 struct LmHeadSmem {
     union {

@@ -116,7 +116,8 @@ print((a, gemms(e, lambda: e.verify_block(32)), tiles))
 
 
 def test_grouped_gate_up_runs_blocked_where_experts_have_rows_enough(tmp_path):
-    """128 experts, top 8: 12 pairs per expert at 6 row tiles, where the streaming kernel is faster, 14 at 7."""
+    """128 small experts, top 8: 12 pairs per expert at 6 row tiles, below the line of their gate/up projections (14) and at that
+    of their down projections (12); 14 at 7."""
     got = routes(tmp_path, """
 t = di.ModelShape(1, 256, 4, 2, 32, 0, 1024, n_experts=128, top_k=8, d_ff_expert=128, rope_base=1e4)
 e = engine(t, di.CONFIGS["tiny"]["drafter"], 1, 512)
