@@ -78,11 +78,11 @@ def test_the_search_for_scalar_writes():
 @pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
 def test_registers_of_streamed_loads_are_left_alone(tmp_path):
     text = open(build.device_assembly(str(tmp_path / "deer_device.s"))).read()
-    kernels, row_indices = 0, 0
+    kernels, row_indices, partials = 0, 0, 0
     for name, body in re.findall(r"^(_ZN4deer\w*(?:k_gemm_moe|k_moe_block|k_lm_head|k_gemm_gateup)\w*):(.*?)^\.Lfunc_end", text, re.S | re.M):
         ops, asm, labels = parse(body)
         products = [i for i, o in enumerate(ops) if o[0].startswith("v_mfma")]
-        loads = [i for i in sorted(asm) if ops[i][0] == "global_load_dwordx4" and "sc1" not in ops[i]]   # (partial sums, sc1: waited for where they are requested)
+        loads = [i for i in sorted(asm) if ops[i][0] == "global_load_dwordx4" and "sc1" not in ops[i]]   # (sc1: partial sums, behind the products)
         held = set().union(*(registers(ops[i][1]) for i in loads))
         assert len(loads) >= 16 and len(held) >= 64, name
         for i in range(loads[0], products[-1] + 1):
@@ -91,12 +91,17 @@ def test_registers_of_streamed_loads_are_left_alone(tmp_path):
         for i in loads:
             assert scalars(ops[i][3]), (name, ops[i])
             assert scalar_written_just_before(ops, labels, i, scalars(ops[i][3])) is None, (name, i, ops[i])
-        for i in (i for i in asm if ops[i][0] == "global_load_dword"):
+        for i in (i for i in asm if ops[i][0] == "global_load_dword" or "sc1" in ops[i] and ops[i][0] == "global_load_dwordx4"):
             wait = next(j for j in range(i, len(ops)) if j in asm and ops[j][0] == "s_waitcnt" and "vmcnt" in ops[j][1])
-            assert i < loads[0] < wait and not any(o[0].startswith(("s_branch", "s_cbranch")) for o in ops[i:wait]), (name, "the wait for the row index")
+            assert not any(o[0].startswith(("s_branch", "s_cbranch")) for o in ops[i:wait]), (name, ops[i], "the wait for it")
             assert not any(registers(x) & registers(ops[i][1]) for o in ops[i + 1 : wait] for x in o[1:]), (name, ops[i])
-            row_indices += 1
+            if ops[i][0] == "global_load_dword":
+                assert i < loads[0] < wait, name
+                row_indices += 1
+            else:
+                assert "vmcnt(0)" in ops[wait][1], (name, ops[wait])
+                partials += 1
         assert not any(o[0].startswith(("scratch_", "v_accvgpr")) for o in ops), name
         kernels += 1
     # two projections in two ways to fold, for few and for many rows; LM heads of one and two row tiles in two ways to fold; gate/up of two row tiles
-    assert kernels == 4 + 4 + 4 + 1 and row_indices == 2
+    assert kernels == 4 + 4 + 4 + 1 and row_indices == 2 and partials >= 16
