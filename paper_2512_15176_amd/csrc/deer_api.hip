@@ -391,12 +391,13 @@ int choose_split(int N, int KS, int zgroups) {
     S = std::min(S, std::max(1, KS / 16));           // at least 16 k-steps per workgroup
     S = std::min<int>(S, (int)(PART_COLS / (size_t)N));
     S = std::max(S, 1);
-    // Fewer where that saves a round on some XCDs, down to five (drafter down, 5 and 6 row tiles, 7 and 6 shares: 16.7 and 17.4 us,
-    // in 6 and 5 shares 12.8 and 13.4).  Not fewer: the waves' chains of sums grow (error against 64 bits at 7, 9 and 11 row tiles,
-    // 5, 4 and 3 shares: 0.97, 1.00 and 1.03e-7; one share fewer 0.99, 1.04 and 1.15e-7).  And not where it saves none: the
-    // router, one column group, has at most eight pairs, one to an XCD, however many shares, and its shares are what spreads
-    // it over the XCDs (128 x 2048 over 33, 66 and 128 row tiles in 6, 6 and 3 shares: 19, 35 and 51 us, in one 33, 53 and 60).
-    for (int s = S - 1; s >= 5; --s)
+    // Fewer where that saves a round on some XCDs and leaves a wave a chain of up to eight k-steps (drafter down, 5 and 6 row tiles,
+    // 7 and 6 shares: 16.7 and 17.4 us, in 6 and 5 shares 12.8 and 13.4).  Not with longer chains, whose sums are further off (error against
+    // 64 bits, drafter down at 7, 9 and 11 row tiles in 5, 4 and 3 shares 0.97, 1.00 and 1.03e-7, in one fewer 0.99, 1.04 and 1.15e-7;
+    // 1536 x 8960 at 3 in 7 shares 1.05, in 6 1.07e-7).  And not where it saves none: the router, one column group, has at most
+    // eight pairs, one to an XCD, however many shares, and its shares are what spreads it over the XCDs (128 x 2048 over 33, 66 and
+    // 128 row tiles in 6, 6 and 3 shares: 19, 35 and 51 us, in one 33, 53 and 60).
+    for (int s = S - 1; s >= 1 && KS <= 64 * s; --s)
         if (stream_rounds(N, s, zgroups) < stream_rounds(N, S, zgroups)) S = s;
     return S;
 }

@@ -68,17 +68,18 @@ def test_the_faster_kernel_runs(tmp_path):
     assert not off, off
 
 
-# Shares of K of the drafter's down projection: as many as fill the chip (7 row tiles: error against 64 bits 0.97e-7 in five,
-# 0.99 in four; 11: 1.03 in three, 1.15 in two), one fewer where five or more are left and a round is saved (5 and 6 row tiles: the same error).
-SHARES = {5: 6, 6: 5, 7: 5, 9: 4, 11: 3, 12: 3, 18: 4, 24: 3}
+# Shares of K of down projections: as many as fill the chip (7 row tiles of d = 896: error against 64 bits 0.97e-7 in five, 0.99 in four;
+# 11: 1.03 in three, 1.15 in two; 3 of d = 1536: 1.05 in seven, 1.07 in six), fewer where a round is saved and a wave's chain keeps to
+# eight k-steps (5 and 6 row tiles of d = 896: the same error).
+SHARES = {("d896", 5): 6, ("d896", 6): 5, ("d896", 7): 5, ("d896", 9): 4, ("d896", 11): 3, ("d896", 12): 3, ("d896", 18): 4, ("d896", 24): 3, ("d1536", 3): 7}
 # The router of a mixture of d_model 2048: one column group, whose shares are what spreads it over the XCDs.  Microseconds at 33, 63,
 # 66 and 128 row tiles 19, 30, 35 and 51, in one share 33, 37, 53 and 60.
 ROUTER = {16: 8, 32: 8, 33: 6, 63: 3, 64: 7, 66: 6, 75: 2, 100: 4, 111: 2, 113: 1, 128: 3}
 
 
 def test_shares_of_k(tmp_path):
-    got = launches(tmp_path, [("d896", t, "down") for t in SHARES])
-    assert {t: got["d896", t, "down"] for t in SHARES} == {t: ("streaming", s) for t, s in SHARES.items()}
+    got = launches(tmp_path, [(d, t, "down") for d, t in SHARES])
+    assert {(d, t): got[d, t, "down"] for d, t in SHARES} == {at: ("streaming", s) for at, s in SHARES.items()}
     got = eval(run_script(tmp_path, f"""
 import deer_inputs as di
 t = di.scaled(di.CONFIGS["qwen3_30b_a3b"]["target"], n_layers=1, vocab=1024)
